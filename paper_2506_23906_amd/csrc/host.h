@@ -175,19 +175,17 @@ WsLayout ws_layout(mmv_op op, mmv_dtype dt, mmv_flag_fmt ff, uint64_t n) {
     return L;
 }
 
-// Workspace of COMPRESS: header, one count descriptor per tile, packed mask if the caller gave bytes.
+// Workspace of COMPRESS: header and one count descriptor per tile, all of it zeroed by every call.
 struct CompressLayout {
-    size_t desc, packed, total;
+    size_t desc, total;
     uint64_t tiles;
 };
-CompressLayout compress_layout(mmv_flag_fmt ff, uint64_t n) {
+CompressLayout compress_layout(uint64_t n) {
     CompressLayout L;
     L.tiles = (n + compress_tile(n) - 1) / compress_tile(n);
     size_t off = kHdrBytes;
     L.desc = off;
     off += round256(L.tiles * 8);
-    L.packed = off;
-    if (ff == MMV_FLAGS_U8) off += round256(((n + 63) / 64) * 8);
     L.total = off;
     return L;
 }
@@ -209,7 +207,7 @@ ScdLayout scd_layout(mmv_dtype dt, mmv_flag_fmt ff, uint64_t n, uint64_t cap) {
     L.fminus = off;
     off += round256(((n + 63) / 64) * 8);
     L.compress_ws = off;
-    off += round256(compress_layout(MMV_FLAGS_PACKED32, n).total);
+    off += round256(compress_layout(n).total);
     L.w = off;
     off += round256((cap < n ? cap : n) * 4 + 16);
     L.total = off;
@@ -234,7 +232,7 @@ SscrLayout sscr_layout(mmv_dtype dt, mmv_flag_fmt ff, uint64_t n) {
     L.fminus = off;
     off += round256(((n + 63) / 64) * 8);
     L.compress_ws = off;
-    off += round256(compress_layout(MMV_FLAGS_PACKED32, n).total);
+    off += round256(compress_layout(n).total);
     L.w = off;
     off += round256(n * 4 + 16);   // one entry per segment, at most n
     L.total = off;
@@ -251,7 +249,7 @@ CsrLayout csr_layout(uint64_t n_rows, uint64_t nnz) {
     L.main_ws = off;   // the two workspaces that hold tickets and descriptors lie next to each other:
     off += round256(ws_layout(MMV_OP_SPMV_CSR, MMV_F32_F32, MMV_FLAGS_PACKED32, nnz).total);
     L.compress_ws = off;   // one fill clears both (and the flag words between them)
-    off += round256(compress_layout(MMV_FLAGS_PACKED32, n_rows).total);
+    off += round256(compress_layout(n_rows).total);
     L.rowmask = off;
     off += round256(((n_rows + 63) / 64) * 8);
     L.rowmap = off;
@@ -408,35 +406,29 @@ mmv_status scan_impl(const void *d_x, uint64_t n, void *d_z, mmv_dtype dt, mmv_v
 mmv_status compress_impl(const void *d_x, const void *d_mask, uint64_t n, void *d_out, uint64_t out_capacity,
                          uint64_t *d_count, mmv_flag_fmt ff, void *d_ws, size_t ws_bytes, hipStream_t s,
                          bool ws_is_reset = false, const uint32_t *d_needed = nullptr) {
-    const CompressLayout L = compress_layout(ff, n);
+    const CompressLayout L = compress_layout(n);
     if (((uintptr_t)d_ws & 255u) != 0 || ws_bytes < L.total) return MMV_ERR_WORKSPACE;
     if (L.tiles > 0x7fffffffull) return MMV_ERR_INVALID_ARG;
     char *ws = (char *)d_ws;
     if (!ws_is_reset) {
-        const uint64_t zero_words = L.packed / 4;
+        const uint64_t zero_words = L.total / 4;
         fill_zero_kernel<<<grid_for(zero_words), 256, 0, s>>>((uint32_t *)ws, zero_words, nullptr, 0);
         if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     }
-    const uint32_t *mw = (const uint32_t *)d_mask;
-    if (ff == MMV_FLAGS_U8) {
-        const uint64_t nwords = (n + 31) / 32;
-        uint32_t *packed = (uint32_t *)(ws + L.packed);
-        pack_flags_kernel<<<grid_for(nwords), 256, 0, s>>>((const uint8_t *)d_mask, n, packed, nwords);
-        if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
-        mw = packed;
-    }
     if (tl_ev_start && hipEventRecord(tl_ev_start, s) != hipSuccess) return MMV_ERR_HIP;
     // the workgroups that are resident from the start take the tile of their own index, the others a ticket
-    static std::atomic<uint32_t> occupancy[4][kMaxDevices];
-    void (*kernel)(const uint32_t *, const uint32_t *, uint64_t, uint32_t *, uint64_t, uint64_t *, uint32_t *, uint64_t *,
-                   uint32_t, const uint32_t *, uint32_t) = compress_kernel<64, 1>;
-    int which = 1;
-    if (compress_words(n) == 16) kernel = compress_kernel<16, 1>, which = 0;
-    else if (compress_groups(n) == 2) kernel = compress_kernel<64, 2>, which = 2;
-    else if (compress_groups(n) == 4) kernel = compress_kernel<64, 4>, which = 3;
+    static std::atomic<uint32_t> occupancy[8][kMaxDevices];
+    typedef void (*Kernel)(const uint32_t *, const void *, uint64_t, uint32_t *, uint64_t, uint64_t *, uint32_t *, uint64_t *,
+                           uint32_t, const uint32_t *, uint32_t);
+    static const Kernel kernels[8] = {compress_kernel<16, 1, false>, compress_kernel<64, 1, false>, compress_kernel<64, 2, false>,
+                                      compress_kernel<64, 4, false>, compress_kernel<16, 1, true>,  compress_kernel<64, 1, true>,
+                                      compress_kernel<64, 2, true>,  compress_kernel<64, 4, true>};
+    const int which = (compress_words(n) == 16 ? 0 : compress_groups(n) == 1 ? 1 : compress_groups(n) == 2 ? 2 : 3) +
+                      (ff == MMV_FLAGS_U8 ? 4 : 0);
+    const Kernel kernel = kernels[which];
     const uint32_t resident = resident_workgroups((const void *)kernel, kCompressWaves * 64, occupancy[which]);
     const uint32_t first_round = (uint32_t)L.tiles < resident ? (uint32_t)L.tiles : resident;
-    kernel<<<(unsigned)L.tiles, kCompressWaves * 64, 0, s>>>((const uint32_t *)d_x, mw, n, (uint32_t *)d_out, out_capacity,
+    kernel<<<(unsigned)L.tiles, kCompressWaves * 64, 0, s>>>((const uint32_t *)d_x, d_mask, n, (uint32_t *)d_out, out_capacity,
                                                              d_count, (uint32_t *)ws, (uint64_t *)(ws + L.desc),
                                                              (uint32_t)L.tiles, d_needed, first_round);
     const hipError_t e = hipGetLastError();

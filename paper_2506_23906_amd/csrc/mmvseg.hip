@@ -93,7 +93,7 @@ size_t mmv_workspace_bytes(mmv_op op, mmv_dtype dt, mmv_flag_fmt ff, uint64_t n)
         case MMV_OP_SEGSUM:
         case MMV_OP_SCAN: return ws_layout(op, dt, ff, n).total;
         case MMV_OP_SPMV_COO: return ws_layout(op, MMV_F32_F32, ff, n).total;
-        case MMV_OP_COMPRESS: return compress_layout(ff, n).total;
+        case MMV_OP_COMPRESS: return compress_layout(n).total;
         case MMV_OP_SEGSUM_SCD: return scd_layout(dt, ff, n, n).total;
         case MMV_OP_SEGSCAN_SSCR: return sscr_layout(dt, ff, n).total;
         case MMV_OP_SPMV_CSR: return 0;  // two sizes: see mmv_spmv_csr_workspace_bytes
@@ -420,7 +420,7 @@ mmv_status mmv_spmv_csr(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
     char *ws = (char *)d_ws;
     const WsLayout L = ws_layout(MMV_OP_SPMV_CSR, MMV_F32_F32, MMV_FLAGS_PACKED32, nnz);
     // zero: the main kernel's header, descriptors and flag words, the header and descriptors of COMPRESS; y
-    const uint64_t zero_words = (C.compress_ws + compress_layout(MMV_FLAGS_PACKED32, n_rows).packed) / 4;
+    const uint64_t zero_words = (C.compress_ws + compress_layout(n_rows).total) / 4;
     fill_zero_kernel<<<grid_for(zero_words > n_rows ? zero_words : n_rows), 256, 0, s>>>((uint32_t *)ws, zero_words,
                                                                                       (uint32_t *)d_y, n_rows);
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
@@ -474,7 +474,7 @@ mmv_status mmv_spmv_csr_prepare(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, 
     hipStream_t s = (hipStream_t)hip_stream;
     char *ws = (char *)d_ws;
     const WsLayout L = ws_layout(MMV_OP_SPMV_CSR, MMV_F32_F32, MMV_FLAGS_PACKED32, nnz);
-    const uint64_t zero_words = (C.compress_ws + compress_layout(MMV_FLAGS_PACKED32, n_rows).packed) / 4;
+    const uint64_t zero_words = (C.compress_ws + compress_layout(n_rows).total) / 4;
     fill_zero_kernel<<<grid_for(zero_words), 256, 0, s>>>((uint32_t *)ws, zero_words, nullptr, 0);
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     const TilePlan plan = tile_plan(MMV_OP_SPMV_CSR, MMV_F32_F32, nnz);

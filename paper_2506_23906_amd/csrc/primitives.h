@@ -36,55 +36,109 @@ __global__ __launch_bounds__(256) void unpack_flags_kernel(const uint32_t *fw, u
 }
 
 // COMPRESS (Sec. 2): out = the 32-bit entries of x whose mask bit is set, in order; with
-// x == nullptr the positions themselves are compressed.  The mask is bit-packed; the output
+// x == nullptr the positions themselves are compressed.  The output
 // index of an entry is the number of set bits before it (the scan of the mask in the paper's
 // COMPRESS), found per tile from popcounts and across tiles by decoupled look-back.
 // A wave owns kGroups groups of 64 * kWords consecutive positions (kWords = 64 or 16): lane j < kWords
-// holds the 64-bit mask word j of every group, and for every word the wave reads only the selected entries
-// (one coalesced load, skipped when the word is empty) and writes them to consecutive output slots; a wave with
-// few selected entries lets every lane walk its own words instead.  Short masks take the short
+// holds the 64-bit mask word j of every group.  A mask of one byte per position (kBytes) is read by this kernel itself:
+// 16 bytes per lane and load, turned into 16 bits, and the pieces of a word brought together through LDS.
+// A wave with few selected entries (at most 1 in 32) lets every lane walk the set bits of its own words: up to
+// there most 128-byte lines of x hold at most one of them (n = 2^28, 3 % selected: 0.184 ms; 4 %: 0.175 in pieces, 0.238 walked).  Any other wave takes its positions in pieces of 1024: it
+// loads all of x (128 bits per lane, the next piece on its way while one is stored, the first before the look-back), drops
+// the selected entries into LDS at their rank, and stores them from there with 128-bit stores.  Bound by the memory;
+// n = 2^26 values, 30 % selected by a byte mask: 126 us for packing kernel and a loop over the words of 64 positions (one load and
+// one store instruction of 64 lanes each, 30 % of them active), 81 us now (whole calls, with the 5 us of the reset).
+// Short masks take the short
 // spans: four times the waves, a quarter of the words each wave visits one after the other.  Long masks take
 // two or four groups per wave: a tile costs a ticket (11 ns each, one after the other), a barrier and a look-back
 // whatever its length, and with one group per wave the tickets alone took 93 us of the 111 us at n = 2^28
-// and 0.1 % selected (now 0.048 ms; 30 % selected: 0.454 -> 0.415 ms).
+// and 0.1 % selected (now 0.048 ms).
 // The workgroups that are resident from the start take the tile of their own index, as in the main kernel.
 constexpr int kCompressWaves = 8;
 constexpr uint64_t kCompressShortN = 1ull << 22;   // masks up to this length take 16 words per wave
-// masks from 2^26 positions on take two groups of words per wave, from 2^28 on four: the mask has to be long enough
-// for several rounds of workgroups (n = 2^26, 30 % selected: 0.125 ms with one group, 0.110 with two, 0.164 with four,
-// which leaves two workgroups per compute unit; 0.1 % selected: 0.038, 0.015, 0.014 ms)
+// masks from 2^26 positions on take two groups of words per wave, from 2^27 on four: the most that still leaves a tile
+// for each of the 1024 workgroups that are resident at once (n = 2^27, 1 % selected: 0.054 ms with two groups, 0.039
+// with four; n = 2^26, 0.1 % selected: 0.038 ms with one group, 0.015 with two)
 inline int compress_words(uint64_t n) { return n <= kCompressShortN ? 16 : 64; }
-inline int compress_groups(uint64_t n) { return n >= (1ull << 28) ? 4 : n >= (1ull << 26) ? 2 : 1; }
+inline int compress_groups(uint64_t n) { return n >= (1ull << 27) ? 4 : n >= (1ull << 26) ? 2 : 1; }
 inline uint64_t compress_tile(uint64_t n) { return (uint64_t)kCompressWaves * 64u * compress_words(n) * compress_groups(n); }
 
-template <int kWords, int kGroups>
+constexpr int kPieceElems = 1024;                  // positions a wave compacts at a time
+constexpr int kPieceWords = kPieceElems + 4;       // LDS words of a wave: a piece, shifted by up to three
+
+// 16 mask bytes -> 16 bits (bit set iff the byte is not zero).
+__device__ __forceinline__ uint32_t bits_of_16_bytes(v4u w) {
+    uint32_t bits = 0;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        // the highest bit of every byte that is not zero, moved to bits 0, 8, 16, 24, and those next to each other
+        // (the multiplication puts the bit of byte j at bit 28 + j; no two partial products meet there)
+        const uint32_t nz = ((((w[d] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w[d]) >> 7) & 0x01010101u;
+        bits |= ((nz * 0x10204080u) >> 28) << (4 * d);
+    }
+    return bits;
+}
+
+// One piece of 1024 positions on its way: the values (word i of lane l = positions 256 i + 4 l .. + 3 of the piece) and,
+// per word, the rank of the lane's first position among the selected ones of the piece (upper bits) and which of the
+// four are selected (lowest four bits).
+struct CompressPiece {
+    v4u w[4];
+    uint32_t rank_sel[4];
+};
+
+template <int kWords, int kGroups, bool kBytes>
 __global__ __launch_bounds__(kCompressWaves * 64, 8) void compress_kernel(
-    const uint32_t *__restrict__ x, const uint32_t *__restrict__ mw, uint64_t n, uint32_t *__restrict__ out,
+    const uint32_t *__restrict__ x, const void *__restrict__ mask, uint64_t n, uint32_t *__restrict__ out,
     uint64_t out_cap, uint64_t *__restrict__ count, uint32_t *hdr, uint64_t *desc, uint32_t num_tiles,
     const uint32_t *needed, uint32_t first_round) {
     __shared__ uint32_t s_tile, s_wave[kCompressWaves], s_carry;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ __attribute__((aligned(16))) uint32_t s_piece[kCompressWaves][kPieceWords];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (needed && *needed == 0) return;   // CSR SpMV without empty rows: nobody reads the row map
     const bool own_index = blockIdx.x < first_round;
     if (tid == 0 && !own_index)
         s_tile = first_round + __hip_atomic_fetch_add(hdr + kHdrTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    const uint32_t tile = own_index ? blockIdx.x : s_tile;
+    const uint32_t tile = __builtin_amdgcn_readfirstlane(own_index ? blockIdx.x : s_tile);
     constexpr uint32_t kGroupSpan = 64u * kWords;                                   // positions of one group
     constexpr uint32_t kSpan = kGroupSpan * kGroups;                                // positions of a wave
     const uint64_t span = ((uint64_t)tile * kCompressWaves + wave) * kSpan;          // first position of my wave
+    uint32_t *piece_buf = s_piece[wave];
     uint64_t m[kGroups];
     uint32_t before[kGroups];   // selected entries of my wave before my word of group g
     uint32_t wave_cnt = 0;
+    if constexpr (kBytes) {
+        const uint8_t *mb = (const uint8_t *)mask;
+        constexpr int kLoads = kWords / 16;   // 1024 mask bytes of the wave each
 #pragma unroll
-    for (int g = 0; g < kGroups; ++g) {
-        const uint64_t p0 = span + (uint64_t)g * kGroupSpan + 64u * lane;            // first position of my word
-        m[g] = 0;
-        if (lane < kWords && p0 < n) {
-            const uint64_t wi = p0 >> 5;
-            m[g] = mw[wi];
-            if (p0 + 32 < n) m[g] |= (uint64_t)mw[wi + 1] << 32;
-            if (p0 + 64 > n) m[g] &= (1ull << (n - p0)) - 1ull;
+        for (int g = 0; g < kGroups; ++g) {
+            v4u b[kLoads];
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i) {
+                const uint64_t p = span + (uint64_t)g * kGroupSpan + 1024u * i + 16u * lane;
+                b[i] = load128(mb, p, n, p + 16 <= n);
+            }
+            uint16_t *piece16 = reinterpret_cast<uint16_t *>(piece_buf);
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i) piece16[64 * i + lane] = (uint16_t)bits_of_16_bytes(b[i]);
+            wave_lds_sync();
+            m[g] = 0;
+            if (lane < kWords) m[g] = *reinterpret_cast<const uint64_t *>(piece_buf + 2 * lane);
+            wave_lds_sync();   // read before the next group overwrites it
+        }
+    } else {
+        const uint32_t *mw = (const uint32_t *)mask;
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) {
+            const uint64_t p0 = span + (uint64_t)g * kGroupSpan + 64u * lane;            // first position of my word
+            m[g] = 0;
+            if (lane < kWords && p0 < n) {
+                const uint64_t wi = p0 >> 5;
+                m[g] = mw[wi];
+                if (p0 + 32 < n) m[g] |= (uint64_t)mw[wi + 1] << 32;
+                if (p0 + 64 > n) m[g] &= (1ull << (n - p0)) - 1ull;
+            }
         }
     }
 #pragma unroll
@@ -100,6 +154,37 @@ __global__ __launch_bounds__(kCompressWaves * 64, 8) void compress_kernel(
         wave_cnt += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
     }
     if (lane == 0) s_wave[wave] = wave_cnt;
+
+    // ---- a wave with many selected entries: its values, piece by piece ----
+    const bool dense = wave_cnt > 2u * kWords * kGroups;
+    constexpr int kPieces = kGroups * kWords / 16;
+    CompressPiece pc;
+    // (c is the same for all lanes: the selects below run on scalar conditions)
+    auto load_piece = [&](int c) {
+        uint64_t mg = m[0];
+        uint32_t bg = before[0];
+#pragma unroll
+        for (int g = 1; g < kGroups; ++g)
+            if (c / (kWords / 16) == g) mg = m[g], bg = before[g];
+        const uint64_t piece0 = span + (uint64_t)c * kPieceElems;   // (uniform)
+        const int word0 = 16 * (c % (kWords / 16));   // first of the piece's sixteen mask words
+        const uint32_t rank0 = (uint32_t)__builtin_amdgcn_readlane((int)bg, word0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int src = word0 + 4 * i + (lane >> 4);
+            const uint64_t word = ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(mg >> 32), src) << 32) | (uint32_t)__shfl((int)(uint32_t)mg, src);
+            const uint32_t at = 4u * (lane & 15);
+            const uint32_t rank = (uint32_t)__shfl((int)bg, src) - rank0 + (uint32_t)__popcll((unsigned long long)(word & ((1ull << at) - 1ull)));
+            const uint32_t sel = (uint32_t)(word >> at) & 0xFu;
+            pc.rank_sel[i] = (rank << 4) | sel;
+            const uint32_t p = 256u * i + 4u * lane;
+            if (x) {
+                // a lane without selected entries has nothing to read; the 16-byte block of a selected entry begins inside x
+                if (sel) pc.w[i] = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(x + piece0 + p));
+            }
+        }
+    };
+    if (dense) load_piece(0);
     __syncthreads();
     uint32_t wave_ex = 0, tile_cnt = 0;
 #pragma unroll
@@ -119,27 +204,32 @@ __global__ __launch_bounds__(kCompressWaves * 64, 8) void compress_kernel(
     }
     __syncthreads();
     const uint64_t wave_base = (uint64_t)s_carry + wave_ex;   // output index of the first selected entry of my wave
-    if (wave_cnt <= 4u * kWords * kGroups) {
+    if (!dense) {
         // few selected entries in my wave's positions: every lane walks the set bits of its own
-        // words (a handful of independent loads per lane) instead of the wave visiting every word
+        // words (a handful of independent loads per lane)
         // Four entries of a word at a time, their loads all under way before the first store: one memory round trip
         // per four entries instead of one per entry.
-#pragma unroll
+#pragma unroll 1
         for (int g = 0; g < kGroups; ++g) {
-            const uint64_t p0 = span + (uint64_t)g * kGroupSpan + 64u * lane;
-            uint64_t mm = m[g], k = wave_base + before[g];
+            const uint64_t group0 = span + (uint64_t)g * kGroupSpan;   // (uniform)
+            uint64_t mm = m[0];
+            uint32_t bg = before[0];
+#pragma unroll
+            for (int i = 1; i < kGroups; ++i)
+                if (g == i) mm = m[i], bg = before[i];
+            uint64_t k = wave_base + bg;
             while (mm) {
-                uint64_t p[4];
+                uint32_t p[4];
                 uint32_t v[4];
                 bool on[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     on[i] = mm != 0;
-                    p[i] = p0 + (on[i] ? (uint32_t)__builtin_ctzll((unsigned long long)mm) : 0u);
+                    p[i] = 64u * lane + (on[i] ? (uint32_t)__builtin_ctzll((unsigned long long)mm) : 0u);
                     mm &= mm - 1;   // (0 stays 0)
                 }
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = !on[i] ? 0u : (x ? __builtin_nontemporal_load(x + p[i]) : (uint32_t)p[i]);
+                for (int i = 0; i < 4; ++i) v[i] = !on[i] ? 0u : (x ? __builtin_nontemporal_load(x + group0 + p[i]) : (uint32_t)group0 + p[i]);
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
                     if (on[i] && k + i < out_cap) out[k + i] = v[i];
@@ -148,25 +238,40 @@ __global__ __launch_bounds__(kCompressWaves * 64, 8) void compress_kernel(
         }
         return;
     }
-    const uint64_t lane_below = (1ull << lane) - 1ull;
+    uint64_t piece_base = wave_base;   // output index of the first selected entry of the piece at hand
+#pragma unroll 1
+    for (int c = 0; c < kPieces; ++c) {
+        // the selected entries into LDS, shifted so that a 16-byte block there is one in `out`
+        const uint32_t shift = (uint32_t)piece_base & 3u;
+        const uint32_t pos0 = (uint32_t)(span + (uint64_t)c * kPieceElems) + 4u * lane;
 #pragma unroll
-    for (int g = 0; g < kGroups; ++g) {
-        const uint64_t word_base = wave_base + before[g];
-        const uint32_t m_lo = (uint32_t)m[g], m_hi = (uint32_t)(m[g] >> 32);
-        const uint32_t base_lo = (uint32_t)word_base, base_hi = (uint32_t)(word_base >> 32);
-#pragma unroll 8
-        for (int j = 0; j < kWords; ++j) {
-            const uint64_t mj = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)m_hi, j) << 32) |
-                                (uint32_t)__builtin_amdgcn_readlane((int)m_lo, j);
-            const uint64_t bj = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)base_hi, j) << 32) |
-                                (uint32_t)__builtin_amdgcn_readlane((int)base_lo, j);
-            if ((mj >> lane) & 1ull) {
-                const uint64_t p = span + (uint64_t)g * kGroupSpan + 64u * j + lane;
-                const uint32_t v = x ? __builtin_nontemporal_load(x + p) : (uint32_t)p;
-                const uint64_t k = bj + (uint32_t)__popcll((unsigned long long)(mj & lane_below));
-                if (k < out_cap) out[k] = v;
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t sel = pc.rank_sel[i] & 0xFu;
+            const uint32_t at = (pc.rank_sel[i] >> 4) + shift;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if ((sel >> k) & 1u) piece_buf[at + (uint32_t)__popc(sel & ((1u << k) - 1u))] = x ? pc.w[i][k] : pos0 + 256u * i + k;
+        }
+        // entries of the piece: the rank of the last lane's last position, and that one
+        const uint32_t last = pc.rank_sel[3];
+        const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)((last >> 4) + (uint32_t)__popc(last & 0xFu)), 63);
+        wave_lds_sync();
+        if (c + 1 < kPieces) load_piece(c + 1);   // on its way while this one is stored
+        const uint64_t out0 = piece_base - shift;   // a multiple of four
+        const uint64_t stop = piece_base + cnt < out_cap ? piece_base + cnt : out_cap;
+        for (uint32_t q = 4u * lane; q < shift + cnt; q += 256u) {
+            const v4u v = *reinterpret_cast<const v4u *>(piece_buf + q);
+            const uint64_t k = out0 + q;
+            if (k >= piece_base && k + 4 <= stop) {
+                *reinterpret_cast<v4u *>(out + k) = v;
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (k + j >= piece_base && k + j < stop) out[k + j] = v[j];
             }
         }
+        wave_lds_sync();   // read before the next piece overwrites it
+        piece_base += cnt;
     }
 }
 
