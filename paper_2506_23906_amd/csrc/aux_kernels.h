@@ -32,26 +32,31 @@ __global__ void mark_prepared_kernel(uint32_t *hdr, uint32_t mark) {
 }
 
 // Segmented sum, step "scan of the end markers" of COMPRESS (proof of the SCD / SSCR theorem)
-// at tile granularity: workgroup b counts the segment starts inside tile b (position 0 is not
-// counted: it opens segment 0 whatever its flag says; bits at or beyond n are not counted), and, if asked
-// (span_cnt), inside each of the `unit / 2048` equal spans of the tile that the waves of the main kernel take.
+// at the granularity of the spans that the waves of the main kernel take: a workgroup counts the segment starts inside
+// each of the 64 spans of a group of eight tiles, and in the group (position 0 is not counted: it opens segment 0
+// whatever its flag says; bits at or beyond n are not counted).  A wave of the main kernel then adds up the groups
+// before its own and the spans of its group before its own: two loads per lane for up to 512 tiles, where a table per
+// tile took as many dependent loads as there are 64 tiles (or a launch more that made prefix sums of it: 6.3 us at
+// 6104 tiles).  Sixteen lanes share a span, so a wave works on four.
 // The same launch zeroes the header and the descriptors of the main kernel.
-__global__ __launch_bounds__(256) void count_tiles_kernel(uint32_t *zero, uint64_t zero_words, const uint32_t *fw,
-                                                          uint64_t n, TileRegions reg, uint32_t unit, uint32_t *cnt,
-                                                          uint32_t *span_cnt) {
-    __shared__ uint32_t s_part[4];
-    const uint32_t b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (uint64_t i = (uint64_t)b * 256 + tid; i < zero_words; i += (uint64_t)gridDim.x * 256) zero[i] = 0;
-    const TileSpan span = tile_span(reg, b, unit);
-    const uint32_t spans = unit / kChunkElems;
-    const uint64_t span_words = (uint64_t)span.cpw * (kChunkElems / 32);
-    const uint64_t last_word = (n + 31) >> 5;
-    uint32_t mine = 0;   // the spans are dealt to the four waves in turn
-    for (uint32_t sp = wave; sp < spans; sp += 4) {
-        const uint64_t w0 = (span.base >> 5) + sp * span_words;   // tiles and spans begin on word borders, spans are multiples of 64 words
-        uint32_t sum = 0;
-        for (uint64_t w = w0 + 4 * lane; w < w0 + span_words && w < last_word; w += 256) {
-            // four words at a time (the workspace behind the caller's words is not ours to read: the last ones singly)
+__global__ __launch_bounds__(1024) void count_spans_kernel(uint32_t *zero, uint64_t zero_words, const uint32_t *fw,
+                                                           uint64_t n, TileRegions reg, uint32_t unit, uint32_t *group_cnt,
+                                                           uint32_t *span_cnt) {
+    __shared__ uint32_t s_part[16];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (uint64_t i = (uint64_t)blockIdx.x * 1024 + tid; i < zero_words; i += (uint64_t)gridDim.x * 1024) zero[i] = 0;
+    const uint32_t sp = blockIdx.x * kGroupSpans + wave * 4 + (lane >> 4);   // my span, of all tiles
+    const uint32_t tile = sp / kSpans;
+    uint32_t sum = 0;
+    if (tile < reg.num_tiles) {
+        const TileSpan span = tile_span(reg, tile, unit);
+        const uint64_t span_words = (uint64_t)span.cpw * (unit / kSpans / 32);
+        const uint64_t w0 = (span.base >> 5) + (sp % kSpans) * span_words;   // tiles and spans begin on word borders, spans are multiples of 32 words
+        const uint64_t last_word = (n + 31) >> 5;
+#pragma unroll 4
+        for (uint64_t w = w0 + 4 * (lane & 15); w < w0 + span_words; w += 64) {
+            if (w >= last_word) break;
+            // four words at a time (what lies behind the caller's words is not ours to read: the last ones singly)
             uint32_t v[4] = {0, 0, 0, 0};
             if (w + 4 <= last_word) {
                 const v4u q = *reinterpret_cast<const v4u *>(fw + w);
@@ -59,32 +64,44 @@ __global__ __launch_bounds__(256) void count_tiles_kernel(uint32_t *zero, uint64
             } else {
                 for (int j = 0; j < 4 && w + j < last_word; ++j) v[j] = fw[w + j];
             }
+            if (w == 0) v[0] &= ~1u;
+            if ((w + 4) * 32 > n) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint64_t wj = w + j;
-                if (wj == 0) v[j] &= ~1u;
-                if ((wj + 1) * 32 > n) v[j] = wj * 32 < n ? (v[j] & ((1u << (uint32_t)(n - wj * 32)) - 1u)) : 0u;
-                sum += __popc(v[j]);
+                for (int j = 0; j < 4; ++j) {
+                    const uint64_t wj = w + j;
+                    if ((wj + 1) * 32 > n) v[j] = wj * 32 < n ? (v[j] & ((1u << (uint32_t)(n - wj * 32)) - 1u)) : 0u;
+                }
             }
+            sum += (__popc(v[0]) + __popc(v[1])) + (__popc(v[2]) + __popc(v[3]));
         }
-        sum = wave_sum(sum);
-        if (span_cnt && lane == 0) span_cnt[(uint64_t)b * spans + sp] = sum;
-        mine += sum;
     }
-    if (lane == 0) s_part[wave] = mine;
+    // sums over the sixteen lanes of a span (lane 15 of a row of lanes has it), then over the wave
+    sum += dpp_or_zero<0x111, 0xF>(sum);
+    sum += dpp_or_zero<0x112, 0xF>(sum);
+    sum += dpp_or_zero<0x114, 0xF>(sum);
+    sum += dpp_or_zero<0x118, 0xF>(sum);
+    if ((lane & 15) == 15 && tile < reg.num_tiles) span_cnt[sp] = sum;
+    sum += dpp_or_zero<0x142, 0xA>(sum);
+    sum += dpp_or_zero<0x143, 0xC>(sum);
+    if (lane == 63) s_part[wave] = sum;
     __syncthreads();
-    if (tid == 0) cnt[b] = s_part[0] + s_part[1] + s_part[2] + s_part[3];
+    if (tid == 0) {
+        uint32_t all = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) all += s_part[w];
+        group_cnt[blockIdx.x] = all;
+    }
 }
 
-// Exclusive prefix sums of the per-tile counts, in place, by one workgroup; the total (+ 1 for
-// segment 0) is the number of segments.
-__global__ __launch_bounds__(1024) void scan_counts_kernel(uint32_t *cnt, uint32_t num_tiles, uint64_t *nseg) {
+// Exclusive prefix sums of the counts per group, in place, by one workgroup (only for very long vectors); the total (+ 1
+// for segment 0) is the number of segments.
+__global__ __launch_bounds__(1024) void scan_counts_kernel(uint32_t *cnt, uint32_t num_groups, uint64_t *nseg) {
     __shared__ uint32_t s_wave[16];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t running = 0;
-    for (uint32_t base = 0; base < num_tiles; base += 1024) {
+    for (uint32_t base = 0; base < num_groups; base += 1024) {
         const uint32_t i = base + tid;
-        const uint32_t v = i < num_tiles ? cnt[i] : 0u;
+        const uint32_t v = i < num_groups ? cnt[i] : 0u;
         uint32_t inc = v;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
@@ -99,7 +116,7 @@ __global__ __launch_bounds__(1024) void scan_counts_kernel(uint32_t *cnt, uint32
             if (w == wave) before = total;
             total += s_wave[w];
         }
-        if (i < num_tiles) cnt[i] = running + before + inc - v;
+        if (i < num_groups) cnt[i] = running + before + inc - v;
         running += total;
         __syncthreads();
     }
@@ -129,40 +146,17 @@ __global__ __launch_bounds__(256) void pack_flags_kernel(const uint8_t *f, uint6
     }
 }
 
-// One wave looks at 512 pairs of neighbouring column indices spread over the matrix and notes in the
-// (zeroed) workspace header whether most of them are consecutive, as in blocked and banded matrices.
-__device__ __forceinline__ void sample_column_runs(const int32_t *col, uint64_t nnz, uint32_t *hdr, int lane) {
-    const uint64_t stride = nnz / 512 > 0 ? nnz / 512 : 1;
-    uint32_t runs = 0, pairs = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const uint64_t p = (uint64_t)(lane * 8 + j) * stride;
-        if (p + 1 < nnz) {
-            ++pairs;
-            runs += col[p + 1] == col[p] + 1 ? 1u : 0u;
-        }
-    }
-    runs = wave_sum(runs);
-    pairs = wave_sum(pairs);
-    if (lane == 0 && 2 * runs > pairs) hdr[kHdrColumnRuns] = 1u;
-}
-
 // Segment-start flags of a row-sorted COO matrix, f(e) = [e == 0 or row(e) != row(e-1)], bit-packed; the same
 // launch zero fills the workspace words (header, descriptors) and y.  A wave takes 2048 entries: every lane reads
 // eight times four consecutive indices (all loads in flight at once), compares them with their left neighbours
 // (the lane before it holds the one before its first: a DPP move), and eight lanes OR their nibbles into one
 // flag word (DPP again; no LDS traffic).
 __global__ __launch_bounds__(256) void row_flags_kernel(const int32_t *row, uint64_t nnz, uint32_t *words,
-                                                        const int32_t *col, uint32_t *ws, uint64_t ws_words, uint32_t *y,
-                                                        uint64_t n_rows) {
+                                                        uint32_t *ws, uint64_t ws_words, uint32_t *y, uint64_t n_rows) {
     const int lane = threadIdx.x & 63;
     const uint64_t stride = (uint64_t)gridDim.x * 256;
     for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < ws_words; i += stride) ws[i] = 0;
     for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n_rows; i += stride) y[i] = 0;
-    if (blockIdx.x == 0) {   // (workgroup 0 has zeroed the header words itself)
-        __syncthreads();
-        if (threadIdx.x < 64) sample_column_runs(col, nnz, ws, lane);
-    }
     const uint64_t wave0 = ((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 2048;   // eight rounds of 256 entries
     if (wave0 >= nnz) return;
     v4i r[8];
@@ -200,36 +194,45 @@ __global__ __launch_bounds__(256) void row_flags_kernel(const int32_t *row, uint
 // Row pointers of a CSR matrix -> (a) bit-packed segment-start flags over the non-zeros (a row
 // with entries sets the bit of its first entry; rows that share a word meet in an atomic OR on
 // a zeroed word), (b) the bit-packed mask of rows that have entries (one ballot per 64 rows),
-// (c) the number of segment starts inside every tile of the main kernel (position 0 not counted,
-// as in count_tiles_kernel; the rows of a wave that start in the same tile share one atomic add
-// on a zeroed table) and (d) the mark that some row is empty.
+// (c) the number of segment starts inside every wave span of the main kernel and every group of its tiles (as in
+// count_spans_kernel; the rows of a wave that start in the same span share the atomic adds
+// on zeroed tables) and (d) the mark that some row is empty.
 __global__ __launch_bounds__(256) void csr_flags_kernel(const int32_t *rowptr, uint64_t n_rows, uint32_t *fw,
                                                         uint32_t *rowmask, uint32_t *hdr, TileRegions reg, uint32_t unit,
-                                                        uint32_t *tile_count, const int32_t *col, uint64_t nnz) {
+                                                        uint32_t *group_count, uint32_t *span_count) {
     const int lane = threadIdx.x & 63;
-    if (blockIdx.x == 0 && threadIdx.x < 64) sample_column_runs(col, nnz, hdr, lane);
     const uint64_t r = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     bool nonempty = false;
-    uint32_t tile = 0xFFFFFFFFu;   // tile of the first entry of a row that is counted
+    uint32_t mine = 0xFFFFFFFFu;   // span (of all tiles) of the first entry of a row that is counted
     if (r < n_rows) {
         const int32_t a = rowptr[r], b = rowptr[r + 1];
         nonempty = b > a;
         if (nonempty) {
             atomicOr(fw + ((uint32_t)a >> 5), 1u << ((uint32_t)a & 31u));
-            if (a > 0) tile = tile_of_element(reg, (uint64_t)a, unit);
+            if (a > 0) {
+                const uint32_t tile = tile_of_element(reg, (uint64_t)a, unit);
+                const TileSpan ts = tile_span(reg, tile, unit);
+                mine = tile * kSpans + ((uint32_t)((uint64_t)a - ts.base)) / (ts.cpw * (unit / kSpans));
+            }
         }
     }
     const uint64_t m = __ballot(nonempty);
     // a matrix none of whose rows is empty needs no row map: segment k is row k
     if (__ballot(r < n_rows && !nonempty) != 0 && lane == 0) hdr[kHdrEmptyRows] = 1u;
-    uint64_t todo = __ballot(tile != 0xFFFFFFFFu);
-    while (todo) {   // one round per distinct tile among the rows of the wave
-        const int first = __ffsll((unsigned long long)todo) - 1;
-        const uint32_t t = __shfl(tile, first);
-        const uint64_t same = __ballot(tile == t);
-        if (lane == first) atomicAdd(tile_count + t, (uint32_t)__popcll((unsigned long long)same));
-        todo &= ~same;
-    }
+    // one atomic add per distinct span among the rows of the wave, and one per distinct group (adds to one address are
+    // served one after the other, about 11 ns each)
+    auto add_distinct = [&](uint32_t key, uint32_t *table) {
+        uint64_t todo = __ballot(key != 0xFFFFFFFFu);
+        while (todo) {
+            const int first = __ffsll((unsigned long long)todo) - 1;
+            const uint32_t t = __shfl(key, first);
+            const uint64_t same = __ballot(key == t);
+            if (lane == first) atomicAdd(table + t, (uint32_t)__popcll((unsigned long long)same));
+            todo &= ~same;
+        }
+    };
+    add_distinct(mine, span_count);
+    add_distinct(mine == 0xFFFFFFFFu ? mine : mine / kGroupSpans, group_count);
     const uint64_t r0 = r - lane;
     if (lane == 0 && r0 < n_rows) {
         rowmask[r0 >> 5] = (uint32_t)m;

@@ -25,12 +25,10 @@ constexpr uint64_t kResident = MMV_MIN_TILES;   // workgroups resident at once (
 #ifndef MMV_TAIL_TILES
 #define MMV_TAIL_TILES 128   // tiles of one chunk per wave at the very end (the last of them is ragged)
 #endif
-// Up to this many tiles the segmented sum needs no prefix kernel: every wave of the main kernel adds up the counts of
-// the tiles before its own.  That loop costs in proportion to the number of tiles (1224 tiles: 5.6 us of a 42 us
-// kernel; 2448: 15 us), the prefix kernel 3 us of the call.
-constexpr uint64_t kCountSumTiles = 768;
-// CSR SpMV: one wave per tile adds up (959 tiles: the loop 1.4 us of the kernel, the prefix kernel 3 us of the call)
-constexpr uint64_t kCountSumTilesCsr = 2048;
+// Up to this many groups of eight tiles the segmented sum and CSR SpMV need no prefix kernel: every wave of the main
+// kernel adds up the counts of the groups before its own, eight loads per lane at most, four of them under way at a time.
+constexpr uint64_t kCountGroups = 512;
+inline uint64_t groups_of(uint64_t tiles) { return (tiles + kGroupTiles - 1) / kGroupTiles; }
 inline bool is_spmv(mmv_op op) { return op == MMV_OP_SPMV_COO || op == MMV_OP_SPMV_CSR; }
 // Most chunks per wave of the tile body that carries its pair from row to row (seg_tile): what the kernel
 // instantiation for this operation, type and variant is built with.
@@ -42,7 +40,6 @@ template <typename TT> inline int row_form_cpw_of(mmv_op op, bool mfma) {
     }
 }
 inline int row_form_cpw(mmv_op op, mmv_dtype dt, bool mfma) {
-    if (is_spmv(op)) return TSpmv::kMaxCpw;
     switch (dt) {
         case MMV_F32_F32: return row_form_cpw_of<TF32>(op, mfma);
         case MMV_F16_F32: return row_form_cpw_of<TF16>(op, mfma);
@@ -79,12 +76,31 @@ inline int waves_of(mmv_op op, mmv_dtype dt) {
 struct TilePlan {
     TileRegions reg;
     uint64_t tiles;        // all tiles (reg.num_tiles holds it when it fits 31 bits)
-    uint32_t unit;         // elements of one chunk per wave
+    uint32_t unit;         // elements that one step of a region's `cpw` stands for: one chunk per wave (stream form: one unit of 1024)
     uint32_t body_elems;   // elements of a tile in the middle of the vector
     bool chunk_form;       // segmented sum: the kernel that streams through long spans (sum_kernel) takes it
 };
 inline TilePlan tile_plan(mmv_op op, mmv_dtype dt, uint64_t n, bool mfma = true) {
     TilePlan p = {};
+    TileRegions &R = p.reg;
+    if (is_spmv(op) || (op == MMV_OP_SEGSUM && dt == MMV_F32_F32)) {   // (stream_form)
+        // Equal tiles, and as many as a whole number of rounds of resident workgroups takes (or nearly): where every
+        // compute unit is busy with gathers all the time, one that holds three tiles when others hold two finishes last
+        // (SpMV of 2^25 scattered entries: 683 tiles 0.238 ms, 763 tiles 0.213 ms; shorter tiles for the last 5 to 20 % of
+        // the vector make sums and SpMV 1 to 10 % slower).  A tile has at least one unit per wave.
+        const uint64_t resident = 128 * (uint64_t)stream_waves_per_simd(is_spmv(op) ? kSpmv : kSum, mfma);
+        const uint64_t units = (n + kUnitElems - 1) / kUnitElems;
+        const uint64_t rounds = (units + resident * kMaxUnits - 1) / (resident * kMaxUnits);
+        uint64_t c = rounds ? (units + resident * rounds - 1) / (resident * rounds) : 1;
+        if (c < kSpans) c = kSpans;
+        p.unit = kUnitElems;
+        p.body_elems = (uint32_t)(c * kUnitElems);
+        R.cpw[0] = (uint32_t)c;
+        R.count = 1;
+        p.tiles = (units + c - 1) / c;
+        R.num_tiles = (uint32_t)(p.tiles < 0x7fffffffull ? p.tiles : 0x7fffffffull);
+        return p;
+    }
     const uint64_t unit = (uint64_t)waves_of(op, dt) * kChunkElems;  // one chunk per wave
     // A sum that fits one round of workgroups is bound by the life of one tile, and the tile that holds all its
     // values, publishes its aggregate and then walks its ends has the shorter life (workload 2, fp16 2^24: 12.4
@@ -94,7 +110,6 @@ inline TilePlan tile_plan(mmv_op op, mmv_dtype dt, uint64_t n, bool mfma = true)
     p.chunk_form = chunk_cpw > 0 && (MMV_SHORT_SUMS_ROW_FORM == 0 || n > MMV_SHORT_SUMS_ROW_FORM * kResident * unit * (uint64_t)cpw);
     if (p.chunk_form) cpw = chunk_cpw;
     p.unit = (uint32_t)unit;
-    TileRegions &R = p.reg;
     uint64_t tiles = 0, at = 0;
     auto add = [&](uint32_t c, uint64_t count) {   // `count` tiles of c chunks per wave from element `at` on
         if (count == 0) return;
@@ -165,10 +180,10 @@ WsLayout ws_layout(mmv_op op, mmv_dtype dt, mmv_flag_fmt ff, uint64_t n) {
     size_t off = kHdrBytes;
     L.desc_v = off;
     off += round256(t * 8);
-    L.desc_c = off;   // counts of segment starts: per tile, and (segmented sum) per wave span
-    if (op == MMV_OP_SEGSUM || op == MMV_OP_SPMV_CSR) off += round256(t * 8);
+    L.desc_c = off;   // counts of segment starts: per group of tiles, and per wave span
+    if (op == MMV_OP_SEGSUM || op == MMV_OP_SPMV_CSR) off += round256(groups_of(t) * 4);
     L.span_c = off;
-    if (op == MMV_OP_SEGSUM) off += round256(t * 4 * (uint64_t)waves_of(op, dt));
+    if (op == MMV_OP_SEGSUM || op == MMV_OP_SPMV_CSR) off += round256(t * 4 * kSpans);
     L.packed = off;
     if (is_spmv(op) || (ff == MMV_FLAGS_U8 && op != MMV_OP_SCAN)) off += round256(((n + 63) / 64) * 8);
     L.total = off;
@@ -284,17 +299,23 @@ uint32_t resident_workgroups(const void *kernel, int threads, std::atomic<uint32
 
 template <typename TT, int kOp, bool kMfma> hipError_t launch_variant(Params P, bool chunk_form, hipStream_t s) {
     static std::atomic<uint32_t> occupancy[2][kMaxDevices];
-    void (*kernel)(Params, const uint32_t *) = seg_kernel<TT, kOp, kMfma>;
-    if constexpr (chunk_sum_kernel<TT, kOp, kMfma>()) {
-        if (chunk_form) kernel = sum_kernel<TT, kMfma>;
+    void (*kernel)(Params, const uint32_t *);
+    int which = 0;
+    if constexpr (stream_form<TT, kOp>()) {
+        kernel = stream_kernel<TT, kOp, kMfma, true>;
+        if constexpr (kOp != kSum) {
+            which = P.cols_narrow ? 0 : 1;
+            if (!P.cols_narrow) kernel = stream_kernel<TT, kOp, kMfma, false>;
+        }
+    } else {
+        kernel = seg_kernel<TT, kOp, kMfma>;
+        if constexpr (chunk_sum_kernel<TT, kOp, kMfma>()) {
+            which = chunk_form ? 1 : 0;
+            if (chunk_form) kernel = sum_kernel<TT, kMfma>;
+        }
     }
-    const uint32_t resident = resident_workgroups((const void *)kernel, TT::kWaves * 64, occupancy[chunk_form ? 1 : 0]);
+    const uint32_t resident = resident_workgroups((const void *)kernel, TT::kWaves * 64, occupancy[which]);
     P.first_round = P.num_tiles < resident ? P.num_tiles : resident;
-    // SpMV: the workgroups of the first round start spread over about one tile time.  Started together
-    // they stay in step (load, gather, compute all at the same time) and the memory pipe idles half the
-    // time; measured 4 to 7 % on the long SpMV kernels, nothing on the scans.
-    P.stagger_wgs = resident;
-    P.stagger_ticks = ((kOp == kSpmv || kOp == kSpmvCsr) && P.num_tiles > resident) ? MMV_SPMV_STAGGER_US * 100u : 0u;
     kernel<<<P.num_tiles, TT::kWaves * 64, 0, s>>>(P, P.hdr + kHdrHints);
     return hipGetLastError();
 }

@@ -132,4 +132,24 @@ __device__ T lookback(const uint64_t *desc, int tile, int lane, uint32_t *hdr) {
     return lookback_from<T, kAlu, 0>(desc, tile, lane, hdr, nullptr);
 }
 
+// Number of segment starts before span `sp` (of all tiles; a multiple of kSpans: before that tile), from the counts
+// per group of tiles and per span.  Wave-wide in two halves, so that the loads can go out ahead of others: the lane's
+// part, and their sum.
+__device__ __forceinline__ uint32_t starts_before_part(const Params &P, uint32_t sp, int lane) {
+    const uint32_t g = sp / kGroupSpans;
+    uint32_t part = 0;
+    if (lane < (int)(sp % kGroupSpans)) part = P.span_count[g * kGroupSpans + lane];
+    if (P.count_is_prefix) {
+        if (lane == 0) part += P.group_count[g];
+    } else {
+        for (uint32_t i = lane; i < g; i += 256) {   // four loads under way at a time
+            uint32_t v[4];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) v[j] = i + 64 * j < g ? P.group_count[i + 64 * j] : 0u;
+            part += (v[0] + v[1]) + (v[2] + v[3]);
+        }
+    }
+    return part;
+}
+
 }  // namespace

@@ -21,10 +21,11 @@
 //
 // Layout of a workgroup tile: 8 waves x (1 to 4) chunks x 64 rows x 32 elements.
 // Lane r of a wave owns row r of the wave's current 2048-element chunk for steps 3-5;
-// one packed flag word is exactly one row.
+// one packed flag word is exactly one row.  Sums of 32-bit values and SpMV (stream_kernel) and long sums of 8- and 16-bit
+// values (sum_kernel) have tile bodies of their own.
 //
 // Small kernels around it: workspace reset, flag packing (bytes, COO row indices, CSR row
-// pointers), per-tile counts of segment starts (the output positions of the segmented sum),
+// pointers), counts of segment starts per wave span (the output positions of the segmented sum),
 // COMPRESS, DIFF, REVERT, and two reference kernels for the benchmark: a streaming copy
 // (bandwidth) and a gather of x[col] (what the random accesses of SpMV cost on their own).
 #include <hip/hip_runtime.h>
@@ -41,6 +42,7 @@
 #include "tile_math.h"
 #include "seg_kernel.h"
 #include "sum_kernel.h"
+#include "stream_kernel.h"
 #include "seg_entry.h"
 #include "aux_kernels.h"
 #include "primitives.h"
@@ -148,23 +150,22 @@ mmv_status mmv_segsum(const void *d_x, const void *d_flags, uint64_t n, void *d_
     P.out = d_out;
     P.out_cap = out_capacity;
     P.nseg = d_nseg;
-    // number of segment starts before every tile: per-tile counts, then their exclusive scan
+    // number of segment starts per span and per group of tiles
     const TilePlan plan = tile_plan(MMV_OP_SEGSUM, dt, n, v == MMV_VARIANT_MFMA);
     const WsLayout L = ws_layout(MMV_OP_SEGSUM, dt, ff, n);
-    uint32_t *tile_count = (uint32_t *)((char *)d_ws + L.desc_c);
     if (plan.tiles > 0x7fffffffull) return MMV_ERR_INVALID_ARG;
+    uint32_t *group_count = (uint32_t *)((char *)d_ws + L.desc_c);
     uint32_t *span_count = (uint32_t *)((char *)d_ws + L.span_c);
-    count_tiles_kernel<<<(unsigned)plan.tiles, 256, 0, s>>>((uint32_t *)d_ws, L.desc_c / 4, P.fw, n, plan.reg,
-                                                             plan.unit, tile_count, span_count);
+    const uint64_t groups = groups_of(plan.tiles);
+    count_spans_kernel<<<(unsigned)groups, 1024, 0, s>>>((uint32_t *)d_ws, L.desc_c / 4, P.fw, n, plan.reg, plan.unit,
+                                                          group_count, span_count);
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
-    // few tiles: every tile of the main kernel adds up the counts before it; many: one more small kernel
-    // turns the counts into prefix sums first
-    P.count_is_prefix = plan.tiles > kCountSumTiles ? 1u : 0u;
+    P.count_is_prefix = groups > kCountGroups ? 1u : 0u;
     if (P.count_is_prefix) {
-        scan_counts_kernel<<<1, 1024, 0, s>>>(tile_count, (uint32_t)plan.tiles, d_nseg);
+        scan_counts_kernel<<<1, 1024, 0, s>>>(group_count, (uint32_t)groups, d_nseg);
         if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     }
-    P.tile_count = tile_count;
+    P.group_count = group_count;
     P.span_count = span_count;
     return launch_dt<kSum>(P, dt, v, s) == hipSuccess ? MMV_OK : MMV_ERR_HIP;
 }
@@ -192,6 +193,7 @@ mmv_status mmv_spmv_coo(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
     P.row = d_row;
     P.col = d_col;
     P.xv = d_x;
+    P.cols_narrow = n_cols <= (1ull << 30) ? 1u : 0u;
     P.y = d_y;
     P.hdr = (uint32_t *)ws;
     P.desc_v = (uint64_t *)(ws + L.desc_v);
@@ -203,15 +205,17 @@ mmv_status mmv_spmv_coo(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
     if (flag_blocks > 0x7fffffffull) return MMV_ERR_INVALID_ARG;
     const uint64_t fill_blocks = (uint64_t)grid_for(zero_words > n_rows ? zero_words : n_rows);   // (few entries, many rows)
     if (flag_blocks < fill_blocks) flag_blocks = fill_blocks;
-    row_flags_kernel<<<(unsigned)flag_blocks, 256, 0, s>>>(d_row, nnz, (uint32_t *)(ws + L.packed), d_col, (uint32_t *)ws,
+    row_flags_kernel<<<(unsigned)flag_blocks, 256, 0, s>>>(d_row, nnz, (uint32_t *)(ws + L.packed), (uint32_t *)ws,
                                                            zero_words, (uint32_t *)d_y, n_rows);
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     return launch_seg<TSpmv, kSpmv>(P, v, s) == hipSuccess ? MMV_OK : MMV_ERR_HIP;
 }
 
-// SpMV in two steps: the mark that the first step leaves in the header for this matrix shape (never 0).
+// SpMV in two steps: the mark that the first step leaves in the header for this matrix shape (never 0).  It names the
+// layout of the counts as well (kPlanLayout), which the product kernel relies on.
+static constexpr uint64_t kPlanLayout = 2;
 static uint32_t prepared_mark(mmv_op op, uint64_t n_rows, uint64_t nnz) {
-    uint64_t h = (nnz + 0x9E3779B97F4A7C15ull) * 0xD6E8FEB86659FD93ull + n_rows * 0xCA5A826395121157ull + (uint64_t)op;
+    uint64_t h = (nnz + 0x9E3779B97F4A7C15ull) * 0xD6E8FEB86659FD93ull + n_rows * 0xCA5A826395121157ull + (uint64_t)op + (kPlanLayout << 32);
     h ^= h >> 32;
     return (uint32_t)h | 1u;
 }
@@ -231,7 +235,7 @@ mmv_status mmv_spmv_coo_prepare(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, 
     if (flag_blocks > 0x7fffffffull) return MMV_ERR_INVALID_ARG;
     const uint64_t fill_blocks = (uint64_t)grid_for(zero_words);
     if (flag_blocks < fill_blocks) flag_blocks = fill_blocks;
-    row_flags_kernel<<<(unsigned)flag_blocks, 256, 0, s>>>(d_row, nnz, (uint32_t *)(ws + L.packed), d_col, (uint32_t *)ws,
+    row_flags_kernel<<<(unsigned)flag_blocks, 256, 0, s>>>(d_row, nnz, (uint32_t *)(ws + L.packed), (uint32_t *)ws,
                                                            zero_words, nullptr, 0);
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     mark_prepared_kernel<<<1, 64, 0, s>>>((uint32_t *)ws, prepared_mark(MMV_OP_SPMV_COO, n_rows, nnz));
@@ -261,6 +265,7 @@ mmv_status mmv_spmv_coo_run(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, cons
     P.row = d_row;
     P.col = d_col;
     P.xv = d_x;
+    P.cols_narrow = n_cols <= (1ull << 30) ? 1u : 0u;
     P.y = d_y;
     P.hdr = (uint32_t *)ws;
     P.desc_v = (uint64_t *)(ws + L.desc_v);
@@ -428,11 +433,11 @@ mmv_status mmv_spmv_csr(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
     // rows that have entries
     const TilePlan plan = tile_plan(MMV_OP_SPMV_CSR, MMV_F32_F32, nnz);
     uint32_t *fw = (uint32_t *)(ws + C.main_ws + L.packed);
-    uint32_t *tile_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
+    uint32_t *group_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
     const uint64_t row_blocks = (n_rows + 255) / 256;
     csr_flags_kernel<<<(unsigned)row_blocks, 256, 0, s>>>(d_rowptr, n_rows, fw, (uint32_t *)(ws + C.rowmask),
                                                           (uint32_t *)(ws + C.main_ws), plan.reg, plan.unit,
-                                                          tile_count, d_col, nnz);
+                                                          group_count, (uint32_t *)(ws + C.main_ws + L.span_c));
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     // rowmap = COMPRESS(0 .. n_rows - 1, rowmask): the k-th segment belongs to row rowmap[k]
     {
@@ -448,18 +453,20 @@ mmv_status mmv_spmv_csr(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
     P.n = nnz;
     P.col = d_col;
     P.xv = d_x;
+    P.cols_narrow = n_cols <= (1ull << 30) ? 1u : 0u;
     P.y = d_y;
     P.rowmap = (const uint32_t *)(ws + C.rowmap);
     P.out_cap = n_rows;
     P.hdr = (uint32_t *)(ws + C.main_ws);
     P.desc_v = (uint64_t *)(ws + C.main_ws + L.desc_v);
     P.fw = fw;
-    P.count_is_prefix = plan.tiles > kCountSumTilesCsr ? 1u : 0u;
+    P.count_is_prefix = groups_of(plan.tiles) > kCountGroups ? 1u : 0u;
     if (P.count_is_prefix) {
-        scan_counts_kernel<<<1, 1024, 0, s>>>(tile_count, (uint32_t)plan.tiles, (uint64_t *)(ws + C.rowcount));
+        scan_counts_kernel<<<1, 1024, 0, s>>>(group_count, (uint32_t)groups_of(plan.tiles), (uint64_t *)(ws + C.rowcount));
         if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     }
-    P.tile_count = tile_count;
+    P.group_count = group_count;
+    P.span_count = (const uint32_t *)(ws + C.main_ws + L.span_c);
     return launch_seg<TSpmv, kSpmvCsr>(P, v, s) == hipSuccess ? MMV_OK : MMV_ERR_HIP;
 }
 
@@ -479,11 +486,11 @@ mmv_status mmv_spmv_csr_prepare(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, 
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     const TilePlan plan = tile_plan(MMV_OP_SPMV_CSR, MMV_F32_F32, nnz);
     uint32_t *fw = (uint32_t *)(ws + C.main_ws + L.packed);
-    uint32_t *tile_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
+    uint32_t *group_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
     const uint64_t row_blocks = (n_rows + 255) / 256;
     csr_flags_kernel<<<(unsigned)row_blocks, 256, 0, s>>>(d_rowptr, n_rows, fw, (uint32_t *)(ws + C.rowmask),
                                                           (uint32_t *)(ws + C.main_ws), plan.reg, plan.unit,
-                                                          tile_count, d_col, nnz);
+                                                          group_count, (uint32_t *)(ws + C.main_ws + L.span_c));
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     {
         EventsOff quiet;
@@ -493,8 +500,8 @@ mmv_status mmv_spmv_csr_prepare(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, 
                                             (const uint32_t *)(ws + C.main_ws) + kHdrEmptyRows);
         if (st != MMV_OK) return st;
     }
-    if (plan.tiles > kCountSumTilesCsr) {
-        scan_counts_kernel<<<1, 1024, 0, s>>>(tile_count, (uint32_t)plan.tiles, (uint64_t *)(ws + C.rowcount));
+    if (groups_of(plan.tiles) > kCountGroups) {
+        scan_counts_kernel<<<1, 1024, 0, s>>>(group_count, (uint32_t)groups_of(plan.tiles), (uint64_t *)(ws + C.rowcount));
         if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     }
     mark_prepared_kernel<<<1, 64, 0, s>>>((uint32_t *)(ws + C.main_ws), prepared_mark(MMV_OP_SPMV_CSR, n_rows, nnz));
@@ -526,14 +533,16 @@ mmv_status mmv_spmv_csr_run(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, cons
     P.n = nnz;
     P.col = d_col;
     P.xv = d_x;
+    P.cols_narrow = n_cols <= (1ull << 30) ? 1u : 0u;
     P.y = d_y;
     P.rowmap = (const uint32_t *)(ws + C.rowmap);
     P.out_cap = n_rows;
     P.hdr = (uint32_t *)(ws + C.main_ws);
     P.desc_v = (uint64_t *)(ws + C.main_ws + L.desc_v);
     P.fw = (const uint32_t *)(ws + C.main_ws + L.packed);
-    P.count_is_prefix = plan.tiles > kCountSumTilesCsr ? 1u : 0u;
-    P.tile_count = (const uint32_t *)(ws + C.main_ws + L.desc_c);
+    P.count_is_prefix = groups_of(plan.tiles) > kCountGroups ? 1u : 0u;
+    P.group_count = (const uint32_t *)(ws + C.main_ws + L.desc_c);
+    P.span_count = (const uint32_t *)(ws + C.main_ws + L.span_c);
     P.prepared = prepared_mark(MMV_OP_SPMV_CSR, n_rows, nnz);
     // header and value descriptors of the main kernel; the counts, flag words, row mask and row map behind them stay
     const uint64_t zero_words = L.desc_c / 4;

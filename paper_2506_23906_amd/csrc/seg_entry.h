@@ -15,13 +15,6 @@ template <typename Shared> __device__ __forceinline__ uint32_t take_tile(const P
     if (threadIdx.x == 0) {
         sm.ready = 0;
         sm.arrived = 0;
-        if (blockIdx.x < P.stagger_wgs && P.stagger_ticks) {
-            // low-discrepancy spread of the start times: fraction of blockIdx * golden ratio
-            const uint32_t frac = blockIdx.x * 2654435769u;
-            const uint64_t wait = ((uint64_t)frac * P.stagger_ticks) >> 32;
-            const uint64_t t0 = wall_clock64();
-            while (wall_clock64() - t0 < wait) __builtin_amdgcn_s_sleep(8);
-        }
         if (!own_index)
             sm.tile = P.first_round +
                       __hip_atomic_fetch_add(P.hdr + kHdrTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -31,32 +24,15 @@ template <typename Shared> __device__ __forceinline__ uint32_t take_tile(const P
 }
 
 template <typename TT, int kOp, bool kMfma>
-__global__ __launch_bounds__(TT::kWaves * 64, MMV_MIN_WAVES_PER_SIMD) void seg_kernel(Params P, const uint32_t *__restrict__ hints) {
+__global__ __launch_bounds__(TT::kWaves * 64, MMV_MIN_WAVES_PER_SIMD) void seg_kernel(Params P, const uint32_t *__restrict__) {
     __shared__ SegShared<TT::kWaves> sm;
-    constexpr bool kProduct = kOp == kSpmv || kOp == kSpmvCsr;
     // A workgroup that starts competes with the ones in the middle of their arithmetic: its ticket
     // and its loads go first (measured: 2 to 3 % on the long scans)
 #if MMV_LOAD_PRIO
     __builtin_amdgcn_s_setprio(MMV_LOAD_PRIO);
 #endif
-    // SpMV, where neighbouring entries mostly sit in consecutive columns (blocked, banded matrices): the
-    // gathers are cheap and the memory pipe is the limit, so the values are loaded behind the gathers
-    // instead of beside the columns: half the burst at the start of the tile, the columns arrive
-    // sooner (measured 11-15 % on the blocked sparse-attention matrices).  With scattered columns the
-    // gathers are the limit and values loaded that late only add to their burst (4-8 % slower).
-    // Uniform words, written by the kernel that makes the flags.
-    bool late_val = false;
-    if constexpr (kProduct) {
-        // SpMV in two steps: without the mark of the preparing call for this matrix the flags, counts and row map of
-        // the workspace are not to be trusted (the reset launch has put that into the status word)
-        if (P.prepared && hints[kHdrPrepared - kHdrHints] != P.prepared) return;
-        late_val = hints[kHdrColumnRuns - kHdrHints] != 0;
-    }
     const uint32_t tile = take_tile(P, sm);
-    if (kProduct && late_val)
-        seg_tile<TT, kOp, kMfma, kProduct>(P, hints, sm, tile);
-    else
-        seg_tile<TT, kOp, kMfma, false>(P, hints, sm, tile);
+    seg_tile<TT, kOp, kMfma>(P, sm, tile);
 }
 
 // The segmented sum of 8- and 16-bit inputs (speculation over whole chunks): its waves keep less in LDS and in
@@ -69,6 +45,22 @@ __global__ __launch_bounds__(TT::kWaves * 64, sum_waves_per_simd<TT>()) void sum
 #endif
     const uint32_t tile = take_tile(P, sm);
     sum_tile<TT, kMfma>(P, sm, tile);
+}
+
+// The segmented sum of 32-bit values and SpMV.
+template <typename TT, int kOp, bool kMfma, bool kNarrow>
+__global__ __launch_bounds__(TT::kWaves * 64, stream_waves_per_simd(kOp, kMfma)) void stream_kernel(Params P, const uint32_t *__restrict__ hints) {
+    __shared__ StreamShared<TT::kWaves> sm;
+#if MMV_LOAD_PRIO
+    __builtin_amdgcn_s_setprio(MMV_LOAD_PRIO);
+#endif
+    // SpMV in two steps: without the mark of the preparing call for this matrix the flags, counts and row map of
+    // the workspace are not to be trusted (the reset launch has put that into the status word)
+    if constexpr (kOp != kSum) {
+        if (P.prepared && hints[kHdrPrepared - kHdrHints] != P.prepared) return;
+    }
+    const uint32_t tile = take_tile(P, sm);
+    stream_tile<TT, kOp, kMfma, kNarrow>(P, hints, sm, tile);
 }
 
 }  // namespace

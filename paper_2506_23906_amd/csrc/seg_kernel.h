@@ -1,5 +1,5 @@
 // libmmvseg, part of the one translation unit mmvseg.hip (included there, in order).
-// The single-pass kernel: segmented scan, segmented sum, SpMV (COO and CSR) and the unsegmented scan.
+// The single-pass kernel: segmented scan, the unsegmented scan, and the segmented sum of short vectors of 8- and 16-bit values.
 #pragma once
 
 namespace {
@@ -47,11 +47,9 @@ template <int kWaves> struct SegShared {
     uint32_t tile, carry_v, carry_c, ready, arrived;
 };
 
-// One tile, from the loads on.  kLateVal (SpMV only): the values are loaded behind the gathers of
-// x[col] instead of beside the columns.
-template <typename TT, int kOp, bool kMfma, bool kLateVal>
-__device__ __forceinline__ void seg_tile(const Params &P, const uint32_t *__restrict__ hints, SegShared<TT::kWaves> &sm,
-                                         const uint32_t tile) {
+// One tile, from the loads on.
+template <typename TT, int kOp, bool kMfma>
+__device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves> &sm, const uint32_t tile) {
     typedef typename TT::acc_t A;
     typedef typename TT::in_t In;
     constexpr int kWaves = TT::kWaves;
@@ -61,12 +59,12 @@ __device__ __forceinline__ void seg_tile(const Params &P, const uint32_t *__rest
     // The chunk loops are either rolled, with the per-chunk registers rotated so that the body always
     // works on the first slot(s) (about 45 moves per rotation and phase, small code), or unrolled.  Unrolled, the
     // scan kernels spill registers (measured: 100 to 700 bytes per lane) and so does the shuffle-only
-    // int8 sum kernel with its four chunks; the other sum / SpMV kernels do not.
+    // int8 sum kernel with its four chunks; the other sum kernels do not.
     constexpr bool kUnrollChunks = MMV_UNROLL_CHUNKS != 0 && !kScanLike && (kMfma || kCpw <= 2);
     // chunks per iteration of the chunk loops: all (unrolled), or MMV_ROLL_STEP with the registers
     // rotated by as many slots afterwards (the moves of a rotation do not depend on the distance)
     constexpr int kStep = kUnrollChunks ? kCpw : (kCpw >= 2 * MMV_ROLL_STEP && kCpw % MMV_ROLL_STEP == 0 ? MMV_ROLL_STEP : 1);
-    // A wave with a single chunk (fp32, SpMV) keeps the row scans of phase A in its LDS rows for
+    // A wave with a single chunk (fp32) keeps the row scans of phase A in its LDS rows for
     // phase B instead of making them a second time; with more chunks LDS holds only the last one made.
     // Matrix-core variant only: there it saves the second 3-way split and 50 registers (fp32 scan
     // 4-5 % faster); in the shuffle variant the same change was measured 3 % slower.
@@ -74,16 +72,15 @@ __device__ __forceinline__ void seg_tile(const Params &P, const uint32_t *__rest
     // lane exchanges through the vector ALU for the sum-type kernels and the 16-bit scans (measured 2 %
     // faster), through the LDS hardware for the int8 and fp32 scans (0.9 % faster / no difference)
     constexpr bool kAluLanes = MMV_DPP_SCAN != 0 && (!kScanLike || TT::kEpl == 8);
-    constexpr bool kCounts = kOp == kSum || kOp == kSpmvCsr;        // output index = segment ordinal
+    constexpr bool kCounts = kOp == kSum;        // output index = segment ordinal
     // A chunk in which every position starts a segment is its own result (Algorithm "Revert Speculative
     // Prefix Sums", the case of all flags set, taken here for 64 rows at once): with 32-bit inputs and one
     // chunk per wave the striped registers are stored as they are, straight after the load (all-flag
     // vectors 8 % faster).  Matrix-core variant only: in the other one the test cost 1 % on vectors without
     // such chunks and gained 2 % on those with.
     constexpr bool kDenseShortcut = MMV_DENSE_SHORTCUT != 0 && kOp == kScan && sizeof(In) == 4 && kKeepRows;
-    // the count of the segments before the tile comes from a table of per-tile counts made by a
-    // small kernel before this one, so that no chunk has to wait for it
-    constexpr bool kProduct = kOp == kSpmv || kOp == kSpmvCsr;      // values are val * x[col]
+    // (the count of the segments before the tile comes from tables made by a
+    // small kernel before this one, so that no chunk has to wait for it)
     // A tile that holds no flag hands on a plain sum, and its successors cannot finish before they have it.  In the
     // scan kernels such a tile publishes that sum as soon as its loads have landed, ahead of the row scans of
     // phase A (which take several microseconds when all waves of a compute unit are at it): the wave whose loads
@@ -114,10 +111,9 @@ __device__ __forceinline__ void seg_tile(const Params &P, const uint32_t *__rest
     const uint64_t tile_base = span.base;
     const uint64_t wave_base = tile_base + (uint64_t)wave * cpw_t * kChunkElems;
 
-    // ---- all inputs of my span: flag word of my row and raw values (and columns) per chunk ----
+    // ---- all inputs of my span: flag word of my row and raw values per chunk ----
     uint32_t F[kCpw];
     v4u raw[kCpw][2 * K];
-    v4u rawc[kProduct ? kCpw : 1][2 * K];  // column indices (spmv)
     v4u striped[kExactStarts && kKeepRows ? 2 * K : 1];   // the loaded words as they came, where phase A reorders raw[]
     // (the flag words go first: a wave knows whether its span holds a flag before the values have landed)
 #pragma unroll
@@ -131,10 +127,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, const uint32_t *__rest
 #pragma unroll
     for (int c = 0; c < kCpw; ++c) {
         const uint64_t cb = wave_base + (uint64_t)c * kChunkElems;
-        if (c < cpw_t) {
-            if constexpr (kProduct) load_raw<TInt, kMfma>(P.col, cb, n, lane, rawc[c]);
-            if constexpr (!kProduct || !kLateVal) load_raw<TT, kMfma>((const In *)P.x, cb, n, lane, raw[c]);
-        }
+        if (c < cpw_t) load_raw<TT, kMfma>((const In *)P.x, cb, n, lane, raw[c]);
     }
 
 #if MMV_LOAD_PRIO
@@ -197,20 +190,11 @@ __device__ __forceinline__ void seg_tile(const Params &P, const uint32_t *__rest
         }
     }
 
-    // CSR SpMV: without empty rows the k-th segment is row k and the row map was not made
-    bool rows_dense = false;
-    if constexpr (kOp == kSpmvCsr) rows_dense = hints[kHdrEmptyRows - kHdrHints] == 0;
     if constexpr (kCounts) {
-        // number of segment starts before my tile, while the loads are in flight: either the table
-        // holds the prefix sums already, or (few tiles) wave 1 adds up the counts of the tiles before
+        // number of segment starts before my tile, while the loads are in flight
+        static_assert(kWaves == (int)kSpans, "one span per wave");
         if (wave == 1) {
-            uint32_t c = 0;
-            if (P.count_is_prefix) {
-                c = P.tile_count[tile];
-            } else {
-                for (uint32_t i = lane; i < tile; i += 64) c += P.tile_count[i];
-                c = wave_sum<uint32_t, kAluLanes>(c);
-            }
+            const uint32_t c = wave_sum<uint32_t, kAluLanes>(starts_before_part(P, tile * kSpans, lane));
             if (lane == 0) sm.carry_c = c;
         }
     }
@@ -238,49 +222,6 @@ __device__ __forceinline__ void seg_tile(const Params &P, const uint32_t *__rest
       if (c < cpw_t) {
         const uint64_t cb = wave_base + (uint64_t)c * kChunkElems;
         const uint64_t row_start = cb + 32u * lane;  // first element of the row this lane owns
-        if constexpr (kProduct && kLateVal) {
-            // product vector p(i) = val(i) * x(col(i)), in the layout the columns were loaded in: the
-            // gathers go out as soon as the columns are there, the loads of the values right behind them
-            float xg[2 * K][4];
-            if (cb + kChunkElems <= n) {   // all of the chunk lies inside the matrix: no checks
-#pragma unroll
-                for (int i = 0; i < 2 * K; ++i)
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) xg[i][k] = P.xv[rawc[S][i][k]];
-            } else {
-#pragma unroll
-                for (int i = 0; i < 2 * K; ++i)
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const uint64_t e = cb + 1024u * (i / K) + raw_offset<TT, kMfma>(i % K, lane) + k;
-                        xg[i][k] = e < n ? P.xv[rawc[S][i][k]] : 0.0f;
-                    }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            load_raw<TT, kMfma>((const In *)P.x, cb, n, lane, raw[S]);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < 2 * K; ++i)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) raw[S][i][k] = to_bits(from_bits<float>(raw[S][i][k]) * xg[i][k]);
-        } else if constexpr (kProduct) {
-            // product vector p(i) = val(i) * x(col(i)), in the layout the values were loaded in (the
-            // checks stay even in full chunks: without them the compiler issues all gathers of the chunk
-            // at once, which was measured 4 % slower with scattered columns)
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int i = 0; i < K; ++i) {
-                    const uint64_t e0 = cb + 1024u * t + raw_offset<TT, kMfma>(i, lane);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const float p =
-                            (e0 + k < n) ? from_bits<float>(raw[S][t * K + i][k]) * P.xv[rawc[S][t * K + i][k]] : 0.0f;
-                        raw[S][t * K + i][k] = to_bits(p);
-                    }
-                }
-        }
-
         // ---- steps 1-4 for the aggregate of my row: last element after the revert, any flag ----
         const uint32_t has_flag = F[S] != 0;
         A agg_v;
@@ -419,7 +360,6 @@ __device__ __forceinline__ void seg_tile(const Params &P, const uint32_t *__rest
             for (int r = 0; r < kStep; ++r) {
                 rotate(F);
                 rotate_rows(raw);
-                if constexpr (kProduct) rotate_rows(rawc);
                 rotate(ex_v);
                 rotate(ex_f);
                 rotate(pre_v);
@@ -463,7 +403,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, const uint32_t *__rest
     wex_f = __builtin_amdgcn_readfirstlane(wex_f);
 
     if constexpr (kCounts) {
-        if (kOp == kSum && !P.count_is_prefix && tile == P.num_tiles - 1 && tid == 0) *P.nseg = (uint64_t)sm.carry_c + tagg_c + 1u;
+        if (!P.count_is_prefix && tile == P.num_tiles - 1 && tid == 0) *P.nseg = (uint64_t)sm.carry_c + tagg_c + 1u;
     }
 
     // ---- step 5c, first half: publish this tile ----
@@ -524,7 +464,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, const uint32_t *__rest
                 const uint64_t cb = wave_base + (uint64_t)c * kChunkElems;
                 const bool chunk_full = cb + kChunkElems <= n;
                 const uint64_t row_start = cb + 32u * lane;
-                // sum, spmv: end mask of my row, bit p set iff position p + 1 starts a segment or p is
+                // sum: end mask of my row, bit p set iff position p + 1 starts a segment or p is
                 // the last element; a 32x32 tile none of whose rows holds a segment end needs no x-bar
                 uint32_t E = 0;
                 uint64_t rows_with_ends = ~0ull;
@@ -620,7 +560,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, const uint32_t *__rest
                         }
                     }
                 } else {
-                    // ---- sum, spmv: only the segment ends produce output; the lane that owns a row
+                    // ---- sum: only the segment ends produce output; the lane that owns a row
                     // walks the ends of its row (steps 2 + 6 for those positions only) ----
                     wave_lds_sync();
                     const uint32_t *rp = rows + lane * kRowStride + kRowData;
@@ -637,15 +577,8 @@ __device__ __forceinline__ void seg_tile(const Params &P, const uint32_t *__rest
                         } else {
                             v += carry;                                  // the segment began before this row
                         }
-                        if (kOp == kSum) {
-                            const uint64_t k = count_base + __popc(Fc & ((2u << e) - 1u));
-                            if (k < P.out_cap) ((A *)P.out)[k] = v;
-                        } else if (kOp == kSpmvCsr) {
-                            const uint64_t k = count_base + __popc(Fc & ((2u << e) - 1u));
-                            if (k < P.out_cap) P.y[rows_dense ? (uint32_t)k : P.rowmap[k]] = from_bits<float>(to_bits(v));
-                        } else {
-                            P.y[P.row[row_start + e]] = from_bits<float>(to_bits(v));
-                        }
+                        const uint64_t k = count_base + __popc(Fc & ((2u << e) - 1u));
+                        if (k < P.out_cap) ((A *)P.out)[k] = v;
                     }
                 }
                 wave_lds_sync();  // the rows are read before the next chunk overwrites them

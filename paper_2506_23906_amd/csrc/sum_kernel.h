@@ -341,16 +341,10 @@ __device__ __forceinline__ void sum_tile(const Params &P, SumShared<TT> &sm, con
     const int cpw_t = (int)span.cpw;
     const uint64_t wave_base = span.base + (uint64_t)wave * cpw_t * kChunkElems;
 
-    // segment starts before my span (position 0 of the vector is not counted): those before my tile (the table holds
-    // them per tile, or, for long vectors, their prefix sums already) and those in the spans of the waves before mine.
+    // segment starts before my span (position 0 of the vector is not counted).
     // Asked for ahead of the values (loads come back in the order they went out), added up when the first end needs them.
-    uint32_t count_part = 0;
-    if (P.count_is_prefix) {
-        if (lane == 0) count_part = P.tile_count[tile];
-    } else {
-        for (uint32_t i = lane; i < tile; i += 64) count_part += P.tile_count[i];
-    }
-    if (lane < wave) count_part += P.span_count[(uint64_t)tile * kWaves + lane];
+    static_assert(kWaves == (int)kSpans, "one span per wave");
+    const uint32_t count_part = starts_before_part(P, tile * kSpans + wave, lane);
     __builtin_amdgcn_sched_barrier(0);
     SumSlot<TT> slot[kDepth];
 #pragma unroll

@@ -65,26 +65,18 @@ struct TF32 {
     static constexpr mmv_dtype kDtype = MMV_F32_F32;
     static __device__ __forceinline__ acc_t widen(in_t v) { return v; }
 };
-struct TSpmv : TF32 {  // COO SpMV: values and column indices both sit in registers, so fewer chunks
-    static constexpr int kMaxCpw = MMV_CPW_SPMV;
+struct TSpmv : TF32 {  // SpMV: the products of values and gathered entries of x
     static constexpr int kWaves = MMV_WAVES_SPMV;
 };
 // Most chunks a wave of seg_tile takes.  Bytes under exclusive or in the matrix-core variant hold four accumulators
 // of bit-plane sums per tile next to the raw words: two chunks fit the registers, four spill.  The scan without a
-// flag vector keeps no flag words and no carried flags, which leaves room for longer tiles of 16- and 32-bit inputs; so does
-// the segmented sum of fp32 values in the variant without the matrix cores.
+// flag vector keeps no flag words and no carried flags, which leaves room for longer tiles of 16- and 32-bit inputs.
 template <typename TT, int kOp, bool kMfma> constexpr int chunks_per_wave() {
     if (TT::kDtype == MMV_U8_XOR && kMfma) return MMV_CPW_X8_MFMA;
     if (kOp == kPlainScan && sizeof(typename TT::in_t) == 2) return MMV_CPW_F16_SCAN;
     if (kOp == kPlainScan && sizeof(typename TT::in_t) == 4) return MMV_CPW_F32_SCAN;
-    if (kOp == kSum && TT::kDtype == MMV_F32_F32 && !kMfma) return MMV_CPW_F32_SUM_SHUFFLE;
     return TT::kMaxCpw;
 }
-
-struct TInt {  // column indices of the COO matrix, loaded in the same layout as its values
-    typedef int32_t in_t;
-    static constexpr int kEpl = 4;
-};
 
 // ---- raw inputs of one wave chunk (2048 elements), kept in registers ---------------------------------
 //
@@ -347,8 +339,6 @@ template <> struct SpecMfma<TF32> {
     }
 };
 
-template <> struct SpecMfma<TSpmv> : SpecMfma<TF32> {};
-
 // ---- plain sum of the raw registers of one chunk (for the aggregate of a tile that holds no flag) ----------
 //
 // A lane's partial sum over its 2 * K words; the layout does not matter.  Elements beyond n were loaded as zeros.
@@ -406,7 +396,6 @@ template <> struct RawSum<TF32> {
         return (s[0] + s[1]) + (s[2] + s[3]);
     }
 };
-template <> struct RawSum<TSpmv> : RawSum<TF32> {};
 
 // ---- steps 2-4 without the detour through LDS: row aggregates from the raw registers -----------------
 //
@@ -526,7 +515,6 @@ template <> struct RowAgg<TF32> {
         return lane < 32 ? tot[0] : tot[1];
     }
 };
-template <> struct RowAgg<TSpmv> : RowAgg<TF32> {};
 
 
 // Writes the 16 results of a lane into the LDS rows of 32x32 tile t of this wave.
@@ -559,7 +547,6 @@ template <> __device__ __forceinline__ float raw_elem<TBF16>(const v4u &w, int i
     return from_bits<float>((w[i >> 1] >> (16 * (i & 1))) << 16);
 }
 template <> __device__ __forceinline__ float raw_elem<TF32>(const v4u &w, int i) { return from_bits<float>(w[i]); }
-template <> __device__ __forceinline__ float raw_elem<TSpmv>(const v4u &w, int i) { return from_bits<float>(w[i]); }
 
 template <typename TT, bool kAlu>
 __device__ __forceinline__ void spec_shuffle_tile(const v4u *raw, int lane, uint32_t *rows, int t) {

@@ -40,24 +40,11 @@ namespace {
 #ifndef MMV_CPW_F32_SCAN
 #define MMV_CPW_F32_SCAN 2
 #endif
-// Segmented sum of fp32 values without the matrix cores: two chunks per wave fit the registers (111) and halve the
-// tickets, barriers and look-backs per element: n = 2^28 52 -> 73 % of peak.  On the matrix cores two chunks spill
-// (the three-way split of a chunk and its 16 accumulators beside the other chunk's 32 registers: 40 to 144 bytes
-// per lane however the loops are shaped) and end at 46 to 50 %, so that variant keeps one.
-#ifndef MMV_CPW_F32_SUM_SHUFFLE
-#define MMV_CPW_F32_SUM_SHUFFLE 2
-#endif
-#ifndef MMV_CPW_SPMV
-#define MMV_CPW_SPMV 1
-#endif
 #ifndef MMV_UNROLL_CHUNKS
-#define MMV_UNROLL_CHUNKS 1   // 1: the chunk loops of the sum / SpMV kernels are unrolled (see kUnrollChunks)
+#define MMV_UNROLL_CHUNKS 1   // 1: the chunk loops of the sum kernels of short vectors are unrolled (see kUnrollChunks)
 #endif
 #ifndef MMV_MIN_WAVES_PER_SIMD
 #define MMV_MIN_WAVES_PER_SIMD 4   // register budget: 512 / 4 = 128 VGPRs per lane
-#endif
-#ifndef MMV_SPMV_STAGGER_US
-#define MMV_SPMV_STAGGER_US 15   // SpMV: start times of the first round spread over this many microseconds
 #endif
 #ifndef MMV_KEEP_ROWS
 #define MMV_KEEP_ROWS 1   // 1: single-chunk waves of the matrix-core variant keep their row scans in LDS (see kKeepRows)
@@ -146,7 +133,6 @@ constexpr uint32_t kErrLookback = 1, kErrNotPrepared = 2;   // values of the sta
 constexpr uint32_t kHdrHints = 32;              // first of the words the SpMV kernels read as hints (a cache line of
                                                 // their own: the line of the ticket is busy with atomics):
 constexpr uint32_t kHdrEmptyRows = 32;          // CSR SpMV: set when some row of the matrix has no entries
-constexpr uint32_t kHdrColumnRuns = 33;         // SpMV: set when neighbouring entries mostly have consecutive columns
 constexpr uint32_t kHdrPrepared = 34;         // SpMV in two steps: what the preparing call left for this matrix (0: nothing)
 constexpr size_t kHdrBytes = 256;
 
@@ -164,6 +150,10 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef short v8s __attribute__((ext_vector_type(8)));
+
+constexpr uint32_t kSpans = 8;                  // wave spans per tile of the kernels that number their segments
+constexpr uint32_t kGroupTiles = 8;             // tiles whose counts of segment starts are also kept as one sum
+constexpr uint32_t kGroupSpans = kSpans * kGroupTiles;   // = lanes of a wave
 
 // What a kernel instantiation computes (values match mmv_op where there is one):
 //   kScan       segmented inclusive scan
@@ -231,19 +221,18 @@ struct Params {
     uint32_t first_one;     // plain scan of a flag vector: element 0 counts as 1 whatever it holds
     const int32_t *col;
     const float *xv;
+    uint32_t cols_narrow;   // spmv: x has at most 2^30 entries
     float *y;
     uint32_t *hdr;          // workspace header
     uint64_t *desc_v;       // value descriptors, one per tile
-    const uint32_t *tile_count;  // sum: segment starts per tile (position 0 not counted), or ...
-    uint32_t count_is_prefix;    // ... their exclusive prefix sums already (long vectors)
-    const uint32_t *span_count;  // sum of 8- and 16-bit inputs: segment starts per wave span (kWaves of them per tile)
+    const uint32_t *group_count; // sum, CSR spmv: segment starts per group of eight tiles (position 0 not counted), or ...
+    uint32_t count_is_prefix;    // ... their exclusive prefix sums already (very long vectors)
+    const uint32_t *span_count;  // ... and per wave span (kSpans of them per tile)
     uint32_t num_tiles;
     TileRegions reg;        // which elements a tile covers
     uint32_t prepared;      // SpMV in two steps: the mark the preparing call must have left in the header (0: not asked for)
     uint32_t first_round;   // workgroups [0, first_round) are resident together from the start and take the tile
                             // of their own index; the others take tickets
-    uint32_t stagger_wgs;   // workgroups [0, stagger_wgs) start after a delay of up to ...
-    uint32_t stagger_ticks; // ... this many ticks of the 100 MHz clock, spread evenly over them
 };
 
 }  // namespace
