@@ -31,77 +31,91 @@ __global__ void mark_prepared_kernel(uint32_t *hdr, uint32_t mark) {
     if (threadIdx.x == 0 && blockIdx.x == 0) hdr[kHdrPrepared] = mark;
 }
 
+// 32 flag bytes -> one flag word (bit set iff the byte is not zero).
+__device__ __forceinline__ uint32_t bits_of_16_bytes(v4u w) {
+    uint32_t bits = 0;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        // the highest bit of every byte that is not zero, moved to bits 0, 8, 16, 24, and those next to each other
+        // (the multiplication puts the bit of byte j at bit 28 + j; no two partial products meet there)
+        const uint32_t nz = ((((w[d] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w[d]) >> 7) & 0x01010101u;
+        bits |= ((nz * 0x10204080u) >> 28) << (4 * d);
+    }
+    return bits;
+}
+__device__ __forceinline__ uint32_t bits_of_32_bytes(const uint8_t *f, uint64_t e0, uint64_t n) {   // flags e0 .. e0 + 31; 0 beyond n
+    const bool full = e0 + 32 <= n;
+    const v4u a = load128<uint8_t, false>(f, e0, n, full), b = load128<uint8_t, false>(f, e0 + 16, n, full);
+    return bits_of_16_bytes(a) | (bits_of_16_bytes(b) << 16);
+}
+
 // Segmented sum, step "scan of the end markers" of COMPRESS (proof of the SCD / SSCR theorem)
-// at the granularity of the spans that the waves of the main kernel take: a workgroup counts the segment starts inside
-// each of the 64 spans of a group of eight tiles, and in the group (position 0 is not counted: it opens segment 0
-// whatever its flag says; bits at or beyond n are not counted).  A wave of the main kernel then adds up the groups
-// before its own and the spans of its group before its own: two loads per lane for up to 512 tiles, where a table per
-// tile took as many dependent loads as there are 64 tiles (or a launch more that made prefix sums of it: 6.3 us at
-// 6104 tiles).  Sixteen lanes share a span, so a wave works on four.
+// at the granularity of the spans that the waves of the main kernel take: workgroup t counts the segment starts in tile t
+// and in each of its eight spans, one span per wave (position 0 is not counted: it opens segment 0
+// whatever its flag says; bits at or beyond n are not counted).  The main kernel adds up what it needs (starts_before_part).
+// Flags of one byte per element (kBytes) are packed on the way: the words go to `packed` (10^8 values: packing kernel
+// 19.4 us and counting kernel 5.3 us -> 18.2 us together).
 // The same launch zeroes the header and the descriptors of the main kernel.
-__global__ __launch_bounds__(1024) void count_spans_kernel(uint32_t *zero, uint64_t zero_words, const uint32_t *fw,
-                                                           uint64_t n, TileRegions reg, uint32_t unit, uint32_t *group_cnt,
-                                                           uint32_t *span_cnt) {
-    __shared__ uint32_t s_part[16];
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (uint64_t i = (uint64_t)blockIdx.x * 1024 + tid; i < zero_words; i += (uint64_t)gridDim.x * 1024) zero[i] = 0;
-    const uint32_t sp = blockIdx.x * kGroupSpans + wave * 4 + (lane >> 4);   // my span, of all tiles
-    const uint32_t tile = sp / kSpans;
+template <bool kBytes>
+__global__ __launch_bounds__(512) void count_spans_kernel(uint32_t *zero, uint64_t zero_words, const void *flags,
+                                                          uint32_t *packed, uint64_t n, TileRegions reg, uint32_t unit,
+                                                          uint32_t *tile_cnt, uint32_t *span_cnt) {
+    __shared__ uint32_t s_part[kSpans];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tile = blockIdx.x;
+    for (uint64_t i = (uint64_t)tile * 512 + tid; i < zero_words; i += (uint64_t)gridDim.x * 512) zero[i] = 0;
+    const TileSpan span = tile_span(reg, tile, unit);
+    const uint64_t span_words = (uint64_t)span.cpw * (unit / kSpans / 32);
+    const uint64_t w0 = (span.base >> 5) + wave * span_words;   // tiles and spans begin on word borders, spans are multiples of 32 words
+    const uint64_t last_word = (n + 31) >> 5;
+    const uint64_t end = w0 + span_words < last_word ? w0 + span_words : last_word;
     uint32_t sum = 0;
-    if (tile < reg.num_tiles) {
-        const TileSpan span = tile_span(reg, tile, unit);
-        const uint64_t span_words = (uint64_t)span.cpw * (unit / kSpans / 32);
-        const uint64_t w0 = (span.base >> 5) + (sp % kSpans) * span_words;   // tiles and spans begin on word borders, spans are multiples of 32 words
-        const uint64_t last_word = (n + 31) >> 5;
+    if constexpr (kBytes) {
 #pragma unroll 4
-        for (uint64_t w = w0 + 4 * (lane & 15); w < w0 + span_words; w += 64) {
-            if (w >= last_word) break;
-            // four words at a time (what lies behind the caller's words is not ours to read: the last ones singly)
-            uint32_t v[4] = {0, 0, 0, 0};
-            if (w + 4 <= last_word) {
-                const v4u q = *reinterpret_cast<const v4u *>(fw + w);
-                v[0] = q[0], v[1] = q[1], v[2] = q[2], v[3] = q[3];
-            } else {
-                for (int j = 0; j < 4 && w + j < last_word; ++j) v[j] = fw[w + j];
-            }
+        for (uint64_t w = w0 + lane; w < end; w += 64) {
+            const uint32_t v = bits_of_32_bytes((const uint8_t *)flags, w * 32, n);
+            packed[w] = v;
+            sum += __popc(w == 0 ? v & ~1u : v);
+        }
+    } else {
+        const uint32_t *fw = (const uint32_t *)flags;
+#pragma unroll 4
+        for (uint64_t w = w0 + 4 * lane; w < end; w += 256) {
+            // (the aligned block of the last word is read whole)
+            v4u v = *reinterpret_cast<const v4u *>(fw + w);
             if (w == 0) v[0] &= ~1u;
             if ((w + 4) * 32 > n) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const uint64_t wj = w + j;
-                    if ((wj + 1) * 32 > n) v[j] = wj * 32 < n ? (v[j] & ((1u << (uint32_t)(n - wj * 32)) - 1u)) : 0u;
+                    const uint64_t e0 = (w + j) * 32;
+                    if (e0 + 32 > n) v[j] = e0 < n ? (v[j] & ((1u << (uint32_t)(n - e0)) - 1u)) : 0u;
                 }
             }
             sum += (__popc(v[0]) + __popc(v[1])) + (__popc(v[2]) + __popc(v[3]));
         }
     }
-    // sums over the sixteen lanes of a span (lane 15 of a row of lanes has it), then over the wave
-    sum += dpp_or_zero<0x111, 0xF>(sum);
-    sum += dpp_or_zero<0x112, 0xF>(sum);
-    sum += dpp_or_zero<0x114, 0xF>(sum);
-    sum += dpp_or_zero<0x118, 0xF>(sum);
-    if ((lane & 15) == 15 && tile < reg.num_tiles) span_cnt[sp] = sum;
-    sum += dpp_or_zero<0x142, 0xA>(sum);
-    sum += dpp_or_zero<0x143, 0xC>(sum);
-    if (lane == 63) s_part[wave] = sum;
+    sum = wave_sum(sum);
+    if (lane == 0) {
+        span_cnt[tile * kSpans + wave] = sum;
+        s_part[wave] = sum;
+    }
     __syncthreads();
     if (tid == 0) {
         uint32_t all = 0;
 #pragma unroll
-        for (int w = 0; w < 16; ++w) all += s_part[w];
-        group_cnt[blockIdx.x] = all;
+        for (uint32_t w = 0; w < kSpans; ++w) all += s_part[w];
+        tile_cnt[tile] = all;
     }
 }
 
-// Exclusive prefix sums of the counts per group, in place, by one workgroup (only for very long vectors); the total (+ 1
+// Exclusive prefix sums of the counts per tile, in place, by one workgroup (only for very long vectors); the total (+ 1
 // for segment 0) is the number of segments.
-__global__ __launch_bounds__(1024) void scan_counts_kernel(uint32_t *cnt, uint32_t num_groups, uint64_t *nseg) {
+__global__ __launch_bounds__(1024) void scan_counts_kernel(uint32_t *cnt, uint32_t num_tiles, uint64_t *nseg) {
     __shared__ uint32_t s_wave[16];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t running = 0;
-    for (uint32_t base = 0; base < num_groups; base += 1024) {
+    for (uint32_t base = 0; base < num_tiles; base += 1024) {
         const uint32_t i = base + tid;
-        const uint32_t v = i < num_groups ? cnt[i] : 0u;
+        const uint32_t v = i < num_tiles ? cnt[i] : 0u;
         uint32_t inc = v;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
@@ -116,34 +130,21 @@ __global__ __launch_bounds__(1024) void scan_counts_kernel(uint32_t *cnt, uint32
             if (w == wave) before = total;
             total += s_wave[w];
         }
-        if (i < num_groups) cnt[i] = running + before + inc - v;
+        if (i < num_tiles) cnt[i] = running + before + inc - v;
         running += total;
         __syncthreads();
     }
     if (tid == 0) *nseg = (uint64_t)running + 1u;
 }
 
-// One byte per element -> one bit per element; a thread builds one 32-bit word.
-__global__ __launch_bounds__(256) void pack_flags_kernel(const uint8_t *f, uint64_t n, uint32_t *words,
-                                                         uint64_t nwords) {
+// One byte per element -> one bit per element; a thread builds one 32-bit word.  The same launch zeroes the words that
+// the main kernel needs zeroed (a launch of its own takes 4.6 us of a stream that is never empty).
+__global__ __launch_bounds__(256) void pack_flags_kernel(const uint8_t *f, uint64_t n, uint32_t *words, uint64_t nwords,
+                                                         uint32_t *zero, uint64_t zero_words) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t w = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; w < nwords; w += stride) {
-        uint32_t bits = 0;
-        const uint64_t e0 = w * 32;
-        if (e0 + 32 <= n) {
-            const v4u a = *reinterpret_cast<const v4u *>(f + e0), b = *reinterpret_cast<const v4u *>(f + e0 + 16);
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    bits |= (((a[k] >> (8 * j)) & 0xFFu) ? 1u : 0u) << (4 * k + j);
-                    bits |= (((b[k] >> (8 * j)) & 0xFFu) ? 1u : 0u) << (16 + 4 * k + j);
-                }
-        } else {
-            for (int i = 0; i < 32 && e0 + i < n; ++i) bits |= (f[e0 + i] ? 1u : 0u) << i;
-        }
-        words[w] = bits;
-    }
+    const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (uint64_t i = i0; i < zero_words; i += stride) zero[i] = 0;
+    for (uint64_t w = i0; w < nwords; w += stride) words[w] = bits_of_32_bytes(f, w * 32, n);
 }
 
 // Segment-start flags of a row-sorted COO matrix, f(e) = [e == 0 or row(e) != row(e-1)], bit-packed; the same
@@ -194,12 +195,12 @@ __global__ __launch_bounds__(256) void row_flags_kernel(const int32_t *row, uint
 // Row pointers of a CSR matrix -> (a) bit-packed segment-start flags over the non-zeros (a row
 // with entries sets the bit of its first entry; rows that share a word meet in an atomic OR on
 // a zeroed word), (b) the bit-packed mask of rows that have entries (one ballot per 64 rows),
-// (c) the number of segment starts inside every wave span of the main kernel and every group of its tiles (as in
+// (c) the number of segment starts inside every wave span of the main kernel and every one of its tiles (as in
 // count_spans_kernel; the rows of a wave that start in the same span share the atomic adds
 // on zeroed tables) and (d) the mark that some row is empty.
 __global__ __launch_bounds__(256) void csr_flags_kernel(const int32_t *rowptr, uint64_t n_rows, uint32_t *fw,
                                                         uint32_t *rowmask, uint32_t *hdr, TileRegions reg, uint32_t unit,
-                                                        uint32_t *group_count, uint32_t *span_count) {
+                                                        uint32_t *tile_count, uint32_t *span_count) {
     const int lane = threadIdx.x & 63;
     const uint64_t r = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     bool nonempty = false;
@@ -219,7 +220,7 @@ __global__ __launch_bounds__(256) void csr_flags_kernel(const int32_t *rowptr, u
     const uint64_t m = __ballot(nonempty);
     // a matrix none of whose rows is empty needs no row map: segment k is row k
     if (__ballot(r < n_rows && !nonempty) != 0 && lane == 0) hdr[kHdrEmptyRows] = 1u;
-    // one atomic add per distinct span among the rows of the wave, and one per distinct group (adds to one address are
+    // one atomic add per distinct span among the rows of the wave, and one per distinct tile (adds to one address are
     // served one after the other, about 11 ns each)
     auto add_distinct = [&](uint32_t key, uint32_t *table) {
         uint64_t todo = __ballot(key != 0xFFFFFFFFu);
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(256) void csr_flags_kernel(const int32_t *rowptr, u
         }
     };
     add_distinct(mine, span_count);
-    add_distinct(mine == 0xFFFFFFFFu ? mine : mine / kGroupSpans, group_count);
+    add_distinct(mine == 0xFFFFFFFFu ? mine : mine / kSpans, tile_count);
     const uint64_t r0 = r - lane;
     if (lane == 0 && r0 < n_rows) {
         rowmask[r0 >> 5] = (uint32_t)m;

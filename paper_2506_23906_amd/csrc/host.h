@@ -25,10 +25,11 @@ constexpr uint64_t kResident = MMV_MIN_TILES;   // workgroups resident at once (
 #ifndef MMV_TAIL_TILES
 #define MMV_TAIL_TILES 128   // tiles of one chunk per wave at the very end (the last of them is ragged)
 #endif
-// Up to this many groups of eight tiles the segmented sum and CSR SpMV need no prefix kernel: every wave of the main
-// kernel adds up the counts of the groups before its own, eight loads per lane at most, four of them under way at a time.
-constexpr uint64_t kCountGroups = 512;
-inline uint64_t groups_of(uint64_t tiles) { return (tiles + kGroupTiles - 1) / kGroupTiles; }
+// Up to this many tiles the segmented sum and CSR SpMV need no prefix kernel: every wave of the main
+// kernel adds up the counts of the tiles before its own, sixteen 128-bit loads per lane at most, four of them under way at a
+// time (one load per lane and 64 tiles, waited for one by one, took 5.6 us of a 42 us kernel at 1224 tiles; the prefix
+// kernel takes 5 to 6 us of the call).
+constexpr uint64_t kCountTiles = 4096;
 inline bool is_spmv(mmv_op op) { return op == MMV_OP_SPMV_COO || op == MMV_OP_SPMV_CSR; }
 // Most chunks per wave of the tile body that carries its pair from row to row (seg_tile): what the kernel
 // instantiation for this operation, type and variant is built with.
@@ -180,8 +181,8 @@ WsLayout ws_layout(mmv_op op, mmv_dtype dt, mmv_flag_fmt ff, uint64_t n) {
     size_t off = kHdrBytes;
     L.desc_v = off;
     off += round256(t * 8);
-    L.desc_c = off;   // counts of segment starts: per group of tiles, and per wave span
-    if (op == MMV_OP_SEGSUM || op == MMV_OP_SPMV_CSR) off += round256(groups_of(t) * 4);
+    L.desc_c = off;   // counts of segment starts: per tile, and per wave span
+    if (op == MMV_OP_SEGSUM || op == MMV_OP_SPMV_CSR) off += round256(t * 4);
     L.span_c = off;
     if (op == MMV_OP_SEGSUM || op == MMV_OP_SPMV_CSR) off += round256(t * 4 * kSpans);
     L.packed = off;
@@ -377,20 +378,20 @@ mmv_status prepare(mmv_op op, const void *d_x, const void *d_flags, uint64_t n, 
     P.hdr = (uint32_t *)ws;
     P.desc_v = (uint64_t *)(ws + L.desc_v);
     P.num_tiles = (uint32_t)tiles_for(n, op, dt);
-    if (op != MMV_OP_SEGSUM) {   // the segmented sum zeroes them in its tile-count kernel
-        const uint64_t zero_words = L.packed / 4;  // header + descriptors
-        fill_zero_kernel<<<grid_for(zero_words), 256, 0, s>>>((uint32_t *)ws, zero_words, nullptr, 0);
-        if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
-    }
+    // header and descriptors zeroed, flags packed if they came as bytes: one launch (none for a single tile of packed flags,
+    // whose kernel needs nothing zeroed).  The segmented sum does both in its counting kernel.
+    uint32_t *packed = (uint32_t *)(ws + L.packed);
+    P.fw = ff == MMV_FLAGS_U8 ? packed : (const uint32_t *)d_flags;
+    if (op == MMV_OP_SEGSUM) return MMV_OK;
+    const uint64_t zero_words = L.packed / 4;
     if (ff == MMV_FLAGS_U8) {
         const uint64_t nwords = (n + 31) / 32;
-        uint32_t *packed = (uint32_t *)(ws + L.packed);
-        pack_flags_kernel<<<grid_for(nwords), 256, 0, s>>>((const uint8_t *)d_flags, n, packed, nwords);
-        if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
-        P.fw = packed;
-    } else {
-        P.fw = (const uint32_t *)d_flags;
+        pack_flags_kernel<<<grid_for(nwords > zero_words ? nwords : zero_words), 256, 0, s>>>((const uint8_t *)d_flags, n, packed, nwords,
+                                                                                             (uint32_t *)ws, zero_words);
+    } else if (tile_plan(op, dt, n, v == MMV_VARIANT_MFMA).tiles > 1) {
+        fill_zero_kernel<<<grid_for(zero_words), 256, 0, s>>>((uint32_t *)ws, zero_words, nullptr, 0);
     }
+    if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     return MMV_OK;
 }
 
@@ -417,9 +418,11 @@ mmv_status scan_impl(const void *d_x, uint64_t n, void *d_z, mmv_dtype dt, mmv_v
     P.hdr = (uint32_t *)ws;
     P.desc_v = (uint64_t *)(ws + L.desc_v);
     P.first_one = first_one ? 1u : 0u;
-    const uint64_t zero_words = L.total / 4;
-    fill_zero_kernel<<<grid_for(zero_words), 256, 0, s>>>((uint32_t *)ws, zero_words, nullptr, 0);
-    if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
+    if (tile_plan(MMV_OP_SCAN, dt, n, v == MMV_VARIANT_MFMA).tiles > 1) {   // (a single tile needs nothing zeroed)
+        const uint64_t zero_words = L.total / 4;
+        fill_zero_kernel<<<grid_for(zero_words), 256, 0, s>>>((uint32_t *)ws, zero_words, nullptr, 0);
+        if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
+    }
     return launch_dt<kPlainScan>(P, dt, v, s) == hipSuccess ? MMV_OK : MMV_ERR_HIP;
 }
 

@@ -133,21 +133,29 @@ __device__ T lookback(const uint64_t *desc, int tile, int lane, uint32_t *hdr) {
 }
 
 // Number of segment starts before span `sp` (of all tiles; a multiple of kSpans: before that tile), from the counts
-// per group of tiles and per span.  Wave-wide in two halves, so that the loads can go out ahead of others: the lane's
-// part, and their sum.
+// per tile and per span.  Wave-wide in two halves, so that the loads can go out ahead of others: the lane's part, and their
+// sum.  A lane takes eight tiles (two 128-bit loads), so the wave covers 512 tiles before the first one of its own group
+// of eight; of that group it takes the spans before its own.
 __device__ __forceinline__ uint32_t starts_before_part(const Params &P, uint32_t sp, int lane) {
     const uint32_t g = sp / kGroupSpans;
     uint32_t part = 0;
-    if (lane < (int)(sp % kGroupSpans)) part = P.span_count[g * kGroupSpans + lane];
     if (P.count_is_prefix) {
-        if (lane == 0) part += P.group_count[g];
-    } else {
-        for (uint32_t i = lane; i < g; i += 256) {   // four loads under way at a time
-            uint32_t v[4];
+        if (lane < (int)(sp % kSpans)) part = P.span_count[sp / kSpans * kSpans + lane];
+        if (lane == 0) part += P.tile_count[sp / kSpans];
+        return part;
+    }
+    if (lane < (int)(sp % kGroupSpans)) part = P.span_count[g * kGroupSpans + lane];
+    for (uint32_t i = lane; i < g; i += 128) {   // four loads under way at a time
+        v4u a[4] = {};
 #pragma unroll
-            for (uint32_t j = 0; j < 4; ++j) v[j] = i + 64 * j < g ? P.group_count[i + 64 * j] : 0u;
-            part += (v[0] + v[1]) + (v[2] + v[3]);
-        }
+        for (uint32_t j = 0; j < 2; ++j)
+            if (i + 64 * j < g) {
+                const v4u *t = reinterpret_cast<const v4u *>(P.tile_count + (i + 64 * j) * kGroupTiles);
+                a[2 * j] = t[0];
+                a[2 * j + 1] = t[1];
+            }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) part += (a[j][0] + a[j][1]) + (a[j][2] + a[j][3]);
     }
     return part;
 }

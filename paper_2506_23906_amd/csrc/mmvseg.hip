@@ -150,22 +150,22 @@ mmv_status mmv_segsum(const void *d_x, const void *d_flags, uint64_t n, void *d_
     P.out = d_out;
     P.out_cap = out_capacity;
     P.nseg = d_nseg;
-    // number of segment starts per span and per group of tiles
+    // number of segment starts per span and per tile
     const TilePlan plan = tile_plan(MMV_OP_SEGSUM, dt, n, v == MMV_VARIANT_MFMA);
     const WsLayout L = ws_layout(MMV_OP_SEGSUM, dt, ff, n);
     if (plan.tiles > 0x7fffffffull) return MMV_ERR_INVALID_ARG;
-    uint32_t *group_count = (uint32_t *)((char *)d_ws + L.desc_c);
+    uint32_t *tile_count = (uint32_t *)((char *)d_ws + L.desc_c);
     uint32_t *span_count = (uint32_t *)((char *)d_ws + L.span_c);
-    const uint64_t groups = groups_of(plan.tiles);
-    count_spans_kernel<<<(unsigned)groups, 1024, 0, s>>>((uint32_t *)d_ws, L.desc_c / 4, P.fw, n, plan.reg, plan.unit,
-                                                          group_count, span_count);
+    auto count = ff == MMV_FLAGS_U8 ? count_spans_kernel<true> : count_spans_kernel<false>;
+    count<<<(unsigned)plan.tiles, 512, 0, s>>>((uint32_t *)d_ws, L.desc_c / 4, d_flags, (uint32_t *)((char *)d_ws + L.packed), n,
+                                               plan.reg, plan.unit, tile_count, span_count);
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
-    P.count_is_prefix = groups > kCountGroups ? 1u : 0u;
+    P.count_is_prefix = plan.tiles > kCountTiles ? 1u : 0u;
     if (P.count_is_prefix) {
-        scan_counts_kernel<<<1, 1024, 0, s>>>(group_count, (uint32_t)groups, d_nseg);
+        scan_counts_kernel<<<1, 1024, 0, s>>>(tile_count, (uint32_t)plan.tiles, d_nseg);
         if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     }
-    P.group_count = group_count;
+    P.tile_count = tile_count;
     P.span_count = span_count;
     return launch_dt<kSum>(P, dt, v, s) == hipSuccess ? MMV_OK : MMV_ERR_HIP;
 }
@@ -213,7 +213,7 @@ mmv_status mmv_spmv_coo(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
 
 // SpMV in two steps: the mark that the first step leaves in the header for this matrix shape (never 0).  It names the
 // layout of the counts as well (kPlanLayout), which the product kernel relies on.
-static constexpr uint64_t kPlanLayout = 2;
+static constexpr uint64_t kPlanLayout = 3;
 static uint32_t prepared_mark(mmv_op op, uint64_t n_rows, uint64_t nnz) {
     uint64_t h = (nnz + 0x9E3779B97F4A7C15ull) * 0xD6E8FEB86659FD93ull + n_rows * 0xCA5A826395121157ull + (uint64_t)op + (kPlanLayout << 32);
     h ^= h >> 32;
@@ -347,7 +347,7 @@ mmv_status mmv_segsum_scd(const void *d_x, const void *d_flags, uint64_t n, void
     const uint32_t *fw = (const uint32_t *)d_flags;
     if (ff == MMV_FLAGS_U8) {
         uint32_t *packed = (uint32_t *)(ws + L.packed);
-        pack_flags_kernel<<<grid_for(nwords), 256, 0, s>>>((const uint8_t *)d_flags, n, packed, nwords);
+        pack_flags_kernel<<<grid_for(nwords), 256, 0, s>>>((const uint8_t *)d_flags, n, packed, nwords, nullptr, 0);
         if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
         fw = packed;
     }
@@ -381,7 +381,7 @@ mmv_status mmv_segscan_sscr(const void *d_x, const void *d_flags, uint64_t n, vo
     const uint32_t *fw = (const uint32_t *)d_flags;
     if (ff == MMV_FLAGS_U8) {
         uint32_t *packed = (uint32_t *)(ws + L.packed);
-        pack_flags_kernel<<<grid_for(nwords), 256, 0, s>>>((const uint8_t *)d_flags, n, packed, nwords);
+        pack_flags_kernel<<<grid_for(nwords), 256, 0, s>>>((const uint8_t *)d_flags, n, packed, nwords, nullptr, 0);
         if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
         fw = packed;
     }
@@ -433,11 +433,11 @@ mmv_status mmv_spmv_csr(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
     // rows that have entries
     const TilePlan plan = tile_plan(MMV_OP_SPMV_CSR, MMV_F32_F32, nnz);
     uint32_t *fw = (uint32_t *)(ws + C.main_ws + L.packed);
-    uint32_t *group_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
+    uint32_t *tile_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
     const uint64_t row_blocks = (n_rows + 255) / 256;
     csr_flags_kernel<<<(unsigned)row_blocks, 256, 0, s>>>(d_rowptr, n_rows, fw, (uint32_t *)(ws + C.rowmask),
                                                           (uint32_t *)(ws + C.main_ws), plan.reg, plan.unit,
-                                                          group_count, (uint32_t *)(ws + C.main_ws + L.span_c));
+                                                          tile_count, (uint32_t *)(ws + C.main_ws + L.span_c));
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     // rowmap = COMPRESS(0 .. n_rows - 1, rowmask): the k-th segment belongs to row rowmap[k]
     {
@@ -460,12 +460,12 @@ mmv_status mmv_spmv_csr(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
     P.hdr = (uint32_t *)(ws + C.main_ws);
     P.desc_v = (uint64_t *)(ws + C.main_ws + L.desc_v);
     P.fw = fw;
-    P.count_is_prefix = groups_of(plan.tiles) > kCountGroups ? 1u : 0u;
+    P.count_is_prefix = plan.tiles > kCountTiles ? 1u : 0u;
     if (P.count_is_prefix) {
-        scan_counts_kernel<<<1, 1024, 0, s>>>(group_count, (uint32_t)groups_of(plan.tiles), (uint64_t *)(ws + C.rowcount));
+        scan_counts_kernel<<<1, 1024, 0, s>>>(tile_count, (uint32_t)plan.tiles, (uint64_t *)(ws + C.rowcount));
         if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     }
-    P.group_count = group_count;
+    P.tile_count = tile_count;
     P.span_count = (const uint32_t *)(ws + C.main_ws + L.span_c);
     return launch_seg<TSpmv, kSpmvCsr>(P, v, s) == hipSuccess ? MMV_OK : MMV_ERR_HIP;
 }
@@ -486,11 +486,11 @@ mmv_status mmv_spmv_csr_prepare(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, 
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     const TilePlan plan = tile_plan(MMV_OP_SPMV_CSR, MMV_F32_F32, nnz);
     uint32_t *fw = (uint32_t *)(ws + C.main_ws + L.packed);
-    uint32_t *group_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
+    uint32_t *tile_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
     const uint64_t row_blocks = (n_rows + 255) / 256;
     csr_flags_kernel<<<(unsigned)row_blocks, 256, 0, s>>>(d_rowptr, n_rows, fw, (uint32_t *)(ws + C.rowmask),
                                                           (uint32_t *)(ws + C.main_ws), plan.reg, plan.unit,
-                                                          group_count, (uint32_t *)(ws + C.main_ws + L.span_c));
+                                                          tile_count, (uint32_t *)(ws + C.main_ws + L.span_c));
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     {
         EventsOff quiet;
@@ -500,8 +500,8 @@ mmv_status mmv_spmv_csr_prepare(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, 
                                             (const uint32_t *)(ws + C.main_ws) + kHdrEmptyRows);
         if (st != MMV_OK) return st;
     }
-    if (groups_of(plan.tiles) > kCountGroups) {
-        scan_counts_kernel<<<1, 1024, 0, s>>>(group_count, (uint32_t)groups_of(plan.tiles), (uint64_t *)(ws + C.rowcount));
+    if (plan.tiles > kCountTiles) {
+        scan_counts_kernel<<<1, 1024, 0, s>>>(tile_count, (uint32_t)plan.tiles, (uint64_t *)(ws + C.rowcount));
         if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     }
     mark_prepared_kernel<<<1, 64, 0, s>>>((uint32_t *)(ws + C.main_ws), prepared_mark(MMV_OP_SPMV_CSR, n_rows, nnz));
@@ -540,8 +540,8 @@ mmv_status mmv_spmv_csr_run(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, cons
     P.hdr = (uint32_t *)(ws + C.main_ws);
     P.desc_v = (uint64_t *)(ws + C.main_ws + L.desc_v);
     P.fw = (const uint32_t *)(ws + C.main_ws + L.packed);
-    P.count_is_prefix = groups_of(plan.tiles) > kCountGroups ? 1u : 0u;
-    P.group_count = (const uint32_t *)(ws + C.main_ws + L.desc_c);
+    P.count_is_prefix = plan.tiles > kCountTiles ? 1u : 0u;
+    P.tile_count = (const uint32_t *)(ws + C.main_ws + L.desc_c);
     P.span_count = (const uint32_t *)(ws + C.main_ws + L.span_c);
     P.prepared = prepared_mark(MMV_OP_SPMV_CSR, n_rows, nnz);
     // header and value descriptors of the main kernel; the counts, flag words, row mask and row map behind them stay

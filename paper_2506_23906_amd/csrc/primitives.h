@@ -66,19 +66,6 @@ inline uint64_t compress_tile(uint64_t n) { return (uint64_t)kCompressWaves * 64
 constexpr int kPieceElems = 1024;                  // positions a wave compacts at a time
 constexpr int kPieceWords = kPieceElems + 4;       // LDS words of a wave: a piece, shifted by up to three
 
-// 16 mask bytes -> 16 bits (bit set iff the byte is not zero).
-__device__ __forceinline__ uint32_t bits_of_16_bytes(v4u w) {
-    uint32_t bits = 0;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        // the highest bit of every byte that is not zero, moved to bits 0, 8, 16, 24, and those next to each other
-        // (the multiplication puts the bit of byte j at bit 28 + j; no two partial products meet there)
-        const uint32_t nz = ((((w[d] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w[d]) >> 7) & 0x01010101u;
-        bits |= ((nz * 0x10204080u) >> 28) << (4 * d);
-    }
-    return bits;
-}
-
 // One piece of 1024 positions on its way: the values (word i of lane l = positions 256 i + 4 l .. + 3 of the piece) and,
 // per word, the rank of the lane's first position among the selected ones of the piece (upper bits) and which of the
 // four are selected (lowest four bits).

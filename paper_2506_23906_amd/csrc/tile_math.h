@@ -151,13 +151,14 @@ template <> __device__ __forceinline__ void to_operand_layout<2>(v4u (&raw)[4], 
 // 128 bits = 16 / sizeof(T) consecutive elements starting at element e0 (a multiple
 // of 16 bytes); elements at or beyond n read as zero.  The aligned 16-byte block that
 // holds the last element is read whole (it cannot straddle a page) and masked.
-template <typename T> __device__ __forceinline__ v4u load128(const T *x, uint64_t e0, uint64_t n, bool full) {
+template <typename T, bool kStreamed = true> __device__ __forceinline__ v4u load128(const T *x, uint64_t e0, uint64_t n, bool full) {
     // streamed once: non-temporal, so that the inputs do not push the gather vector (spmv)
     // and the descriptors out of L2
-    if (full) return __builtin_nontemporal_load(reinterpret_cast<const v4u *>(x + e0));
+    const v4u *p = reinterpret_cast<const v4u *>(x + e0);
+    if (full) return kStreamed ? __builtin_nontemporal_load(p) : *p;
     v4u w = {0, 0, 0, 0};
     if (e0 < n) {
-        w = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(x + e0));
+        w = kStreamed ? __builtin_nontemporal_load(p) : *p;
         const uint64_t valid_bytes = (n - e0) * sizeof(T);
 #pragma unroll
         for (int d = 0; d < 4; ++d) {

@@ -152,7 +152,7 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef short v8s __attribute__((ext_vector_type(8)));
 
 constexpr uint32_t kSpans = 8;                  // wave spans per tile of the kernels that number their segments
-constexpr uint32_t kGroupTiles = 8;             // tiles whose counts of segment starts are also kept as one sum
+constexpr uint32_t kGroupTiles = 8;             // tiles whose counts of segment starts one lane adds up
 constexpr uint32_t kGroupSpans = kSpans * kGroupTiles;   // = lanes of a wave
 
 // What a kernel instantiation computes (values match mmv_op where there is one):
@@ -225,7 +225,7 @@ struct Params {
     float *y;
     uint32_t *hdr;          // workspace header
     uint64_t *desc_v;       // value descriptors, one per tile
-    const uint32_t *group_count; // sum, CSR spmv: segment starts per group of eight tiles (position 0 not counted), or ...
+    const uint32_t *tile_count;  // sum, CSR spmv: segment starts per tile (position 0 not counted), or ...
     uint32_t count_is_prefix;    // ... their exclusive prefix sums already (very long vectors)
     const uint32_t *span_count;  // ... and per wave span (kSpans of them per tile)
     uint32_t num_tiles;
