@@ -110,8 +110,11 @@ def _check(status: int, what: str) -> None:
 
 
 def _stream_ptr(stream) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    # the handle of torch.cuda.current_stream(), without the Stream object around it: that takes 2.7 us to make, a
+    # quarter of a small call (the two queries 0.2 us)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dev(t: torch.Tensor, name: str) -> int:

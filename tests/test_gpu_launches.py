@@ -44,3 +44,11 @@ def test_one_tile_and_more_on_a_workspace_of_garbage(packed, dtype):
                 z = B.mmv_scan(dev(x), n=n, variant=variant, ws=ws)
                 assert B.mmv_workspace_status(ws) == 0
                 assert np.array_equal(z.cpu().numpy().astype(np.float64), oracle.scan(x).astype(np.float64))
+
+
+def test_calls_go_to_the_current_stream():
+    side = torch.cuda.Stream()
+    assert B._stream_ptr(None) == int(torch.cuda.current_stream().cuda_stream)
+    with torch.cuda.stream(side):
+        assert B._stream_ptr(None) == int(side.cuda_stream)
+    assert B._stream_ptr(side) == int(side.cuda_stream)
