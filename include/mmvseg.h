@@ -166,9 +166,9 @@ mmv_status mmv_segscan_static(const void *d_x, const void *d_flags, uint64_t n, 
  * Sums with index >= out_capacity are not written (d_nseg still holds the true
  * count); pass out_capacity = n to be safe.  The number of segments must be
  * below 2^32 (counts are carried in 32 bits).
- * Speed on long vectors (0.1 % of the flags set, % of the HBM peak): 8- and 16-bit inputs are fastest
- * with MMV_VARIANT_MFMA (n = 2^28: bytes 59 % against 52 %, fp16 69 % against 60 %: the same kernel, its 32x32 tiles
- * scanned by the matrix cores or by vector instructions), fp32 inputs are as fast with either (n = 2^27: 73 %). */
+ * Speed on long vectors (n = 2^28, 0.1 % of the flags set, % of the HBM peak): 8- and 16-bit inputs are fastest
+ * with MMV_VARIANT_MFMA (bytes 59 % against 52 %, fp16 69 % against 60 %: the same kernel, its 32x32 tiles
+ * scanned by the matrix cores or by vector instructions), fp32 inputs are about as fast with either (78 % and 80 %). */
 mmv_status mmv_segsum(const void *d_x, const void *d_flags, uint64_t n,
                       void *d_out, uint64_t out_capacity, uint64_t *d_nseg,
                       mmv_dtype dt, mmv_flag_fmt ff, mmv_variant v,

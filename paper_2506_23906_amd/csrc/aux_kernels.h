@@ -31,7 +31,7 @@ __global__ void mark_prepared_kernel(uint32_t *hdr, uint32_t mark) {
     if (threadIdx.x == 0 && blockIdx.x == 0) hdr[kHdrPrepared] = mark;
 }
 
-// 32 flag bytes -> one flag word (bit set iff the byte is not zero).
+// 16 flag bytes -> 16 bits (bit set iff the byte is not zero).
 __device__ __forceinline__ uint32_t bits_of_16_bytes(v4u w) {
     uint32_t bits = 0;
 #pragma unroll
