@@ -196,10 +196,11 @@ __global__ __launch_bounds__(256) void row_flags_kernel(const int32_t *row, uint
 // with entries sets the bit of its first entry; rows that share a word meet in an atomic OR on
 // a zeroed word), (b) the bit-packed mask of rows that have entries (one ballot per 64 rows),
 // (c) the number of segment starts inside every wave span of the main kernel and every one of its tiles (as in
-// count_spans_kernel; the rows of a wave that start in the same span share the atomic adds
+// count_spans_kernel; the tiles are equal here, so entry e lies in span e / span_elems; the rows of a wave that start in
+// the same span share the atomic adds
 // on zeroed tables) and (d) the mark that some row is empty.
 __global__ __launch_bounds__(256) void csr_flags_kernel(const int32_t *rowptr, uint64_t n_rows, uint32_t *fw,
-                                                        uint32_t *rowmask, uint32_t *hdr, TileRegions reg, uint32_t unit,
+                                                        uint32_t *rowmask, uint32_t *hdr, uint32_t span_elems,
                                                         uint32_t *tile_count, uint32_t *span_count) {
     const int lane = threadIdx.x & 63;
     const uint64_t r = (uint64_t)blockIdx.x * 256 + threadIdx.x;
@@ -210,11 +211,7 @@ __global__ __launch_bounds__(256) void csr_flags_kernel(const int32_t *rowptr, u
         nonempty = b > a;
         if (nonempty) {
             atomicOr(fw + ((uint32_t)a >> 5), 1u << ((uint32_t)a & 31u));
-            if (a > 0) {
-                const uint32_t tile = tile_of_element(reg, (uint64_t)a, unit);
-                const TileSpan ts = tile_span(reg, tile, unit);
-                mine = tile * kSpans + ((uint32_t)((uint64_t)a - ts.base)) / (ts.cpw * (unit / kSpans));
-            }
+            if (a > 0) mine = (uint32_t)a / span_elems;
         }
     }
     const uint64_t m = __ballot(nonempty);

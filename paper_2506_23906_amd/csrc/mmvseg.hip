@@ -436,7 +436,7 @@ mmv_status mmv_spmv_csr(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
     uint32_t *tile_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
     const uint64_t row_blocks = (n_rows + 255) / 256;
     csr_flags_kernel<<<(unsigned)row_blocks, 256, 0, s>>>(d_rowptr, n_rows, fw, (uint32_t *)(ws + C.rowmask),
-                                                          (uint32_t *)(ws + C.main_ws), plan.reg, plan.unit,
+                                                          (uint32_t *)(ws + C.main_ws), plan.body_elems / kSpans,
                                                           tile_count, (uint32_t *)(ws + C.main_ws + L.span_c));
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     // rowmap = COMPRESS(0 .. n_rows - 1, rowmask): the k-th segment belongs to row rowmap[k]
@@ -489,7 +489,7 @@ mmv_status mmv_spmv_csr_prepare(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, 
     uint32_t *tile_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
     const uint64_t row_blocks = (n_rows + 255) / 256;
     csr_flags_kernel<<<(unsigned)row_blocks, 256, 0, s>>>(d_rowptr, n_rows, fw, (uint32_t *)(ws + C.rowmask),
-                                                          (uint32_t *)(ws + C.main_ws), plan.reg, plan.unit,
+                                                          (uint32_t *)(ws + C.main_ws), plan.body_elems / kSpans,
                                                           tile_count, (uint32_t *)(ws + C.main_ws + L.span_c));
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     {

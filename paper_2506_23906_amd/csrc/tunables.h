@@ -194,20 +194,6 @@ __host__ __device__ __forceinline__ TileSpan tile_span(const TileRegions &R, uin
         }
     return {base + (uint64_t)(tile - first) * cpw * unit, cpw};
 }
-// The tile that holds element e.
-__host__ __device__ __forceinline__ uint32_t tile_of_element(const TileRegions &R, uint64_t e, uint32_t unit) {
-    uint64_t base = R.base[0];
-    uint32_t first = 0, cpw = R.cpw[0];
-#pragma unroll
-    for (int i = 1; i < kMaxRegions; ++i)
-        if (i < (int)R.count && e >= R.base[i]) {
-            base = R.base[i];
-            first = R.first[i];
-            cpw = R.cpw[i];
-        }
-    return first + (uint32_t)((e - base) / ((uint64_t)cpw * unit));
-}
-
 struct Params {
     const void *x;          // values (scan, sum) / val (spmv)
     const uint32_t *fw;     // packed flag words (scan, sum)
