@@ -298,6 +298,12 @@ uint32_t resident_workgroups(const void *kernel, int threads, std::atomic<uint32
     return value;
 }
 
+// Workgroups that take the tile of their own index: those resident from the start, and the first one in any case (the
+// number is 0 when the device could not be asked).  A single tile is launched without a reset, so it must draw no ticket.
+constexpr uint32_t first_round_of(uint32_t num_tiles, uint32_t resident) {
+    return num_tiles < resident ? num_tiles : resident > 0 ? resident : 1u;
+}
+
 template <typename TT, int kOp, bool kMfma> hipError_t launch_variant(Params P, bool chunk_form, hipStream_t s) {
     static std::atomic<uint32_t> occupancy[2][kMaxDevices];
     void (*kernel)(Params, const uint32_t *);
@@ -316,7 +322,7 @@ template <typename TT, int kOp, bool kMfma> hipError_t launch_variant(Params P, 
         }
     }
     const uint32_t resident = resident_workgroups((const void *)kernel, TT::kWaves * 64, occupancy[which]);
-    P.first_round = P.num_tiles < resident ? P.num_tiles : resident;
+    P.first_round = first_round_of(P.num_tiles, resident);
     kernel<<<P.num_tiles, TT::kWaves * 64, 0, s>>>(P, P.hdr + kHdrHints);
     return hipGetLastError();
 }
