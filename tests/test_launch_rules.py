@@ -1,11 +1,13 @@
-"""Rules of the host side that no call can force on a machine at hand, checked at compile time on the CPU: the
-translation unit is parsed for the host only, with static assertions behind it."""
+"""Rules of the host side that no call can force on a machine at hand, checked on the CPU: those of the C++ side at compile
+time (the translation unit is parsed for the host only, with static assertions behind it)."""
 import os
 import subprocess
+import types
 
 import pytest
+import torch
 
-from paper_2506_23906_amd import build
+from paper_2506_23906_amd import binding, build
 
 CSRC = os.path.dirname(build.SRC)
 
@@ -27,3 +29,10 @@ def test_the_first_workgroup_never_draws_a_ticket(tmp_path, tiles, resident, fir
     without a reset of the ticket."""
     assert holds(tmp_path, "first_round_of(%d, %d) == %d" % (tiles, resident, first))
     assert not holds(tmp_path, "first_round_of(%d, %d) == 0" % (tiles, resident))
+
+
+def test_the_current_stream_without_the_raw_queries(monkeypatch):
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    assert binding._stream_ptr(None) == 77
+    assert binding._stream_ptr(types.SimpleNamespace(cuda_stream=5)) == 5
