@@ -50,8 +50,8 @@ __device__ __forceinline__ uint32_t bits_of_32_bytes(const uint8_t *f, uint64_t 
 }
 
 // Segmented sum, step "scan of the end markers" of COMPRESS (proof of the SCD / SSCR theorem)
-// at the granularity of the spans that the waves of the main kernel take: workgroup t counts the segment starts in tile t
-// and in each of its eight spans, one span per wave (position 0 is not counted: it opens segment 0
+// at tile granularity: workgroup t counts the segment starts in tile t and (sum_kernel, whose waves take a span of the tile
+// each) in each of its eight spans (position 0 is not counted: it opens segment 0
 // whatever its flag says; bits at or beyond n are not counted).  The main kernel adds up what it needs (starts_before_part).
 // Flags of one byte per element (kBytes) are packed on the way: the words go to `packed` (10^8 values: packing kernel
 // 19.4 us and counting kernel 5.3 us -> 18.2 us together).
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(512) void count_spans_kernel(uint32_t *zero, uint64
     }
     sum = wave_sum(sum);
     if (lane == 0) {
-        span_cnt[tile * kSpans + wave] = sum;
+        if (span_cnt) span_cnt[tile * kSpans + wave] = sum;
         s_part[wave] = sum;
     }
     __syncthreads();
@@ -199,42 +199,35 @@ __global__ __launch_bounds__(256) void row_flags_kernel(const int32_t *row, uint
 // Row pointers of a CSR matrix -> (a) bit-packed segment-start flags over the non-zeros (a row
 // with entries sets the bit of its first entry; rows that share a word meet in an atomic OR on
 // a zeroed word), (b) the bit-packed mask of rows that have entries (one ballot per 64 rows),
-// (c) the number of segment starts inside every wave span of the main kernel and every one of its tiles (as in
-// count_spans_kernel; the tiles are equal here, so entry e lies in span e / span_elems; the rows of a wave that start in
-// the same span share the atomic adds
-// on zeroed tables) and (d) the mark that some row is empty.
+// (c) the number of segment starts inside every tile of the main kernel (as in count_spans_kernel; the tiles are equal
+// here, so entry e lies in tile e / tile_elems; the rows of a wave that start in the same tile share one atomic add on a
+// zeroed table: adds to one address are served one after the other, about 11 ns each) and (d) the mark that some row is empty.
 __global__ __launch_bounds__(256) void csr_flags_kernel(const int32_t *rowptr, uint64_t n_rows, uint32_t *fw,
-                                                        uint32_t *rowmask, uint32_t *hdr, uint32_t span_elems,
-                                                        uint32_t *tile_count, uint32_t *span_count) {
+                                                        uint32_t *rowmask, uint32_t *hdr, uint32_t tile_elems,
+                                                        uint32_t *tile_count) {
     const int lane = threadIdx.x & 63;
     const uint64_t r = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     bool nonempty = false;
-    uint32_t mine = 0xFFFFFFFFu;   // span (of all tiles) of the first entry of a row that is counted
+    uint32_t tile = 0xFFFFFFFFu;   // tile of the first entry of a row that is counted
     if (r < n_rows) {
         const int32_t a = rowptr[r], b = rowptr[r + 1];
         nonempty = b > a;
         if (nonempty) {
             atomicOr(fw + ((uint32_t)a >> 5), 1u << ((uint32_t)a & 31u));
-            if (a > 0) mine = (uint32_t)a / span_elems;
+            if (a > 0) tile = (uint32_t)a / tile_elems;
         }
     }
     const uint64_t m = __ballot(nonempty);
     // a matrix none of whose rows is empty needs no row map: segment k is row k
     if (__ballot(r < n_rows && !nonempty) != 0 && lane == 0) hdr[kHdrEmptyRows] = 1u;
-    // one atomic add per distinct span among the rows of the wave, and one per distinct tile (adds to one address are
-    // served one after the other, about 11 ns each)
-    auto add_distinct = [&](uint32_t key, uint32_t *table) {
-        uint64_t todo = __ballot(key != 0xFFFFFFFFu);
-        while (todo) {
-            const int first = __ffsll((unsigned long long)todo) - 1;
-            const uint32_t t = __shfl(key, first);
-            const uint64_t same = __ballot(key == t);
-            if (lane == first) atomicAdd(table + t, (uint32_t)__popcll((unsigned long long)same));
-            todo &= ~same;
-        }
-    };
-    add_distinct(mine, span_count);
-    add_distinct(mine == 0xFFFFFFFFu ? mine : mine / kSpans, tile_count);
+    uint64_t todo = __ballot(tile != 0xFFFFFFFFu);
+    while (todo) {   // one round per distinct tile among the rows of the wave
+        const int first = __ffsll((unsigned long long)todo) - 1;
+        const uint32_t t = __shfl(tile, first);
+        const uint64_t same = __ballot(tile == t);
+        if (lane == first) atomicAdd(tile_count + t, (uint32_t)__popcll((unsigned long long)same));
+        todo &= ~same;
+    }
     const uint64_t r0 = r - lane;
     if (lane == 0 && r0 < n_rows) {
         rowmask[r0 >> 5] = (uint32_t)m;

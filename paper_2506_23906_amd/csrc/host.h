@@ -62,6 +62,11 @@ inline int chunk_form_cpw(mmv_op op, mmv_dtype dt, bool mfma) {
     if (dt == MMV_BF16_F32 && chunk_sum_kernel<TBF16, kSum, true>()) return sum_cpw<TBF16>();
     return 0;
 }
+// Whether the segmented sum of this type needs its counts of segment starts per wave span too (sum_kernel, whose waves take
+// a span of the tile each).  The waves of stream_kernel count inside their tile from its flag words; with a table per span
+// beside the one per tile, csr_flags_kernel did its atomic adds twice, and the reset cleared eight times the words (CSR product
+// in one step, 3.5 M entries in blocks of 16: 22.2 us before there was one, 24.3 with it, 21.4 without it again).
+inline bool segsum_spans(mmv_dtype dt) { return dt != MMV_F32_F32; }
 inline int waves_of(mmv_op op, mmv_dtype dt) {
     if (is_spmv(op)) return TSpmv::kWaves;
     switch (dt) {
@@ -181,10 +186,10 @@ WsLayout ws_layout(mmv_op op, mmv_dtype dt, mmv_flag_fmt ff, uint64_t n) {
     size_t off = kHdrBytes;
     L.desc_v = off;
     off += round256(t * 8);
-    L.desc_c = off;   // counts of segment starts: per tile, and per wave span
+    L.desc_c = off;   // counts of segment starts: per tile, and (sum_kernel) per wave span
     if (op == MMV_OP_SEGSUM || op == MMV_OP_SPMV_CSR) off += round256(t * 4);
     L.span_c = off;
-    if (op == MMV_OP_SEGSUM || op == MMV_OP_SPMV_CSR) off += round256(t * 4 * kSpans);
+    if (op == MMV_OP_SEGSUM && segsum_spans(dt)) off += round256(t * 4 * kSpans);
     L.packed = off;
     if (is_spmv(op) || (ff == MMV_FLAGS_U8 && op != MMV_OP_SCAN)) off += round256(((n + 63) / 64) * 8);
     L.total = off;

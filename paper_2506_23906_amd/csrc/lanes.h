@@ -132,19 +132,23 @@ __device__ T lookback(const uint64_t *desc, int tile, int lane, uint32_t *hdr) {
     return lookback_from<T, kAlu, 0>(desc, tile, lane, hdr, nullptr);
 }
 
-// Number of segment starts before span `sp` (of all tiles; a multiple of kSpans: before that tile), from the counts
-// per tile and per span.  Wave-wide in two halves, so that the loads can go out ahead of others: the lane's part, and their
-// sum.  A lane takes eight tiles (two 128-bit loads), so the wave covers 512 tiles before the first one of its own group
-// of eight; of that group it takes the spans before its own.
-__device__ __forceinline__ uint32_t starts_before_part(const Params &P, uint32_t sp, int lane) {
-    const uint32_t g = sp / kGroupSpans;
+// Number of segment starts before span `span` of a tile (0: before the tile), from the counts per tile and (kUseSpans, or
+// there is no table of them and `span` is 0) per span.  Wave-wide in two halves, so that the loads can go out ahead of others:
+// the lane's part, and their sum.  A lane takes eight tiles (two 128-bit loads), so the wave covers 512 tiles before the
+// first one of the tile's own group of eight; of that group it takes the spans (or tiles) before its own.
+template <bool kUseSpans> __device__ __forceinline__ uint32_t starts_before_part(const Params &P, uint32_t tile, uint32_t span, int lane) {
+    const uint32_t g = tile / kGroupTiles;
     uint32_t part = 0;
     if (P.count_is_prefix) {
-        if (lane < (int)(sp % kSpans)) part = P.span_count[sp / kSpans * kSpans + lane];
-        if (lane == 0) part += P.tile_count[sp / kSpans];
+        if (kUseSpans && lane < (int)span) part = P.span_count[tile * kSpans + lane];
+        if (lane == 0) part += P.tile_count[tile];
         return part;
     }
-    if (lane < (int)(sp % kGroupSpans)) part = P.span_count[g * kGroupSpans + lane];
+    if constexpr (kUseSpans) {
+        if (lane < (int)(tile % kGroupTiles * kSpans + span)) part = P.span_count[g * kGroupSpans + lane];
+    } else {
+        if (lane < (int)(tile % kGroupTiles)) part = P.tile_count[g * kGroupTiles + lane];
+    }
     for (uint32_t i = lane; i < g; i += 128) {   // four loads under way at a time
         v4u a[4] = {};
 #pragma unroll

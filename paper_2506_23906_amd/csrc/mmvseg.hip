@@ -150,12 +150,12 @@ mmv_status mmv_segsum(const void *d_x, const void *d_flags, uint64_t n, void *d_
     P.out = d_out;
     P.out_cap = out_capacity;
     P.nseg = d_nseg;
-    // number of segment starts per span and per tile
+    // number of segment starts per tile and, where the main kernel needs it, per span
     const TilePlan plan = tile_plan(MMV_OP_SEGSUM, dt, n, v == MMV_VARIANT_MFMA);
     const WsLayout L = ws_layout(MMV_OP_SEGSUM, dt, ff, n);
     if (plan.tiles > 0x7fffffffull) return MMV_ERR_INVALID_ARG;
     uint32_t *tile_count = (uint32_t *)((char *)d_ws + L.desc_c);
-    uint32_t *span_count = (uint32_t *)((char *)d_ws + L.span_c);
+    uint32_t *span_count = segsum_spans(dt) ? (uint32_t *)((char *)d_ws + L.span_c) : nullptr;
     auto count = ff == MMV_FLAGS_U8 ? count_spans_kernel<true> : count_spans_kernel<false>;
     count<<<(unsigned)plan.tiles, 512, 0, s>>>((uint32_t *)d_ws, L.desc_c / 4, d_flags, (uint32_t *)((char *)d_ws + L.packed), n,
                                                plan.reg, plan.unit, tile_count, span_count);
@@ -213,7 +213,7 @@ mmv_status mmv_spmv_coo(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
 
 // SpMV in two steps: the mark that the first step leaves in the header for this matrix shape (never 0).  It names the
 // layout of the counts as well (kPlanLayout), which the product kernel relies on.
-static constexpr uint64_t kPlanLayout = 3;
+static constexpr uint64_t kPlanLayout = 4;
 static uint32_t prepared_mark(mmv_op op, uint64_t n_rows, uint64_t nnz) {
     uint64_t h = (nnz + 0x9E3779B97F4A7C15ull) * 0xD6E8FEB86659FD93ull + n_rows * 0xCA5A826395121157ull + (uint64_t)op + (kPlanLayout << 32);
     h ^= h >> 32;
@@ -436,8 +436,7 @@ mmv_status mmv_spmv_csr(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
     uint32_t *tile_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
     const uint64_t row_blocks = (n_rows + 255) / 256;
     csr_flags_kernel<<<(unsigned)row_blocks, 256, 0, s>>>(d_rowptr, n_rows, fw, (uint32_t *)(ws + C.rowmask),
-                                                          (uint32_t *)(ws + C.main_ws), plan.body_elems / kSpans,
-                                                          tile_count, (uint32_t *)(ws + C.main_ws + L.span_c));
+                                                          (uint32_t *)(ws + C.main_ws), plan.body_elems, tile_count);
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     // rowmap = COMPRESS(0 .. n_rows - 1, rowmask): the k-th segment belongs to row rowmap[k]
     {
@@ -466,7 +465,6 @@ mmv_status mmv_spmv_csr(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
         if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     }
     P.tile_count = tile_count;
-    P.span_count = (const uint32_t *)(ws + C.main_ws + L.span_c);
     return launch_seg<TSpmv, kSpmvCsr>(P, v, s) == hipSuccess ? MMV_OK : MMV_ERR_HIP;
 }
 
@@ -489,8 +487,7 @@ mmv_status mmv_spmv_csr_prepare(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, 
     uint32_t *tile_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
     const uint64_t row_blocks = (n_rows + 255) / 256;
     csr_flags_kernel<<<(unsigned)row_blocks, 256, 0, s>>>(d_rowptr, n_rows, fw, (uint32_t *)(ws + C.rowmask),
-                                                          (uint32_t *)(ws + C.main_ws), plan.body_elems / kSpans,
-                                                          tile_count, (uint32_t *)(ws + C.main_ws + L.span_c));
+                                                          (uint32_t *)(ws + C.main_ws), plan.body_elems, tile_count);
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     {
         EventsOff quiet;
@@ -542,7 +539,6 @@ mmv_status mmv_spmv_csr_run(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, cons
     P.fw = (const uint32_t *)(ws + C.main_ws + L.packed);
     P.count_is_prefix = plan.tiles > kCountTiles ? 1u : 0u;
     P.tile_count = (const uint32_t *)(ws + C.main_ws + L.desc_c);
-    P.span_count = (const uint32_t *)(ws + C.main_ws + L.span_c);
     P.prepared = prepared_mark(MMV_OP_SPMV_CSR, n_rows, nnz);
     // header and value descriptors of the main kernel; the counts, flag words, row mask and row map behind them stay
     const uint64_t zero_words = L.desc_c / 4;

@@ -194,7 +194,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves> 
         // number of segment starts before my tile, while the loads are in flight
         static_assert(kWaves == (int)kSpans, "one span per wave");
         if (wave == 1) {
-            const uint32_t c = wave_sum<uint32_t, kAluLanes>(starts_before_part(P, tile * kSpans, lane));
+            const uint32_t c = wave_sum<uint32_t, kAluLanes>(starts_before_part<true>(P, tile, 0, lane));
             if (lane == 0) sm.carry_c = c;
         }
     }

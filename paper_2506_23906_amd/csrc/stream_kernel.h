@@ -117,7 +117,7 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
     uint32_t count_part = 0;
     v4u fl[2] = {};
     if constexpr (kCounts) {
-        count_part = starts_before_part(P, tile * kSpans, lane);
+        count_part = starts_before_part<false>(P, tile, 0, lane);
         const uint64_t words = (n + 31) >> 5, w0 = (span.base >> 5) + 8u * part;
         if (part < 4u * (uint32_t)units) {
 #pragma unroll
@@ -151,14 +151,14 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
     }
     // starts of the tile: (alone) up to and with my eight words; else before the pair of units 2 lane, 2 lane + 1, and in
     // the first of them
-    uint32_t count_carry = 0, starts_upto = 0, starts_even = 0;
+    uint32_t count_carry = 0, starts_upto = 0, starts_even = 0, starts_all = 0;   // (starts_all: of the whole tile, in lane 63)
     if constexpr (kCounts) {
         count_carry = wave_sum<uint32_t, true>(count_part);
         uint32_t s = 0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) s += __popc(fl[i / 4][i % 4]);
         if (alone) {
-            starts_upto = wave_inclusive_scan(s);
+            starts_all = starts_upto = wave_inclusive_scan(s);
         } else {
             s += dpp_or_zero<0x111, 0xF>(s);
             s += dpp_or_zero<0x112, 0xF>(s);
@@ -166,11 +166,11 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
             __syncthreads();
             starts_even = 2 * lane < kMaxUnits ? sm.unit_c[2 * lane] : 0u;
             const uint32_t both = starts_even + (2 * lane < kMaxUnits ? sm.unit_c[2 * lane + 1] : 0u);
-            starts_upto = wave_inclusive_scan(both) - both;
+            starts_all = wave_inclusive_scan(both);
+            starts_upto = starts_all - both;
         }
         if (kOp == kSum && !P.count_is_prefix && tile == P.num_tiles - 1 && wave == 0) {   // (else an earlier kernel has written it)
-            const uint32_t all = wave_sum<uint32_t, true>(starts_before_part(P, (tile + 1) * kSpans, lane));
-            if (lane == 0) *P.nseg = (uint64_t)all + 1u;
+            if (lane == 63) *P.nseg = (uint64_t)count_carry + starts_all + 1u;
         }
     }
 

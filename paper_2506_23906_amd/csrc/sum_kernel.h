@@ -344,7 +344,7 @@ __device__ __forceinline__ void sum_tile(const Params &P, SumShared<TT> &sm, con
     // segment starts before my span (position 0 of the vector is not counted).
     // Asked for ahead of the values (loads come back in the order they went out), added up when the first end needs them.
     static_assert(kWaves == (int)kSpans, "one span per wave");
-    const uint32_t count_part = starts_before_part(P, tile * kSpans + wave, lane);
+    const uint32_t count_part = starts_before_part<true>(P, tile, wave, lane);
     __builtin_amdgcn_sched_barrier(0);
     SumSlot<TT> slot[kDepth];
 #pragma unroll

@@ -213,7 +213,7 @@ struct Params {
     uint64_t *desc_v;       // value descriptors, one per tile
     const uint32_t *tile_count;  // sum, CSR spmv: segment starts per tile (position 0 not counted), or ...
     uint32_t count_is_prefix;    // ... their exclusive prefix sums already (very long vectors)
-    const uint32_t *span_count;  // ... and per wave span (kSpans of them per tile)
+    const uint32_t *span_count;  // sum of 8- and 16-bit values: ... and per wave span (kSpans of them per tile)
     uint32_t num_tiles;
     TileRegions reg;        // which elements a tile covers
     uint32_t prepared;      // SpMV in two steps: the mark the preparing call must have left in the header (0: not asked for)
