@@ -15,6 +15,7 @@ inline size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 // tile time), and those of the last round would leave most of the chip idle while the last ones finish.
 // (Measured on the int8 scan: the time of a launch is a fixed 22 us plus 0.216 ms per 2^28 elements with
 // full tiles throughout and one group of short tiles at the end.)
+constexpr uint64_t kComputeUnits = 256;   // of an MI355X (not asked from the device: the sizes of workspaces depend on the plans)
 constexpr uint64_t kResident = MMV_MIN_TILES;   // workgroups resident at once (2 per compute unit)
 #ifndef MMV_HEAD_GROUP
 #define MMV_HEAD_GROUP 128   // tiles per length at the start of a long vector (0: full tiles from the start)
@@ -85,6 +86,7 @@ struct TilePlan {
     uint32_t unit;         // elements that one step of a region's `cpw` stands for: one chunk per wave (stream form: one unit of 1024)
     uint32_t body_elems;   // elements of a tile in the middle of the vector
     bool chunk_form;       // segmented sum: the kernel that streams through long spans (sum_kernel) takes it
+    bool short_form;       // stream form: at most kShortUnits units per tile, which a wave loads at once
 };
 inline TilePlan tile_plan(mmv_op op, mmv_dtype dt, uint64_t n, bool mfma = true) {
     TilePlan p = {};
@@ -94,11 +96,18 @@ inline TilePlan tile_plan(mmv_op op, mmv_dtype dt, uint64_t n, bool mfma = true)
         // compute unit is busy with gathers all the time, one that holds three tiles when others hold two finishes last
         // (SpMV of 2^25 scattered entries: 683 tiles 0.238 ms, 763 tiles 0.213 ms; shorter tiles for the last 5 to 20 % of
         // the vector make sums and SpMV 1 to 10 % slower).  A tile has at least one unit per wave.
-        const uint64_t resident = 128 * (uint64_t)stream_waves_per_simd(is_spmv(op) ? kSpmv : kSum, mfma);
+        uint64_t resident = kComputeUnits / 2 * (uint64_t)stream_waves_per_simd(is_spmv(op) ? kSpmv : kSum, mfma);
         const uint64_t units = (n + kUnitElems - 1) / kUnitElems;
+        // A short vector gets one workgroup per compute unit as long as the form for short tiles takes that (sums then two):
+        // with some of them holding two, it takes longer than with two units for a wave instead of one (sum of 3 * 10^6
+        // values: 366 tiles of 8 units 11.5 us, 245 tiles of 12 units 10.6; CSR SpMV of 2.5 M entries: 14.6 and 13.3).
+        // SpMV of 5 to 8 M entries in 512 short tiles: from 13 % faster (scattered) to 6 % slower (blocks of 16) than in 768.
+        if (units <= kComputeUnits * kShortUnits) resident = kComputeUnits, p.short_form = true;
+        else if (!is_spmv(op) && units <= 2 * kComputeUnits * kShortUnits) resident = 2 * kComputeUnits;
         const uint64_t rounds = (units + resident * kMaxUnits - 1) / (resident * kMaxUnits);
         uint64_t c = rounds ? (units + resident * rounds - 1) / (resident * rounds) : 1;
         if (c < kSpans) c = kSpans;
+        if (!is_spmv(op) && c <= (uint64_t)kShortUnits) p.short_form = true;
         p.unit = kUnitElems;
         p.body_elems = (uint32_t)(c * kUnitElems);
         R.cpw[0] = (uint32_t)c;
@@ -309,21 +318,22 @@ constexpr uint32_t first_round_of(uint32_t num_tiles, uint32_t resident) {
     return num_tiles < resident ? num_tiles : resident > 0 ? resident : 1u;
 }
 
-template <typename TT, int kOp, bool kMfma> hipError_t launch_variant(Params P, bool chunk_form, hipStream_t s) {
-    static std::atomic<uint32_t> occupancy[2][kMaxDevices];
+template <typename TT, int kOp, bool kMfma> hipError_t launch_variant(Params P, const TilePlan &plan, hipStream_t s) {
+    static std::atomic<uint32_t> occupancy[3][kMaxDevices];
     void (*kernel)(Params, const uint32_t *);
     int which = 0;
     if constexpr (stream_form<TT, kOp>()) {
-        kernel = stream_kernel<TT, kOp, kMfma, true>;
+        const bool narrow = kOp == kSum || P.cols_narrow;   // (a long x, whatever the matrix: the form for long vectors)
+        which = !narrow ? 1 : plan.short_form ? 2 : 0;
+        kernel = which == 2 ? stream_kernel<TT, kOp, kMfma, true, true> : stream_kernel<TT, kOp, kMfma, true, false>;
         if constexpr (kOp != kSum) {
-            which = P.cols_narrow ? 0 : 1;
-            if (!P.cols_narrow) kernel = stream_kernel<TT, kOp, kMfma, false>;
+            if (!narrow) kernel = stream_kernel<TT, kOp, kMfma, false, false>;
         }
     } else {
         kernel = seg_kernel<TT, kOp, kMfma>;
         if constexpr (chunk_sum_kernel<TT, kOp, kMfma>()) {
-            which = chunk_form ? 1 : 0;
-            if (chunk_form) kernel = sum_kernel<TT, kMfma>;
+            which = plan.chunk_form ? 1 : 0;
+            if (plan.chunk_form) kernel = sum_kernel<TT, kMfma>;
         }
     }
     const uint32_t resident = resident_workgroups((const void *)kernel, TT::kWaves * 64, occupancy[which]);
@@ -340,9 +350,9 @@ hipError_t launch_seg(Params P, mmv_variant v, hipStream_t s) {
     P.reg = plan.reg;
     if (tl_ev_start && hipEventRecord(tl_ev_start, s) != hipSuccess) return hipErrorUnknown;
     if (v == MMV_VARIANT_MFMA) {
-        if (launch_variant<TT, kOp, true>(P, plan.chunk_form, s) != hipSuccess) return hipErrorUnknown;
+        if (launch_variant<TT, kOp, true>(P, plan, s) != hipSuccess) return hipErrorUnknown;
     } else {
-        if (launch_variant<TT, kOp, false>(P, plan.chunk_form, s) != hipSuccess) return hipErrorUnknown;
+        if (launch_variant<TT, kOp, false>(P, plan, s) != hipSuccess) return hipErrorUnknown;
     }
     const hipError_t e = hipGetLastError();
     if (tl_ev_stop && hipEventRecord(tl_ev_stop, s) != hipSuccess) return hipErrorUnknown;

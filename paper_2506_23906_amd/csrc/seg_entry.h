@@ -52,8 +52,8 @@ __global__ __launch_bounds__(TT::kWaves * 64, sum_waves_per_simd<TT>()) void sum
 }
 
 // The segmented sum of 32-bit values and SpMV.
-template <typename TT, int kOp, bool kMfma, bool kNarrow>
-__global__ __launch_bounds__(TT::kWaves * 64, stream_waves_per_simd(kOp, kMfma)) void stream_kernel(Params P, const uint32_t *__restrict__ hints) {
+template <typename TT, int kOp, bool kMfma, bool kNarrow, bool kShort>
+__global__ __launch_bounds__(TT::kWaves * 64, stream_waves_per_simd(kOp, kMfma, kShort)) void stream_kernel(Params P, const uint32_t *__restrict__ hints) {
     __shared__ StreamShared<TT::kWaves> sm;
 #if MMV_LOAD_PRIO
     __builtin_amdgcn_s_setprio(MMV_LOAD_PRIO);
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(TT::kWaves * 64, stream_waves_per_simd(kOp, kMfma))
         if (P.prepared && hints[kHdrPrepared - kHdrHints] != P.prepared) return;
     }
     const uint32_t tile = take_tile(P, sm);
-    stream_tile<TT, kOp, kMfma, kNarrow>(P, hints, sm, tile);
+    stream_tile<TT, kOp, kMfma, kNarrow, kShort>(P, hints, sm, tile);
 }
 
 }  // namespace

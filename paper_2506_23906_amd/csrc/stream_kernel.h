@@ -19,7 +19,6 @@ namespace {
 // without, with one chunk (two) of 2048 elements per wave and tile held in registers as in seg_tile -> now:
 //   sum of 10^8 fp32 values, 1 % of them starts    123 / 88 us -> 82 / 73 us (5.1 / 5.7 TB/s)
 //   ... 30 % starts                                193 / 143 -> 133 / 133
-//   sum of 2^23, 1 % starts                        13.5 / 13.6 -> 15.3 / 15.2 (bound by the life of one tile)
 //   CSR SpMV, sparse attention, 62.8 M entries in blocks of 64 (prepared)     127 -> 103 us (4.9 TB/s)
 //   ... 9.5 M entries in blocks of 16                                         37.7 -> 24.9
 //   COO SpMV, 33.6 M entries in scattered columns                             236 -> 239 (bound by the gathers)
@@ -48,16 +47,34 @@ constexpr int kUnitRows = 32;
 #define MMV_STREAM_WPS_SPMV 6
 #endif
 
+// Vectors of at most 16 units per tile are bound by the life of one tile, and get a form of their own (kShort): a wave has
+// both its units loaded before the first is worked on.  In the other form the loads of its second unit are waited for behind
+// the stores of the first (one counter counts both in order, and the number of stores is not known), and the table lookups,
+// which stand in branches, ahead of the first value.  Whole calls in a graph, one chunk of 2048 elements per wave as in
+// seg_tile / the form for long vectors / this one (sums: matrix cores, 1 % of the values start a segment):
+//   sum of 3 * 10^5 values    9.0 /  9.4 /  9.0 us        sum of 2^22 values   11.3 / 13.0 / 11.7
+//   sum of 3 * 10^6          10.9 / 12.6 / 10.9           sum of 2^23          13.3 / 16.0 / 14.1
+//   ... 30 % starts          14.5 / 13.8 / 12.7           ... 30 % starts      21.7 / 19.5 / 18.2
+//   CSR SpMV, prepared, 3.9 M entries in blocks of 4   15.4 / 16.2 / 15.3;  3.5 M in blocks of 16   14.8 / 15.5 / 14.7
+// (2^22 and 2^23 fill the rounds of seg_tile exactly; there, with few starts, one chunk per wave in seg_tile was 4 to 6 %
+// ahead.)
+constexpr int kShortRounds = 2;
+
 template <typename TT, int kOp> constexpr bool stream_form() {
     return kOp == kSpmv || kOp == kSpmvCsr || (kOp == kSum && sizeof(typename TT::in_t) == 4);
 }
 
-constexpr int stream_waves_per_simd(int op, bool mfma) {
-    return op == kSum ? (mfma ? MMV_STREAM_WPS_SUM : MMV_STREAM_WPS_SUM_SHUFFLE) : MMV_STREAM_WPS_SPMV;
+constexpr int stream_waves_per_simd(int op, bool mfma, bool is_short = false) {
+    return is_short ? 4 : op == kSum ? (mfma ? MMV_STREAM_WPS_SUM : MMV_STREAM_WPS_SUM_SHUFFLE) : MMV_STREAM_WPS_SPMV;
 }
 
+constexpr int kShortUnits = (int)kSpans * kShortRounds;   // most units of a tile of the form for short vectors
 constexpr int kMaxUnits = (int)kSpans * MMV_STREAM_CPW;   // units of a tile: two per lane of a wave
 static_assert(kMaxUnits <= 128, "the units of a tile are scanned by one wave, two per lane");
+
+constexpr uint32_t kShortCounts = 3;   // 256 tiles each
+static_assert(128 * stream_waves_per_simd(kSum, true) <= 256 * (int)kShortCounts && 128 * stream_waves_per_simd(kSum, false) <= 256 * (int)kShortCounts,
+              "tiles of a short vector: one round of workgroups");
 
 template <int kWaves> struct StreamShared {
     __attribute__((aligned(16))) uint32_t rows[kWaves][kUnitRows * kRowStride];
@@ -92,13 +109,13 @@ __device__ __forceinline__ void stream_load(const Params &P, uint64_t unit_base,
 
 // kNarrow: x has at most 2^30 entries, so byte offsets into it fit 32 bits (one register per address, no 64-bit
 // additions: SpMV with short rows 8 % faster, with scattered columns 2 %).
-template <typename TT, int kOp, bool kMfma, bool kNarrow>
+template <typename TT, int kOp, bool kMfma, bool kNarrow, bool kShort>
 __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__restrict__ hints, StreamShared<TT::kWaves> &sm,
                                             const uint32_t tile) {
     constexpr int kWaves = TT::kWaves;
     constexpr bool kProduct = kOp != kSum;
     constexpr bool kCounts = kOp != kSpmv;   // the index of an output is the ordinal of its segment
-    constexpr int kDepth = kProduct ? MMV_STREAM_DEPTH_SPMV : MMV_STREAM_DEPTH_SUM;
+    constexpr int kDepth = kShort ? kShortRounds : kProduct ? MMV_STREAM_DEPTH_SPMV : MMV_STREAM_DEPTH_SUM;
     static_assert(kWaves == (int)kSpans, "units are dealt to eight waves");
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -112,25 +129,42 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
     // its flag words, eight words per lane.  In a tile of up to 16 units every wave counts for itself; in a longer one
     // each wave counts its part (four threads per unit) and they exchange the counts through LDS.
     // Asked for ahead of the values (loads come back in the order they went out).
-    const bool alone = units <= 16;
+    const bool alone = kShort || units <= 16;
     const uint32_t part = alone ? (uint32_t)lane : (uint32_t)tid;   // which eight flag words of the tile I count
+    // The first bits of words that do not count are cleared: those beyond n, and position 0, which opens segment 0 whatever
+    // its flag says.
     uint32_t count_part = 0;
-    v4u fl[2] = {};
-    if constexpr (kCounts) {
+    v4u fl[2] = {}, tc[kShort ? kShortCounts : 1];
+    const bool mine = part < 4u * (uint32_t)units;
+    const uint64_t w0 = (span.base >> 5) + 8u * part, words = (n + 31) >> 5;
+    auto clear_uncounted = [&] {
+        if (tile == 0 && part == 0) fl[0][0] &= ~1u;
+        if (!mine || w0 * 32 + 256u > n) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint64_t e0 = w0 * 32 + 32u * i;
+                if (!mine || e0 >= n) fl[i / 4][i % 4] = 0;
+                else if (e0 + 32 > n) fl[i / 4][i % 4] &= (1u << (uint32_t)(n - e0)) - 1u;
+            }
+        }
+    };
+    if constexpr (kCounts && kShort) {
+        // no branch around these loads: what is loaded in a branch is waited for where it ends
+        // (a lane with nothing to read reads the first words)
+#pragma unroll
+        for (uint32_t j = 0; j < kShortCounts; ++j) {
+            const uint32_t e = 256u * j + 4u * lane;
+            tc[j] = *reinterpret_cast<const v4u *>(P.tile_count + (e < tile ? e : 0u));
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) fl[i] = *reinterpret_cast<const v4u *>(P.fw + (mine && w0 + 4 * i < words ? w0 + 4 * i : 0));
+    } else if constexpr (kCounts) {
         count_part = starts_before_part<false>(P, tile, 0, lane);
-        const uint64_t words = (n + 31) >> 5, w0 = (span.base >> 5) + 8u * part;
-        if (part < 4u * (uint32_t)units) {
+        if (mine) {
 #pragma unroll
             for (int i = 0; i < 2; ++i)
                 if (w0 + 4 * i < words) fl[i] = *reinterpret_cast<const v4u *>(P.fw + w0 + 4 * i);   // (the aligned block of the last word is read whole)
-            if (tile == 0 && part == 0) fl[0][0] &= ~1u;   // position 0 opens segment 0 whatever its flag says: not counted
-            if (span.base + 256u * part + 256u > n) {      // bits beyond n do not count
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const uint64_t e0 = span.base + 256u * part + 32u * i;
-                    if (e0 + 32 > n) fl[i / 4][i % 4] = e0 < n ? fl[i / 4][i % 4] & ((1u << (uint32_t)(n - e0)) - 1u) : 0u;
-                }
-            }
+            clear_uncounted();
         }
     }
     // CSR: without empty rows the k-th segment is row k and the row map was not made
@@ -152,6 +186,13 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
     // starts of the tile: (alone) up to and with my eight words; else before the pair of units 2 lane, 2 lane + 1, and in
     // the first of them
     uint32_t count_carry = 0, starts_upto = 0, starts_even = 0, starts_all = 0;   // (starts_all: of the whole tile, in lane 63)
+    if constexpr (kCounts && kShort) {
+#pragma unroll
+        for (uint32_t j = 0; j < kShortCounts; ++j)
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) count_part += 256u * j + 4u * lane + k < tile ? tc[j][k] : 0u;
+        clear_uncounted();
+    }
     if constexpr (kCounts) {
         count_carry = wave_sum<uint32_t, true>(count_part);
         uint32_t s = 0;
@@ -184,8 +225,13 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
         else P.y[at] = v;
     };
 
+    if constexpr (kShort) {   // (so that no wait for the second unit stands behind the stores of the first)
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+        __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll 1
-    for (int u0 = 0; u0 < rounds; u0 += kDepth) {
+    for (int u0 = 0; u0 < (kShort ? 1 : rounds); u0 += kDepth) {
 #pragma unroll
         for (int i = 0; i < kDepth; ++i) {
             const int u = u0 + i;
@@ -329,6 +375,7 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
                     wave_lds_sync();   // the rows are read before the next unit overwrites them
                 }
             }
+            if constexpr (kShort) continue;
             // the registers of this unit take the one that many rounds ahead
             __builtin_amdgcn_sched_barrier(0);
             if (q + kWaves * kDepth < units) stream_load<kProduct>(P, span.base + (uint64_t)(kWaves * (u + kDepth) + wave) * kUnitElems, lane, slot[i]);

@@ -124,3 +124,34 @@ def test_csr_of_more_tiles_than_the_tables_without_prefix_sums_cover():
     print("long csr", nnz, flush=True)
     y = B.mmv_spmv_csr(n_rows, n_cols, rowptr, col, val, x)
     assert bool((y == 2.0 * length).all())
+
+
+@pytest.mark.parametrize("variant", ["mfma", "shuffle"])
+def test_borders_of_the_form_for_short_vectors(variant):
+    """256 tiles of 8 to 16 units, 512 (sums) of 8 to 16, 768 (sums without the matrix cores) of up to 16, and what lies
+    just beyond each; ragged ends in the first and in the second unit of a wave."""
+    rng = np.random.default_rng(74)
+    for n in [2 * UNIT + 3, 9 * UNIT + 5, 15 * UNIT - 1, 256 * 8 * UNIT, 256 * 8 * UNIT + 1, 256 * 11 * UNIT + 31, 256 * 16 * UNIT, 256 * 16 * UNIT + 1,
+              512 * 12 * UNIT + 7, 512 * 16 * UNIT + 1, 768 * 16 * UNIT, 768 * 16 * UNIT + 1]:
+        x = rng.integers(-3, 4, size=n).astype(np.float32)
+        for density in (0.0002, 0.3):
+            f = (rng.random(n) < density).astype(np.uint8)
+            print("short sum", variant, n, density, flush=True)
+            ref = oracle.segsum(x, f)
+            out, nseg = B.mmv_segsum(dev(x), flags_dev(f, density < 0.1), n=n, out=torch.full((len(ref) + 3,), 99.0, device="cuda"), variant=variant)
+            assert int(nseg.item()) == len(ref)
+            got = out.cpu().numpy()
+            assert np.array_equal(got[:len(ref)].astype(np.float64), ref) and (got[len(ref):] == 99.0).all()
+    for nnz in [2 * UNIT + 3, 9 * UNIT + 5, 256 * 8 * UNIT, 256 * 8 * UNIT + 1, 256 * 16 * UNIT, 256 * 16 * UNIT + 1]:
+        n_cols, n_rows = 3000, max(2, nnz // 37)
+        row = np.sort(rng.integers(0, n_rows, size=nnz)).astype(np.int32)
+        col = rng.integers(0, n_cols, size=nnz, dtype=np.int32)
+        val, x = rng.integers(-2, 3, size=nnz).astype(np.float32), rng.integers(-2, 3, size=n_cols).astype(np.float32)
+        ref = np.bincount(row, weights=val.astype(np.float64) * x[col], minlength=n_rows)
+        args = [dev(a) for a in (col, val, x)]
+        rowptr = dev(W.csr_rowptr(row, n_rows))
+        print("short spmv", variant, nnz, flush=True)
+        assert np.array_equal(B.mmv_spmv_coo(n_rows, n_cols, dev(row), *args, variant=variant).cpu().numpy().astype(np.float64), ref)
+        assert np.array_equal(B.mmv_spmv_csr(n_rows, n_cols, rowptr, *args, variant=variant).cpu().numpy().astype(np.float64), ref)
+        ws = B.mmv_spmv_csr_prepare(n_rows, n_cols, rowptr, args[0])
+        assert np.array_equal(B.mmv_spmv_csr_run(n_rows, n_cols, rowptr, *args, ws, variant=variant).cpu().numpy().astype(np.float64), ref)
