@@ -51,17 +51,26 @@ def test_sums_at_borders(variant):
                 assert (got[capacity:] == 99.0).all()
 
 
+def varied_lengths(total, shortest):
+    """Lengths of shortest .. shortest + 600 that follow no period of a tile, about `total` together."""
+    k = torch.arange(int(total // (shortest + 300)) + 1, device="cuda")
+    return shortest + (k * 389) % 601
+
+
 def test_sums_of_more_tiles_than_the_tables_without_prefix_sums_cover():
-    for dtype, n in ((torch.float32, 4100 * 128 * UNIT + 777), (torch.int8, 4200 * 131072 + 5)):
+    for dtype, total in ((torch.float32, 4110 * 128 * UNIT + 777), (torch.int8, 4300 * 131072 + 5)):
+        lengths = varied_lengths(total, 700)
+        count, n = lengths.numel(), int(lengths.sum())
+        assert n > (4097 * 128 * UNIT if dtype == torch.float32 else 4200 * 131072)
         print("long sum", dtype, n, flush=True)
-        length = 1000
         f = torch.zeros(n, dtype=torch.uint8, device="cuda")
-        f[::length] = 1
-        x = torch.full((n,), 2, dtype=dtype, device="cuda")
-        count = (n + length - 1) // length
-        out, nseg = B.mmv_segsum(x, f, n=n, out=torch.empty(count, dtype=torch.int32 if dtype == torch.int8 else dtype, device="cuda"))
+        f[torch.cumsum(lengths, 0) - lengths] = 1
+        value = torch.arange(count, device="cuda") % 7 - 3          # of every element of a segment
+        x = value.to(dtype).repeat_interleave(lengths)
+        odt = torch.int32 if dtype == torch.int8 else dtype
+        out, nseg = B.mmv_segsum(x, f, n=n, out=torch.full((count + 5,), 99, dtype=odt, device="cuda"))
         assert int(nseg.item()) == count
-        assert bool((out[:-1] == 2 * length).all()) and float(out[-1]) == 2 * (n - (count - 1) * length)
+        assert torch.equal(out[:count].long(), value * lengths) and bool((out[count:] == 99).all())
         del f, x, out
 
 
@@ -114,16 +123,23 @@ def test_spmv_with_columns_beyond_32_bit_byte_offsets():
 
 
 def test_csr_of_more_tiles_than_the_tables_without_prefix_sums_cover():
-    length, n_cols = 1000, 4096
-    n_rows = 4100 * 128 * UNIT // length + 3
-    nnz = n_rows * length
-    rowptr = torch.arange(0, nnz + 1, length, dtype=torch.int32, device="cuda")
+    n_cols = 4096
+    lengths = varied_lengths(1.5 * 4110 * 128 * UNIT, 700)
+    lengths[1::3] = 0                                                # a third of the rows is empty
+    n_rows, nnz = lengths.numel(), int(lengths.sum())
+    assert 4097 * 128 * UNIT < nnz < 2 ** 31
+    rowptr = torch.zeros(n_rows + 1, dtype=torch.int32, device="cuda")
+    rowptr[1:] = torch.cumsum(lengths, 0).int()
     col = (torch.arange(nnz, dtype=torch.int32, device="cuda") % n_cols)
-    val = torch.ones(nnz, dtype=torch.float32, device="cuda")
+    value = torch.arange(n_rows, device="cuda") % 5 - 2              # of every entry of a row
+    val = value.float().repeat_interleave(lengths)
     x = torch.full((n_cols,), 2.0, device="cuda")
     print("long csr", nnz, flush=True)
-    y = B.mmv_spmv_csr(n_rows, n_cols, rowptr, col, val, x)
-    assert bool((y == 2.0 * length).all())
+    y = B.mmv_spmv_csr(n_rows, n_cols, rowptr, col, val, x, y=torch.full((n_rows,), 77.0, device="cuda"))
+    assert torch.equal(y.long(), 2 * value * lengths)
+    ws = B.mmv_spmv_csr_prepare(n_rows, n_cols, rowptr, col)
+    y = B.mmv_spmv_csr_run(n_rows, n_cols, rowptr, col, val, x, ws, y=torch.full((n_rows,), 77.0, device="cuda"), variant="shuffle")
+    assert torch.equal(y.long(), 2 * value * lengths)
 
 
 @pytest.mark.parametrize("variant", ["mfma", "shuffle"])
@@ -155,3 +171,46 @@ def test_borders_of_the_form_for_short_vectors(variant):
         assert np.array_equal(B.mmv_spmv_csr(n_rows, n_cols, rowptr, *args, variant=variant).cpu().numpy().astype(np.float64), ref)
         ws = B.mmv_spmv_csr_prepare(n_rows, n_cols, rowptr, args[0])
         assert np.array_equal(B.mmv_spmv_csr_run(n_rows, n_cols, rowptr, *args, ws, variant=variant).cpu().numpy().astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("variant", ["mfma", "shuffle"])
+@pytest.mark.parametrize("n", [9 * 8 * UNIT + 700, 768 * 17 * UNIT + 900])       # the form for short vectors, the one for long ones
+def test_non_finite_values_reach_their_own_segment_and_those_of_their_row_of_32(variant, n):
+    """Sums and products: a segment that holds an infinity or a NaN has a sum that is not finite, one that lies
+    partly in the same (32-aligned) row may have, every other sum is as accurate as without them (within 2e-5 of the sum of
+    the magnitudes, the margin of parity_util)."""
+    rng = np.random.default_rng(75)
+    x = (rng.random(n, dtype=np.float32) * 2 - 1).astype(np.float32)
+    f = (rng.random(n) < 0.02).astype(np.uint8)
+    quiet = slice(20 * UNIT, 45 * UNIT)                               # units and tiles that lie inside one segment
+    f[quiet] = 0
+    f[0] = 1
+    bad = {5: np.inf, 3 * UNIT - 1: -np.inf, 3 * UNIT + 40: np.nan, 8 * UNIT: np.inf, 16 * UNIT - 1: np.inf, 30 * UNIT + 17: np.inf,
+           n - 1: -np.inf, n - 2000: np.nan, n // 2: np.inf}
+    f[[8 * UNIT, n // 2 + 1]] = 1                                     # one on a segment start, one right ahead of one
+    for p, v in bad.items():
+        x[p] = v
+    segment = np.cumsum(f) - 1
+    starts = np.flatnonzero(f)
+    own = np.unique(segment[list(bad)])
+    near = np.unique(np.concatenate([segment[p // 32 * 32:p // 32 * 32 + 32] for p in bad]))
+    clean = np.ones(len(starts), dtype=bool)
+    clean[near] = False
+    finite = np.where(np.isfinite(x), x, 0).astype(np.float64)
+    ref, size = np.add.reduceat(finite, starts), np.add.reduceat(np.abs(finite), starts)
+
+    def check(got, what):
+        print("non-finite", what, variant, n, flush=True)
+        assert not np.isfinite(got[own]).any()
+        assert (np.abs(got.astype(np.float64) - ref)[clean] <= 2e-5 * np.maximum(size, 1)[clean]).all()
+
+    out, nseg = B.mmv_segsum(dev(x), flags_dev(f, True), n=n, variant=variant)
+    assert int(nseg.item()) == len(starts)
+    check(out.cpu().numpy()[:len(starts)], "sum")
+    # products: one column per entry holds the values, the entries are ones, the rows the segments
+    row, col = segment.astype(np.int32), rng.permutation(n).astype(np.int32)
+    xv = np.empty(n, dtype=np.float32)
+    xv[col] = x
+    args = [dev(a) for a in (col, np.ones(n, dtype=np.float32), xv)]
+    check(B.mmv_spmv_coo(len(starts), n, dev(row), *args, variant=variant).cpu().numpy(), "coo")
+    check(B.mmv_spmv_csr(len(starts), n, dev(W.csr_rowptr(row, len(starts))), *args, variant=variant).cpu().numpy(), "csr")
