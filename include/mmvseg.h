@@ -128,8 +128,8 @@ size_t mmv_spmv_csr_workspace_bytes(uint64_t n_rows, uint64_t nnz);
  * rounding of its own segment alone, so a segment of small values behind large ones in the same row of 32
  * loses relative accuracy.  With fp32 inputs a position that starts a segment receives its input bit for bit.
  * An infinity or NaN makes the rest of its own segment non-finite, as the definition does, and can in addition turn
- * later positions of the same row of 32 into NaN (Inf - Inf); positions outside that row are not affected unless
- * its own segment reaches them.  A block of 2048 positions that all start segments is copied exactly. */
+ * other positions of the same row of 32 and the segments that begin behind it in that row into NaN (Inf - Inf);
+ * positions outside that row are not affected unless one of these segments reaches them.  A block of 2048 positions that all start segments is copied exactly. */
 mmv_status mmv_segscan(const void *d_x, const void *d_flags, uint64_t n, void *d_z,
                        mmv_dtype dt, mmv_flag_fmt ff, mmv_variant v,
                        void *d_ws, size_t ws_bytes, void *hip_stream);
@@ -327,7 +327,7 @@ const char *mmv_status_string(mmv_status s);
 /* Elements per workgroup tile for an operation, input type and length (tiles are
  * smaller for short inputs so that every compute unit gets one).  For tests that want
  * to straddle tile borders and for sizing: the workspace holds one 8-byte descriptor
- * per tile (the segmented sum up to 36 more bytes of counts per tile).  The value is that
+ * per tile (the segmented sum 4 more bytes of counts per tile, for 8- and 16-bit inputs 36).  The value is that
  * of the matrix-core variant (the other one differs for fp32 sums and for bytes under exclusive or).
  * The segmented sum has longer tiles than the scan; mmv_scan of 16- and
  * 32-bit inputs has longer tiles than mmv_segscan.

@@ -65,7 +65,10 @@ __global__ __launch_bounds__(512) void count_spans_kernel(uint32_t *zero, uint64
     for (uint64_t i = (uint64_t)tile * 512 + tid; i < zero_words; i += (uint64_t)gridDim.x * 512) zero[i] = 0;
     const TileSpan span = tile_span(reg, tile, unit);
     const uint64_t span_words = (uint64_t)span.cpw * (unit / kSpans / 32);
-    const uint64_t w0 = (span.base >> 5) + wave * span_words;   // tiles and spans begin on word borders, spans are multiples of 32 words
+    // (tiles and spans begin at multiples of four words, which the 128-bit loads below rely on; the smallest unit is that of
+    // stream_kernel, 1024 elements for the eight waves together)
+    static_assert(kUnitElems / kSpans / 32 % 4 == 0, "128-bit loads of flag words");
+    const uint64_t w0 = (span.base >> 5) + wave * span_words;
     const uint64_t last_word = (n + 31) >> 5;
     const uint64_t end = w0 + span_words < last_word ? w0 + span_words : last_word;
     uint32_t sum = 0;
@@ -152,10 +155,10 @@ __global__ __launch_bounds__(256) void pack_flags_kernel(const uint8_t *f, uint6
 // eight times four consecutive indices (all loads in flight at once), compares them with their left neighbours
 // (the lane before it holds the one before its first: a DPP move), and eight lanes OR their nibbles into one
 // flag word (DPP again; no LDS traffic).
-// Bound by the read of the indices.  The loads are plain ones: the main kernel reads row[] again at the segment ends, and
-// calls repeated on one matrix find part of it in the memory-side cache; non-temporal loads took 23.3 us for 33 million
-// entries, these take 21.0 (6.4 TB/s), and the whole product 238.5 -> 234.4 us (3 million entries: 27.8 -> 26.8, 8 million:
-// 0.98 and 1.01 in the two lane-math variants).
+// Bound by the read of the indices (33 million entries: 21 us, 6.4 TB/s).  The loads are plain ones: the main kernel reads
+// row[] again at the segment ends and finds it in the memory-side cache as far as it fits.  Whole products, each call on
+// another of four matrices (so that nothing is left of the call before), non-temporal loads -> plain ones: 3 million entries
+// 27.9 -> 27.0 us, 8 million 47.9 -> 45.9, 16 million 111.7 -> 108.7, 33 million 239.9 -> 239.7.
 __global__ __launch_bounds__(256) void row_flags_kernel(const int32_t *row, uint64_t nnz, uint32_t *words,
                                                         uint32_t *ws, uint64_t ws_words, uint32_t *y, uint64_t n_rows) {
     const int lane = threadIdx.x & 63;

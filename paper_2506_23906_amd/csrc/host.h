@@ -33,7 +33,7 @@ constexpr uint64_t kResident = MMV_MIN_TILES;   // workgroups resident at once (
 constexpr uint64_t kCountTiles = 4096;
 inline bool is_spmv(mmv_op op) { return op == MMV_OP_SPMV_COO || op == MMV_OP_SPMV_CSR; }
 // Most chunks per wave of the tile body that carries its pair from row to row (seg_tile): what the kernel
-// instantiation for this operation, type and variant is built with.
+// instantiation for this operation, type and variant is built with (sums of fp32 values and SpMV have another body).
 template <typename TT> inline int row_form_cpw_of(mmv_op op, bool mfma) {
     switch (op) {
         case MMV_OP_SCAN: return mfma ? chunks_per_wave<TT, kPlainScan, true>() : chunks_per_wave<TT, kPlainScan, false>();
@@ -68,8 +68,7 @@ inline int chunk_form_cpw(mmv_op op, mmv_dtype dt, bool mfma) {
 // beside the one per tile, csr_flags_kernel did its atomic adds twice, and the reset cleared eight times the words (CSR product
 // in one step, 3.5 M entries in blocks of 16: 22.2 us before there was one, 24.3 with it, 21.4 without it again).
 inline bool segsum_spans(mmv_dtype dt) { return dt != MMV_F32_F32; }
-inline int waves_of(mmv_op op, mmv_dtype dt) {
-    if (is_spmv(op)) return TSpmv::kWaves;
+inline int waves_of(mmv_dtype dt) {   // (SpMV has a tile plan of its own)
     switch (dt) {
         case MMV_F32_F32: return TF32::kWaves;
         case MMV_F16_F32: return TF16::kWaves;
@@ -116,7 +115,7 @@ inline TilePlan tile_plan(mmv_op op, mmv_dtype dt, uint64_t n, bool mfma = true)
         R.num_tiles = (uint32_t)(p.tiles < 0x7fffffffull ? p.tiles : 0x7fffffffull);
         return p;
     }
-    const uint64_t unit = (uint64_t)waves_of(op, dt) * kChunkElems;  // one chunk per wave
+    const uint64_t unit = (uint64_t)waves_of(dt) * kChunkElems;  // one chunk per wave
     // A sum that fits one round of workgroups is bound by the life of one tile, and the tile that holds all its
     // values, publishes its aggregate and then walks its ends has the shorter life (workload 2, fp16 2^24: 12.4
     // against 15.5 us); longer vectors go to the kernel that streams.
