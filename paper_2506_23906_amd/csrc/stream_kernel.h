@@ -21,7 +21,7 @@ namespace {
 //   ... 30 % starts                                193 / 143 -> 133 / 133
 //   CSR SpMV, sparse attention, 62.8 M entries in blocks of 64 (prepared)     127 -> 103 us (4.9 TB/s)
 //   ... 9.5 M entries in blocks of 16                                         37.7 -> 24.9
-//   COO SpMV, 33.6 M entries in scattered columns                             236 -> 239 (bound by the gathers)
+//   COO SpMV, 33.6 M entries in scattered columns                             239 -> 240 (bound by the gathers)
 // Waves per SIMD: SpMV keeps one unit per wave and six waves per SIMD hide the loads (four with two units: 0.128 ms for the
 // 62.8 M entries, eight spill); sums on the matrix cores keep two units in flight and four waves (six with one: level).
 // Precision is that of seg_tile: speculation within rows of 32 elements, segmented carries from there on.
