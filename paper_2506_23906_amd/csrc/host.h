@@ -184,6 +184,8 @@ inline uint64_t tiles_for(uint64_t n, mmv_op op, mmv_dtype dt) {
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 inline bool aligned4(const void *p) { return ((uintptr_t)p & 3u) == 0; }
 
+inline uint64_t short_tiles(uint64_t n) { return (n + kShortTile - 1) / kShortTile; }
+
 struct WsLayout {
     size_t desc_v, desc_c, span_c, packed, total;
 };
@@ -201,6 +203,12 @@ WsLayout ws_layout(mmv_op op, mmv_dtype dt, mmv_flag_fmt ff, uint64_t n) {
     L.packed = off;
     if (is_spmv(op) || (ff == MMV_FLAGS_U8 && op != MMV_OP_SCAN)) off += round256(((n + 63) / 64) * 8);
     L.total = off;
+    // The two launches of a short vector keep one aggregate per tile where the descriptors begin.  (Longer vectors get at least
+    // that much too, so that a workspace of a longer vector always does for a shorter one.)
+    if (!is_spmv(op)) {
+        const size_t aggregates = kHdrBytes + round256(short_tiles(n < short_max(op, dt) ? n : short_max(op, dt)) * 8);
+        if (L.total < aggregates) L.total = aggregates;
+    }
     return L;
 }
 
@@ -312,7 +320,7 @@ uint32_t resident_workgroups(const void *kernel, int threads, std::atomic<uint32
 }
 
 // Workgroups that take the tile of their own index: those resident from the start, and the first one in any case (the
-// number is 0 when the device could not be asked).  A single tile is launched without a reset, so it must draw no ticket.
+// number is 0 when the device could not be asked).
 constexpr uint32_t first_round_of(uint32_t num_tiles, uint32_t resident) {
     return num_tiles < resident ? num_tiles : resident > 0 ? resident : 1u;
 }
@@ -370,6 +378,51 @@ template <int kOp> hipError_t launch_dt(const Params &P, mmv_dtype dt, mmv_varia
     return hipErrorInvalidValue;
 }
 
+// Scans and sums of at most short_max elements on checked arguments (P: where things lie in the workspace).
+template <typename TT, int kOp, int kFlags> hipError_t launch_short(const ShortParams &S, bool single, hipStream_t s) {
+    const unsigned tiles = (unsigned)short_tiles(S.n);
+    if (!single) {
+        short_reduce_kernel<TT, kFlags><<<tiles, kShortThreads, 0, s>>>(S);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (tl_ev_start && hipEventRecord(tl_ev_start, s) != hipSuccess) return hipErrorUnknown;
+    if (single) short_kernel<TT, kOp, kFlags, true><<<tiles, kShortThreads, 0, s>>>(S);
+    else short_kernel<TT, kOp, kFlags, false><<<tiles, kShortThreads, 0, s>>>(S);
+    const hipError_t e = hipGetLastError();
+    if (tl_ev_stop && hipEventRecord(tl_ev_stop, s) != hipSuccess) return hipErrorUnknown;
+    return e;
+}
+template <typename TT, int kOp> hipError_t launch_short_flags(const ShortParams &S, mmv_flag_fmt ff, bool single, hipStream_t s) {
+    if constexpr (kOp == kPlainScan) return launch_short<TT, kOp, kNoFlags>(S, single, s);
+    else return ff == MMV_FLAGS_U8 ? launch_short<TT, kOp, kByteFlags>(S, single, s) : launch_short<TT, kOp, kBitFlags>(S, single, s);
+}
+inline uint64_t elem_bytes(mmv_dtype dt) { return dt == MMV_F32_F32 ? 4 : dt == MMV_F16_F32 || dt == MMV_BF16_F32 ? 2 : 1; }
+inline bool overlap(const void *a, uint64_t a_bytes, const void *b, uint64_t b_bytes) {
+    return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
+}
+template <int kOp>
+mmv_status short_call(const void *d_x, const void *d_flags, uint64_t n, void *d_z, void *d_out, uint64_t out_cap, uint64_t *d_nseg,
+                      bool first_one, mmv_dtype dt, mmv_flag_fmt ff, const Params &P, hipStream_t s) {
+    const ShortParams S = {d_x, d_flags, d_z, d_out, out_cap, d_nseg, P.hdr, P.desc_v, (uint32_t)n, first_one ? 1u : 0u};
+    // One launch: every workgroup reads what lies before its tile, so nothing of that may be written meanwhile.
+    const void *written = kOp == kSum ? d_out : d_z;
+    const uint64_t written_bytes = (kOp == kSum && out_cap < n ? out_cap : n) * 4;
+    const uint64_t value_bytes = n * elem_bytes(dt), flag_bytes = kOp == kPlainScan ? 0 : ff == MMV_FLAGS_U8 ? n : (n + 31) / 32 * 4;
+    const bool single = value_bytes + flag_bytes <= MMV_SINGLE_BYTES && !overlap(written, written_bytes, d_x, value_bytes) &&
+                        !overlap(written, written_bytes, d_flags, flag_bytes);
+    hipError_t e = hipErrorInvalidValue;
+    switch (dt) {
+        case MMV_F32_F32: e = launch_short_flags<TF32, kOp>(S, ff, single, s); break;
+        case MMV_F16_F32: e = launch_short_flags<TF16, kOp>(S, ff, single, s); break;
+        case MMV_BF16_F32: e = launch_short_flags<TBF16, kOp>(S, ff, single, s); break;
+        case MMV_I8_I32: e = launch_short_flags<TI8, kOp>(S, ff, single, s); break;
+        case MMV_U8_XOR: e = launch_short_flags<TX8, kOp>(S, ff, single, s); break;
+        default: break;
+    }
+    return e == hipSuccess ? MMV_OK : MMV_ERR_HIP;
+}
+
 int grid_for(uint64_t items_per_thread_total) {
     uint64_t blocks = (items_per_thread_total + 255) / 256;
     if (blocks < 1) blocks = 1;
@@ -398,17 +451,17 @@ mmv_status prepare(mmv_op op, const void *d_x, const void *d_flags, uint64_t n, 
     P.hdr = (uint32_t *)ws;
     P.desc_v = (uint64_t *)(ws + L.desc_v);
     P.num_tiles = (uint32_t)tiles_for(n, op, dt);
-    // header and descriptors zeroed, flags packed if they came as bytes: one launch (none for a single tile of packed flags,
-    // whose kernel needs nothing zeroed).  The segmented sum does both in its counting kernel.
+    // header and descriptors zeroed, flags packed if they came as bytes: one launch.  The segmented sum does both in its counting
+    // kernel; a short vector needs neither.
     uint32_t *packed = (uint32_t *)(ws + L.packed);
     P.fw = ff == MMV_FLAGS_U8 ? packed : (const uint32_t *)d_flags;
-    if (op == MMV_OP_SEGSUM) return MMV_OK;
+    if (op == MMV_OP_SEGSUM || n <= short_max(op, dt)) return MMV_OK;
     const uint64_t zero_words = L.packed / 4;
     if (ff == MMV_FLAGS_U8) {
         const uint64_t nwords = (n + 31) / 32;
         pack_flags_kernel<<<grid_for(nwords > zero_words ? nwords : zero_words), 256, 0, s>>>((const uint8_t *)d_flags, n, packed, nwords,
                                                                                              (uint32_t *)ws, zero_words);
-    } else if (tile_plan(op, dt, n, v == MMV_VARIANT_MFMA).tiles > 1) {
+    } else {
         fill_zero_kernel<<<grid_for(zero_words), 256, 0, s>>>((uint32_t *)ws, zero_words, nullptr, 0);
     }
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
@@ -438,11 +491,10 @@ mmv_status scan_impl(const void *d_x, uint64_t n, void *d_z, mmv_dtype dt, mmv_v
     P.hdr = (uint32_t *)ws;
     P.desc_v = (uint64_t *)(ws + L.desc_v);
     P.first_one = first_one ? 1u : 0u;
-    if (tile_plan(MMV_OP_SCAN, dt, n, v == MMV_VARIANT_MFMA).tiles > 1) {   // (a single tile needs nothing zeroed)
-        const uint64_t zero_words = L.total / 4;
-        fill_zero_kernel<<<grid_for(zero_words), 256, 0, s>>>((uint32_t *)ws, zero_words, nullptr, 0);
-        if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
-    }
+    if (n <= short_max(MMV_OP_SCAN, dt)) return short_call<kPlainScan>(d_x, nullptr, n, d_z, nullptr, 0, nullptr, first_one, dt, MMV_FLAGS_PACKED32, P, s);
+    const uint64_t zero_words = L.total / 4;
+    fill_zero_kernel<<<grid_for(zero_words), 256, 0, s>>>((uint32_t *)ws, zero_words, nullptr, 0);
+    if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     return launch_dt<kPlainScan>(P, dt, v, s) == hipSuccess ? MMV_OK : MMV_ERR_HIP;
 }
 

@@ -46,6 +46,7 @@
 #include "seg_entry.h"
 #include "aux_kernels.h"
 #include "primitives.h"
+#include "short_kernel.h"
 #include "host.h"
 
 
@@ -78,6 +79,7 @@ mmv_status segscan_call(const void *d_x, const void *d_flags, uint64_t n, void *
     Params P = {};
     const mmv_status st = prepare(MMV_OP_SEGSCAN, d_x, d_flags, n, dt, ff, v, d_ws, ws_bytes, s, P);
     if (st != MMV_OK) return st;
+    if (n <= short_max(MMV_OP_SEGSCAN, dt)) return short_call<kScan>(d_x, d_flags, n, d_z, nullptr, 0, nullptr, false, dt, ff, P, s);
     P.z = d_z;
     return launch_dt<kScan>(P, dt, v, s) == hipSuccess ? MMV_OK : MMV_ERR_HIP;
 }
@@ -147,6 +149,7 @@ mmv_status mmv_segsum(const void *d_x, const void *d_flags, uint64_t n, void *d_
     Params P = {};
     const mmv_status st = prepare(MMV_OP_SEGSUM, d_x, d_flags, n, dt, ff, v, d_ws, ws_bytes, s, P);
     if (st != MMV_OK) return st;
+    if (n <= short_max(MMV_OP_SEGSUM, dt)) return short_call<kSum>(d_x, d_flags, n, nullptr, d_out, out_capacity, d_nseg, false, dt, ff, P, s);
     P.out = d_out;
     P.out_cap = out_capacity;
     P.nseg = d_nseg;
@@ -621,6 +624,7 @@ uint32_t mmv_tile_elems(mmv_op op, mmv_dtype dt, uint64_t n) {
     if (!valid_dtype(dt)) return 0;
     if (op == MMV_OP_COMPRESS) return (uint32_t)compress_tile(n);
     if (op != MMV_OP_SEGSCAN && op != MMV_OP_SEGSUM && op != MMV_OP_SCAN && !is_spmv(op)) return 0;
+    if (!is_spmv(op) && n <= short_max(op, dt)) return kShortTile;
     return tile_plan(op, is_spmv(op) ? MMV_F32_F32 : dt, n).body_elems;
 }
 

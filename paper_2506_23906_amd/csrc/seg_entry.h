@@ -15,10 +15,6 @@ template <typename Shared> __device__ __forceinline__ uint32_t take_tile(const P
     if (threadIdx.x == 0) {
         sm.ready = 0;
         sm.arrived = 0;
-        if (P.num_tiles == 1) {   // (a single tile may be launched without a reset)
-            P.hdr[kHdrError] = 0;
-            if (!P.prepared) P.hdr[kHdrPrepared] = 0;   // the workspace holds no plan any more: callers write behind the header
-        }
         if (!own_index)
             sm.tile = P.first_round +
                       __hip_atomic_fetch_add(P.hdr + kHdrTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

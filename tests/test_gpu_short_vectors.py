@@ -1,0 +1,171 @@
+"""Scans and sums of short vectors: one launch (the sum carried into a tile comes from the input itself) up to 320 KB of
+values and flags, two (from the aggregates of the tiles before) up to 2^21 elements (mmv_scan and fp32 sums 2^22), the
+single-pass kernels beyond.  Tiles have 2048 elements, a thread takes eight, a wave 512; whole numbers, so results are exact."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2506_23906_amd import binding as B
+from parity_util import check_scan, check_sum, dev, flags_dev, run_segscan, run_segsum
+
+pytestmark = pytest.mark.gpu
+TILE = 2048
+TYPES = {"f32": (torch.float32, B.MMV_F32_F32), "f16": (torch.float16, B.MMV_F16_F32), "bf16": (torch.bfloat16, B.MMV_BF16_F32),
+         "i8": (torch.int8, B.MMV_I8_I32), "u8": (torch.uint8, B.MMV_U8_XOR)}
+
+
+def one_launch(dt, flag_bytes):
+    """Most elements that one launch takes (8 * flag_bytes: bits of flags per element)."""
+    size = torch.empty(0, dtype=TYPES[dt][0]).element_size()
+    return int((320 << 10) / (size + flag_bytes)) // 32 * 32
+
+
+def values(rng, n, dt):
+    x = rng.integers(0, 256, size=n) if dt == "u8" else rng.integers(-3, 4, size=n)
+    return x.astype({"f32": np.float32, "f16": np.float16, "bf16": np.float32, "i8": np.int8, "u8": np.uint8}[dt])
+
+
+def garbage(nbytes):
+    return torch.full((max(nbytes, 256),), 0xFF, dtype=torch.uint8, device="cuda")
+
+
+def check(dt, n, packed, f, rng, variant="mfma", scan_too=True):
+    x = values(rng, n, dt)
+    tt, code = TYPES[dt]
+    xt, ft = dev(x).to(tt), flags_dev(f, packed)
+    ff = B.MMV_FLAGS_PACKED32 if packed else B.MMV_FLAGS_U8
+    ws = garbage(B.mmv_workspace_bytes(B.MMV_OP_SEGSCAN, code, ff, n))
+    z = B.mmv_segscan(xt, ft, n=n, variant=variant, ws=ws)
+    assert B.mmv_workspace_status(ws) == 0
+    assert np.array_equal(z.cpu().numpy().astype(np.float64), oracle.segscan(x, f).astype(np.float64))
+    ws = garbage(B.mmv_workspace_bytes(B.MMV_OP_SEGSUM, code, ff, n))
+    ref = oracle.segsum(x, f)
+    cap = len(ref) - len(ref) // 3                              # an output array that is too short
+    out = torch.full((cap + 64,), -77, dtype=B._OUT_DTYPE[code], device="cuda")
+    _, nseg = B.mmv_segsum(xt, ft, n=n, out=out[:cap], variant=variant, ws=ws)
+    assert B.mmv_workspace_status(ws) == 0 and int(nseg.item()) == len(ref)
+    assert np.array_equal(out.cpu().numpy()[:cap].astype(np.float64), ref[:cap].astype(np.float64))
+    assert bool((out[cap:] == -77).all())
+    if scan_too:
+        ws = garbage(B.mmv_workspace_bytes(B.MMV_OP_SCAN, code, ff, n))
+        z = B.mmv_scan(xt, n=n, variant=variant, ws=ws)
+        assert B.mmv_workspace_status(ws) == 0
+        assert np.array_equal(z.cpu().numpy().astype(np.float64), oracle.scan(x).astype(np.float64))
+
+
+@pytest.mark.parametrize("packed", [True, False])
+@pytest.mark.parametrize("dt", list(TYPES))
+def test_edges_of_threads_waves_tiles_and_of_the_two_forms(dt, packed):
+    rng = np.random.default_rng(2390700)
+    line = one_launch(dt, 1 / 8 if packed else 1)
+    sizes = [1, 2, 7, 8, 9, 31, 33, 511, 513, TILE - 1, TILE, TILE + 1, 5 * TILE + 511, line - 1, line, line + 1, line + TILE + 9,
+             (1 << 21) - 5, 1 << 21, (1 << 21) + 1, (1 << 22) - 3, 1 << 22, (1 << 22) + 1]
+    for n in sizes:
+        for density in (0.0, 3 / n, 0.01, 1.0):
+            f = ((rng.random(n) < density) * rng.integers(1, 256, size=n)).astype(np.uint8)
+            print(dt, packed, n, density, flush=True)
+            check(dt, n, packed, f if not packed else (f != 0).astype(np.uint8), rng)
+
+
+@pytest.mark.parametrize("n", [9 * TILE + 77, 150 * TILE + 77])          # one launch, two
+@pytest.mark.parametrize("packed", [True, False])
+def test_single_flags_at_borders(n, packed):
+    """One flag per vector, at and around the borders of threads, 128-bit words, waves and tiles, and in the first and last
+    positions: what every later tile adds up begins there."""
+    rng = np.random.default_rng(2390701)
+    at = {0, 1, n - 1, n - 2}
+    for b in (8, 16, 128, 512, TILE, 2 * TILE, 3 * TILE + 512, n - n % TILE):
+        at |= {b - 1, b, b + 1}
+    for p in sorted(at):
+        f = np.zeros(n, dtype=np.uint8)
+        f[p] = 1
+        for dt in ("f32", "f16", "i8") if p % 2 else ("bf16", "u8"):
+            print(n, packed, p, dt, flush=True)
+            check(dt, n, packed, f, rng, variant="shuffle", scan_too=p == 0)
+
+
+@pytest.mark.parametrize("n", [60_001, 200_003])
+def test_in_place_and_overlapping(n):
+    """fp32 results over their own input: never in one launch, where other workgroups still read it."""
+    rng = np.random.default_rng(2390702)
+    x = values(rng, n, "f32")
+    f = (rng.random(n) < 0.001).astype(np.uint8)
+    for packed in (True, False):
+        for _ in range(3):
+            xt = dev(x)
+            B.mmv_segscan(xt, flags_dev(f, packed), n=n, z=xt)
+            assert np.array_equal(xt.cpu().numpy(), oracle.segscan(x, f).astype(np.float32))
+    for _ in range(3):
+        xt = dev(x)
+        B.mmv_scan(xt, n=n, z=xt)
+        assert np.array_equal(xt.cpu().numpy(), oracle.scan(x).astype(np.float32))
+
+
+@pytest.mark.parametrize("n", [70_000, (1 << 21) - 1, (1 << 22) + 3])    # one launch, two, the single-pass kernels
+@pytest.mark.parametrize("variant", ["mfma", "shuffle"])
+def test_real_values_starts_and_non_finite_ones(n, variant):
+    rng = np.random.default_rng(2390703)
+    x = (rng.random(n, dtype=np.float32) * 2 - 1).astype(np.float32)
+    f = (rng.random(n) < 0.02).astype(np.uint8)
+    check_scan(run_segscan(x, f, variant), x, f)
+    out, nseg = run_segsum(x, f, variant)
+    check_sum(out, nseg, x, f)
+    bad = {5 * 32 + 7: np.inf, 700 * 32 + 11: -np.inf, n - 2048 - 40: np.nan, 0: -0.0}
+    for p, v in bad.items():
+        x[p] = v
+        f[p // 32 * 32 + 32] = 1                                  # the next row of 32 starts a segment
+    z = run_segscan(x, f, variant)
+    starts = np.flatnonzero(f)
+    assert np.array_equal(z[starts].view(np.uint32), x[starts].view(np.uint32))
+    with np.errstate(invalid="ignore"):
+        ref = oracle.segscan(x, f)
+    rows = {p // 32 for p in bad}
+    assert set((np.flatnonzero(~np.isfinite(z)) // 32).tolist()) <= rows
+    assert not np.isfinite(z[[p for p in bad if p]]).any()        # (an infinity or a NaN: the row scans subtract prefixes)
+    if n <= 1 << 21:                                              # no speculation: exactly the values of the definition
+        assert np.array_equal(np.isfinite(z), np.isfinite(ref))
+        for p in bad:
+            assert np.array_equal(z[p:p + 1], ref[p:p + 1].astype(np.float32), equal_nan=True)
+
+
+def test_graph_replays_and_a_workspace_shared_by_lengths():
+    """One workspace, sized for the longest of them, serves vectors of all three forms in turn, also in a graph."""
+    rng = np.random.default_rng(2390704)
+    sizes = [(1 << 22) + 5, 30_000, 1 << 21, 1, 1_000_000]
+    data = []
+    ws = garbage(B.mmv_workspace_bytes(B.MMV_OP_SEGSUM, B.MMV_I8_I32, B.MMV_FLAGS_PACKED32, max(sizes)))
+    for n in sizes:
+        x, f = values(rng, n, "i8"), (rng.random(n) < 0.003).astype(np.uint8)
+        assert B.mmv_workspace_bytes(B.MMV_OP_SEGSUM, B.MMV_I8_I32, B.MMV_FLAGS_PACKED32, n) <= ws.numel()
+        data.append((dev(x), flags_dev(f, True), n, torch.zeros(n, dtype=torch.int32, device="cuda"),
+                     torch.zeros(1, dtype=torch.int64, device="cuda"), oracle.segsum(x, f)))
+    g = torch.cuda.CUDAGraph()
+
+    def calls():
+        for xt, ft, n, out, nseg, _ in data:
+            B.mmv_segsum(xt, ft, n=n, out=out, nseg=nseg, ws=ws)
+    calls()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        calls()
+    for rep in range(4):
+        for d in data:
+            d[3].zero_(), d[4].zero_()
+        if rep:
+            torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for _, _, n, out, nseg, ref in data:
+            assert int(nseg.item()) == len(ref) and np.array_equal(out.cpu().numpy()[:len(ref)], ref), (rep, n)
+
+
+def test_sscr_counts_position_zero_whatever_its_flag():
+    """The composition scans flag bytes with element 0 counted as 1, through both forms of a short scan."""
+    rng = np.random.default_rng(2390705)
+    for n in (100, 250_000, 400_000):
+        x, f = values(rng, n, "i8"), (rng.random(n) < 0.01).astype(np.uint8)
+        f[0] = 0
+        z = B.mmv_segscan_sscr(dev(x), flags_dev(f, True), n=n)
+        torch.cuda.synchronize()
+        assert np.array_equal(z.cpu().numpy(), oracle.segscan(x, f))
