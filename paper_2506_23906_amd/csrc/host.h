@@ -79,12 +79,31 @@ inline int waves_of(mmv_dtype dt) {   // (SpMV has a tile plan of its own)
     }
     return 1;
 }
+// Scans of bytes and, in the variant without the matrix cores, of 16-bit values have a form with three workgroups per compute
+// unit (OneRound) for vectors whose tiles are all resident at once: more waves hide one another's latencies, and a vector
+// of up to 768 chunks per wave no longer needs tiles of two.  Whole calls, two workgroups -> three (us; lengths up to 512 / one
+// segment): bytes 5 * 10^6 11.6 / 13.4 -> 10.5 / 12.8, 12 * 10^6 17.1 / 19.0 -> 14.5 / 18.6, 20 * 10^6 24.0 / 26.0 -> 20.1 / 23.9,
+// mmv_scan 25.4 -> 23.6; fp16 20 * 10^6 28.2 / 30.3 -> 22.9 / 25.7, 25 * 10^6 30.8 / 34.7 -> 27.4 / 29.4.
+// Longer vectors: three workgroups take 5 % more than two (the memory is short of neither, and more tiles are being read and
+// written at a time: bytes 2^26 62.2 -> 65.3, 2^28 235 -> 245).  16-bit values: up to 1024 chunks per wave two workgroups are level
+// (12 * 10^6 17.0 / 18.5 -> 15.3 / 19.2, 14 * 10^6 18.5 / 20.6 -> 18.5 / 21.6); on the matrix cores the form spills 20 registers and is
+// 20 % slower, and its row scans by vector instructions have a larger error (30 % starts 5.5e-9 against 4.9e-9).
+template <typename TT, int kOp, bool kMfma> constexpr bool has_round_form() {
+    return (kOp == kScan || kOp == kPlainScan) && (TT::kDtype == MMV_I8_I32 || (sizeof(typename TT::in_t) <= 2 && !kMfma));
+}
+constexpr uint64_t kRoundTiles = 3 * kComputeUnits;
+constexpr bool round_form(mmv_op op, mmv_dtype dt, uint64_t chunks, bool mfma) {   // `chunks`: per wave, of the whole vector
+    if ((op != MMV_OP_SEGSCAN && op != MMV_OP_SCAN) || dt == MMV_F32_F32 || chunks > (uint64_t)kRoundCpw * kRoundTiles) return false;
+    if (dt == MMV_I8_I32) return true;
+    return !mfma && (dt == MMV_U8_XOR || chunks > (uint64_t)kRoundCpw * kResident);
+}
 struct TilePlan {
     TileRegions reg;
     uint64_t tiles;        // all tiles (reg.num_tiles holds it when it fits 31 bits)
     uint32_t unit;         // elements that one step of a region's `cpw` stands for: one chunk per wave (stream form: one unit of 1024)
     uint32_t body_elems;   // elements of a tile in the middle of the vector
     bool chunk_form;       // segmented sum: the kernel that streams through long spans (sum_kernel) takes it
+    bool round_form;       // scans of 8- and 16-bit values: all tiles resident at once (OneRound)
     bool short_form;       // stream form: at most kShortUnits units per tile, which a wave loads at once
 };
 inline TilePlan tile_plan(mmv_op op, mmv_dtype dt, uint64_t n, bool mfma = true) {
@@ -116,6 +135,27 @@ inline TilePlan tile_plan(mmv_op op, mmv_dtype dt, uint64_t n, bool mfma = true)
         return p;
     }
     const uint64_t unit = (uint64_t)waves_of(dt) * kChunkElems;  // one chunk per wave
+    const uint64_t chunks = (n + unit - 1) / unit;
+    if (round_form(op, dt, chunks, mfma)) {
+        // short tiles first, as many long ones behind them as it takes: no compute unit gets more than one chunk per wave more
+        p.round_form = true;
+        p.unit = (uint32_t)unit;
+        const uint64_t longer = chunks > kRoundTiles ? chunks - kRoundTiles : 0, shorter = chunks - 2 * longer;
+        p.body_elems = (uint32_t)(longer ? 2 * unit : unit);
+        if (shorter) {
+            R.cpw[0] = 1;
+            R.count = 1;
+        }
+        if (longer) {
+            R.base[R.count] = shorter * unit;
+            R.first[R.count] = (uint32_t)shorter;
+            R.cpw[R.count] = 2;
+            ++R.count;
+        }
+        p.tiles = shorter + longer;
+        R.num_tiles = (uint32_t)p.tiles;
+        return p;
+    }
     // A sum that fits one round of workgroups is bound by the life of one tile, and the tile that holds all its
     // values, publishes its aggregate and then walks its ends has the shorter life (workload 2, fp16 2^24: 12.4
     // against 15.5 us); longer vectors go to the kernel that streams.
@@ -338,6 +378,10 @@ template <typename TT, int kOp, bool kMfma> hipError_t launch_variant(Params P, 
         }
     } else {
         kernel = seg_kernel<TT, kOp, kMfma>;
+        if constexpr (has_round_form<TT, kOp, kMfma>()) {
+            which = plan.round_form ? 2 : 0;
+            if (plan.round_form) kernel = seg_kernel<OneRound<TT>, kOp, kMfma>;
+        }
         if constexpr (chunk_sum_kernel<TT, kOp, kMfma>()) {
             which = plan.chunk_form ? 1 : 0;
             if (plan.chunk_form) kernel = sum_kernel<TT, kMfma>;

@@ -23,9 +23,10 @@ template <typename Shared> __device__ __forceinline__ uint32_t take_tile(const P
     return __builtin_amdgcn_readfirstlane(own_index ? blockIdx.x : sm.tile);   // a scalar, like the wave index
 }
 
+template <typename TT> constexpr int seg_waves_per_simd() { return TT::kOneRound ? 6 : MMV_MIN_WAVES_PER_SIMD; }
 template <typename TT, int kOp, bool kMfma>
-__global__ __launch_bounds__(TT::kWaves * 64, MMV_MIN_WAVES_PER_SIMD) void seg_kernel(Params P, const uint32_t *__restrict__) {
-    __shared__ SegShared<TT::kWaves> sm;
+__global__ __launch_bounds__(TT::kWaves * 64, seg_waves_per_simd<TT>()) void seg_kernel(Params P, const uint32_t *__restrict__) {
+    __shared__ SegShared<TT::kWaves, lds_rows<TT>()> sm;
     // A workgroup that starts competes with the ones in the middle of their arithmetic: its ticket
     // and its loads go first (measured: 2 to 3 % on the long scans)
 #if MMV_LOAD_PRIO

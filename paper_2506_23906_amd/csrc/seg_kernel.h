@@ -40,16 +40,26 @@ template <int N, int M> __device__ __forceinline__ void rotate_rows(v4u (&a)[N][
 }
 
 // LDS of one workgroup: the row buffers of the waves and the words the waves exchange.
-template <int kWaves> struct SegShared {
-    __attribute__((aligned(16))) uint32_t rows[kWaves][kRowsPerChunk * kRowStride];
+template <int kWaves, int kRows> struct SegShared {
+    __attribute__((aligned(16))) uint32_t rows[kWaves][kRows * kRowStride];
     uint32_t wave_v[kWaves], wave_f[kWaves], wave_c[kWaves];
     uint32_t early_v[kWaves], early_f[kWaves];   // plain sum and any-flag of every wave's span, written as the loads land
     uint32_t tile, carry_v, carry_c, ready, arrived;
 };
 
 // One tile, from the loads on.
+// A wave with a single chunk (fp32) keeps the row scans of phase A in its LDS rows for
+// phase B instead of making them a second time; with more chunks LDS holds only the last one made.
+// Matrix-core variant only: there it saves the second 3-way split and 50 registers (fp32 scan
+// 4-5 % faster); in the shuffle variant the same change was measured 3 % slower.
+template <typename TT, int kOp, bool kMfma> constexpr bool keeps_rows() {
+    return MMV_KEEP_ROWS != 0 && chunks_per_wave<TT, kOp, kMfma>() == 1 && kMfma;
+}
+// In the one-round form LDS holds one 32x32 tile of a wave at a time, half a chunk (37 instead of 74 KB per workgroup).
+template <typename TT> constexpr int lds_rows() { return TT::kOneRound ? kS : kRowsPerChunk; }
 template <typename TT, int kOp, bool kMfma>
-__device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves> &sm, const uint32_t tile) {
+__device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, lds_rows<TT>()> &sm, const uint32_t tile) {
+    typedef typename TT::base_t BT;
     typedef typename TT::acc_t A;
     typedef typename TT::in_t In;
     constexpr int kWaves = TT::kWaves;
@@ -64,11 +74,8 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves> 
     // chunks per iteration of the chunk loops: all (unrolled), or MMV_ROLL_STEP with the registers
     // rotated by as many slots afterwards (the moves of a rotation do not depend on the distance)
     constexpr int kStep = kUnrollChunks ? kCpw : (kCpw >= 2 * MMV_ROLL_STEP && kCpw % MMV_ROLL_STEP == 0 ? MMV_ROLL_STEP : 1);
-    // A wave with a single chunk (fp32) keeps the row scans of phase A in its LDS rows for
-    // phase B instead of making them a second time; with more chunks LDS holds only the last one made.
-    // Matrix-core variant only: there it saves the second 3-way split and 50 registers (fp32 scan
-    // 4-5 % faster); in the shuffle variant the same change was measured 3 % slower.
-    constexpr bool kKeepRows = MMV_KEEP_ROWS != 0 && kCpw == 1 && kMfma;
+    constexpr bool kKeepRows = keeps_rows<TT, kOp, kMfma>();
+    constexpr bool kHalf = lds_rows<TT>() == kS;   // LDS holds the rows of one 32x32 tile
     // lane exchanges through the vector ALU for the sum-type kernels and the 16-bit scans (measured 2 %
     // faster), through the LDS hardware for the int8 and fp32 scans (0.9 % faster / no difference)
     constexpr bool kAluLanes = MMV_DPP_SCAN != 0 && (!kScanLike || TT::kEpl == 8);
@@ -127,7 +134,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves> 
 #pragma unroll
     for (int c = 0; c < kCpw; ++c) {
         const uint64_t cb = wave_base + (uint64_t)c * kChunkElems;
-        if (c < cpw_t) load_raw<TT, kMfma>((const In *)P.x, cb, n, lane, raw[c]);
+        if (c < cpw_t) load_raw<BT, kMfma>((const In *)P.x, cb, n, lane, raw[c]);
     }
 
 #if MMV_LOAD_PRIO
@@ -156,7 +163,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves> 
         if (!span_flagged) {
 #pragma unroll
             for (int c = 0; c < kCpw; ++c)
-                if (c < cpw_t) s += RawSum<TT>::run(raw[c]);
+                if (c < cpw_t) s += RawSum<BT>::run(raw[c]);
             s = wave_sum<A, kAluLanes>(s);
         }
         uint32_t before = 0;
@@ -233,8 +240,8 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves> 
                 // values, and the 0 / 1 operands are made before that, as they are without the branch (a branch
                 // ahead of the loads' first use, or operands made behind it: 1.5 to 3 % on vectors without such
                 // chunks).
-                typename SpecMfma<TT>::Operand op = SpecMfma<TT>::operand(lane);
-                SpecMfma<TT>::pin(op);
+                typename SpecMfma<BT>::Operand op = SpecMfma<BT>::operand(lane);
+                SpecMfma<BT>::pin(op);
                 if constexpr (kExactStarts) {
 #pragma unroll
                     for (int i = 0; i < 2 * K; ++i) striped[i] = raw[S][i];
@@ -246,13 +253,13 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves> 
                     for (int i = 0; i < 2 * K; ++i)
                         __builtin_nontemporal_store(
                             raw[S][i],
-                            reinterpret_cast<v4u *>((A *)P.z + cb + 1024u * (i / K) + raw_offset<TT, kMfma>(i % K, lane)));
+                            reinterpret_cast<v4u *>((A *)P.z + cb + 1024u * (i / K) + raw_offset<BT, kMfma>(i % K, lane)));
                 }
                 operand_layout_read4(raw[S], rows, lane);
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
                     A acc[16];
-                    SpecMfma<TT>::run(raw[S] + t * K, lane, acc, op);
+                    SpecMfma<BT>::run(raw[S] + t * K, lane, acc, op);
                     store_spec_rows(rows, t, lane, acc);
                 }
             } else {
@@ -264,7 +271,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves> 
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
                     A acc[16];
-                    SpecMfma<TT>::run(raw[S] + t * K, lane, acc);
+                    SpecMfma<BT>::run(raw[S] + t * K, lane, acc);
                     store_spec_rows(rows, t, lane, acc);
                 }
             }
@@ -274,11 +281,23 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves> 
             const int slot = kSlotZero + last_flag_pos(F[S]);  // x-bar(start - 1)
             agg_v = last - from_bits<A>(rows[lane * kRowStride + slot]);
         } else if constexpr (kMfma) {
+            static_assert(K == 1 || !kHalf, "a whole chunk passes through LDS on its way into the operand layout");
             if constexpr (K > 1) to_operand_layout<K>(raw[S], rows, lane);
-            agg_v = RowAgg<TT>::template run<kAluLanes>(raw[S], F[S], lane);
+            agg_v = RowAgg<BT>::template run<kAluLanes>(raw[S], F[S], lane);
+        } else if constexpr (kHalf) {
+            agg_v = A(0);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {   // (the lanes of half t own the rows of tile t)
+                uint32_t *rp = rows + (lane & 31) * kRowStride;
+                spec_shuffle_tile<BT, kAluLanes>(raw[S] + t * K, lane, rows, 0);
+                if ((lane >> 5) == t) rp[kSlotZero] = 0;
+                wave_lds_sync();
+                if ((lane >> 5) == t) agg_v = from_bits<A>(rp[kRowData + 31]) - from_bits<A>(rp[kSlotZero + last_flag_pos(F[S])]);
+                wave_lds_sync();
+            }
         } else {
 #pragma unroll
-            for (int t = 0; t < 2; ++t) spec_shuffle_tile<TT, kAluLanes>(raw[S] + t * K, lane, rows, t);
+            for (int t = 0; t < 2; ++t) spec_shuffle_tile<BT, kAluLanes>(raw[S] + t * K, lane, rows, t);
             rows[lane * kRowStride + kSlotZero] = 0;
             wave_lds_sync();
             const A last = from_bits<A>(rows[lane * kRowStride + kRowData + 31]);
@@ -486,33 +505,41 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves> 
                     }
                     rows_with_ends = __ballot(E != 0);
                 }
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    if (kKeepRows) continue;   // still there from phase A
-                    if (((rows_with_ends >> (32 * t)) & 0xFFFFFFFFull) == 0) continue;
+                auto make_rows = [&](int t, int at) {   // the row scans of tile t into the LDS rows of tile `at`
                     if (kMfma) {
                         A acc[16];
-                        SpecMfma<TT>::run(raw[S] + t * K, lane, acc);
-                        store_spec_rows(rows, t, lane, acc);
+                        SpecMfma<BT>::run(raw[S] + t * K, lane, acc);
+                        store_spec_rows(rows, at, lane, acc);
                     } else {
-                        spec_shuffle_tile<TT, kAluLanes>(raw[S] + t * K, lane, rows, t);
+                        spec_shuffle_tile<BT, kAluLanes>(raw[S] + t * K, lane, rows, at);
                     }
+                };
+                if constexpr (!kHalf && !kKeepRows) {   // (kept: still there from phase A)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        if ((rows_with_ends >> (32 * t)) & 0xFFFFFFFFull) make_rows(t, t);
                 }
                 // ---- step 6: carry into my row ----
                 const A carry = ex_f[S] ? ex_v[S] : (pre_f[S] ? pre_v[S] + ex_v[S] : (span_carry + pre_v[S]) + ex_v[S]);
                 if constexpr (kScanLike) {
-                    // stored negated in the slot before x-bar(-1), so that the revert subtracts it
-                    rows[lane * kRowStride + kSlotZero] = 0;
-                    rows[lane * kRowStride + kSlotF] = F[S];
-                    rows[lane * kRowStride + kSlotNegCarry] = to_bits(A(0) - carry);
                     const uint64_t row_any = __ballot(F[S] != 0);
+#pragma unroll
+                    for (int t = 0; t < (kHalf ? 2 : 1); ++t) {   // the tiles one after the other, or both at once
+                    if constexpr (kHalf) make_rows(t, 0);
+                    // stored negated in the slot before x-bar(-1), so that the revert subtracts it
+                    if (!kHalf || (lane >> 5) == t) {
+                        uint32_t *mine = rows + (kHalf ? lane & 31 : lane) * kRowStride;
+                        mine[kSlotZero] = 0;
+                        mine[kSlotF] = F[S];
+                        mine[kSlotNegCarry] = to_bits(A(0) - carry);
+                    }
                     wave_lds_sync();
 
                     // ---- steps 2 + 6 on every element, then store; a lane owns 4 consecutive positions ----
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
+                    for (int j = kHalf ? 4 * t : 0; j < (kHalf ? 4 * t + 4 : 8); ++j) {
                         const int R = 8 * j + (lane >> 3), p0 = 4 * (lane & 7);
-                        const uint32_t *rp = rows + R * kRowStride;
+                        const uint32_t *rp = rows + (kHalf ? R & 31 : R) * kRowStride;
                         const v4u xb = *reinterpret_cast<const v4u *>(rp + kRowData + p0);
                         A o[4];
                         if (((row_any >> (8 * j)) & 0xFFull) == 0) {
@@ -558,6 +585,8 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves> 
                             for (int i = 0; i < 4; ++i)
                                 if (e0 + i < n) z[e0 + i] = o[i];
                         }
+                    }
+                    if (kHalf && t == 0) wave_lds_sync();   // the rows are read before the next tile overwrites them
                     }
                 } else {
                     // ---- sum: only the segment ends produce output; the lane that owns a row

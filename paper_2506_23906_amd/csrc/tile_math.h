@@ -8,6 +8,8 @@ namespace {
 // ---- element types ------------------------------------------------------------------------------
 
 struct TI8 {
+    typedef TI8 base_t;
+    static constexpr bool kOneRound = false;
     typedef int8_t in_t;
     typedef uint32_t acc_t;  // int32 with wrap-around
     static constexpr int kEpl = 16;  // elements per 128-bit load
@@ -30,6 +32,8 @@ struct XorWord {
     __device__ __forceinline__ XorWord &operator-=(XorWord b) { v ^= b.v; return *this; }
 };
 struct TX8 {
+    typedef TX8 base_t;
+    static constexpr bool kOneRound = false;
     typedef uint8_t in_t;
     typedef XorWord acc_t;   // the result byte in the low bits of a 32-bit word
     static constexpr int kEpl = 16;
@@ -39,6 +43,8 @@ struct TX8 {
 };
 
 struct TF16 {
+    typedef TF16 base_t;
+    static constexpr bool kOneRound = false;
     typedef _Float16 in_t;
     typedef float acc_t;
     static constexpr int kEpl = 8;
@@ -48,6 +54,8 @@ struct TF16 {
     static __device__ __forceinline__ acc_t widen(in_t v) { return (float)v; }
 };
 struct TBF16 {
+    typedef TBF16 base_t;
+    static constexpr bool kOneRound = false;
     typedef __bf16 in_t;
     typedef float acc_t;
     static constexpr int kEpl = 8;
@@ -57,6 +65,8 @@ struct TBF16 {
     static __device__ __forceinline__ acc_t widen(in_t v) { return (float)v; }
 };
 struct TF32 {
+    typedef TF32 base_t;
+    static constexpr bool kOneRound = false;
     typedef float in_t;
     typedef float acc_t;
     static constexpr int kEpl = 4;
@@ -68,11 +78,18 @@ struct TF32 {
 struct TSpmv : TF32 {  // SpMV: the products of values and gathered entries of x
     static constexpr int kWaves = MMV_WAVES_SPMV;
 };
+// A scan whose tiles are all resident at once, three workgroups per compute unit instead of two: at most two chunks per wave
+// (80 registers), and half the LDS.  Which vectors take it, and what it gains: round_form in host.h.
+constexpr int kRoundCpw = 2;
+template <typename TT> struct OneRound : TT {
+    static constexpr bool kOneRound = true;
+};
 // Most chunks a wave of seg_tile takes.  Bytes under exclusive or in the matrix-core variant hold four accumulators
 // of bit-plane sums per tile next to the raw words: two chunks fit the registers, four spill.  The scan without a
 // flag vector keeps no flag words and no carried flags, which leaves room for longer tiles of 16- and 32-bit inputs.
 template <typename TT, int kOp, bool kMfma> constexpr int chunks_per_wave() {
     if (TT::kDtype == MMV_U8_XOR && kMfma) return MMV_CPW_X8_MFMA;
+    if (TT::kOneRound) return kRoundCpw;
     if (kOp == kPlainScan && sizeof(typename TT::in_t) == 2) return MMV_CPW_F16_SCAN;
     if (kOp == kPlainScan && sizeof(typename TT::in_t) == 4) return MMV_CPW_F32_SCAN;
     return TT::kMaxCpw;
