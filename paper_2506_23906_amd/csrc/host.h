@@ -550,24 +550,30 @@ mmv_status compress_impl(const void *d_x, const void *d_mask, uint64_t n, void *
     if (((uintptr_t)d_ws & 255u) != 0 || ws_bytes < L.total) return MMV_ERR_WORKSPACE;
     if (L.tiles > 0x7fffffffull) return MMV_ERR_INVALID_ARG;
     char *ws = (char *)d_ws;
-    if (!ws_is_reset) {
+    // one launch: every workgroup reads the mask before its tile, so nothing of that may be written meanwhile
+    const uint64_t mask_bytes = ff == MMV_FLAGS_U8 ? n : (n + 31) / 32 * 4;
+    const bool single = !ws_is_reset && compress_words(n) == 16 && n <= (ff == MMV_FLAGS_U8 ? kCompressSingleBytes : kCompressSingleBits) &&
+                        !overlap(d_out, (out_capacity < n ? out_capacity : n) * 4, d_mask, mask_bytes);
+    if (!ws_is_reset && !single) {
         const uint64_t zero_words = L.total / 4;
         fill_zero_kernel<<<grid_for(zero_words), 256, 0, s>>>((uint32_t *)ws, zero_words, nullptr, 0);
         if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     }
     if (tl_ev_start && hipEventRecord(tl_ev_start, s) != hipSuccess) return MMV_ERR_HIP;
     // the workgroups that are resident from the start take the tile of their own index, the others a ticket
-    static std::atomic<uint32_t> occupancy[8][kMaxDevices];
+    static std::atomic<uint32_t> occupancy[10][kMaxDevices];
     typedef void (*Kernel)(const uint32_t *, const void *, uint64_t, uint32_t *, uint64_t, uint64_t *, uint32_t *, uint64_t *,
                            uint32_t, const uint32_t *, uint32_t);
-    static const Kernel kernels[8] = {compress_kernel<16, 1, false>, compress_kernel<64, 1, false>, compress_kernel<64, 2, false>,
-                                      compress_kernel<64, 4, false>, compress_kernel<16, 1, true>,  compress_kernel<64, 1, true>,
-                                      compress_kernel<64, 2, true>,  compress_kernel<64, 4, true>};
-    const int which = (compress_words(n) == 16 ? 0 : compress_groups(n) == 1 ? 1 : compress_groups(n) == 2 ? 2 : 3) +
+    static const Kernel kernels[10] = {compress_kernel<16, 1, false>, compress_kernel<64, 1, false>, compress_kernel<64, 2, false>,
+                                       compress_kernel<64, 4, false>, compress_kernel<16, 1, true>,  compress_kernel<64, 1, true>,
+                                       compress_kernel<64, 2, true>,  compress_kernel<64, 4, true>,  compress_kernel<16, 1, false, true>,
+                                       compress_kernel<16, 1, true, true>};
+    const int which = single ? (ff == MMV_FLAGS_U8 ? 9 : 8) :
+                      (compress_words(n) == 16 ? 0 : compress_groups(n) == 1 ? 1 : compress_groups(n) == 2 ? 2 : 3) +
                       (ff == MMV_FLAGS_U8 ? 4 : 0);
     const Kernel kernel = kernels[which];
     const uint32_t resident = resident_workgroups((const void *)kernel, kCompressWaves * 64, occupancy[which]);
-    const uint32_t first_round = (uint32_t)L.tiles < resident ? (uint32_t)L.tiles : resident;
+    const uint32_t first_round = single || (uint32_t)L.tiles < resident ? (uint32_t)L.tiles : resident;   // (no tickets in one launch)
     kernel<<<(unsigned)L.tiles, kCompressWaves * 64, 0, s>>>((const uint32_t *)d_x, d_mask, n, (uint32_t *)d_out, out_capacity,
                                                              d_count, (uint32_t *)ws, (uint64_t *)(ws + L.desc),
                                                              (uint32_t)L.tiles, d_needed, first_round);

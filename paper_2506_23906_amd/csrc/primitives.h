@@ -54,7 +54,12 @@ __global__ __launch_bounds__(256) void unpack_flags_kernel(const uint32_t *fw, u
 // whatever its length, and with one group per wave the tickets alone took 93 us of the 111 us at n = 2^28
 // and 0.1 % selected (now 0.048 ms).
 // The workgroups that are resident from the start take the tile of their own index, as in the main kernel.
+// kSingle: short masks.  Every workgroup counts the set bits before its tile itself, so nothing has to be zeroed and nobody
+// waits: one launch instead of two.  Whole calls, 30 % selected: 3000 positions 7.6 -> 5.3 us, 2^18 bits 7.8 -> 5.4, 2^20 bits 8.3 ->
+// 5.7, 2^21 bits 9.4 -> 6.9, 2^17 bytes 7.6 -> 6.4.  Beyond, the count takes longer than the launch (2^22 bits 11.6 -> 12.2, 2^18 bytes
+// 8.2 -> 8.2, 2^19 8.2 -> 12.3: sixteen flag bytes take twenty instructions, and a workgroup reads some 150 GB/s).
 constexpr int kCompressWaves = 8;
+constexpr uint64_t kCompressSingleBits = 1ull << 21, kCompressSingleBytes = 1ull << 17;   // positions
 constexpr uint64_t kCompressShortN = 1ull << 22;   // masks up to this length take 16 words per wave
 // masks from 2^26 positions on take two groups of words per wave, from 2^27 on four: the most that still leaves a tile
 // for each of the 1024 workgroups that are resident at once (n = 2^27, 1 % selected: 0.054 ms with two groups, 0.039
@@ -74,12 +79,12 @@ struct CompressPiece {
     uint32_t rank_sel[4];
 };
 
-template <int kWords, int kGroups, bool kBytes>
+template <int kWords, int kGroups, bool kBytes, bool kSingle = false>
 __global__ __launch_bounds__(kCompressWaves * 64, 8) void compress_kernel(
     const uint32_t *__restrict__ x, const void *__restrict__ mask, uint64_t n, uint32_t *__restrict__ out,
     uint64_t out_cap, uint64_t *__restrict__ count, uint32_t *hdr, uint64_t *desc, uint32_t num_tiles,
     const uint32_t *needed, uint32_t first_round) {
-    __shared__ uint32_t s_tile, s_wave[kCompressWaves], s_carry;
+    __shared__ uint32_t s_tile, s_wave[kCompressWaves], s_carry, s_before[kCompressWaves];
     __shared__ __attribute__((aligned(16))) uint32_t s_piece[kCompressWaves][kPieceWords];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (needed && *needed == 0) return;   // CSR SpMV without empty rows: nobody reads the row map
@@ -95,6 +100,18 @@ __global__ __launch_bounds__(kCompressWaves * 64, 8) void compress_kernel(
     uint64_t m[kGroups];
     uint32_t before[kGroups];   // selected entries of my wave before my word of group g
     uint32_t wave_cnt = 0;
+    if constexpr (kSingle) {   // set bits before the tile (which begins at a multiple of 128 positions)
+        const uint64_t start = (uint64_t)tile * kCompressWaves * kSpan;
+        uint32_t cnt = 0;
+#pragma unroll 4
+        for (uint32_t i = tid; i < (uint32_t)(start / (kBytes ? 16 : 128)); i += kCompressWaves * 64) {
+            const v4u w = ((const v4u *)mask)[i];
+            cnt += kBytes ? __popc(bits_of_16_bytes(w)) : (__popc(w[0]) + __popc(w[1])) + (__popc(w[2]) + __popc(w[3]));
+        }
+        cnt = wave_sum(cnt);
+        if (lane == 0) s_before[wave] = cnt;
+        if (tile == 0 && tid == 0) hdr[kHdrError] = hdr[kHdrPrepared] = 0;
+    }
     if constexpr (kBytes) {
         const uint8_t *mb = (const uint8_t *)mask;
         constexpr int kLoads = kWords / 16;   // 1024 mask bytes of the wave each
@@ -179,18 +196,26 @@ __global__ __launch_bounds__(kCompressWaves * 64, 8) void compress_kernel(
         if (w == wave) wave_ex = tile_cnt;
         tile_cnt += s_wave[w];
     }
-    if (tid == 0) desc_store(desc + tile, tile == 0 ? kStatusPrefix : kStatusAggregate, tile_cnt);
-    if (wave == 0) {
-        uint32_t carry = 0;
-        if (tile > 0) carry = lookback<uint32_t>(desc, (int)tile, lane, hdr);
-        if (lane == 0) {
-            if (tile > 0) desc_store(desc + tile, kStatusPrefix, carry + tile_cnt);
-            s_carry = carry;
-            if (tile == num_tiles - 1) *count = (uint64_t)carry + tile_cnt;
+    uint32_t tile_before = 0;   // selected entries before the tile
+    if constexpr (kSingle) {
+#pragma unroll
+        for (int w = 0; w < kCompressWaves; ++w) tile_before += s_before[w];
+        if (tid == 0 && tile == num_tiles - 1) *count = (uint64_t)tile_before + tile_cnt;
+    } else {
+        if (tid == 0) desc_store(desc + tile, tile == 0 ? kStatusPrefix : kStatusAggregate, tile_cnt);
+        if (wave == 0) {
+            uint32_t carry = 0;
+            if (tile > 0) carry = lookback<uint32_t>(desc, (int)tile, lane, hdr);
+            if (lane == 0) {
+                if (tile > 0) desc_store(desc + tile, kStatusPrefix, carry + tile_cnt);
+                s_carry = carry;
+                if (tile == num_tiles - 1) *count = (uint64_t)carry + tile_cnt;
+            }
         }
+        __syncthreads();
+        tile_before = s_carry;
     }
-    __syncthreads();
-    const uint64_t wave_base = (uint64_t)s_carry + wave_ex;   // output index of the first selected entry of my wave
+    const uint64_t wave_base = (uint64_t)tile_before + wave_ex;   // output index of the first selected entry of my wave
     if (!dense) {
         // few selected entries in my wave's positions: every lane walks the set bits of its own
         // words (a handful of independent loads per lane)

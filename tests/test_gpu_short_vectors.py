@@ -169,3 +169,24 @@ def test_sscr_counts_position_zero_whatever_its_flag():
         z = B.mmv_segscan_sscr(dev(x), flags_dev(f, True), n=n)
         torch.cuda.synchronize()
         assert np.array_equal(z.cpu().numpy(), oracle.segscan(x, f))
+
+
+@pytest.mark.parametrize("packed", [True, False])
+def test_compress_in_one_launch(packed):
+    """Masks of at most 2^21 bits or 2^17 bytes: every workgroup of 8192 positions counts the set bits before its tile itself."""
+    rng = np.random.default_rng(2390706)
+    line = 1 << (21 if packed else 17)
+    for n in (1, 127, 128, 129, 8191, 8192, 8193, 5 * 8192 + 1023, line - 33, line, line + 1):
+        for density in (0.0, 2 / n, 0.01, 0.3, 1.0):
+            m = (rng.random(n) < density) * rng.integers(1, 256, size=n)
+            m = (m if not packed else m != 0).astype(np.uint8)
+            x = rng.integers(-2**31, 2**31, size=n, dtype=np.int64).astype(np.int32)
+            print(packed, n, density, flush=True)
+            ref, pos = oracle.compress(x, m), np.flatnonzero(m).astype(np.int32)
+            cap = len(ref) - len(ref) // 3
+            for src, want in ((dev(x), ref), (None, pos)):
+                out = torch.full((cap + 9,), -7, dtype=torch.int32, device="cuda")
+                ws = garbage(B.mmv_workspace_bytes(B.MMV_OP_COMPRESS, B.MMV_I8_I32, B.MMV_FLAGS_PACKED32 if packed else B.MMV_FLAGS_U8, n))
+                _, count = B.mmv_compress(src, flags_dev(m, packed), n, out=out[:cap], ws=ws)
+                assert B.mmv_workspace_status(ws) == 0 and int(count.item()) == len(want)
+                assert np.array_equal(out.cpu().numpy()[:cap], want[:cap]) and bool((out[cap:] == -7).all())
