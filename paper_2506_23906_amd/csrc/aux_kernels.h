@@ -238,6 +238,164 @@ __global__ __launch_bounds__(256) void csr_flags_kernel(const int32_t *rowptr, u
     }
 }
 
+// The same in one launch that needs nothing zeroed first: workgroup t makes all that the product kernel needs for its tile t.
+// It finds the rows that start in the tile by a search in the row pointers, all threads probing, sets their bits in LDS and
+// stores the words, and leaves
+//   tile_base[t]    the first row that starts in the tile (r0), bit 31 set if none of the tile's rows is empty: then the
+//                   j-th start of the tile is row r0 + j, and what is open where it begins is row r0 - 1, the last that starts
+//                   before the tile and reaches it;
+//   rowmap[r0 - 1 + j]  those rows else.  (The slots of two tiles meet in one alone, which both give the row of its number.)
+// The same launch zeroes the header and descriptors of the product kernel, and y.
+// Bound by its chain of dependent loads: four to five for the two ends of the tile, then one per 2048 rows.  Four waves: eight
+// or sixteen start later (blocks of 16, 65536 rows: 33.4 and 38.5 us the call against 31.5).  Products in one step, four
+// launches over the rows (reset, csr_flags_kernel, COMPRESS of the row list, product) -> this kernel and the product, us:
+//   sparse attention, 65536 rows: 11.5 M entries 34.5 -> 31.4; 63 M 114 -> 106; 8192 rows, 1.4 M 16.5 -> 13.2
+//   equal rows of 1, 2, 8, 32 entries, 2^20 rows: 135 -> 35, 98 -> 28, 114 -> 63, 222 -> 209; 65536 rows: 32 -> 24, 28 -> 16,
+//   21 -> 13.6, 19.7 -> 17; Zipf lengths, 2^20 rows and 2^25 entries 244 -> 222
+// (In the four launches, adds and ORs of many rows meet in the same words, and each launch costs 2.5 to 5.)
+constexpr int kPlanThreads = 256, kPlanRows = 8;
+__global__ __launch_bounds__(kPlanThreads) void csr_plan_kernel(const int32_t *rowptr, uint32_t n_rows, uint32_t nnz, uint32_t tile_elems,
+                                                                uint32_t *fw, uint32_t *tile_base, uint32_t *rowmap, uint32_t *ws,
+                                                                uint64_t ws_words, uint32_t *y, uint32_t y_rows) {
+    constexpr int kWaves = kPlanThreads / 64;
+    __shared__ __attribute__((aligned(16))) uint32_t s_words[kMaxUnits * (kUnitElems / 32)];
+    __shared__ uint32_t s_cnt[2][kWaves], s_kept[2][kWaves];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tile = blockIdx.x;
+    const uint64_t stride = (uint64_t)gridDim.x * kPlanThreads;
+    for (uint64_t i = (uint64_t)tile * kPlanThreads + tid; i < ws_words; i += stride) ws[i] = 0;
+    for (uint64_t i = (uint64_t)tile * kPlanThreads + tid; i < y_rows; i += stride) y[i] = 0;
+    const uint32_t base = tile * tile_elems, end = nnz - base < tile_elems ? nnz : base + tile_elems;
+    const uint32_t words = (end - base + 31) / 32;
+    for (uint32_t w = tid; w < (words + 3) / 4 * 4; w += kPlanThreads) s_words[w] = 0;
+
+    // first index in [lo, hi] whose row pointer is at least the target (hi: none), for two targets at once
+    auto search = [&](uint32_t (&lo)[2], uint32_t (&hi)[2], const uint32_t (&target)[2]) {
+        while (lo[0] < hi[0] || lo[1] < hi[1]) {
+            uint32_t step[2];
+            for (int k = 0; k < 2; ++k) {
+                step[k] = (hi[k] - lo[k]) / kPlanThreads + 1;
+                const uint32_t p = lo[k] + (tid + 1) * step[k] - 1;
+                const bool below = p < hi[k] && (uint32_t)rowptr[p] < target[k];
+                const uint64_t b = __ballot(below);
+                if (lane == 0) s_cnt[k][wave] = (uint32_t)__popcll((unsigned long long)b);
+            }
+            __syncthreads();
+            for (int k = 0; k < 2; ++k) {
+                uint32_t c = 0;
+                for (int w = 0; w < kWaves; ++w) c += s_cnt[k][w];
+                lo[k] += c * step[k];
+                hi[k] = hi[k] < lo[k] + step[k] - 1 ? hi[k] : lo[k] + step[k] - 1;
+            }
+            __syncthreads();
+        }
+    };
+    uint32_t first[2] = {0, 0}, behind[2] = {n_rows, n_rows};
+    search(first, behind, {base, end});
+    const uint32_t r0 = first[0], r1 = first[1];   // rows that start in the tile
+    uint32_t kept = 0;                             // those with entries so far
+    __syncthreads();
+    // rows found in a round, in their order: masks of 64 candidates each -> where a wave's first one goes
+    auto place = [&](const uint64_t (&mask)[kPlanRows], uint32_t odd, uint32_t &total) {
+        uint32_t mine = 0;
+#pragma unroll
+        for (int i = 0; i < kPlanRows; ++i) mine += (uint32_t)__popcll((unsigned long long)mask[i]);
+        if (lane == 0) s_kept[odd][wave] = mine;
+        __syncthreads();
+        uint32_t at = r0 + kept;
+        total = 0;
+        for (int w = 0; w < kWaves; ++w) {
+            if (w < (int)wave) at += s_kept[odd][w];
+            total += s_kept[odd][w];
+        }
+        kept += total;
+        return at;
+    };
+    const uint32_t e0 = r0 < r1 ? (uint32_t)rowptr[r0] : 0u, starts = r0 < r1 ? (uint32_t)rowptr[r1 - 1] - e0 + 1 : 0u;
+    if (r1 - r0 > kPlanThreads * kPlanRows * 2 && (r1 - r0) / 24 > starts) {
+        // Many rows, almost all of them empty: a search for every position instead that a row may start at, for the last row
+        // that starts up to there.  (2048 positions take about 20 us, 2048 rows 0.9: the two meet at 22 rows per position.
+        // 2^20 rows, one in 2048 with an entry, all in one tile: 101 us the call, row by row 480.)
+        uint32_t top = 1u << 31;
+        while (top > r1 - r0) top >>= 1;
+        for (uint32_t cur = (e0 - base) & ~63u, odd = 0; cur < e0 - base + starts; cur += kPlanThreads * kPlanRows, odd ^= 1) {
+            const uint32_t at0 = cur + 64 * kPlanRows * wave;   // (in the tile)
+            uint32_t row[kPlanRows], start[kPlanRows];
+#pragma unroll
+            for (int i = 0; i < kPlanRows; ++i) row[i] = r0, start[i] = e0;
+            for (uint32_t step = top; step; step >>= 1) {
+#pragma unroll
+                for (int i = 0; i < kPlanRows; ++i) {
+                    const uint32_t next = row[i] + step < r1 ? row[i] + step : row[i], v = (uint32_t)rowptr[next];
+                    if (v <= base + at0 + 64 * i + lane) row[i] = next, start[i] = v;
+                }
+            }
+            uint64_t mask[kPlanRows];
+#pragma unroll
+            for (int i = 0; i < kPlanRows; ++i) mask[i] = __ballot(start[i] == base + at0 + 64 * i + lane);
+            uint32_t total, at = place(mask, odd, total);
+#pragma unroll
+            for (int i = 0; i < kPlanRows; ++i) {
+                if (mask[i] == 0) continue;
+                if (mask[i] >> lane & 1) rowmap[at + __popcll((unsigned long long)(mask[i] & ((1ull << lane) - 1)))] = row[i];
+                if (lane < 2 && at0 + 64 * i + 32 * lane < end - base) s_words[at0 / 32 + 2 * i + lane] = (uint32_t)(mask[i] >> (32 * lane));
+                at += (uint32_t)__popcll((unsigned long long)mask[i]);
+            }
+        }
+    } else {
+        // A round is kPlanRows rows per thread: lane l of a wave takes rows l, l + 64, ... of the wave's share (those from r1 on
+        // count as empty).  The next round's pointers are under way meanwhile.
+        auto load_rows = [&](uint32_t cur, uint32_t (&p)[kPlanRows + 1]) {
+            const uint32_t r = cur + 64 * kPlanRows * wave + lane;
+#pragma unroll
+            for (int i = 0; i <= kPlanRows; ++i) p[i] = (uint32_t)rowptr[r + 64 * i < r1 ? r + 64 * i : r1];
+        };
+        uint32_t p[kPlanRows + 1];
+        load_rows(r0, p);
+        for (uint32_t cur = r0, odd = 0; cur < r1; odd ^= 1) {
+            const uint32_t r = cur + 64 * kPlanRows * wave + lane;
+            uint32_t ahead[kPlanRows + 1];
+            cur += kPlanThreads * kPlanRows;
+            if (cur < r1) load_rows(cur, ahead);
+            uint64_t mask[kPlanRows];
+#pragma unroll
+            for (int i = 0; i < kPlanRows; ++i) {
+                // the next row's pointer: the next lane's; of lane 63, the first of the next 64
+                const int after = __builtin_amdgcn_readfirstlane((int)p[i + 1]);
+                mask[i] = __ballot((uint32_t)__builtin_amdgcn_update_dpp(after, (int)p[i], 0x130, 0xF, 0xF, false) > p[i]);
+            }
+            uint32_t total, at = place(mask, odd, total);
+#pragma unroll
+            for (int i = 0; i < kPlanRows; ++i) {
+                if (mask[i] == 0) continue;
+                if (mask[i] >> lane & 1) {
+                    rowmap[at + __popcll((unsigned long long)(mask[i] & ((1ull << lane) - 1)))] = r + 64 * i;
+                    if (p[i] - base < end - base) atomicOr(s_words + ((p[i] - base) >> 5), 1u << ((p[i] - base) & 31u));
+                }
+                at += (uint32_t)__popcll((unsigned long long)mask[i]);
+            }
+            if (cur < r1) {
+                if (total == 0) {   // a long run of empty rows: on to the row behind it
+                    const uint32_t v = (uint32_t)rowptr[cur];
+                    uint32_t lo[2] = {cur, cur}, hi[2] = {r1, cur};
+                    search(lo, hi, {v + 1, v + 1});
+                    cur = lo[0] - 1;
+                    load_rows(cur, p);
+                } else {
+#pragma unroll
+                    for (int i = 0; i <= kPlanRows; ++i) p[i] = ahead[i];
+                }
+            }
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        tile_base[tile] = r0 | (kept == r1 - r0 ? 0x80000000u : 0u);
+        if (r0 > 0) rowmap[r0 - 1] = r0 - 1;
+    }
+    v4u *out = reinterpret_cast<v4u *>(fw + base / 32);
+    for (uint32_t w = tid; w < (words + 3) / 4; w += kPlanThreads) out[w] = reinterpret_cast<const v4u *>(s_words)[w];
+}
+
 // Random-access reference for SpMV: streams val and col with 128-bit loads, gathers x[col] and
 // keeps one partial sum per thread: everything the product vector of SpMV costs, and nothing of
 // the segmented sum.  A column index at or beyond n_cols reads x[0] instead (no access out of bounds).

@@ -582,6 +582,51 @@ mmv_status compress_impl(const void *d_x, const void *d_mask, uint64_t n, void *
     return e == hipSuccess ? MMV_OK : MMV_ERR_HIP;
 }
 
+// Matrices that csr_plan_kernel prepares tile by tile; the launches over the rows, spread over the chip whatever the rows, are
+// left to those with so few entries that a tile holds too many rows.  Products in one step, launches over the rows / tile by
+// tile (us), rows with one entry or none, 0.4, 0.25 and 0.06 entries per row: 2^14 rows 31 / 26, 28 / 23, 22 / 22; 2^16 37 / 32,
+// 37 / 39, 31 / 54; 2^18 77 / 34, 77 / 41, 72 / 103; 2^20 154 / 44, 175 / 52, 211 / 106.
+// Beyond the line also where the rows are uneven: 2^18 rows, half of them of 16 entries, then one in 20 of one entry in a
+// tile or two, 53 / 64 us; without those empty rows 36 / 20.
+constexpr bool rows_by_tile(uint64_t n_rows, uint64_t nnz) { return n_rows / 3 <= nnz; }
+
+// What the CSR product needs of the matrix alone, header and descriptors zeroed, and y (nullptr: not).
+mmv_status csr_plan(uint64_t n_rows, uint64_t nnz, const int32_t *d_rowptr, uint32_t *d_y, char *ws, const CsrLayout &C, const WsLayout &L,
+                    const TilePlan &plan, hipStream_t s) {
+    uint32_t *fw = (uint32_t *)(ws + C.main_ws + L.packed);
+    uint32_t *tile_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
+    if (rows_by_tile(n_rows, nnz)) {
+        csr_plan_kernel<<<(unsigned)plan.tiles, kPlanThreads, 0, s>>>(d_rowptr, (uint32_t)n_rows, (uint32_t)nnz, plan.body_elems, fw, tile_count,
+                                                                      (uint32_t *)(ws + C.rowmap), (uint32_t *)(ws + C.main_ws),
+                                                                      L.desc_c / 4, d_y, d_y ? (uint32_t)n_rows : 0u);
+        return hipGetLastError() == hipSuccess ? MMV_OK : MMV_ERR_HIP;
+    }
+    // zero: the main kernel's header, descriptors and flag words, the header and descriptors of COMPRESS; y
+    const uint64_t zero_words = (C.compress_ws + compress_layout(n_rows).total) / 4, y_rows = d_y ? n_rows : 0;
+    fill_zero_kernel<<<grid_for(zero_words > y_rows ? zero_words : y_rows), 256, 0, s>>>((uint32_t *)ws, zero_words, d_y, y_rows);
+    if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
+    // segment-start flags over the non-zeros, their number per tile of the main kernel, and the mask of
+    // rows that have entries
+    const uint64_t row_blocks = (n_rows + 255) / 256;
+    csr_flags_kernel<<<(unsigned)row_blocks, 256, 0, s>>>(d_rowptr, n_rows, fw, (uint32_t *)(ws + C.rowmask),
+                                                          (uint32_t *)(ws + C.main_ws), plan.body_elems, tile_count);
+    if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
+    // rowmap = COMPRESS(0 .. n_rows - 1, rowmask): the k-th segment belongs to row rowmap[k]
+    {
+        EventsOff quiet;
+        const mmv_status st = compress_impl(nullptr, ws + C.rowmask, n_rows, ws + C.rowmap, n_rows,
+                                            (uint64_t *)(ws + C.rowcount), MMV_FLAGS_PACKED32, ws + C.compress_ws,
+                                            C.rowmask - C.compress_ws, s, true,
+                                            (const uint32_t *)(ws + C.main_ws) + kHdrEmptyRows);
+        if (st != MMV_OK) return st;
+    }
+    if (plan.tiles > kCountTiles) {
+        scan_counts_kernel<<<1, 1024, 0, s>>>(tile_count, (uint32_t)plan.tiles, (uint64_t *)(ws + C.rowcount));
+        if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
+    }
+    return MMV_OK;
+}
+
 mmv_status diff_impl(const void *d_x, uint64_t n, void *d_z, mmv_elem et, hipStream_t s,
                      const uint64_t *d_limit = nullptr) {
     const uint64_t blocks = (n + 1023) / 1024;

@@ -216,7 +216,7 @@ mmv_status mmv_spmv_coo(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
 
 // SpMV in two steps: the mark that the first step leaves in the header for this matrix shape (never 0).  It names the
 // layout of the counts as well (kPlanLayout), which the product kernel relies on.
-static constexpr uint64_t kPlanLayout = 4;
+static constexpr uint64_t kPlanLayout = 5;
 static uint32_t prepared_mark(mmv_op op, uint64_t n_rows, uint64_t nnz) {
     uint64_t h = (nnz + 0x9E3779B97F4A7C15ull) * 0xD6E8FEB86659FD93ull + n_rows * 0xCA5A826395121157ull + (uint64_t)op + (kPlanLayout << 32);
     h ^= h >> 32;
@@ -427,29 +427,11 @@ mmv_status mmv_spmv_csr(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
     if (((uintptr_t)d_ws & 255u) != 0 || ws_bytes < C.total) return MMV_ERR_WORKSPACE;
     char *ws = (char *)d_ws;
     const WsLayout L = ws_layout(MMV_OP_SPMV_CSR, MMV_F32_F32, MMV_FLAGS_PACKED32, nnz);
-    // zero: the main kernel's header, descriptors and flag words, the header and descriptors of COMPRESS; y
-    const uint64_t zero_words = (C.compress_ws + compress_layout(n_rows).total) / 4;
-    fill_zero_kernel<<<grid_for(zero_words > n_rows ? zero_words : n_rows), 256, 0, s>>>((uint32_t *)ws, zero_words,
-                                                                                      (uint32_t *)d_y, n_rows);
-    if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
-    // segment-start flags over the non-zeros, their number per tile of the main kernel, and the mask of
-    // rows that have entries
     const TilePlan plan = tile_plan(MMV_OP_SPMV_CSR, MMV_F32_F32, nnz);
     uint32_t *fw = (uint32_t *)(ws + C.main_ws + L.packed);
     uint32_t *tile_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
-    const uint64_t row_blocks = (n_rows + 255) / 256;
-    csr_flags_kernel<<<(unsigned)row_blocks, 256, 0, s>>>(d_rowptr, n_rows, fw, (uint32_t *)(ws + C.rowmask),
-                                                          (uint32_t *)(ws + C.main_ws), plan.body_elems, tile_count);
-    if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
-    // rowmap = COMPRESS(0 .. n_rows - 1, rowmask): the k-th segment belongs to row rowmap[k]
-    {
-        EventsOff quiet;
-        const mmv_status st = compress_impl(nullptr, ws + C.rowmask, n_rows, ws + C.rowmap, n_rows,
-                                            (uint64_t *)(ws + C.rowcount), MMV_FLAGS_PACKED32, ws + C.compress_ws,
-                                            C.rowmask - C.compress_ws, s, true,
-                                            (const uint32_t *)(ws + C.main_ws) + kHdrEmptyRows);
-        if (st != MMV_OK) return st;
-    }
+    const mmv_status st = csr_plan(n_rows, nnz, d_rowptr, (uint32_t *)d_y, ws, C, L, plan, s);
+    if (st != MMV_OK) return st;
     Params P = {};
     P.x = d_val;
     P.n = nnz;
@@ -463,11 +445,8 @@ mmv_status mmv_spmv_csr(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
     P.desc_v = (uint64_t *)(ws + C.main_ws + L.desc_v);
     P.fw = fw;
     P.count_is_prefix = plan.tiles > kCountTiles ? 1u : 0u;
-    if (P.count_is_prefix) {
-        scan_counts_kernel<<<1, 1024, 0, s>>>(tile_count, (uint32_t)plan.tiles, (uint64_t *)(ws + C.rowcount));
-        if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
-    }
     P.tile_count = tile_count;
+    if (rows_by_tile(n_rows, nnz)) P.tile_base = tile_count;
     return launch_seg<TSpmv, kSpmvCsr>(P, v, s) == hipSuccess ? MMV_OK : MMV_ERR_HIP;
 }
 
@@ -482,28 +461,9 @@ mmv_status mmv_spmv_csr_prepare(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, 
     hipStream_t s = (hipStream_t)hip_stream;
     char *ws = (char *)d_ws;
     const WsLayout L = ws_layout(MMV_OP_SPMV_CSR, MMV_F32_F32, MMV_FLAGS_PACKED32, nnz);
-    const uint64_t zero_words = (C.compress_ws + compress_layout(n_rows).total) / 4;
-    fill_zero_kernel<<<grid_for(zero_words), 256, 0, s>>>((uint32_t *)ws, zero_words, nullptr, 0);
-    if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
     const TilePlan plan = tile_plan(MMV_OP_SPMV_CSR, MMV_F32_F32, nnz);
-    uint32_t *fw = (uint32_t *)(ws + C.main_ws + L.packed);
-    uint32_t *tile_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
-    const uint64_t row_blocks = (n_rows + 255) / 256;
-    csr_flags_kernel<<<(unsigned)row_blocks, 256, 0, s>>>(d_rowptr, n_rows, fw, (uint32_t *)(ws + C.rowmask),
-                                                          (uint32_t *)(ws + C.main_ws), plan.body_elems, tile_count);
-    if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
-    {
-        EventsOff quiet;
-        const mmv_status st = compress_impl(nullptr, ws + C.rowmask, n_rows, ws + C.rowmap, n_rows,
-                                            (uint64_t *)(ws + C.rowcount), MMV_FLAGS_PACKED32, ws + C.compress_ws,
-                                            C.rowmask - C.compress_ws, s, true,
-                                            (const uint32_t *)(ws + C.main_ws) + kHdrEmptyRows);
-        if (st != MMV_OK) return st;
-    }
-    if (plan.tiles > kCountTiles) {
-        scan_counts_kernel<<<1, 1024, 0, s>>>(tile_count, (uint32_t)plan.tiles, (uint64_t *)(ws + C.rowcount));
-        if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
-    }
+    const mmv_status st = csr_plan(n_rows, nnz, d_rowptr, nullptr, ws, C, L, plan, s);
+    if (st != MMV_OK) return st;
     mark_prepared_kernel<<<1, 64, 0, s>>>((uint32_t *)(ws + C.main_ws), prepared_mark(MMV_OP_SPMV_CSR, n_rows, nnz));
     return hipGetLastError() == hipSuccess ? MMV_OK : MMV_ERR_HIP;
 }
@@ -542,6 +502,7 @@ mmv_status mmv_spmv_csr_run(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, cons
     P.fw = (const uint32_t *)(ws + C.main_ws + L.packed);
     P.count_is_prefix = plan.tiles > kCountTiles ? 1u : 0u;
     P.tile_count = (const uint32_t *)(ws + C.main_ws + L.desc_c);
+    if (rows_by_tile(n_rows, nnz)) P.tile_base = P.tile_count;
     P.prepared = prepared_mark(MMV_OP_SPMV_CSR, n_rows, nnz);
     // header and value descriptors of the main kernel; the counts, flag words, row mask and row map behind them stay
     const uint64_t zero_words = L.desc_c / 4;

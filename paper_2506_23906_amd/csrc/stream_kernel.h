@@ -138,7 +138,7 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
     const bool mine = part < 4u * (uint32_t)units;
     const uint64_t w0 = (span.base >> 5) + 8u * part, words = (n + 31) >> 5;
     auto clear_uncounted = [&] {
-        if (tile == 0 && part == 0) fl[0][0] &= ~1u;
+        if (kOp == kSum && tile == 0 && part == 0) fl[0][0] &= ~1u;   // (SpMV: a row starts there)
         if (!mine || w0 * 32 + 256u > n) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
@@ -159,7 +159,7 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
 #pragma unroll
         for (int i = 0; i < 2; ++i) fl[i] = *reinterpret_cast<const v4u *>(P.fw + (mine && w0 + 4 * i < words ? w0 + 4 * i : 0));
     } else if constexpr (kCounts) {
-        count_part = starts_before_part<false>(P, tile, 0, lane);
+        if (kOp == kSum || !P.tile_base) count_part = starts_before_part<false>(P, tile, 0, lane);
         if (mine) {
 #pragma unroll
             for (int i = 0; i < 2; ++i)
@@ -167,9 +167,14 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
             clear_uncounted();
         }
     }
-    // CSR: without empty rows the k-th segment is row k and the row map was not made
+    // CSR: without empty rows (in the tile; in the matrix) the k-th segment is row k and the row map need not be read
     bool rows_dense = false;
-    if constexpr (kOp == kSpmvCsr) rows_dense = hints[kHdrEmptyRows - kHdrHints] == 0;
+    uint32_t tile_base = 0;
+    if constexpr (kOp == kSpmvCsr) {
+        // (no branch around the load, for the same reason)
+        tile_base = *(P.tile_base ? P.tile_base + tile : hints + (kHdrEmptyRows - kHdrHints));
+        rows_dense = P.tile_base ? (tile_base >> 31) != 0 : tile_base == 0;
+    }
     __builtin_amdgcn_sched_barrier(0);
     StreamSlot<kProduct> slot[kDepth];
 #pragma unroll
@@ -195,6 +200,8 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
     }
     if constexpr (kCounts) {
         count_carry = wave_sum<uint32_t, true>(count_part);
+        // CSR: (the number of starts, or the first row) before the tile, minus 1: the index of the segment that is open there
+        if constexpr (kOp == kSpmvCsr) count_carry = P.tile_base ? (tile_base & 0x7FFFFFFFu) - 1u : tile == 0 ? ~0u : count_carry;
         uint32_t s = 0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) s += __popc(fl[i / 4][i % 4]);
@@ -347,7 +354,7 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
                         } else if (q > 0) {
                             count_base += (uint32_t)__builtin_amdgcn_readlane((int)starts_upto, 4 * q - 1);
                         }
-                        if (ub == 0) count_base -= 1u;   // position 0 is a flag in F, but counted nowhere else
+                        if (kOp == kSum && ub == 0) count_base -= 1u;   // position 0 is a flag in F, but counted nowhere else
                     }
                     // ---- steps 2 and 6 at the segment ends: half h of the wave takes the ends in its half of the rows ----
                     uint32_t Eh = E & (h ? 0xFFFF0000u : 0x0000FFFFu);

@@ -203,7 +203,8 @@ struct Params {
     uint64_t out_cap;
     uint64_t *nseg;
     const int32_t *row;     // spmv (coo)
-    const uint32_t *rowmap; // spmv (csr): row index of the k-th non-empty row
+    const uint32_t *rowmap; // spmv (csr): row index of the k-th non-empty row, or (tile_base) slots of their own per tile
+    const uint32_t *tile_base;   // spmv (csr): as csr_plan_kernel leaves it (nullptr: made row by row, see csr_flags_kernel)
     uint32_t first_one;     // plain scan of a flag vector: element 0 counts as 1 whatever it holds
     const int32_t *col;
     const float *xv;
