@@ -22,10 +22,11 @@
 // Layout of a workgroup tile: 8 waves x (1 to 4) chunks x 64 rows x 32 elements.
 // Lane r of a wave owns row r of the wave's current 2048-element chunk for steps 3-5;
 // one packed flag word is exactly one row.  Sums of 32-bit values and SpMV (stream_kernel) and long sums of 8- and 16-bit
-// values (sum_kernel) have tile bodies of their own.
+// values (sum_kernel) have tile bodies of their own.  Short vectors (short_kernel) are scanned element by element, without
+// speculation, in one launch that takes the carry from the input or in two that take it from tile sums.
 //
 // Small kernels around it: workspace reset, flag packing (bytes, COO row indices, CSR row
-// pointers), counts of segment starts per wave span (the output positions of the segmented sum),
+// pointers: csr_plan_kernel, or csr_flags_kernel and COMPRESS), counts of segment starts per wave span (the output positions of the segmented sum),
 // COMPRESS, DIFF, REVERT, and two reference kernels for the benchmark: a streaming copy
 // (bandwidth) and a gather of x[col] (what the random accesses of SpMV cost on their own).
 #include <hip/hip_runtime.h>

@@ -25,9 +25,11 @@ namespace {
 // Where the lines lie.  One launch: a workgroup alone reads its L2 at some 150 GB/s, so with the whole input before the last
 // tile to be read (a vector without flags) one launch takes as long as two from about 320 KB of values and flags on (fp32
 // values: 65536 6.2 against 6.5 us, 131072 9.9 against 6.5; with flags every hundred elements one launch takes 4.3 there).
-// Two launches: up to 2^21 elements everything gains (segmented scan of bytes 9.9 -> 7.8); at 2^22, where the data is read
-// twice, fp32 sums (12.0 -> 10.8) and scans without flags (fp32 14.2 -> 11.9, bytes 12.2 -> 10.8, fp16 level) still do,
-// segmented scans (11.6 -> 11.9, bytes 10.8 -> 11.2) and sums of bytes do not.  Four elements per thread: level up to 2^19, 10 %
+// Two launches: up to 2^21 elements everything gains (segmented scan of bytes 9.9 -> 7.8).  Beyond, where the data read twice
+// shows, with the inputs of several calls in turn: scans without flags of 3.3 million and 2^22, fp32 13.5 -> 11.1 and 13.8 -> 13.0,
+// bytes 11.6 -> 9.3 and 11.7 -> 11.0, 16-bit 11.5 -> 10.1 and 11.9 -> 12.3; fp32 sums with 1 of 1000 set 10.8 -> 10.8 and 11.3 ->
+// 12.0, with 1 of 5 13.0 -> 11.9 and 13.3 -> 13.2: so 16-bit scans and fp32 sums up to 3 * 2^20, the other scans up to 2^22.
+// Segmented scans (2^22: 11.6 -> 11.9, bytes 10.8 -> 11.2) and sums of bytes stay at 2^21.  Four elements per thread: level up to 2^19, 10 %
 // slower at 2^21; sixteen: 20 % slower there.
 constexpr int kShortThreads = 256, kShortWaves = kShortThreads / 64;
 constexpr int kShortElems = 8;                                  // consecutive elements of a thread
@@ -39,7 +41,9 @@ constexpr uint32_t kShortTile = kShortThreads * kShortElems;
 #define MMV_SHORT_MAX (1u << 21)        // most elements that two launches take
 #endif
 constexpr uint64_t short_max(mmv_op op, mmv_dtype dt) {
-    return op == MMV_OP_SCAN || (op == MMV_OP_SEGSUM && dt == MMV_F32_F32) ? 2 * (uint64_t)MMV_SHORT_MAX : MMV_SHORT_MAX;
+    const uint64_t n = MMV_SHORT_MAX;
+    if (op == MMV_OP_SCAN) return dt == MMV_F16_F32 || dt == MMV_BF16_F32 ? n / 2 * 3 : 2 * n;
+    return op == MMV_OP_SEGSUM && dt == MMV_F32_F32 ? n / 2 * 3 : n;
 }
 
 enum ShortFlags { kNoFlags = 0, kBitFlags = 1, kByteFlags = 2 };

@@ -1,5 +1,5 @@
 """Scans and sums of short vectors: one launch (the sum carried into a tile comes from the input itself) up to 320 KB of
-values and flags, two (from the aggregates of the tiles before) up to 2^21 elements (mmv_scan and fp32 sums 2^22), the
+values and flags, two (from the aggregates of the tiles before) up to 2^21 elements (fp32 sums and 16-bit mmv_scan 3 * 2^20, other mmv_scan 2^22), the
 single-pass kernels beyond.  Tiles have 2048 elements, a thread takes eight, a wave 512; whole numbers, so results are exact."""
 import numpy as np
 import pytest
@@ -60,7 +60,7 @@ def test_edges_of_threads_waves_tiles_and_of_the_two_forms(dt, packed):
     rng = np.random.default_rng(2390700)
     line = one_launch(dt, 1 / 8 if packed else 1)
     sizes = [1, 2, 7, 8, 9, 31, 33, 511, 513, TILE - 1, TILE, TILE + 1, 5 * TILE + 511, line - 1, line, line + 1, line + TILE + 9,
-             (1 << 21) - 5, 1 << 21, (1 << 21) + 1, (1 << 22) - 3, 1 << 22, (1 << 22) + 1]
+             (1 << 21) - 5, 1 << 21, (1 << 21) + 1, 3 << 20, (3 << 20) + 1, (1 << 22) - 3, 1 << 22, (1 << 22) + 1]
     for n in sizes:
         for density in (0.0, 3 / n, 0.01, 1.0):
             f = ((rng.random(n) < density) * rng.integers(1, 256, size=n)).astype(np.uint8)
