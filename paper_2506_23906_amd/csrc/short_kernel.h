@@ -121,9 +121,10 @@ template <int kCtrl, int kRowMask, typename V> __device__ __forceinline__ V dpp_
     }
 }
 
-// Sum of the elements in one 128-bit word.
-template <typename TT> __device__ __forceinline__ typename TT::acc_t word_sum(const v4u &w) {
+// Sum of the elements in one 128-bit word (floats in 64 bits from the first addition on: neighbours may cancel, or overflow 32).
+template <typename TT> __device__ __forceinline__ typename Wide<typename TT::acc_t>::type word_sum(const v4u &w) {
     typedef typename TT::acc_t A;
+    typedef typename Wide<A>::type V;
     if constexpr (TT::kDtype == MMV_I8_I32) {
         int s = 0;
 #pragma unroll
@@ -135,9 +136,9 @@ template <typename TT> __device__ __forceinline__ typename TT::acc_t word_sum(co
         x ^= x >> 8;
         return A(x & 0xFFu);
     } else {
-        A s[2] = {raw_elem<TT>(w, 0), raw_elem<TT>(w, 1)};
+        V s[2] = {V(raw_elem<TT>(w, 0)), V(raw_elem<TT>(w, 1))};
 #pragma unroll
-        for (int i = 2; i < TT::kEpl; ++i) s[i & 1] += raw_elem<TT>(w, i);
+        for (int i = 2; i < TT::kEpl; ++i) s[i & 1] += V(raw_elem<TT>(w, i));
         return s[0] + s[1];
     }
 }
@@ -348,7 +349,7 @@ __global__ __launch_bounds__(kShortThreads) void short_kernel(ShortParams P) {
             if constexpr (!kFlagged && TT::kDtype == MMV_I8_I32) {
                 if (P.first_one && at == 0) w[0] = (w[0] & ~0xFFu) | 1u;
             }
-            part_v += V(word_sum<TT>(w));
+            part_v += word_sum<TT>(w);
         };
         add(near, near_at);   // (the words before the vector are not added: near_at < 0)
 #pragma unroll 4

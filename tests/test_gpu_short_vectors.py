@@ -190,3 +190,26 @@ def test_compress_in_one_launch(packed):
                 _, count = B.mmv_compress(src, flags_dev(m, packed), n, out=out[:cap], ws=ws)
                 assert B.mmv_workspace_status(ws) == 0 and int(count.item()) == len(want)
                 assert np.array_equal(out.cpu().numpy()[:cap], want[:cap]) and bool((out[cap:] == -7).all())
+
+
+@pytest.mark.parametrize("n", [30_003, 200_003])                       # one launch, two
+@pytest.mark.parametrize("dt,big,small", [("f32", 2.0 ** 40, 1.0), ("bf16", 2.0 ** 40, 1.0), ("f16", 2.0 ** 15, 2.0 ** -10), ("f32", 2e38, 0.0)])
+def test_sums_across_tiles_are_carried_in_64_bits(n, dt, big, small):
+    """big, small, -big, small over and over: in 64 bits every running sum is exact (sums of 2^40 and up to 10^5 ones, of 2^15
+    and 10^5 / 2^10; those of whole tiles, which two launches keep in 32 bits, are 1024 smalls), so results are the definition's
+    rounded once.  In 32 bits the smalls are lost beside big.  With 2e38 and nothing between, every running sum is 0 or 2e38,
+    while two of the same sign overflow 32 bits.  One segment, then one that begins inside a 128-bit word."""
+    x = np.tile(np.array([big, small, -big, small] if small else [big, -big, big, -big]), n // 4 + 1)[:n].astype(np.float32)
+    xt = dev(x).to(TYPES[dt][0])
+    x = xt.float().cpu().numpy()                                       # (as the type holds them)
+    for starts in ([], [4 * 777]):
+        f = np.zeros(n, dtype=np.uint8)
+        f[starts] = 1
+        want = oracle.segscan(x, f).astype(np.float32)
+        for packed in (True, False):
+            z = B.mmv_segscan(xt, flags_dev(f, packed), n=n)
+            assert np.array_equal(z.cpu().numpy(), want), (starts, packed)
+            out, nseg = B.mmv_segsum(xt, flags_dev(f, packed), n=n)
+            assert np.array_equal(out.cpu().numpy()[:int(nseg.item())], oracle.segsum(x, f).astype(np.float32)), (starts, packed)
+        if not starts:
+            assert np.array_equal(B.mmv_scan(xt, n=n).cpu().numpy(), want)
