@@ -123,7 +123,7 @@ size_t mmv_spmv_csr_workspace_bytes(uint64_t n_rows, uint64_t nnz);
  * paper's recursion passes) and the first-segment carry update.
  *   d_x      n input values of the type `dt` names
  *   d_flags  n flags in format `ff`
- *   d_z      n outputs (fp32 or int32); may alias d_x only for MMV_F32_F32
+ *   d_z      n outputs (fp32 or int32); may be d_x itself for MMV_F32_F32, and overlaps no input otherwise
  * Integers (and bytes under exclusive or) are exact: they form a group, as Sec. 2 requires.  Floats do not, and
  * the method subtracts two speculative prefixes of a row of 32 elements: a result is off by the rounding of that
  * row's prefix (about 32 * 2^-24 of the row's sum of |x|; the carries add one rounding per level), not by the
@@ -159,7 +159,7 @@ mmv_status mmv_segscan_static(const void *d_x, const void *d_flags, uint64_t n, 
 /* Segmented sum (Sec. 2): the last element of every segment of the segmented
  * scan, in segment order; equals Algorithm SCD (Sec. 4.1) with the compress
  * step fused (output index = number of segment ends before the element).
- *   d_out         room for `out_capacity` sums (fp32 or int32)
+ *   d_out         room for `out_capacity` sums (fp32 or int32); overlaps no input
  *   d_nseg        device uint64: receives the true number of segments,
  *                 1 + #{i >= 1 : f(i) = 1} for n >= 1
  * Floating point: as for mmv_segscan (a sum is off by the rounding of the prefixes of the rows of 32 it starts
@@ -253,8 +253,8 @@ mmv_status mmv_scan(const void *d_x, uint64_t n, void *d_z, mmv_dtype dt, mmv_va
  *   d_x      n 32-bit entries of any type, copied bit for bit; NULL = compress
  *            the positions 0 .. n-1 themselves (uint32)
  *   d_mask   n mask entries in format `ff` (position 0 has no special role here)
- *   d_out    room for `out_capacity` entries; entries with index >= out_capacity
- *            are not written
+ *   d_out    room for `out_capacity` entries, overlaps neither d_x nor d_mask; entries
+ *            with index >= out_capacity are not written
  *   d_count  device uint64: receives the number of selected entries, which
  *            must be below 2^32 */
 mmv_status mmv_compress(const void *d_x, const void *d_mask, uint64_t n,

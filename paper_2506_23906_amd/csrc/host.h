@@ -243,8 +243,9 @@ WsLayout ws_layout(mmv_op op, mmv_dtype dt, mmv_flag_fmt ff, uint64_t n) {
     L.packed = off;
     if (is_spmv(op) || (ff == MMV_FLAGS_U8 && op != MMV_OP_SCAN)) off += round256(((n + 63) / 64) * 8);
     L.total = off;
-    // The two launches of a short vector keep one aggregate per tile where the descriptors begin.  (Longer vectors get at least
-    // that much too, so that a workspace of a longer vector always does for a shorter one.)
+    // The two launches of a short vector keep one aggregate per tile where the descriptors begin; longer vectors get at least the
+    // room for those of a vector of short_max elements.  (The size does not grow with n throughout: where a vector stops
+    // fitting one round of workgroups it takes fewer, longer tiles, and fewer descriptors.)
     if (!is_spmv(op)) {
         const size_t aggregates = kHdrBytes + round256(short_tiles(n < short_max(op, dt) ? n : short_max(op, dt)) * 8);
         if (L.total < aggregates) L.total = aggregates;
@@ -445,16 +446,26 @@ inline uint64_t elem_bytes(mmv_dtype dt) { return dt == MMV_F32_F32 ? 4 : dt == 
 inline bool overlap(const void *a, uint64_t a_bytes, const void *b, uint64_t b_bytes) {
     return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
 }
+inline uint64_t flag_bytes(mmv_flag_fmt ff, uint64_t n) { return ff == MMV_FLAGS_U8 ? n : (n + 31) / 32 * 4; }
+
+// What a scan or sum takes: one launch of short_kernel, two, or the single-pass kernel (always beyond short_max).  In one launch
+// every workgroup reads what lies before its tile, so nothing of that may be written meanwhile; in two a workgroup
+// still loads the values and flags of its own tile (a sum also the flag behind it), so an output may lie over nothing but a
+// scan's own values, each thread's results over its own.  Any other overlap is left to the single-pass kernel, whose
+// launches pack byte flags before the first result is written.  (`flags`: nullptr where there are none.)
+enum ShortRoute { kSinglePass, kTwoLaunches, kOneLaunch };
+inline ShortRoute short_route(mmv_op op, mmv_dtype dt, mmv_flag_fmt ff, uint64_t n, const void *x, const void *flags, const void *out,
+                              uint64_t out_bytes) {
+    if (n > short_max(op, dt)) return kSinglePass;
+    const uint64_t xb = n * elem_bytes(dt), fb = flags ? flag_bytes(ff, n) : 0;
+    if (flags && overlap(out, out_bytes, flags, fb)) return kSinglePass;
+    if (overlap(out, out_bytes, x, xb)) return op != MMV_OP_SEGSUM && out == x ? kTwoLaunches : kSinglePass;
+    return xb + fb <= MMV_SINGLE_BYTES ? kOneLaunch : kTwoLaunches;
+}
 template <int kOp>
 mmv_status short_call(const void *d_x, const void *d_flags, uint64_t n, void *d_z, void *d_out, uint64_t out_cap, uint64_t *d_nseg,
-                      bool first_one, mmv_dtype dt, mmv_flag_fmt ff, const Params &P, hipStream_t s) {
+                      bool first_one, mmv_dtype dt, mmv_flag_fmt ff, const Params &P, bool single, hipStream_t s) {
     const ShortParams S = {d_x, d_flags, d_z, d_out, out_cap, d_nseg, P.hdr, P.desc_v, (uint32_t)n, first_one ? 1u : 0u};
-    // One launch: every workgroup reads what lies before its tile, so nothing of that may be written meanwhile.
-    const void *written = kOp == kSum ? d_out : d_z;
-    const uint64_t written_bytes = (kOp == kSum && out_cap < n ? out_cap : n) * 4;
-    const uint64_t value_bytes = n * elem_bytes(dt), flag_bytes = kOp == kPlainScan ? 0 : ff == MMV_FLAGS_U8 ? n : (n + 31) / 32 * 4;
-    const bool single = value_bytes + flag_bytes <= MMV_SINGLE_BYTES && !overlap(written, written_bytes, d_x, value_bytes) &&
-                        !overlap(written, written_bytes, d_flags, flag_bytes);
     hipError_t e = hipErrorInvalidValue;
     switch (dt) {
         case MMV_F32_F32: e = launch_short_flags<TF32, kOp>(S, ff, single, s); break;
@@ -480,9 +491,9 @@ bool valid_variant(int v) { return v == 0 || v == 1; }
 bool valid_elem(int et) { return et == 0 || et == 1; }
 constexpr uint64_t kMaxN = 1ull << 40;
 
-// Common part of scan and sum: checks, workspace reset, flag packing.
-mmv_status prepare(mmv_op op, const void *d_x, const void *d_flags, uint64_t n, mmv_dtype dt, mmv_flag_fmt ff,
-                   mmv_variant v, void *d_ws, size_t ws_bytes, hipStream_t s, Params &P) {
+// Common part of scan and sum: checks, which launches follow, workspace reset, flag packing.
+mmv_status prepare(mmv_op op, const void *d_x, const void *d_flags, uint64_t n, const void *d_out, uint64_t out_bytes, mmv_dtype dt,
+                   mmv_flag_fmt ff, mmv_variant v, void *d_ws, size_t ws_bytes, hipStream_t s, Params &P, ShortRoute &route) {
     if (!valid_dtype(dt) || !valid_ff(ff) || !valid_variant(v) || n > kMaxN) return MMV_ERR_INVALID_ARG;
     if (!d_x || !d_flags) return MMV_ERR_NULL;
     if (!aligned16(d_x) || !aligned16(d_flags)) return MMV_ERR_INVALID_ARG;
@@ -499,7 +510,8 @@ mmv_status prepare(mmv_op op, const void *d_x, const void *d_flags, uint64_t n, 
     // kernel; a short vector needs neither.
     uint32_t *packed = (uint32_t *)(ws + L.packed);
     P.fw = ff == MMV_FLAGS_U8 ? packed : (const uint32_t *)d_flags;
-    if (op == MMV_OP_SEGSUM || n <= short_max(op, dt)) return MMV_OK;
+    route = short_route(op, dt, ff, n, d_x, d_flags, d_out, out_bytes);
+    if (op == MMV_OP_SEGSUM || route != kSinglePass) return MMV_OK;
     const uint64_t zero_words = L.packed / 4;
     if (ff == MMV_FLAGS_U8) {
         const uint64_t nwords = (n + 31) / 32;
@@ -535,7 +547,9 @@ mmv_status scan_impl(const void *d_x, uint64_t n, void *d_z, mmv_dtype dt, mmv_v
     P.hdr = (uint32_t *)ws;
     P.desc_v = (uint64_t *)(ws + L.desc_v);
     P.first_one = first_one ? 1u : 0u;
-    if (n <= short_max(MMV_OP_SCAN, dt)) return short_call<kPlainScan>(d_x, nullptr, n, d_z, nullptr, 0, nullptr, first_one, dt, MMV_FLAGS_PACKED32, P, s);
+    const ShortRoute route = short_route(MMV_OP_SCAN, dt, MMV_FLAGS_PACKED32, n, d_x, nullptr, d_z, n * 4);
+    if (route != kSinglePass)
+        return short_call<kPlainScan>(d_x, nullptr, n, d_z, nullptr, 0, nullptr, first_one, dt, MMV_FLAGS_PACKED32, P, route == kOneLaunch, s);
     const uint64_t zero_words = L.total / 4;
     fill_zero_kernel<<<grid_for(zero_words), 256, 0, s>>>((uint32_t *)ws, zero_words, nullptr, 0);
     if (hipGetLastError() != hipSuccess) return MMV_ERR_HIP;
@@ -550,10 +564,11 @@ mmv_status compress_impl(const void *d_x, const void *d_mask, uint64_t n, void *
     if (((uintptr_t)d_ws & 255u) != 0 || ws_bytes < L.total) return MMV_ERR_WORKSPACE;
     if (L.tiles > 0x7fffffffull) return MMV_ERR_INVALID_ARG;
     char *ws = (char *)d_ws;
-    // one launch: every workgroup reads the mask before its tile, so nothing of that may be written meanwhile
-    const uint64_t mask_bytes = ff == MMV_FLAGS_U8 ? n : (n + 31) / 32 * 4;
+    // one launch: every workgroup reads the mask before its tile, and none waits for another, so an output over the mask
+    // or over x would be written before others have read there
+    const uint64_t out_bytes = (out_capacity < n ? out_capacity : n) * 4;
     const bool single = !ws_is_reset && compress_words(n) == 16 && n <= (ff == MMV_FLAGS_U8 ? kCompressSingleBytes : kCompressSingleBits) &&
-                        !overlap(d_out, (out_capacity < n ? out_capacity : n) * 4, d_mask, mask_bytes);
+                        !overlap(d_out, out_bytes, d_mask, flag_bytes(ff, n)) && !(d_x && overlap(d_out, out_bytes, d_x, n * 4));
     if (!ws_is_reset && !single) {
         const uint64_t zero_words = L.total / 4;
         fill_zero_kernel<<<grid_for(zero_words), 256, 0, s>>>((uint32_t *)ws, zero_words, nullptr, 0);

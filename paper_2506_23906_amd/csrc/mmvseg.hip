@@ -78,9 +78,10 @@ void *static_scratch() {
 mmv_status segscan_call(const void *d_x, const void *d_flags, uint64_t n, void *d_z, mmv_dtype dt, mmv_flag_fmt ff,
                         mmv_variant v, void *d_ws, size_t ws_bytes, hipStream_t s) {
     Params P = {};
-    const mmv_status st = prepare(MMV_OP_SEGSCAN, d_x, d_flags, n, dt, ff, v, d_ws, ws_bytes, s, P);
+    ShortRoute route;
+    const mmv_status st = prepare(MMV_OP_SEGSCAN, d_x, d_flags, n, d_z, n * 4, dt, ff, v, d_ws, ws_bytes, s, P, route);
     if (st != MMV_OK) return st;
-    if (n <= short_max(MMV_OP_SEGSCAN, dt)) return short_call<kScan>(d_x, d_flags, n, d_z, nullptr, 0, nullptr, false, dt, ff, P, s);
+    if (route != kSinglePass) return short_call<kScan>(d_x, d_flags, n, d_z, nullptr, 0, nullptr, false, dt, ff, P, route == kOneLaunch, s);
     P.z = d_z;
     return launch_dt<kScan>(P, dt, v, s) == hipSuccess ? MMV_OK : MMV_ERR_HIP;
 }
@@ -148,9 +149,11 @@ mmv_status mmv_segsum(const void *d_x, const void *d_flags, uint64_t n, void *d_
     if (!d_out && out_capacity > 0) return MMV_ERR_NULL;
     if (!aligned16(d_out) || ((uintptr_t)d_nseg & 7u)) return MMV_ERR_INVALID_ARG;
     Params P = {};
-    const mmv_status st = prepare(MMV_OP_SEGSUM, d_x, d_flags, n, dt, ff, v, d_ws, ws_bytes, s, P);
+    ShortRoute route;
+    const mmv_status st = prepare(MMV_OP_SEGSUM, d_x, d_flags, n, d_out, (out_capacity < n ? out_capacity : n) * 4, dt, ff, v, d_ws, ws_bytes, s, P, route);
     if (st != MMV_OK) return st;
-    if (n <= short_max(MMV_OP_SEGSUM, dt)) return short_call<kSum>(d_x, d_flags, n, nullptr, d_out, out_capacity, d_nseg, false, dt, ff, P, s);
+    if (route != kSinglePass)
+        return short_call<kSum>(d_x, d_flags, n, nullptr, d_out, out_capacity, d_nseg, false, dt, ff, P, route == kOneLaunch, s);
     P.out = d_out;
     P.out_cap = out_capacity;
     P.nseg = d_nseg;

@@ -213,3 +213,22 @@ def test_sums_across_tiles_are_carried_in_64_bits(n, dt, big, small):
             assert np.array_equal(out.cpu().numpy()[:int(nseg.item())], oracle.segsum(x, f).astype(np.float32)), (starts, packed)
         if not starts:
             assert np.array_equal(B.mmv_scan(xt, n=n).cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n", [300, 60_001, 200_003])
+def test_outputs_over_byte_flags(n):
+    """Byte flags are packed by a launch of their own before the first result is written, as for long vectors."""
+    rng = np.random.default_rng(2390707)
+    f = (rng.random(n) < 0.003).astype(np.uint8)
+    for dt in ("f32", "i8"):
+        x = values(rng, n, dt)
+        for shift in (0, 3 * n // 16 * 16):                            # the flags under the first results, under the last ones
+            room = torch.zeros(4 * n + 16, dtype=torch.uint8, device="cuda")
+            room[shift:shift + n] = dev(f)
+            z = room[:4 * n].view(torch.float32 if dt == "f32" else torch.int32)
+            B.mmv_segscan(dev(x), room[shift:shift + n], n=n, z=z)
+            assert np.array_equal(z.cpu().numpy().astype(np.float64), oracle.segscan(x, f).astype(np.float64))
+            room[shift:shift + n] = dev(f)
+            _, nseg = B.mmv_segsum(dev(x), room[shift:shift + n], n=n, out=z)
+            ref = oracle.segsum(x, f)
+            assert int(nseg.item()) == len(ref) and np.array_equal(z.cpu().numpy()[:len(ref)].astype(np.float64), ref.astype(np.float64))
