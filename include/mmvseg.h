@@ -323,7 +323,8 @@ mmv_status mmv_gather_reference(uint64_t nnz, const float *d_val, const int32_t 
  * mmv_spmv_coo call made by the calling host thread records `ev_start` (a
  * hipEvent_t passed as void*) on the call's stream immediately before its main
  * kernel and `ev_stop` immediately after it, so that the kernel can be timed
- * apart from the workspace reset.  The events stay owned by the caller.  Pass
+ * apart from the workspace reset (where a short vector takes two kernels that
+ * both read it, around the two).  The events stay owned by the caller.  Pass
  * NULL, NULL to switch it off (the default).  Per-thread setting. */
 mmv_status mmv_set_kernel_events(void *ev_start, void *ev_stop);
 

@@ -426,12 +426,13 @@ template <int kOp> hipError_t launch_dt(const Params &P, mmv_dtype dt, mmv_varia
 // Scans and sums of at most short_max elements on checked arguments (P: where things lie in the workspace).
 template <typename TT, int kOp, int kFlags> hipError_t launch_short(const ShortParams &S, bool single, hipStream_t s) {
     const unsigned tiles = (unsigned)short_tiles(S.n);
+    // (both launches read the inputs: the events stand around the two)
+    if (tl_ev_start && hipEventRecord(tl_ev_start, s) != hipSuccess) return hipErrorUnknown;
     if (!single) {
         short_reduce_kernel<TT, kFlags><<<tiles, kShortThreads, 0, s>>>(S);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (tl_ev_start && hipEventRecord(tl_ev_start, s) != hipSuccess) return hipErrorUnknown;
     if (single) short_kernel<TT, kOp, kFlags, true><<<tiles, kShortThreads, 0, s>>>(S);
     else short_kernel<TT, kOp, kFlags, false><<<tiles, kShortThreads, 0, s>>>(S);
     const hipError_t e = hipGetLastError();

@@ -93,3 +93,15 @@ PACK, FILL, COUNT = ["pack_flags_kernel", "seg_kernel"], ["fill_zero_kernel", "s
 ])
 def test_overlapping_outputs_take_the_launches_they_are_safe_in(record, call, want):
     assert record([call]) == [want]
+
+
+@pytest.mark.parametrize("call,want", [
+    (segscan(30_000, F32, BYTES, OUT), ["event 5", *ONE, "event 7"]), (segscan(300_000, F32, BITS, OUT), ["event 5", *TWO, "event 7"]),
+    (segsum(300_000, I8, BYTES, OUT), ["event 5", *TWO, "event 7"]), (scan(300_000, F16, OUT), ["event 5", *TWO, "event 7"]),
+    (segscan(3_000_000, F32, BYTES, OUT), [PACK[0], "event 5", PACK[1], "event 7"]),
+    (segsum(3_000_000, I8, BITS, OUT), [COUNT, "event 5", "seg_kernel", "event 7"]),
+    (compress(30_000, BITS, OUT), ["event 5", "compress_kernel", "event 7"]),
+])
+def test_kernel_events_stand_around_all_that_reads_the_inputs(record, call, want):
+    """... and behind what only resets the workspace, packs or counts flags."""
+    assert record(["lib.mmv_set_kernel_events(vp(5), vp(7))", call])[1] == want
