@@ -87,9 +87,11 @@ typedef enum {
  * of BlockSegScan in the block-recursive algorithm) are computed. */
 typedef enum {
     MMV_VARIANT_MFMA = 0,   /* matrix cores: tile times triangular ones matrix, s = 32 */
-    MMV_VARIANT_SHUFFLE = 1, /* ablation: same rows scanned with vector adds and lane shuffles.  Scans and sums of up
-                                to 2^21 elements (mmv_scan and fp32 sums: 3 * 2^20 or more) take the same kernels with either:
-                                they are bound by launches, and a product would only add its latency */
+    MMV_VARIANT_SHUFFLE = 1, /* ablation: same rows scanned with vector adds and lane shuffles.  Short vectors take the
+                                same kernels with either: they are bound by launches, and a product would only add its
+                                latency.  Short are scans and sums of up to 2^21 elements (16-bit mmv_segscan: 3 * 2^19, fp32
+                                sums and 16-bit mmv_scan: 3 * 2^20, other mmv_scan: 2^22) whose output overlaps no input
+                                (a scan's fp32 values may be its output) */
     MMV_VARIANT_INT_MAX = 0x7fffffff
 } mmv_variant;
 
@@ -128,11 +130,13 @@ size_t mmv_spmv_csr_workspace_bytes(uint64_t n_rows, uint64_t nnz);
  * the method subtracts two speculative prefixes of a row of 32 elements: a result is off by the rounding of that
  * row's prefix (about 32 * 2^-24 of the row's sum of |x|; the carries add one rounding per level), not by the
  * rounding of its own segment alone, so a segment of small values behind large ones in the same row of 32
- * loses relative accuracy.  (Vectors of up to 2^21 elements are scanned without speculation: there a result depends on
- * its own segment alone, floats are added up in 64 bits and rounded at the end.)  With fp32 inputs a position that starts a segment receives its input bit for bit.
+ * loses relative accuracy.  (Short vectors, see MMV_VARIANT_SHUFFLE, are scanned without speculation: there a result depends on
+ * its own segment alone, and floats are added up in 64 bits and rounded at the end; beyond 320 KB of values and flags the sums of whole
+ * tiles of 2048 elements are rounded to 32 bits on the way, beyond 256 KB with 16-bit values.)
+ * With fp32 inputs a position that starts a segment receives its input bit for bit.
  * An infinity or NaN makes the rest of its own segment non-finite, as the definition does, and can in addition turn
  * other positions of the same row of 32 and the segments that begin behind it in that row into NaN (Inf - Inf; not in
- * vectors of up to 2^21 elements);
+ * short vectors);
  * positions outside that row are not affected unless one of these segments reaches them.  A block of 2048 positions that all start segments is copied exactly. */
 mmv_status mmv_segscan(const void *d_x, const void *d_flags, uint64_t n, void *d_z,
                        mmv_dtype dt, mmv_flag_fmt ff, mmv_variant v,
@@ -163,8 +167,8 @@ mmv_status mmv_segscan_static(const void *d_x, const void *d_flags, uint64_t n, 
  *   d_nseg        device uint64: receives the true number of segments,
  *                 1 + #{i >= 1 : f(i) = 1} for n >= 1
  * Floating point: as for mmv_segscan (a sum is off by the rounding of the prefixes of the rows of 32 it starts
- * and ends in; a non-finite value can reach the sums of the segments that share its row of 32; neither in vectors of
- * up to 2^21 elements, fp32 3 * 2^20).  16-bit inputs
+ * and ends in; a non-finite value can reach the sums of the segments that share its row of 32; neither in short
+ * vectors).  16-bit inputs
  * on vectors longer than one round of workgroups (either variant) speculate over chunks of 2048 elements
  * (2048-aligned): there a sum is the difference of two prefixes of its chunk and is off by their rounding
  * (2^-24 of the chunk's running sum each), and a non-finite value reaches the other sums of its chunk.
@@ -336,8 +340,8 @@ const char *mmv_status_string(mmv_status s);
  * per tile (the segmented sum 4 more bytes of counts per tile, for 8- and 16-bit inputs 36).  The value is that
  * of the matrix-core variant (the other one differs for fp32 sums and for bytes under exclusive or).
  * The segmented sum has longer tiles than the scan; mmv_scan of 16- and
- * 32-bit inputs has longer tiles than mmv_segscan.  Scans and sums of up to 2^21 elements (3 * 2^20: fp32
- * sums and mmv_scan of 16-bit inputs, 2^22: other mmv_scan) have tiles of 2048 and need no descriptors; one 8-byte sum per tile takes their place.
+ * 32-bit inputs has longer tiles than mmv_segscan.  Short vectors (see MMV_VARIANT_SHUFFLE) have tiles of 2048 and need
+ * no descriptors; one 8-byte sum per tile takes their place.
  * 0 for invalid arguments. */
 uint32_t mmv_tile_elems(mmv_op op, mmv_dtype dt, uint64_t n);
 

@@ -43,6 +43,12 @@ __device__ __forceinline__ uint32_t bits_of_16_bytes(v4u w) {
     }
     return bits;
 }
+// How many of 16 bytes are not zero.
+__device__ __forceinline__ uint32_t nonzero_of_16_bytes(v4u w) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) w[d] = (((w[d] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w[d]) & 0x80808080u;
+    return __popc((w[0] >> 3) | (w[1] >> 2) | (w[2] >> 1) | w[3]);
+}
 __device__ __forceinline__ uint32_t bits_of_32_bytes(const uint8_t *f, uint64_t e0, uint64_t n) {   // flags e0 .. e0 + 31; 0 beyond n
     const bool full = e0 + 32 <= n;
     const v4u a = load128<uint8_t, false>(f, e0, n, full), b = load128<uint8_t, false>(f, e0 + 16, n, full);

@@ -423,6 +423,9 @@ template <int kOp> hipError_t launch_dt(const Params &P, mmv_dtype dt, mmv_varia
     return hipErrorInvalidValue;
 }
 
+inline uint64_t elem_bytes(mmv_dtype dt) { return dt == MMV_F32_F32 ? 4 : dt == MMV_F16_F32 || dt == MMV_BF16_F32 ? 2 : 1; }
+inline uint64_t flag_bytes(mmv_flag_fmt ff, uint64_t n) { return ff == MMV_FLAGS_U8 ? n : (n + 31) / 32 * 4; }
+
 // Scans and sums of at most short_max elements on checked arguments (P: where things lie in the workspace).
 template <typename TT, int kOp, int kFlags> hipError_t launch_short(const ShortParams &S, bool single, hipStream_t s) {
     const unsigned tiles = (unsigned)short_tiles(S.n);
@@ -433,8 +436,10 @@ template <typename TT, int kOp, int kFlags> hipError_t launch_short(const ShortP
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (single) short_kernel<TT, kOp, kFlags, true><<<tiles, kShortThreads, 0, s>>>(S);
-    else short_kernel<TT, kOp, kFlags, false><<<tiles, kShortThreads, 0, s>>>(S);
+    const uint64_t bytes = S.n * elem_bytes(TT::kDtype) + (kFlags == kNoFlags ? 0 : flag_bytes(kFlags == kByteFlags ? MMV_FLAGS_U8 : MMV_FLAGS_PACKED32, S.n));
+    if (!single) short_kernel<TT, kOp, kFlags, false, kShortThreads><<<tiles, kShortThreads, 0, s>>>(S);
+    else if (bytes < many_bytes(kFlags != kNoFlags)) short_kernel<TT, kOp, kFlags, true, kShortThreads><<<tiles, kShortThreads, 0, s>>>(S);
+    else short_kernel<TT, kOp, kFlags, true, kManyThreads><<<tiles, kManyThreads, 0, s>>>(S);
     const hipError_t e = hipGetLastError();
     if (tl_ev_stop && hipEventRecord(tl_ev_stop, s) != hipSuccess) return hipErrorUnknown;
     return e;
@@ -443,11 +448,9 @@ template <typename TT, int kOp> hipError_t launch_short_flags(const ShortParams 
     if constexpr (kOp == kPlainScan) return launch_short<TT, kOp, kNoFlags>(S, single, s);
     else return ff == MMV_FLAGS_U8 ? launch_short<TT, kOp, kByteFlags>(S, single, s) : launch_short<TT, kOp, kBitFlags>(S, single, s);
 }
-inline uint64_t elem_bytes(mmv_dtype dt) { return dt == MMV_F32_F32 ? 4 : dt == MMV_F16_F32 || dt == MMV_BF16_F32 ? 2 : 1; }
 inline bool overlap(const void *a, uint64_t a_bytes, const void *b, uint64_t b_bytes) {
     return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
 }
-inline uint64_t flag_bytes(mmv_flag_fmt ff, uint64_t n) { return ff == MMV_FLAGS_U8 ? n : (n + 31) / 32 * 4; }
 
 // What a scan or sum takes: one launch of short_kernel, two, or the single-pass kernel (always beyond short_max).  In one launch
 // every workgroup reads what lies before its tile, so nothing of that may be written meanwhile; in two a workgroup
@@ -461,7 +464,7 @@ inline ShortRoute short_route(mmv_op op, mmv_dtype dt, mmv_flag_fmt ff, uint64_t
     const uint64_t xb = n * elem_bytes(dt), fb = flags ? flag_bytes(ff, n) : 0;
     if (flags && overlap(out, out_bytes, flags, fb)) return kSinglePass;
     if (overlap(out, out_bytes, x, xb)) return op != MMV_OP_SEGSUM && out == x ? kTwoLaunches : kSinglePass;
-    return xb + fb <= MMV_SINGLE_BYTES ? kOneLaunch : kTwoLaunches;
+    return xb + fb <= single_bytes(dt, flags != nullptr) ? kOneLaunch : kTwoLaunches;
 }
 template <int kOp>
 mmv_status short_call(const void *d_x, const void *d_flags, uint64_t n, void *d_z, void *d_out, uint64_t out_cap, uint64_t *d_nseg,

@@ -55,9 +55,10 @@ __global__ __launch_bounds__(256) void unpack_flags_kernel(const uint32_t *fw, u
 // and 0.1 % selected (now 0.048 ms).
 // The workgroups that are resident from the start take the tile of their own index, as in the main kernel.
 // kSingle: short masks.  Every workgroup counts the set bits before its tile itself, so nothing has to be zeroed and nobody
-// waits: one launch instead of two.  Whole calls, 30 % selected: 3000 positions 7.6 -> 5.3 us, 2^18 bits 7.8 -> 5.4, 2^20 bits 8.3 ->
-// 5.7, 2^21 bits 9.4 -> 6.9, 2^17 bytes 7.6 -> 6.4.  Beyond, the count takes longer than the launch (2^22 bits 11.6 -> 12.2, 2^18 bytes
-// 8.2 -> 8.2, 2^19 8.2 -> 12.3: sixteen flag bytes take twenty instructions, and a workgroup reads some 150 GB/s).
+// waits: one launch instead of two.  Whole calls in a graph, 30 % selected, other inputs every time (the same, in brackets): 3000
+// positions 4.6 -> 3.2 us (4.7 -> 3.2), 2^18 bits 6.9 -> 4.7 (6.3 -> 4.0), 2^20 bits 8.3 -> 6.0 (7.8 -> 4.7), 2^21 bits 9.6 -> 7.8 (8.1 -> 5.8),
+// 2^16 bytes 6.7 -> 5.9 (6.3 -> 4.6), 2^17 bytes 7.1 -> 6.8 (6.5 -> 5.3; with the loads of the count in a loop of their own latency
+// each, and the bytes turned into bits ahead of it, 8.5 and 5.9).  Beyond, the count takes longer than the launch.
 constexpr int kCompressWaves = 8;
 constexpr uint64_t kCompressSingleBits = 1ull << 21, kCompressSingleBytes = 1ull << 17;   // positions
 constexpr uint64_t kCompressShortN = 1ull << 22;   // masks up to this length take 16 words per wave
@@ -102,11 +103,18 @@ __global__ __launch_bounds__(kCompressWaves * 64, 8) void compress_kernel(
     uint32_t wave_cnt = 0;
     if constexpr (kSingle) {   // set bits before the tile (which begins at a multiple of 128 positions)
         const uint64_t start = (uint64_t)tile * kCompressWaves * kSpan;
+        // four words under way at a time, also of the last ones (a lane with nothing left reads its first word again)
+        const uint32_t words = (uint32_t)(start / (kBytes ? 16 : 128));
         uint32_t cnt = 0;
-#pragma unroll 4
-        for (uint32_t i = tid; i < (uint32_t)(start / (kBytes ? 16 : 128)); i += kCompressWaves * 64) {
-            const v4u w = ((const v4u *)mask)[i];
-            cnt += kBytes ? __popc(bits_of_16_bytes(w)) : (__popc(w[0]) + __popc(w[1])) + (__popc(w[2]) + __popc(w[3]));
+        for (uint32_t i0 = tid; i0 < words; i0 += 4 * kCompressWaves * 64) {
+            v4u w[4];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) w[j] = ((const v4u *)mask)[i0 + j * kCompressWaves * 64 < words ? i0 + j * kCompressWaves * 64 : i0];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                const uint32_t c = kBytes ? nonzero_of_16_bytes(w[j]) : (__popc(w[j][0]) + __popc(w[j][1])) + (__popc(w[j][2]) + __popc(w[j][3]));
+                cnt += i0 + j * kCompressWaves * 64 < words ? c : 0u;
+            }
         }
         cnt = wave_sum(cnt);
         if (lane == 0) s_before[wave] = cnt;

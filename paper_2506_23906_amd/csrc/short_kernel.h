@@ -16,33 +16,47 @@ namespace {
 // The segmented pair is carried from element to element inside a thread and from lane to lane by DPP moves: no speculation,
 // so both variants of a call take the same kernels (a 32x32 product and its way through LDS would only add latency), and a
 // result depends on its own segment alone.
-// Measured, whole calls one after the other, before -> one launch / two (us; before: two launches, or one up to 16384
-// elements of a scan with packed flags or none):
-//   segmented scan, fp32, byte flags, 1 of 64 set    3000: 8.1 -> 4.4 / 6.5    65536: 8.8 -> 4.4 / 6.3    2^20: 10.0 -> - / 6.6
-//   ... no flags, packed                             3000: 5.9 -> 4.2 / 6.3    65536: 7.8 -> 6.2 / 6.5    2^21: 10.8 -> - / 8.2
-//   segmented sum, fp16, packed, 1 of 1024 set       3000: 7.3 -> 4.7 / 6.9    131072: 8.0 -> 4.7 / 6.9   2^21: 8.2 -> - / 7.7
-//   scan, fp32                                       3000: 7.3 -> 4.0 / 6.3    65536: 10.0 -> 4.7 / 6.1   2^22: 14.2 -> - / 11.9
-// Where the lines lie.  One launch: a workgroup alone reads its L2 at some 150 GB/s, so with the whole input before the last
-// tile to be read (a vector without flags) one launch takes as long as two from about 320 KB of values and flags on (fp32
-// values: 65536 6.2 against 6.5 us, 131072 9.9 against 6.5; with flags every hundred elements one launch takes 4.3 there).
-// Two launches: up to 2^21 elements everything gains (segmented scan of bytes 9.9 -> 7.8).  Beyond, where the data read twice
-// shows, with the inputs of several calls in turn: scans without flags of 3.3 million and 2^22, fp32 13.5 -> 11.1 and 13.8 -> 13.0,
-// bytes 11.6 -> 9.3 and 11.7 -> 11.0, 16-bit 11.5 -> 10.1 and 11.9 -> 12.3; fp32 sums with 1 of 1000 set 10.8 -> 10.8 and 11.3 ->
-// 12.0, with 1 of 5 13.0 -> 11.9 and 13.3 -> 13.2: so 16-bit scans and fp32 sums up to 3 * 2^20, the other scans up to 2^22.
-// Segmented scans (2^22: 11.6 -> 11.9, bytes 10.8 -> 11.2) and sums of bytes stay at 2^21.  Four elements per thread: level up to 2^19, 10 %
-// slower at 2^21; sixteen: 20 % slower there.
+// Measured, whole calls in a graph, on other inputs every time (together beyond every cache) and, in brackets, on the same, the
+// single-pass kernel -> one launch / two (us):
+//   segmented scan, fp32, byte flags, 1 of 64 set    3000: 8.5 -> 3.2 / 5.2 (7.7 -> 2.9 / 5.0)   65536: 9.3 -> 4.3 / 5.6 (9.2 -> 3.7 / 5.2)
+//   ... no flags, packed                             3000: 6.3 -> 3.6 / 5.2 (5.8 -> 3.0 / 4.7)   65536: 8.3 -> 6.6 / 5.4 (7.9 -> 5.5 / 5.0)
+//   segmented sum, fp16, packed, 1 of 1000 set       3000: 6.4 -> 3.1 / 4.9 (6.1 -> 3.0 / 4.8)  105000: 8.0 -> 4.3 / 6.0 (7.0 -> 3.8 / 5.3)
+//   scan, fp32                                       3000: 7.7 -> 2.8 / 4.2 (7.2 -> 2.4 / 3.9)   65536: 10.4 -> 5.2 / 4.5 (10.0 -> 4.3 / 4.2)
+// Where the lines lie (figures on other inputs every time unless said otherwise).
+// One launch, MMV_SINGLE_BYTES: with flags anywhere near it is ahead of two (65536 fp32 values, 1 of 1000 set: 4.2 / 5.4); without any
+// flag set a workgroup reads all that lies before its tile, and two are ahead from 20000 to 80000 elements on.  The host does
+// not know the flags: the line lies where the worst of them is not slower than the single-pass kernel (none set, single-pass -> one
+// launch: fp32 sum, byte flags, 65536 8.1 -> 7.1; bytes, 160000 8.4 -> 7.0; fp16, packed, 105000 8.0 -> 7.3).  16-bit values take as
+// many conversions as 32-bit ones in half the bytes: 145000 in a sum, repeated, 7.1 -> 7.6, so their line is lower where there are flags.
+// Two launches, short_max: up to 2^21 elements nearly everything gains (350000 to 1.5 million fp32 11 -> 6.5 to 9, segmented scan of bytes, 2^21
+// 11.2 -> 9.0); 16-bit segmented scans, 1 of 100 set, 1.5 million 9.6 -> 9.1, 2^21 9.5 -> 10.2: up to 3 * 2^19.  Beyond, where
+// the data read twice show: scans without flags of 2^22, fp32 15.0 -> 14.3, bytes 12.1 -> 12.2, 16-bit, 3 * 2^20 12.1 -> 11.0 (2^22 11.9 -> 12.3);
+// fp32 sums, 3 * 2^20, 1 of 1000 set 11.9 -> 11.5, 1 of 5 12.4 -> 12.4 (2^22 11.3 -> 12.0).  Segmented scans (2^22: 11.6 -> 11.9, bytes
+// 10.8 -> 11.2) and sums of bytes stay at 2^21.  Four elements per thread: level up to 2^19, 10 % slower at 2^21; sixteen: 20 % slower there.
 constexpr int kShortThreads = 256, kShortWaves = kShortThreads / 64;
 constexpr int kShortElems = 8;                                  // consecutive elements of a thread
 constexpr uint32_t kShortTile = kShortThreads * kShortElems;
+// Threads of a workgroup of the one launch from so many bytes of values and flags on: those beyond kShortThreads only help with what
+// lies before the tile.  Calls as above, on other inputs every time, the single-pass kernel / 256 threads / 1024:
+//   segmented scan, fp32, byte flags, 65536: none set 8.8 / 10.0 / 6.8, 1 of 64 9.3 / 5.8 / 4.3;  bits, none set 8.3 / 7.9 / 6.6
+//   segmented sum, byte flags, none set: fp32, 65536 8.1 / 10.3 / 7.1; fp16, 105000 8.3 / 11.8 / 7.7; bytes, 160000 8.4 / 12.1 / 7.0
+//   scan, fp32, 65536 10.4 / 5.9 / 5.2;  20000 11.4 / 4.4 / 3.9
+// With 256 a vector whose segments reach far back took up to 45 % longer than the single-pass kernel.  Below the lines sixteen waves
+// cost more than they bring (sums of 3000 values 3.0 / 3.3 with the inputs in the L2, fp16 with byte flags, 20000 3.8 / 4.5).
+constexpr int kManyThreads = 1024;
+constexpr uint64_t many_bytes(bool flags) { return (flags ? 64u : 16u) << 10; }
 #ifndef MMV_SINGLE_BYTES
 #define MMV_SINGLE_BYTES (320u << 10)   // most values and flags, in bytes, of a vector that one launch takes
 #endif
+constexpr bool is_16_bit(mmv_dtype dt) { return dt == MMV_F16_F32 || dt == MMV_BF16_F32; }
+constexpr uint64_t single_bytes(mmv_dtype dt, bool flags) { return flags && is_16_bit(dt) ? MMV_SINGLE_BYTES / 5 * 4 : MMV_SINGLE_BYTES; }
 #ifndef MMV_SHORT_MAX
 #define MMV_SHORT_MAX (1u << 21)        // most elements that two launches take
 #endif
 constexpr uint64_t short_max(mmv_op op, mmv_dtype dt) {
     const uint64_t n = MMV_SHORT_MAX;
-    if (op == MMV_OP_SCAN) return dt == MMV_F16_F32 || dt == MMV_BF16_F32 ? n / 2 * 3 : 2 * n;
+    if (op == MMV_OP_SCAN) return is_16_bit(dt) ? n / 2 * 3 : 2 * n;
+    if (op == MMV_OP_SEGSCAN) return is_16_bit(dt) ? n / 4 * 3 : n;
     return op == MMV_OP_SEGSUM && dt == MMV_F32_F32 ? n / 2 * 3 : n;
 }
 
@@ -104,7 +118,8 @@ template <int kFlags> __device__ __forceinline__ uint32_t short_flags(const void
 
 // Sums are carried in 64 bits where the results are floats and rounded once, at the end: a vector this short pays nothing for
 // it, and the error is that of the last rounding (segmented scan of 65536 values, 1 of 64 a start: 3.0e-8 against 6.5e-8 of the
-// row scans in 32 bits; in 32 bits the lanes' scans here would come to 8.1e-8).  The aggregates of the tiles are kept in 32.
+// row scans in 32 bits; in 32 bits the lanes' scans here would come to 8.1e-8).  Between two launches the sums of whole tiles are kept
+// in 32: a result there is off by the rounding of the tile sums of its segment as well.
 template <typename A> struct Wide {
     typedef A type;
 };
@@ -175,6 +190,16 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+template <typename V> __device__ __forceinline__ V wave_last(V v) {   // lane 63's
+    if constexpr (sizeof(V) == 8) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        const uint64_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
+        return __builtin_bit_cast(V, (hi << 32) | lo);
+    } else {
+        return from_bits<V>((uint32_t)__builtin_amdgcn_readlane((int)to_bits(v), 63));
+    }
+}
+
 // What a thread knows of its own elements.
 template <typename TT> struct ShortOwn {
     typedef typename TT::acc_t A;
@@ -237,50 +262,75 @@ template <typename TT, int kFlags> __global__ __launch_bounds__(kShortThreads) v
 }
 
 // The only launch (kSingle), or the second of two.
-template <typename TT, int kOp, int kFlags, bool kSingle>
-__global__ __launch_bounds__(kShortThreads) void short_kernel(ShortParams P) {
+template <typename TT, int kOp, int kFlags, bool kSingle, int kThreads>
+__global__ __launch_bounds__(kThreads) void short_kernel(ShortParams P) {
     typedef typename TT::acc_t A;
     typedef typename Wide<A>::type V;
     constexpr bool kFlagged = kFlags != kNoFlags;
     constexpr uint32_t kEpl = TT::kEpl;
-    __shared__ V s_v[kShortWaves], s_pv[kShortWaves];            // of the waves: their aggregates, their part of what lies before the tile
-    __shared__ uint32_t s_c[kShortWaves], s_pc[kShortWaves], s_pl[kShortWaves];
+    constexpr int kWaves = kThreads / 64;
+    constexpr bool kMany = kThreads > kShortThreads;
+    constexpr int kUnder = kMany ? 8 : 4;   // words of values under way at a time
+    static_assert(kSingle || !kMany, "threads that only help with what lies before the tile");
+    __shared__ V s_v[kShortWaves], s_pv[kWaves];                 // of the waves: their aggregates, their part of what lies before the tile
+    __shared__ uint32_t s_c[kShortWaves], s_pc[kWaves], s_pl[kWaves];
     const uint32_t tid = threadIdx.x, lane = tid & 63, tile = blockIdx.x;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const uint32_t n = P.n, start = tile * kShortTile, e0 = start + kShortElems * tid;
+    const bool owner = !kMany || wave < (uint32_t)kShortWaves;   // (uniform) whether my wave has elements of the tile
 
-    const uint32_t flags = short_flags<kFlags>(P.flags, e0, n);
-    uint32_t next = 0;      // whether the element behind mine starts a segment
-    if constexpr (kOp == kSum) next = short_flags<kFlags>(P.flags, e0 + kShortElems, n) & 1u;
+    uint32_t flags = 0, next = 0;      // next: whether the element behind mine starts a segment
     ShortRaw<TT> raw;
-    raw.load(P.x, e0, n);
+    if (owner) {
+        flags = short_flags<kFlags>(P.flags, e0, n);
+        if constexpr (kOp == kSum) next = short_flags<kFlags>(P.flags, e0 + kShortElems, n) & 1u;
+        raw.load(P.x, e0, n);
+    }
 
     // ---- what lies before the tile, first part ----
     V part_v = V(0);
-    uint32_t part_c = 0, last = 0;   // number of starts, the last of them
+    uint32_t part_c = 0, last = 0;   // number of starts (sums), the last of them
     v4u near = {0, 0, 0, 0};         // (kSingle) my 128-bit word of the values that lie right before the tile
-    const int32_t near_at = (int32_t)(start / kEpl) - 1 - (int32_t)tid;
+    const uint32_t words = start / kEpl;
+    const int32_t near_at = (int32_t)words - 1 - (int32_t)tid;
     if constexpr (kSingle) {
         if (near_at >= 0) near = ((const v4u *)P.x)[near_at];
-        if constexpr (kFlags == kBitFlags) {
-#pragma unroll 4
-            for (uint32_t i = tid; i < start / 128; i += kShortThreads) {
-                v4u f = ((const v4u *)P.flags)[i];
-                if (i == 0) f[0] &= ~1u;
+        if constexpr (kFlagged) {
+            // the last 128-bit word with a start, its starts, and how many there are
+            constexpr uint32_t kPerWord = kFlags == kBitFlags ? 128 : 16;
+            const uint32_t flag_words = start / kPerWord;
+            v4u hit = {0, 0, 0, 0};
+            uint32_t hit_at = 0;
+            auto take = [&](v4u f, uint32_t i, bool valid) {   // (selects, no branches: what is loaded in a branch is waited for there)
+                if (i == 0) f[0] &= kFlags == kBitFlags ? ~1u : ~0xFFu;
+                if constexpr (kFlags == kByteFlags) {
 #pragma unroll
-                for (uint32_t d = 0; d < 4; ++d) {
-                    part_c += __popc(f[d]);
-                    if (f[d]) last = 128 * i + 32 * d + 31 - __clz((int)f[d]);
+                    for (int d = 0; d < 4; ++d) f[d] = (((f[d] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | f[d]) & 0x80808080u;   // the bytes that are not zero
                 }
-            }
-        } else if constexpr (kFlags == kByteFlags) {
+                if constexpr (kOp == kSum) {
+                    const uint32_t cnt = kFlags == kByteFlags ? __popc((f[0] >> 3) | (f[1] >> 2) | (f[2] >> 1) | f[3])
+                                                              : (__popc(f[0]) + __popc(f[1])) + (__popc(f[2]) + __popc(f[3]));
+                    part_c += valid ? cnt : 0u;
+                }
+                const bool any = valid && ((f[0] | f[1]) | (f[2] | f[3])) != 0;
+                hit_at = any ? i : hit_at;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) hit[d] = any ? f[d] : hit[d];
+            };
+            if constexpr (kMany) {   // four words under way, also of the last ones
+                for (uint32_t i = tid; i < flag_words; i += 4 * kThreads) {
+                    v4u f[4];
+#pragma unroll
+                    for (uint32_t j = 0; j < 4; ++j) f[j] = ((const v4u *)P.flags)[i + j * kThreads < flag_words ? i + j * kThreads : i];
+#pragma unroll
+                    for (uint32_t j = 0; j < 4; ++j) take(f[j], i + j * kThreads, i + j * kThreads < flag_words);
+                }
+            } else {
 #pragma unroll 4
-            for (uint32_t i = tid; i < start / 16; i += kShortThreads) {
-                uint32_t f = bits_of_16_bytes(((const v4u *)P.flags)[i]);
-                if (i == 0) f &= ~1u;
-                part_c += __popc(f);
-                if (f) last = 16 * i + 31 - __clz((int)f);
+                for (uint32_t i = tid; i < flag_words; i += kThreads) take(((const v4u *)P.flags)[i], i, true);
             }
+            const uint32_t d = hit[3] ? 3 : hit[2] ? 2 : hit[1] ? 1 : 0, bits = hit[3] ? hit[3] : hit[2] ? hit[2] : hit[1] ? hit[1] : hit[0];
+            if (bits) last = kPerWord * hit_at + kPerWord / 4 * d + (31 - __clz((int)bits)) / (kFlags == kBitFlags ? 1 : 8);
         }
     } else {
         // the aggregates of the tiles before, a run of them per thread
@@ -297,10 +347,12 @@ __global__ __launch_bounds__(kShortThreads) void short_kernel(ShortParams P) {
     }
 
     ShortOwn<TT> own;
-    own.template scan<kFlags>(raw, flags, e0, n, P.first_one);
-    if (lane == 63) {
-        s_v[wave] = own.tot_v;
-        s_c[wave] = own.tot_c;
+    if (owner) {
+        own.template scan<kFlags>(raw, flags, e0, n, P.first_one);
+        if (lane == 63) {
+            s_v[wave] = own.tot_v;
+            s_c[wave] = own.tot_c;
+        }
     }
     if constexpr (!kSingle) {
         wave_segmented_scan<kFlagged>(part_v, part_c);
@@ -309,7 +361,7 @@ __global__ __launch_bounds__(kShortThreads) void short_kernel(ShortParams P) {
             s_pc[wave] = part_c;
         }
     } else if constexpr (kFlagged) {
-        part_c = wave_sum(part_c);
+        if (kOp == kSum) part_c = wave_sum(part_c);
         last = wave_max(last);
         if (lane == 0) {
             s_pc[wave] = part_c;
@@ -331,35 +383,47 @@ __global__ __launch_bounds__(kShortThreads) void short_kernel(ShortParams P) {
     } else {
         uint32_t from = 0;   // where the segment begins that reaches into the tile
         if constexpr (kFlagged) {
+            if constexpr (kMany) {
+                if (kOp == kSum) starts = wave_sum(lane < kWaves ? s_pc[lane] : 0u);
+                from = wave_max(lane < kWaves ? s_pl[lane] : 0u);
+            } else {
 #pragma unroll
-            for (int w = 0; w < kShortWaves; ++w) {
-                starts += s_pc[w];
-                from = from > s_pl[w] ? from : s_pl[w];
+                for (int w = 0; w < kWaves; ++w) {
+                    if (kOp == kSum) starts += s_pc[w];
+                    from = from > s_pl[w] ? from : s_pl[w];
+                }
             }
         }
-        // the words that hold elements from .. start - 1, the nearest ones (there already) first
+        // the words that hold elements from .. start - 1: the nearest are there already; the first may hold elements before `from`
         const int32_t first_word = (int32_t)(from / kEpl);
-        auto add = [&](v4u w, int32_t at) {
-            if (at < first_word) return;
-            if (at == first_word) {   // elements before `from` do not count
-                const uint32_t skip = (from % kEpl) * (uint32_t)sizeof(typename TT::in_t);   // bytes
+        const bool far = first_word < (int32_t)words - kThreads;      // (nobody holds the first word yet)
+        v4u w0 = near;
+        if (far && tid == 0) w0 = ((const v4u *)P.x)[first_word];
+        if (near_at > first_word) part_v = word_sum<TT>(near);        // (near_at < 0: none)
+#pragma unroll kUnder
+        for (int32_t at = near_at - kThreads; at > first_word; at -= kThreads) part_v += word_sum<TT>(((const v4u *)P.x)[at]);
+        if (near_at == first_word || (far && tid == 0)) {
+            const uint32_t skip = (from % kEpl) * (uint32_t)sizeof(typename TT::in_t);   // bytes that do not count
 #pragma unroll
-                for (uint32_t d = 0; d < 4; ++d) w[d] = skip >= 4 * d + 4 ? 0u : skip > 4 * d ? w[d] & (~0u << (8 * (skip - 4 * d))) : w[d];
-            }
+            for (uint32_t d = 0; d < 4; ++d) w0[d] = skip >= 4 * d + 4 ? 0u : skip > 4 * d ? w0[d] & (~0u << (8 * (skip - 4 * d))) : w0[d];
             if constexpr (!kFlagged && TT::kDtype == MMV_I8_I32) {
-                if (P.first_one && at == 0) w[0] = (w[0] & ~0xFFu) | 1u;
+                if (P.first_one) w0[0] = (w0[0] & ~0xFFu) | 1u;
             }
-            part_v += word_sum<TT>(w);
-        };
-        add(near, near_at);   // (the words before the vector are not added: near_at < 0)
-#pragma unroll 4
-        for (int32_t at = near_at - kShortThreads; at >= first_word; at -= kShortThreads) add(((const v4u *)P.x)[at], at);
+            part_v += word_sum<TT>(w0);
+        }
         uint32_t none = 0;
         wave_segmented_scan<false>(part_v, none);
         if (lane == 63) s_pv[wave] = part_v;
         __syncthreads();
+        if (!owner) return;
+        if constexpr (kMany) {
+            before = lane < kWaves ? s_pv[lane] : V(0);
+            wave_segmented_scan<false>(before, none);
+            before = wave_last(before);
+        } else {
 #pragma unroll
-        for (int w = 0; w < kShortWaves; ++w) before += s_pv[w];
+            for (int w = 0; w < kWaves; ++w) before += s_pv[w];
+        }
     }
 
     // ---- the waves of the tile before mine ----

@@ -1,6 +1,6 @@
 """Scans and sums of short vectors: one launch (the sum carried into a tile comes from the input itself) up to 320 KB of
-values and flags, two (from the aggregates of the tiles before) up to 2^21 elements (fp32 sums and 16-bit mmv_scan 3 * 2^20, other mmv_scan 2^22), the
-single-pass kernels beyond.  Tiles have 2048 elements, a thread takes eight, a wave 512; whole numbers, so results are exact."""
+values and flags (16-bit values with flags: 256 KB), two (from the aggregates of the tiles before) up to 2^21 elements (16-bit segmented scans 3 * 2^19,
+fp32 sums and 16-bit mmv_scan 3 * 2^20, other mmv_scan 2^22), the single-pass kernels beyond.  Tiles have 2048 elements, a thread takes eight, a wave 512; whole numbers, so results are exact."""
 import numpy as np
 import pytest
 import torch
@@ -18,7 +18,7 @@ TYPES = {"f32": (torch.float32, B.MMV_F32_F32), "f16": (torch.float16, B.MMV_F16
 def one_launch(dt, flag_bytes):
     """Most elements that one launch takes (8 * flag_bytes: bits of flags per element)."""
     size = torch.empty(0, dtype=TYPES[dt][0]).element_size()
-    return int((320 << 10) / (size + flag_bytes)) // 32 * 32
+    return int(((256 if size == 2 else 320) << 10) / (size + flag_bytes)) // 32 * 32
 
 
 def values(rng, n, dt):
@@ -60,7 +60,7 @@ def test_edges_of_threads_waves_tiles_and_of_the_two_forms(dt, packed):
     rng = np.random.default_rng(2390700)
     line = one_launch(dt, 1 / 8 if packed else 1)
     sizes = [1, 2, 7, 8, 9, 31, 33, 511, 513, TILE - 1, TILE, TILE + 1, 5 * TILE + 511, line - 1, line, line + 1, line + TILE + 9,
-             (1 << 21) - 5, 1 << 21, (1 << 21) + 1, 3 << 20, (3 << 20) + 1, (1 << 22) - 3, 1 << 22, (1 << 22) + 1]
+             3 << 19, (3 << 19) + 1, (1 << 21) - 5, 1 << 21, (1 << 21) + 1, 3 << 20, (3 << 20) + 1, (1 << 22) - 3, 1 << 22, (1 << 22) + 1]
     for n in sizes:
         for density in (0.0, 3 / n, 0.01, 1.0):
             f = ((rng.random(n) < density) * rng.integers(1, 256, size=n)).astype(np.uint8)
@@ -232,3 +232,42 @@ def test_outputs_over_byte_flags(n):
             _, nseg = B.mmv_segsum(dev(x), room[shift:shift + n], n=n, out=z)
             ref = oracle.segsum(x, f)
             assert int(nseg.item()) == len(ref) and np.array_equal(z.cpu().numpy()[:len(ref)].astype(np.float64), ref.astype(np.float64))
+
+
+@pytest.mark.parametrize("packed", [True, False])
+@pytest.mark.parametrize("dt", list(TYPES))
+def test_single_flags_where_more_waves_help(dt, packed):
+    """One launch with 1024 threads from 64 KB of values and flags on (16 KB without flags): both sides of these lines, and the
+    start of the last segment at borders of the 128-bit words, just inside and outside what the threads hold from the
+    beginning (one word each before the tile), and far back."""
+    rng = np.random.default_rng(2390708)
+    size = torch.empty(0, dtype=TYPES[dt][0]).element_size()
+    per_elem, epl = size + (1 / 8 if packed else 1), 16 // size
+    line = int((64 << 10) / per_elem)
+    for n in (int((16 << 10) / size) // epl * epl - epl, (16 << 10) // size, line - 1, line + 1, one_launch(dt, per_elem - size) - 3):
+        last_tile = (n - 1) // TILE * TILE
+        near = 1024 * epl                                              # elements that the threads hold
+        at = {1, epl - 1, epl, 5 * epl + 1, TILE - 1, TILE, TILE + epl // 2}
+        for edge in (last_tile, last_tile - near, last_tile - 256 * epl, last_tile - near - 128):
+            at |= {edge - 1, edge, edge + 1, edge - epl, edge + epl - 1}
+        for p in sorted(q for q in at if 0 < q < n):
+            f = np.zeros(n, dtype=np.uint8)
+            f[p] = 1
+            print(dt, packed, n, p, flush=True)
+            check(dt, n, packed, f, rng, scan_too=p == 1)
+
+
+@pytest.mark.parametrize("packed", [True, False])
+def test_compress_counts_what_lies_before_every_tile(packed):
+    """One selected position at a time, in the words that the threads of a later tile count in their first, second and last round."""
+    n = 1 << (20 if packed else 17)
+    word = 128 if packed else 16
+    for p in (0, word - 1, word, 511 * word, 512 * word - 1, 512 * word, 4 * 512 * word - 1, 4 * 512 * word, 5 * 512 * word + 3, n - 8193, n - 8192, n - 1):
+        if p >= n:
+            continue
+        m = np.zeros(n, dtype=np.uint8)
+        m[[p, n - 1]] = 1
+        want = np.flatnonzero(m)
+        print(packed, p, flush=True)
+        out, count = B.mmv_compress(None, flags_dev(m, packed), n)
+        assert int(count.item()) == len(want) and np.array_equal(out.cpu().numpy()[:len(want)], want)

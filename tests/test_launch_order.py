@@ -96,6 +96,17 @@ def test_overlapping_outputs_take_the_launches_they_are_safe_in(record, call, wa
 
 
 @pytest.mark.parametrize("call,want", [
+    (segscan(65_536, F32, BYTES, OUT), ONE), (segscan(65_537, F32, BYTES, OUT), TWO), (segsum(163_840, I8, BYTES, OUT), ONE), (segsum(163_841, I8, BYTES, OUT), TWO),
+    (segsum(87_381, F16, BYTES, OUT), ONE), (segsum(87_382, F16, BYTES, OUT), TWO), (segscan(123_328, F16, BITS, OUT), ONE), (segscan(123_392, F16, BITS, OUT), TWO),
+    (scan(163_840, F16, OUT), ONE), (scan(163_841, F16, OUT), TWO), (scan(3 << 20, F16, OUT), TWO), (scan((3 << 20) + 1, F16, OUT), FILL),
+    (segscan(3 << 19, F16, BYTES, OUT), TWO), (segscan((3 << 19) + 1, F16, BYTES, OUT), PACK), (segscan((3 << 19) + 1, F32, BYTES, OUT), TWO),
+    (segsum((3 << 19) + 1, F16, BITS, OUT), TWO), (segsum(3 << 20, F32, BITS, OUT), TWO), (segsum((3 << 20) + 1, F32, BITS, OUT), [COUNT, "stream_kernel"]),
+])
+def test_lines_between_the_forms(record, call, want):
+    assert record([call]) == [want]
+
+
+@pytest.mark.parametrize("call,want", [
     (segscan(30_000, F32, BYTES, OUT), ["event 5", *ONE, "event 7"]), (segscan(300_000, F32, BITS, OUT), ["event 5", *TWO, "event 7"]),
     (segsum(300_000, I8, BYTES, OUT), ["event 5", *TWO, "event 7"]), (scan(300_000, F16, OUT), ["event 5", *TWO, "event 7"]),
     (segscan(3_000_000, F32, BYTES, OUT), [PACK[0], "event 5", PACK[1], "event 7"]),
