@@ -247,10 +247,16 @@ __global__ __launch_bounds__(256) void csr_flags_kernel(const int32_t *rowptr, u
 // The same in one launch that needs nothing zeroed first: workgroup t makes all that the product kernel needs for its tile t.
 // It finds the rows that start in the tile by a search in the row pointers, all threads probing, sets their bits in LDS and
 // stores the words, and leaves
-//   tile_base[t]    the first row that starts in the tile (r0), bit 31 set if none of the tile's rows is empty: then the
+//   tile_base[t]    the first row that starts in the tile (r0), kPlanDense set if none of the tile's rows is empty: then the
 //                   j-th start of the tile is row r0 + j, and what is open where it begins is row r0 - 1, the last that starts
 //                   before the tile and reaches it;
 //   rowmap[r0 - 1 + j]  those rows else.  (The slots of two tiles meet in one alone, which both give the row of its number.)
+// A tile may hold nearly all rows (those of one entry or none behind the long ones of a matrix sorted by degree), so one of
+// more than share_above rows (see plan_share_above) is shared: tile_base[t] has kPlanByEnd set, and the row whose last entry is
+// position e of the tile stands in rowmap[r0 + e], so that nobody needs to know how many rows with entries lie before its own.  The
+// workgroups behind those of the tiles have a row each, kPlanShare apart: the first position of that row, rounded up to
+// whole 128-bit words of flags, up to that of the next one of them in the tile is theirs, what lies before the tile's own workgroup's.
+// They leave at once where no row of another one, half of share_above away, starts in the same tile.
 // The same launch zeroes the header and descriptors of the product kernel, and y.
 // Bound by its chain of dependent loads: four to five for the two ends of the tile, then one per 2048 rows.  Four waves: eight
 // or sixteen start later (blocks of 16, 65536 rows: 33.4 and 38.5 us the call against 31.5).  Products in one step, four
@@ -260,19 +266,32 @@ __global__ __launch_bounds__(256) void csr_flags_kernel(const int32_t *rowptr, u
 //   21 -> 13.6, 19.7 -> 17; Zipf lengths, 2^20 rows and 2^25 entries 244 -> 222
 // (In the four launches, adds and ORs of many rows meet in the same words, and each launch costs 2.5 to 5.)
 constexpr int kPlanThreads = 256, kPlanRows = 8;
-__global__ __launch_bounds__(kPlanThreads) void csr_plan_kernel(const int32_t *rowptr, uint32_t n_rows, uint32_t nnz, uint32_t tile_elems,
+constexpr uint32_t kPlanShare = 8192;   // rows of a piece
+template <bool kByEnd> struct PlanByEnd {
+    static constexpr bool value = kByEnd;
+};
+__global__ __launch_bounds__(kPlanThreads) void csr_plan_kernel(const int32_t *rowptr, uint32_t n_rows, uint32_t nnz, uint32_t tiles, uint32_t tile_elems, uint32_t share_above,
                                                                 uint32_t *fw, uint32_t *tile_base, uint32_t *rowmap, uint32_t *ws,
                                                                 uint64_t ws_words, uint32_t *y, uint32_t y_rows) {
     constexpr int kWaves = kPlanThreads / 64;
     __shared__ __attribute__((aligned(16))) uint32_t s_words[kMaxUnits * (kUnitElems / 32)];
     __shared__ uint32_t s_cnt[2][kWaves], s_kept[2][kWaves];
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tile = blockIdx.x;
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint64_t stride = (uint64_t)gridDim.x * kPlanThreads;
-    for (uint64_t i = (uint64_t)tile * kPlanThreads + tid; i < ws_words; i += stride) ws[i] = 0;
-    for (uint64_t i = (uint64_t)tile * kPlanThreads + tid; i < y_rows; i += stride) y[i] = 0;
+    for (uint64_t i = (uint64_t)blockIdx.x * kPlanThreads + tid; i < ws_words; i += stride) ws[i] = 0;
+    for (uint64_t i = (uint64_t)blockIdx.x * kPlanThreads + tid; i < y_rows; i += stride) y[i] = 0;
+    const bool helps = blockIdx.x >= tiles;
+    const uint32_t my_row = helps ? (blockIdx.x - tiles) * kPlanShare : 0u, my_start = helps ? (uint32_t)rowptr[my_row] : 0u;
+    if (helps && my_start >= nnz) return;
+    const uint32_t tile = helps ? my_start / tile_elems : blockIdx.x;
     const uint32_t base = tile * tile_elems, end = nnz - base < tile_elems ? nnz : base + tile_elems;
-    const uint32_t words = (end - base + 31) / 32;
-    for (uint32_t w = tid; w < (words + 3) / 4 * 4; w += kPlanThreads) s_words[w] = 0;
+    if (helps) {
+        // more than share_above rows are those of share_above / kPlanShare workgroups or more: one that far off at least, before or behind
+        const uint32_t off = share_above / kPlanShare / 2 * kPlanShare;
+        const bool before = my_row >= off && (uint32_t)rowptr[my_row - off] >= base;
+        const bool behind = n_rows - my_row > off && (uint32_t)rowptr[my_row + off] < end;
+        if (!before && !behind) return;
+    }
 
     // first index in [lo, hi] whose row pointer is at least the target (hi: none), for two targets at once
     auto search = [&](uint32_t (&lo)[2], uint32_t (&hi)[2], const uint32_t (&target)[2]) {
@@ -298,8 +317,30 @@ __global__ __launch_bounds__(kPlanThreads) void csr_plan_kernel(const int32_t *r
     uint32_t first[2] = {0, 0}, behind[2] = {n_rows, n_rows};
     search(first, behind, {base, end});
     const uint32_t r0 = first[0], r1 = first[1];   // rows that start in the tile
-    uint32_t kept = 0;                             // those with entries so far
+    const bool shared = r1 - r0 > share_above;
+    if (helps && !shared) return;
+    uint32_t from = base, upto = end, ra = r0, rb = r1;   // the positions that are mine, the rows that start there
+    if (shared) {
+        auto piece_at = [&](uint32_t start) { return start + 127 < end ? (start + 127) & ~127u : end; };
+        const uint32_t next = helps ? my_row + kPlanShare : (r0 + kPlanShare - 1) / kPlanShare * kPlanShare;
+        if (helps) from = piece_at(my_start);
+        if (next < r1) upto = piece_at((uint32_t)rowptr[next]);
+        uint32_t lo[2] = {r0, r0}, hi[2] = {r1, r1};
+        search(lo, hi, {from, upto});
+        ra = lo[0], rb = lo[1];
+    }
+    const uint32_t words = (upto - from + 31) / 32;
+    for (uint32_t w = tid; w < (words + 3) / 4 * 4; w += kPlanThreads) s_words[w] = 0;
+    uint32_t kept = 0;                             // rows with entries so far
     __syncthreads();
+    auto store_row = [&](bool by_end, uint32_t slot, uint32_t row) {
+        if (!by_end) {
+            rowmap[slot] = row;
+        } else {
+            const uint32_t last = (uint32_t)rowptr[row + 1] - 1u;
+            if (last < end) rowmap[r0 + (last - base)] = row;
+        }
+    };
     // rows found in a round, in their order: masks of 64 candidates each -> where a wave's first one goes
     auto place = [&](const uint64_t (&mask)[kPlanRows], uint32_t odd, uint32_t &total) {
         uint32_t mine = 0;
@@ -307,7 +348,7 @@ __global__ __launch_bounds__(kPlanThreads) void csr_plan_kernel(const int32_t *r
         for (int i = 0; i < kPlanRows; ++i) mine += (uint32_t)__popcll((unsigned long long)mask[i]);
         if (lane == 0) s_kept[odd][wave] = mine;
         __syncthreads();
-        uint32_t at = r0 + kept;
+        uint32_t at = ra + kept;
         total = 0;
         for (int w = 0; w < kWaves; ++w) {
             if (w < (int)wave) at += s_kept[odd][w];
@@ -316,52 +357,24 @@ __global__ __launch_bounds__(kPlanThreads) void csr_plan_kernel(const int32_t *r
         kept += total;
         return at;
     };
-    const uint32_t e0 = r0 < r1 ? (uint32_t)rowptr[r0] : 0u, starts = r0 < r1 ? (uint32_t)rowptr[r1 - 1] - e0 + 1 : 0u;
-    if (r1 - r0 > kPlanThreads * kPlanRows * 2 && (r1 - r0) / 24 > starts) {
-        // Many rows, almost all of them empty: a search for every position instead that a row may start at, for the last row
-        // that starts up to there.  (2048 positions take about 20 us, 2048 rows 0.9: the two meet at 22 rows per position.
-        // 2^20 rows, one in 2048 with an entry, all in one tile: 101 us the call, row by row 480.)
-        uint32_t top = 1u << 31;
-        while (top > r1 - r0) top >>= 1;
-        for (uint32_t cur = (e0 - base) & ~63u, odd = 0; cur < e0 - base + starts; cur += kPlanThreads * kPlanRows, odd ^= 1) {
-            const uint32_t at0 = cur + 64 * kPlanRows * wave;   // (in the tile)
-            uint32_t row[kPlanRows], start[kPlanRows];
-#pragma unroll
-            for (int i = 0; i < kPlanRows; ++i) row[i] = r0, start[i] = e0;
-            for (uint32_t step = top; step; step >>= 1) {
-#pragma unroll
-                for (int i = 0; i < kPlanRows; ++i) {
-                    const uint32_t next = row[i] + step < r1 ? row[i] + step : row[i], v = (uint32_t)rowptr[next];
-                    if (v <= base + at0 + 64 * i + lane) row[i] = next, start[i] = v;
-                }
-            }
-            uint64_t mask[kPlanRows];
-#pragma unroll
-            for (int i = 0; i < kPlanRows; ++i) mask[i] = __ballot(start[i] == base + at0 + 64 * i + lane);
-            uint32_t total, at = place(mask, odd, total);
-#pragma unroll
-            for (int i = 0; i < kPlanRows; ++i) {
-                if (mask[i] == 0) continue;
-                if (mask[i] >> lane & 1) rowmap[at + __popcll((unsigned long long)(mask[i] & ((1ull << lane) - 1)))] = row[i];
-                if (lane < 2 && at0 + 64 * i + 32 * lane < end - base) s_words[at0 / 32 + 2 * i + lane] = (uint32_t)(mask[i] >> (32 * lane));
-                at += (uint32_t)__popcll((unsigned long long)mask[i]);
-            }
-        }
-    } else {
-        // A round is kPlanRows rows per thread: lane l of a wave takes rows l, l + 64, ... of the wave's share (those from r1 on
+    // Row by row.  (Two bodies: a load of the shared one inside the loop would have the other one wait for the next round's pointers,
+    // 2^20 rows of 0.4 entries 16.7 us to prepare, 19.0 so.)
+    auto row_by_row = [&](auto form) {
+        constexpr bool by_end = decltype(form)::value;
+        // A round is kPlanRows rows per thread: lane l of a wave takes rows l, l + 64, ... of the wave's share (those from rb on
         // count as empty).  The next round's pointers are under way meanwhile.
         auto load_rows = [&](uint32_t cur, uint32_t (&p)[kPlanRows + 1]) {
             const uint32_t r = cur + 64 * kPlanRows * wave + lane;
 #pragma unroll
-            for (int i = 0; i <= kPlanRows; ++i) p[i] = (uint32_t)rowptr[r + 64 * i < r1 ? r + 64 * i : r1];
+            for (int i = 0; i <= kPlanRows; ++i) p[i] = (uint32_t)rowptr[r + 64 * i < rb ? r + 64 * i : rb];
         };
         uint32_t p[kPlanRows + 1];
-        load_rows(r0, p);
-        for (uint32_t cur = r0, odd = 0; cur < r1; odd ^= 1) {
+        load_rows(ra, p);
+        for (uint32_t cur = ra, odd = 0; cur < rb; odd ^= 1) {
             const uint32_t r = cur + 64 * kPlanRows * wave + lane;
             uint32_t ahead[kPlanRows + 1];
             cur += kPlanThreads * kPlanRows;
-            if (cur < r1) load_rows(cur, ahead);
+            if (cur < rb) load_rows(cur, ahead);
             uint64_t mask[kPlanRows];
 #pragma unroll
             for (int i = 0; i < kPlanRows; ++i) {
@@ -374,15 +387,15 @@ __global__ __launch_bounds__(kPlanThreads) void csr_plan_kernel(const int32_t *r
             for (int i = 0; i < kPlanRows; ++i) {
                 if (mask[i] == 0) continue;
                 if (mask[i] >> lane & 1) {
-                    rowmap[at + __popcll((unsigned long long)(mask[i] & ((1ull << lane) - 1)))] = r + 64 * i;
-                    if (p[i] - base < end - base) atomicOr(s_words + ((p[i] - base) >> 5), 1u << ((p[i] - base) & 31u));
+                    store_row(by_end, at + __popcll((unsigned long long)(mask[i] & ((1ull << lane) - 1))), r + 64 * i);
+                    if (p[i] - from < upto - from) atomicOr(s_words + ((p[i] - from) >> 5), 1u << ((p[i] - from) & 31u));
                 }
                 at += (uint32_t)__popcll((unsigned long long)mask[i]);
             }
-            if (cur < r1) {
+            if (cur < rb) {
                 if (total == 0) {   // a long run of empty rows: on to the row behind it
                     const uint32_t v = (uint32_t)rowptr[cur];
-                    uint32_t lo[2] = {cur, cur}, hi[2] = {r1, cur};
+                    uint32_t lo[2] = {cur, cur}, hi[2] = {rb, cur};
                     search(lo, hi, {v + 1, v + 1});
                     cur = lo[0] - 1;
                     load_rows(cur, p);
@@ -392,13 +405,73 @@ __global__ __launch_bounds__(kPlanThreads) void csr_plan_kernel(const int32_t *r
                 }
             }
         }
+    };
+    const uint32_t e0 = ra < rb ? (uint32_t)rowptr[ra] : 0u, starts = ra < rb ? (uint32_t)rowptr[rb - 1] - e0 + 1 : 0u;
+    if (rb - ra > kPlanThreads * kPlanRows * 2 && (rb - ra) / 24 > starts) {
+        // Many rows, almost all of them empty: a search for every position instead that a row may start at, for the last row
+        // that starts up to there.  (2048 positions take about 20 us, 2048 rows 0.9: the two meet at 22 rows per position.)
+        uint32_t top = 1u << 31;
+        while (top > rb - ra) top >>= 1;
+        // Up to 256 positions: one for each thread, all its loads in flight for that one, an eighth of the rows left by each step (2^20
+        // rows, one in 2048 of one entry, in one tile: 29 -> 21 us the call).
+        const uint32_t cur0 = (e0 - from) & ~63u, behind_last = e0 - from + starts;
+        const bool one = behind_last - cur0 <= kPlanThreads;
+        for (uint32_t cur = cur0, odd = 0; cur < behind_last; cur += kPlanThreads * kPlanRows, odd ^= 1) {
+            const uint32_t at0 = cur + 64 * (one ? 1 : kPlanRows) * wave;   // (in the piece)
+            uint32_t row[kPlanRows], start[kPlanRows];
+#pragma unroll
+            for (int i = 0; i < kPlanRows; ++i) row[i] = ra, start[i] = e0;
+            if (one) {
+                uint32_t step = 1;
+                while (step <= top / 8) step *= 8;
+                for (; step; step /= 8) {
+                    uint32_t v[kPlanRows - 1], below = 0;
+#pragma unroll
+                    for (int i = 0; i < kPlanRows - 1; ++i) {
+                        const uint64_t next = row[0] + (uint64_t)(i + 1) * step;
+                        v[i] = next < rb ? (uint32_t)rowptr[next] : ~0u;
+                    }
+#pragma unroll
+                    for (int i = 0; i < kPlanRows - 1; ++i)
+                        if (v[i] <= from + at0 + lane) below = i + 1, start[0] = v[i];
+                    row[0] += below * step;
+                }
+            } else {
+                for (uint32_t step = top; step; step >>= 1) {
+#pragma unroll
+                    for (int i = 0; i < kPlanRows; ++i) {
+                        const uint32_t next = row[i] + step < rb ? row[i] + step : row[i], v = (uint32_t)rowptr[next];
+                        if (v <= from + at0 + 64 * i + lane) row[i] = next, start[i] = v;
+                    }
+                }
+            }
+            uint64_t mask[kPlanRows];
+#pragma unroll
+            for (int i = 0; i < kPlanRows; ++i) mask[i] = one && i > 0 ? 0 : __ballot(start[i] == from + at0 + 64 * i + lane);
+            uint32_t total, at = place(mask, odd, total);
+#pragma unroll
+            for (int i = 0; i < kPlanRows; ++i) {
+                if (mask[i] == 0) continue;
+                if (mask[i] >> lane & 1) store_row(shared, at + __popcll((unsigned long long)(mask[i] & ((1ull << lane) - 1))), row[i]);
+                if (lane < 2 && at0 + 64 * i + 32 * lane < upto - from) s_words[at0 / 32 + 2 * i + lane] = (uint32_t)(mask[i] >> (32 * lane));
+                at += (uint32_t)__popcll((unsigned long long)mask[i]);
+            }
+        }
+    } else if (shared) {
+        row_by_row(PlanByEnd<true>());
+    } else {
+        row_by_row(PlanByEnd<false>());
     }
     __syncthreads();
-    if (tid == 0) {
-        tile_base[tile] = r0 | (kept == r1 - r0 ? 0x80000000u : 0u);
-        if (r0 > 0) rowmap[r0 - 1] = r0 - 1;
+    if (tid == 0 && !helps) {
+        tile_base[tile] = r0 | (shared ? kPlanByEnd : kept == r1 - r0 ? kPlanDense : 0u);
+        if (r0 > 0 && !shared) rowmap[r0 - 1] = r0 - 1;
+        if (r0 > 0 && shared) {   // (a row that starts before the tile and ends in it)
+            const uint32_t last = (uint32_t)rowptr[r0] - 1u;
+            if (last >= base && last < end) rowmap[r0 + (last - base)] = r0 - 1;
+        }
     }
-    v4u *out = reinterpret_cast<v4u *>(fw + base / 32);
+    v4u *out = reinterpret_cast<v4u *>(fw + from / 32);
     for (uint32_t w = tid; w < (words + 3) / 4; w += kPlanThreads) out[w] = reinterpret_cast<const v4u *>(s_words)[w];
 }
 

@@ -605,9 +605,22 @@ mmv_status compress_impl(const void *d_x, const void *d_mask, uint64_t n, void *
 // left to those with so few entries that a tile holds too many rows.  Products in one step, launches over the rows / tile by
 // tile (us), rows with one entry or none, 0.4, 0.25 and 0.06 entries per row: 2^14 rows 31 / 26, 28 / 23, 22 / 22; 2^16 37 / 32,
 // 37 / 39, 31 / 54; 2^18 77 / 34, 77 / 41, 72 / 103; 2^20 154 / 44, 175 / 52, 211 / 106.
-// Beyond the line also where the rows are uneven: 2^18 rows, half of them of 16 entries, then one in 20 of one entry in a
-// tile or two, 53 / 64 us; without those empty rows 36 / 20.
-constexpr bool rows_by_tile(uint64_t n_rows, uint64_t nnz) { return n_rows / 3 <= nnz; }
+// Uneven rows, over the rows / tile by tile / with the tiles of many rows shared: 2^18 rows, half of them of 16 entries, then one in
+// 20 of one entry in a tile or two, 51 / 59 / 31; 2^25 entries in 200 000 rows, then 2^20 rows, one in 24 of one entry, 369 / 476 / 198;
+// a row of 600 000, then 2^20 rows, one in 2048 of one entry, 26 / 38 / 21.
+// (A row and two marks share a word of tile_base.)
+constexpr bool rows_by_tile(uint64_t n_rows, uint64_t nnz) { return n_rows / 3 <= nnz && n_rows < kPlanByEnd; }
+// Most rows of a tile that its workgroup takes alone: two pieces, so many as positions (a shared tile needs a slot for each), or twice
+// what a tile has on average, so that the tiles of an even matrix of few entries per row stay whole (2^24 rows, 0.4 entries per row:
+// 168 us the call, 194 with its tiles of 23000 rows shared).
+constexpr uint64_t plan_share_above(uint64_t n_rows, uint64_t tiles, uint32_t tile_elems) {
+    const uint64_t even = 2 * ((n_rows + tiles - 1) / tiles), pieces = 2 * kPlanShare, most = even > pieces ? even : pieces;
+    return most > tile_elems ? most : tile_elems;
+}
+// Workgroups of csr_plan_kernel behind those of the tiles: none where no tile can be shared.
+constexpr uint64_t plan_helpers(uint64_t n_rows, uint64_t share_above) {
+    return n_rows > share_above ? (n_rows + kPlanShare - 1) / kPlanShare : 0;
+}
 
 // What the CSR product needs of the matrix alone, header and descriptors zeroed, and y (nullptr: not).
 mmv_status csr_plan(uint64_t n_rows, uint64_t nnz, const int32_t *d_rowptr, uint32_t *d_y, char *ws, const CsrLayout &C, const WsLayout &L,
@@ -615,9 +628,11 @@ mmv_status csr_plan(uint64_t n_rows, uint64_t nnz, const int32_t *d_rowptr, uint
     uint32_t *fw = (uint32_t *)(ws + C.main_ws + L.packed);
     uint32_t *tile_count = (uint32_t *)(ws + C.main_ws + L.desc_c);
     if (rows_by_tile(n_rows, nnz)) {
-        csr_plan_kernel<<<(unsigned)plan.tiles, kPlanThreads, 0, s>>>(d_rowptr, (uint32_t)n_rows, (uint32_t)nnz, plan.body_elems, fw, tile_count,
-                                                                      (uint32_t *)(ws + C.rowmap), (uint32_t *)(ws + C.main_ws),
-                                                                      L.desc_c / 4, d_y, d_y ? (uint32_t)n_rows : 0u);
+        const uint64_t share_above = plan_share_above(n_rows, plan.tiles, plan.body_elems);
+        const unsigned workgroups = (unsigned)(plan.tiles + plan_helpers(n_rows, share_above));
+        csr_plan_kernel<<<workgroups, kPlanThreads, 0, s>>>(d_rowptr, (uint32_t)n_rows, (uint32_t)nnz, (uint32_t)plan.tiles,
+                                                                      plan.body_elems, (uint32_t)share_above, fw, tile_count, (uint32_t *)(ws + C.rowmap),
+                                                                      (uint32_t *)(ws + C.main_ws), L.desc_c / 4, d_y, d_y ? (uint32_t)n_rows : 0u);
         return hipGetLastError() == hipSuccess ? MMV_OK : MMV_ERR_HIP;
     }
     // zero: the main kernel's header, descriptors and flag words, the header and descriptors of COMPRESS; y

@@ -220,7 +220,7 @@ mmv_status mmv_spmv_coo(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
 
 // SpMV in two steps: the mark that the first step leaves in the header for this matrix shape (never 0).  It names the
 // layout of the counts as well (kPlanLayout), which the product kernel relies on.
-static constexpr uint64_t kPlanLayout = 5;
+static constexpr uint64_t kPlanLayout = 6;
 static uint32_t prepared_mark(mmv_op op, uint64_t n_rows, uint64_t nnz) {
     uint64_t h = (nnz + 0x9E3779B97F4A7C15ull) * 0xD6E8FEB86659FD93ull + n_rows * 0xCA5A826395121157ull + (uint64_t)op + (kPlanLayout << 32);
     h ^= h >> 32;

@@ -168,12 +168,14 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
         }
     }
     // CSR: without empty rows (in the tile; in the matrix) the k-th segment is row k and the row map need not be read
-    bool rows_dense = false;
+    bool rows_dense = false, by_end = false;   // (by_end: the row map goes by the last position of a segment)
     uint32_t tile_base = 0;
     if constexpr (kOp == kSpmvCsr) {
         // (no branch around the load, for the same reason)
         tile_base = *(P.tile_base ? P.tile_base + tile : hints + (kHdrEmptyRows - kHdrHints));
-        rows_dense = P.tile_base ? (tile_base >> 31) != 0 : tile_base == 0;
+        rows_dense = P.tile_base ? (tile_base & kPlanDense) != 0 : tile_base == 0;
+        by_end = P.tile_base && (tile_base & kPlanByEnd) != 0;
+        tile_base &= ~(kPlanDense | kPlanByEnd);
     }
     __builtin_amdgcn_sched_barrier(0);
     StreamSlot<kProduct> slot[kDepth];
@@ -201,7 +203,7 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
     if constexpr (kCounts) {
         count_carry = wave_sum<uint32_t, true>(count_part);
         // CSR: (the number of starts, or the first row) before the tile, minus 1: the index of the segment that is open there
-        if constexpr (kOp == kSpmvCsr) count_carry = P.tile_base ? (tile_base & 0x7FFFFFFFu) - 1u : tile == 0 ? ~0u : count_carry;
+        if constexpr (kOp == kSpmvCsr) count_carry = P.tile_base ? tile_base - 1u : tile == 0 ? ~0u : count_carry;
         uint32_t s = 0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) s += __popc(fl[i / 4][i % 4]);
@@ -222,9 +224,10 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
         }
     }
 
-    auto output_index = [&](uint32_t k, const int32_t *row, uint32_t e) -> uint32_t {   // where the sum of a segment goes
+    // where the sum of a segment goes: the k-th, whose last element is e of unit q
+    auto output_index = [&](uint32_t k, const int32_t *row, uint32_t e, uint32_t q) -> uint32_t {
         if constexpr (kOp == kSpmv) return (uint32_t)row[e];
-        else if constexpr (kOp == kSpmvCsr) return rows_dense ? k : P.rowmap[k];
+        else if constexpr (kOp == kSpmvCsr) return rows_dense ? k : P.rowmap[by_end ? tile_base + kUnitElems * q + e : k];
         else return k;
     };
     auto emit = [&](uint32_t at, float v) {
@@ -369,10 +372,10 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
                         const bool kept = kOp == kSpmv || k < P.out_cap;
                         if (!m && ex_c == 0) {                                 // ... before this unit: at most one end
                             sm.late_v[q] = to_bits(v);
-                            sm.late_k[q] = kept ? output_index(k, row, 32u * c + e) : 0u;
+                            sm.late_k[q] = kept ? output_index(k, row, 32u * c + e, (uint32_t)q) : 0u;
                             sm.late_on[q] = kept ? 1u : 0u;
                         } else if (kept) {
-                            emit(output_index(k, row, 32u * c + e), v);
+                            emit(output_index(k, row, 32u * c + e, (uint32_t)q), v);
                         }
                     }
                     if (lane == 31) {

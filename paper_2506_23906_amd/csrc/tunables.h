@@ -194,6 +194,7 @@ __host__ __device__ __forceinline__ TileSpan tile_span(const TileRegions &R, uin
         }
     return {base + (uint64_t)(tile - first) * cpw * unit, cpw};
 }
+constexpr uint32_t kPlanDense = 1u << 31, kPlanByEnd = 1u << 30;   // marks in Params::tile_base
 struct Params {
     const void *x;          // values (scan, sum) / val (spmv)
     const uint32_t *fw;     // packed flag words (scan, sum)
@@ -204,7 +205,7 @@ struct Params {
     uint64_t *nseg;
     const int32_t *row;     // spmv (coo)
     const uint32_t *rowmap; // spmv (csr): row index of the k-th non-empty row, or (tile_base) slots of their own per tile
-    const uint32_t *tile_base;   // spmv (csr): as csr_plan_kernel leaves it (nullptr: made row by row, see csr_flags_kernel)
+    const uint32_t *tile_base;   // spmv (csr): as csr_plan_kernel leaves it, a row and one of the marks below (nullptr: made row by row, see csr_flags_kernel)
     uint32_t first_one;     // plain scan of a flag vector: element 0 counts as 1 whatever it holds
     const int32_t *col;
     const float *xv;

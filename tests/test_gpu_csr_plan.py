@@ -1,6 +1,6 @@
 """Preparation of the CSR product: matrices of up to three rows per entry take one launch that works tile by tile, the
 others the launches over the rows.  Compared with the oracle where the first can go wrong: rows across tiles and at their
-borders, runs of empty rows, both sides of the rule, a workspace full of garbage.  Whole numbers, sums below 2^24: every
+borders, runs of empty rows, tiles with so many rows that several workgroups share them, both sides of the rule, a workspace full of garbage.  Whole numbers, sums below 2^24: every
 result is exact."""
 import numpy as np
 import pytest
@@ -12,6 +12,7 @@ from parity_util import dev
 
 pytestmark = pytest.mark.gpu
 ROUND = 2048         # rows that a workgroup looks at in a round
+SHARE = 8192         # rows of a piece of a tile that several workgroups share
 
 
 def lengths_of(kind, tile):
@@ -43,12 +44,30 @@ def lengths_of(kind, tile):
         return np.r_[a, b, a[::-1], b]
     if kind == "zipf":
         return np.minimum(rng.zipf(1.4, 30_000), 9000) + 3
+    if kind == "sorted by degree":                     # nearly all rows in the last tiles, one in 20 of one entry
+        tail = np.zeros(300_000, int)
+        tail[rng.choice(300_000, 15_000, replace=False)] = 1
+        return np.r_[np.sort(rng.zipf(1.3, 2000) % 3000)[::-1], rng.integers(8, 24, 4000), tail]
+    if kind == "rows of many tiles among empty ones":  # shared tiles with one start or none of their own
+        return np.concatenate([np.r_[np.zeros(20_000 + 13 * i, int), 6 * tile + 100 * i] for i in range(4)] + [np.zeros(40_000, int), [1]])
+    if kind == "many shared tiles":
+        a = (rng.random(600_000) < 0.33).astype(int)
+        a[::5000] += rng.integers(1, 300, 120)
+        return np.r_[a, 2_000_000]
+    if kind == "most rows of one workgroup":           # and one row more: the second tile, the fourth
+        return np.r_[tile, 5, np.zeros(2 * SHARE - 2, int), tile - 5, 1, tile - 1, 5, np.zeros(2 * SHARE - 1, int), tile - 5, 1, 3 * tile]
+    if kind == "borders of pieces":                    # at whole and broken flag words, at the end of the tile, several at one position
+        a = np.zeros(12 * SHARE, int)
+        for i, n in enumerate([128, 127, 129, 0, 1, 31, 32, 33, 96, 0, 7]):
+            a[i * SHARE + 5], a[(i + 1) * SHARE - 1], a[(i + 1) * SHARE] = n, 1 + i % 2, 3 * (i % 3)
+        return np.r_[np.zeros(SHARE - 77, int), tile // 2, a, 3, np.zeros(3 * SHARE, int), tile // 2, np.zeros(9, int), 40 * SHARE]
     n = {"at the rule": 0, "beyond the rule": 1}[kind]   # three rows per entry, or three rows more
     return np.r_[np.ones(20_000, int), np.zeros(40_000 + 3 * n, int)]
 
 
 KINDS = ["one row", "one row of many tiles", "starts at tile borders", "empty rows around", "long runs of empty rows",
-         "last row of a round", "almost empty rows", "rows of a wave", "some tiles with empty rows", "zipf", "at the rule", "beyond the rule"]
+         "last row of a round", "almost empty rows", "rows of a wave", "some tiles with empty rows", "zipf", "at the rule", "beyond the rule",
+         "sorted by degree", "rows of many tiles among empty ones", "many shared tiles", "most rows of one workgroup", "borders of pieces"]
 
 
 @pytest.mark.parametrize("variant", ["mfma", "shuffle"])

@@ -16,7 +16,8 @@ BYTES, BITS = 0, 1
 
 @pytest.fixture(scope="module")
 def record(tmp_path_factory, libmmvseg_path):
-    """record(calls): what each of the calls (statements on `lib`, the loaded library) would have the device do."""
+    """record(calls): what each of the calls (statements on `lib`, the loaded library) would have the device do;
+    record(calls, grids=True): the launches with their numbers of workgroups."""
     so = str(tmp_path_factory.mktemp("hip") / "libhip_recorder.so")
     subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-Wall", "-o", so, "tests/hip_recorder.c"], cwd=ROOT, check=True, timeout=120)
     child = textwrap.dedent("""
@@ -33,7 +34,7 @@ def record(tmp_path_factory, libmmvseg_path):
             print("--", flush=True)
         """)
 
-    def run(calls):
+    def run(calls, grids=False):
         res = subprocess.run([sys.executable, "-c", child, so, libmmvseg_path], input=";".join(calls), capture_output=True, text=True, timeout=120)
         assert res.returncode == 0, res.stderr[-2000:]
         out = []
@@ -41,7 +42,8 @@ def record(tmp_path_factory, libmmvseg_path):
             lines = block.strip().split("\n")
             assert lines[0] == "status 0", block
             # "launch _ZN..12short_kernelI..E.. grid block" -> "short_kernel" (events stay as they are)
-            out.append([re.search(r"\d+([a-z_]+_kernel)", line).group(1) if line.startswith("launch") else line for line in lines[1:]])
+            names = [re.search(r"\d+([a-z_]+_kernel)", line).group(1) if line.startswith("launch") else line for line in lines[1:]]
+            out.append([(name, int(line.split()[2])) for name, line in zip(names, lines[1:])] if grids else names)
         return out
     return run
 
@@ -116,3 +118,14 @@ def test_lines_between_the_forms(record, call, want):
 def test_kernel_events_stand_around_all_that_reads_the_inputs(record, call, want):
     """... and behind what only resets the workspace, packs or counts flags."""
     assert record(["lib.mmv_set_kernel_events(vp(5), vp(7))", call])[1] == want
+
+
+@pytest.mark.parametrize("n_rows,nnz,tiles,helpers", [
+    (65_536, 1 << 20, 128, 8), (16_384, 1 << 20, 128, 0), (16_385, 1 << 20, 128, 3), (1 << 20, 1 << 25, 763, 128), (44_032, 1 << 25, 763, 0),
+    (44_033, 1 << 25, 763, 6), (1 << 20, (1 << 20) // 3, 43, 128), (49_152, 16_384, 2, 0), (49_152, 16_385, 3, 6),
+])
+def test_rows_of_a_csr_tile_are_shared(record, n_rows, nnz, tiles, helpers):
+    """One workgroup per tile is not enough where nearly all rows may start in one: a workgroup for every 8192 rows besides, from where a
+    tile can hold more than 16384 rows, more rows than entries and twice its part."""
+    prepare = "lib.mmv_spmv_csr_prepare(u64(%d), u64(100), u64(%d), vp(%d), vp(%d), vp(%d), size(1 << 40), None)" % (n_rows, nnz, X, F, WS)
+    assert record([prepare], grids=True)[0][0] == ("csr_plan_kernel", tiles + helpers)
