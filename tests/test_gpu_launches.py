@@ -1,5 +1,5 @@
-"""Calls whose launch ahead of the main kernel is gone or shared: a single tile (nothing is zeroed before it), byte flags
-(packed in the launch that zeroes, or that counts the segment starts), on workspaces full of garbage."""
+"""Calls on workspaces full of garbage: short vectors, before whose kernels nothing is zeroed (longer ones: test_gpu_single_pass.py),
+and the plans of two-step products, which any other call on their workspace ends."""
 import numpy as np
 import pytest
 import torch

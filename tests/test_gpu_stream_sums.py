@@ -147,7 +147,7 @@ def test_borders_of_the_form_for_short_vectors(variant):
     """256 tiles of 8 to 16 units, 512 (sums) of 8 to 16, 768 (sums without the matrix cores) of up to 16, and what lies
     just beyond each; ragged ends in the first and in the second unit of a wave."""
     rng = np.random.default_rng(74)
-    for n in [2 * UNIT + 3, 9 * UNIT + 5, 15 * UNIT - 1, 256 * 8 * UNIT, 256 * 8 * UNIT + 1, 256 * 11 * UNIT + 31, 256 * 16 * UNIT, 256 * 16 * UNIT + 1,
+    for n in [2 * UNIT + 3, 9 * UNIT + 5, 15 * UNIT - 1, 256 * 8 * UNIT, 256 * 8 * UNIT + 1, 256 * 11 * UNIT + 31, 3 * 1024 * UNIT + 1, 256 * 13 * UNIT + 31, 256 * 16 * UNIT, 256 * 16 * UNIT + 1,
               512 * 12 * UNIT + 7, 512 * 16 * UNIT + 1, 768 * 16 * UNIT, 768 * 16 * UNIT + 1]:
         x = rng.integers(-3, 4, size=n).astype(np.float32)
         for density in (0.0002, 0.3):
@@ -174,7 +174,8 @@ def test_borders_of_the_form_for_short_vectors(variant):
 
 
 @pytest.mark.parametrize("variant", ["mfma", "shuffle"])
-@pytest.mark.parametrize("n", [9 * 8 * UNIT + 700, 768 * 17 * UNIT + 900])       # the form for short vectors, the one for long ones
+# products in the form for short vectors and short sums, sums in that form, the form for long vectors
+@pytest.mark.parametrize("n", [9 * 8 * UNIT + 700, (3 << 20) + 700, 768 * 17 * UNIT + 900])
 def test_non_finite_values_reach_their_own_segment_and_those_of_their_row_of_32(variant, n):
     """Sums and products: a segment that holds an infinity or a NaN has a sum that is not finite, one that lies
     partly in the same (32-aligned) row may have, every other sum is as accurate as without them (within 2e-5 of the sum of

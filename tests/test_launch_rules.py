@@ -25,8 +25,8 @@ def holds(tmp_path, condition):
 @pytest.mark.parametrize("tiles,resident,first", [(1, 0, 1), (1, 1, 1), (1, 512, 1), (5, 0, 1), (5, 1, 1), (512, 512, 512),
                                                   (513, 512, 512), (4, 512, 4)])
 def test_the_first_workgroup_never_draws_a_ticket(tmp_path, tiles, resident, first):
-    """resident = 0: the query of how many workgroups the device holds has failed.  A single tile is launched
-    without a reset of the ticket."""
+    """resident = 0: the query of how many workgroups the device holds has failed; then one takes the tile of its own index, the
+    others tickets."""
     assert holds(tmp_path, "first_round_of(%d, %d) == %d" % (tiles, resident, first))
     assert not holds(tmp_path, "first_round_of(%d, %d) == 0" % (tiles, resident))
 
