@@ -117,8 +117,8 @@ inline TilePlan tile_plan(mmv_op op, mmv_dtype dt, uint64_t n, bool mfma = true)
         uint64_t resident = kComputeUnits / 2 * (uint64_t)stream_waves_per_simd(is_spmv(op) ? kSpmv : kSum, mfma);
         const uint64_t units = (n + kUnitElems - 1) / kUnitElems;
         // A short vector gets one workgroup per compute unit as long as the form for short tiles takes that (sums then two):
-        // with some of them holding two, it takes longer than with two units for a wave instead of one (sum of 3 * 10^6
-        // values: 366 tiles of 8 units 11.5 us, 245 tiles of 12 units 10.6; CSR SpMV of 2.5 M entries: 14.6 and 13.3).
+        // with some of them holding two, it takes longer than with two units for a wave instead of one (CSR SpMV of 2.5 M
+        // entries: 306 tiles of 8 units 14.6 us, 245 tiles of 10 units 13.3; sums so short have kernels of their own).
         // SpMV of 5 to 8 M entries in 512 short tiles: from 13 % faster (scattered) to 6 % slower (blocks of 16) than in 768.
         if (units <= kComputeUnits * kShortUnits) resident = kComputeUnits, p.short_form = true;
         else if (!is_spmv(op) && units <= 2 * kComputeUnits * kShortUnits) resident = 2 * kComputeUnits;

@@ -525,68 +525,68 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
                     const uint64_t row_any = __ballot(F[S] != 0);
 #pragma unroll
                     for (int t = 0; t < (kHalf ? 2 : 1); ++t) {   // the tiles one after the other, or both at once
-                    if constexpr (kHalf) make_rows(t, 0);
-                    // stored negated in the slot before x-bar(-1), so that the revert subtracts it
-                    if (!kHalf || (lane >> 5) == t) {
-                        uint32_t *mine = rows + (kHalf ? lane & 31 : lane) * kRowStride;
-                        mine[kSlotZero] = 0;
-                        mine[kSlotF] = F[S];
-                        mine[kSlotNegCarry] = to_bits(A(0) - carry);
-                    }
-                    wave_lds_sync();
+                        if constexpr (kHalf) make_rows(t, 0);
+                        // stored negated in the slot before x-bar(-1), so that the revert subtracts it
+                        if (!kHalf || (lane >> 5) == t) {
+                            uint32_t *mine = rows + (kHalf ? lane & 31 : lane) * kRowStride;
+                            mine[kSlotZero] = 0;
+                            mine[kSlotF] = F[S];
+                            mine[kSlotNegCarry] = to_bits(A(0) - carry);
+                        }
+                        wave_lds_sync();
 
-                    // ---- steps 2 + 6 on every element, then store; a lane owns 4 consecutive positions ----
+                        // ---- steps 2 + 6 on every element, then store; a lane owns 4 consecutive positions ----
 #pragma unroll
-                    for (int j = kHalf ? 4 * t : 0; j < (kHalf ? 4 * t + 4 : 8); ++j) {
-                        const int R = 8 * j + (lane >> 3), p0 = 4 * (lane & 7);
-                        const uint32_t *rp = rows + (kHalf ? R & 31 : R) * kRowStride;
-                        const v4u xb = *reinterpret_cast<const v4u *>(rp + kRowData + p0);
-                        A o[4];
-                        if (((row_any >> (8 * j)) & 0xFFull) == 0) {
-                            // none of these eight rows has a flag: the speculation stands, only the carry is added
-                            const A nc = from_bits<A>(rp[kSlotNegCarry]);
+                        for (int j = kHalf ? 4 * t : 0; j < (kHalf ? 4 * t + 4 : 8); ++j) {
+                            const int R = 8 * j + (lane >> 3), p0 = 4 * (lane & 7);
+                            const uint32_t *rp = rows + (kHalf ? R & 31 : R) * kRowStride;
+                            const v4u xb = *reinterpret_cast<const v4u *>(rp + kRowData + p0);
+                            A o[4];
+                            if (((row_any >> (8 * j)) & 0xFFull) == 0) {
+                                // none of these eight rows has a flag: the speculation stands, only the carry is added
+                                const A nc = from_bits<A>(rp[kSlotNegCarry]);
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) o[i] = from_bits<A>(xb[i]) - nc;
-                        } else {
-                            const uint32_t Fr = rp[kSlotF];
-                            const uint32_t m = Fr & ((2u << p0) - 1u);  // flags at or before my first position
-                            const int slot = m ? kSlotZero + (31 - __clz(m)) : kSlotNegCarry;
-                            A b = from_bits<A>(rp[slot]);
-                            o[0] = from_bits<A>(xb[0]) - b;
-                            if constexpr (kExactStarts) {
-                                const v4u xr = kKeepRows ? striped[kKeepRows ? j : 0] : raw[S][j];   // my four inputs
-                                bool restarted = ((Fr >> p0) & 1u) != 0;
-                                if (restarted) o[0] = from_bits<A>(xr[0]);
+                                for (int i = 0; i < 4; ++i) o[i] = from_bits<A>(xb[i]) - nc;
+                            } else {
+                                const uint32_t Fr = rp[kSlotF];
+                                const uint32_t m = Fr & ((2u << p0) - 1u);  // flags at or before my first position
+                                const int slot = m ? kSlotZero + (31 - __clz(m)) : kSlotNegCarry;
+                                A b = from_bits<A>(rp[slot]);
+                                o[0] = from_bits<A>(xb[0]) - b;
+                                if constexpr (kExactStarts) {
+                                    const v4u xr = kKeepRows ? striped[kKeepRows ? j : 0] : raw[S][j];   // my four inputs
+                                    bool restarted = ((Fr >> p0) & 1u) != 0;
+                                    if (restarted) o[0] = from_bits<A>(xr[0]);
 #pragma unroll
-                                for (int i = 1; i < 4; ++i) {
-                                    const A x = from_bits<A>(xr[i]);
-                                    if ((Fr >> (p0 + i)) & 1u) {
-                                        o[i] = x;
-                                        restarted = true;
-                                    } else {
-                                        o[i] = restarted ? o[i - 1] + x : from_bits<A>(xb[i]) - b;
+                                    for (int i = 1; i < 4; ++i) {
+                                        const A x = from_bits<A>(xr[i]);
+                                        if ((Fr >> (p0 + i)) & 1u) {
+                                            o[i] = x;
+                                            restarted = true;
+                                        } else {
+                                            o[i] = restarted ? o[i - 1] + x : from_bits<A>(xb[i]) - b;
+                                        }
+                                    }
+                                } else {
+#pragma unroll
+                                    for (int i = 1; i < 4; ++i) {
+                                        if ((Fr >> (p0 + i)) & 1u) b = from_bits<A>(xb[i - 1]);
+                                        o[i] = from_bits<A>(xb[i]) - b;
                                     }
                                 }
+                            }
+                            const uint64_t e0 = cb + 256u * j + 4u * lane;
+                            A *z = (A *)P.z;
+                            if (chunk_full) {
+                                v4u w = {to_bits(o[0]), to_bits(o[1]), to_bits(o[2]), to_bits(o[3])};
+                                __builtin_nontemporal_store(w, reinterpret_cast<v4u *>(z + e0));
                             } else {
 #pragma unroll
-                                for (int i = 1; i < 4; ++i) {
-                                    if ((Fr >> (p0 + i)) & 1u) b = from_bits<A>(xb[i - 1]);
-                                    o[i] = from_bits<A>(xb[i]) - b;
-                                }
+                                for (int i = 0; i < 4; ++i)
+                                    if (e0 + i < n) z[e0 + i] = o[i];
                             }
                         }
-                        const uint64_t e0 = cb + 256u * j + 4u * lane;
-                        A *z = (A *)P.z;
-                        if (chunk_full) {
-                            v4u w = {to_bits(o[0]), to_bits(o[1]), to_bits(o[2]), to_bits(o[3])};
-                            __builtin_nontemporal_store(w, reinterpret_cast<v4u *>(z + e0));
-                        } else {
-#pragma unroll
-                            for (int i = 0; i < 4; ++i)
-                                if (e0 + i < n) z[e0 + i] = o[i];
-                        }
-                    }
-                    if (kHalf && t == 0) wave_lds_sync();   // the rows are read before the next tile overwrites them
+                        if (kHalf && t == 0) wave_lds_sync();   // the rows are read before the next tile overwrites them
                     }
                 } else {
                     // ---- sum: only the segment ends produce output; the lane that owns a row

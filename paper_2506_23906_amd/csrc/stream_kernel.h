@@ -51,10 +51,10 @@ constexpr int kUnitRows = 32;
 // both its units loaded before the first is worked on.  In the other form the loads of its second unit are waited for behind
 // the stores of the first (one counter counts both in order, and the number of stores is not known), and the table lookups,
 // which stand in branches, ahead of the first value.  Whole calls in a graph, one chunk of 2048 elements per wave as in
-// seg_tile / the form for long vectors / this one (sums: matrix cores, 1 % of the values start a segment):
-//   sum of 3 * 10^5 values    9.0 /  9.4 /  9.0 us        sum of 2^22 values   11.3 / 13.0 / 11.7
-//   sum of 3 * 10^6          10.9 / 12.6 / 10.9           sum of 2^23          13.3 / 16.0 / 14.1
-//   ... 30 % starts          14.5 / 13.8 / 12.7           ... 30 % starts      21.7 / 19.5 / 18.2
+// seg_tile / the form for long vectors / this one (sums: matrix cores, 1 % of the values start a segment; up to 3 * 2^20 values they
+// come here only with the output over an input, see short_call):
+//   sum of 2^22 values   11.3 / 13.0 / 11.7               sum of 2^23          13.3 / 16.0 / 14.1
+//                                                         ... 30 % starts      21.7 / 19.5 / 18.2
 //   CSR SpMV, prepared, 3.9 M entries in blocks of 4   15.4 / 16.2 / 15.3;  3.5 M in blocks of 16   14.8 / 15.5 / 14.7
 // (2^22 and 2^23 fill the rounds of seg_tile exactly; there, with few starts, one chunk per wave in seg_tile was 4 to 6 %
 // ahead.)
