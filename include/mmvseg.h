@@ -89,8 +89,8 @@ typedef enum {
     MMV_VARIANT_MFMA = 0,   /* matrix cores: tile times triangular ones matrix, s = 32 */
     MMV_VARIANT_SHUFFLE = 1, /* ablation: same rows scanned with vector adds and lane shuffles.  Short vectors take the
                                 same kernels with either: they are bound by launches, and a product would only add its
-                                latency.  Short are scans and sums of up to 2^21 elements (16-bit mmv_segscan: 3 * 2^19, fp32
-                                sums and 16-bit mmv_scan: 3 * 2^20, other mmv_scan: 2^22) whose output overlaps no input
+                                latency.  Short are scans and sums of up to 2^21 elements (fp32 sums and
+                                16-bit mmv_scan: 3 * 2^20, other mmv_scan: 2^22) whose output overlaps no input
                                 (a scan's fp32 values may be its output) */
     MMV_VARIANT_INT_MAX = 0x7fffffff
 } mmv_variant;
@@ -132,7 +132,7 @@ size_t mmv_spmv_csr_workspace_bytes(uint64_t n_rows, uint64_t nnz);
  * rounding of its own segment alone, so a segment of small values behind large ones in the same row of 32
  * loses relative accuracy.  (Short vectors, see MMV_VARIANT_SHUFFLE, are scanned without speculation: there a result depends on
  * its own segment alone, and floats are added up in 64 bits and rounded at the end; beyond 320 KB of values and flags the sums of whole
- * tiles of 2048 elements are rounded to 32 bits on the way, beyond 256 KB with 16-bit values.)
+ * tiles of 2048 elements are rounded to 32 bits on the way.)
  * With fp32 inputs a position that starts a segment receives its input bit for bit.
  * An infinity or NaN makes the rest of its own segment non-finite, as the definition does, and can in addition turn
  * other positions of the same row of 32 and the segments that begin behind it in that row into NaN (Inf - Inf; not in

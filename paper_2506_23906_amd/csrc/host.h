@@ -438,7 +438,7 @@ template <typename TT, int kOp, int kFlags> hipError_t launch_short(const ShortP
     }
     const uint64_t bytes = S.n * elem_bytes(TT::kDtype) + (kFlags == kNoFlags ? 0 : flag_bytes(kFlags == kByteFlags ? MMV_FLAGS_U8 : MMV_FLAGS_PACKED32, S.n));
     if (!single) short_kernel<TT, kOp, kFlags, false, kShortThreads><<<tiles, kShortThreads, 0, s>>>(S);
-    else if (bytes < many_bytes(kFlags != kNoFlags)) short_kernel<TT, kOp, kFlags, true, kShortThreads><<<tiles, kShortThreads, 0, s>>>(S);
+    else if (bytes < many_bytes(TT::kDtype, kFlags)) short_kernel<TT, kOp, kFlags, true, kShortThreads><<<tiles, kShortThreads, 0, s>>>(S);
     else short_kernel<TT, kOp, kFlags, true, kManyThreads><<<tiles, kManyThreads, 0, s>>>(S);
     const hipError_t e = hipGetLastError();
     if (tl_ev_stop && hipEventRecord(tl_ev_stop, s) != hipSuccess) return hipErrorUnknown;
@@ -464,7 +464,7 @@ inline ShortRoute short_route(mmv_op op, mmv_dtype dt, mmv_flag_fmt ff, uint64_t
     const uint64_t xb = n * elem_bytes(dt), fb = flags ? flag_bytes(ff, n) : 0;
     if (flags && overlap(out, out_bytes, flags, fb)) return kSinglePass;
     if (overlap(out, out_bytes, x, xb)) return op != MMV_OP_SEGSUM && out == x ? kTwoLaunches : kSinglePass;
-    return xb + fb <= single_bytes(dt, flags != nullptr) ? kOneLaunch : kTwoLaunches;
+    return xb + fb <= MMV_SINGLE_BYTES ? kOneLaunch : kTwoLaunches;
 }
 template <int kOp>
 mmv_status short_call(const void *d_x, const void *d_flags, uint64_t n, void *d_z, void *d_out, uint64_t out_cap, uint64_t *d_nseg,

@@ -19,48 +19,54 @@ namespace {
 // Measured, whole calls in a graph, on other inputs every time (together beyond every cache) and, in brackets, on the same, the
 // single-pass kernel -> one launch / two (us):
 //   segmented scan, fp32, byte flags, 1 of 64 set    3000: 8.5 -> 3.2 / 5.2 (7.7 -> 2.9 / 5.0)   65536: 9.3 -> 4.3 / 5.6 (9.2 -> 3.7 / 5.2)
-//   ... no flags, packed                             3000: 6.3 -> 3.6 / 5.2 (5.8 -> 3.0 / 4.7)   65536: 8.3 -> 6.6 / 5.4 (7.9 -> 5.5 / 5.0)
-//   segmented sum, fp16, packed, 1 of 1000 set       3000: 6.4 -> 3.1 / 4.9 (6.1 -> 3.0 / 4.8)  105000: 8.0 -> 4.3 / 6.0 (7.0 -> 3.8 / 5.3)
+//   ... no flags, packed                             3000: 6.3 -> 3.6 / 5.2 (5.8 -> 3.0 / 4.7)   65536: 9.0 -> 7.4 / 5.4 (8.3 -> 5.8 / 5.0)
+//   segmented sum, fp16, packed, 1 of 1000 set       3000: 6.4 -> 3.1 / 4.9 (6.1 -> 3.0 / 4.8)  105000: 8.4 -> 4.7 / 6.0 (8.0 -> 3.8 / 5.3)
 //   scan, fp32                                       3000: 7.7 -> 2.8 / 4.2 (7.2 -> 2.4 / 3.9)   65536: 10.4 -> 5.2 / 4.5 (10.0 -> 4.3 / 4.2)
 // Where the lines lie (figures on other inputs every time unless said otherwise).
 // One launch, MMV_SINGLE_BYTES: with flags anywhere near it is ahead of two (65536 fp32 values, 1 of 1000 set: 4.2 / 5.4); without any
 // flag set a workgroup reads all that lies before its tile, and two are ahead from 20000 to 80000 elements on.  The host does
-// not know the flags: the line lies where the worst of them is not slower than the single-pass kernel (none set, single-pass -> one
-// launch: fp32 sum, byte flags, 65536 8.1 -> 7.1; bytes, 160000 8.4 -> 7.0; fp16, packed, 105000 8.0 -> 7.3).  16-bit values take as
-// many conversions as 32-bit ones in half the bytes: 145000 in a sum, repeated, 7.1 -> 7.6, so their line is lower where there are flags.
+// not know the flags: the line lies where the worst of them come out level with the single-pass kernel (none set, single-pass -> one
+// launch: fp32 sum, byte flags, 65536 8.1 -> 7.1; bytes, 160000 8.4 -> 7.0; fp16, packed, 118000 8.6 -> 9.0, 131072 8.4 -> 7.9, 150000
+// 8.4 -> 8.4, repeated 8.0 -> 7.9, 8.0 -> 7.1, 8.0 -> 7.7).
 // Two launches, short_max: up to 2^21 elements nearly everything gains (350000 to 1.5 million fp32 11 -> 6.5 to 9, segmented scan of bytes, 2^21
-// 11.2 -> 9.0); 16-bit segmented scans, 1 of 100 set, 1.5 million 9.6 -> 9.1, 2^21 9.5 -> 10.2: up to 3 * 2^19.  Beyond, where
-// the data read twice show: scans without flags of 2^22, fp32 15.0 -> 14.3, bytes 12.1 -> 12.2, 16-bit, 3 * 2^20 12.1 -> 11.0 (2^22 11.9 -> 12.3);
+// 11.2 -> 9.0).  The least gain have 16-bit segmented scans, whose time in the single-pass kernel is that of whole tiles or
+// of a ragged last one: bits, 1 of 1000 set, 1900000 10.1 -> 9.7 (repeated 9.8 -> 8.6), 2080000 10.6 -> 10.0 (9.7 -> 8.7), but 2^21
+// 9.1 -> 9.9 (8.9 -> 8.7; none set 10.2 -> 9.8, 10.3 -> 8.7).  Beyond, where the data read twice show: scans without flags of 2^22, fp32 15.0 -> 14.3, bytes 12.1 -> 12.2, 16-bit, 3 * 2^20 12.1 -> 11.0 (2^22 11.9 -> 12.3);
 // fp32 sums, 3 * 2^20, 1 of 1000 set 11.9 -> 11.5, 1 of 5 12.4 -> 12.4 (2^22 11.3 -> 12.0).  Segmented scans (2^22: 11.6 -> 11.9, bytes
 // 10.8 -> 11.2) and sums of bytes stay at 2^21.  Four elements per thread: level up to 2^19, 10 % slower at 2^21; sixteen: 20 % slower there.
 constexpr int kShortThreads = 256, kShortWaves = kShortThreads / 64;
 constexpr int kShortElems = 8;                                  // consecutive elements of a thread
 constexpr uint32_t kShortTile = kShortThreads * kShortElems;
-// Threads of a workgroup of the one launch from so many bytes of values and flags on: those beyond kShortThreads only help with what
+// Threads of a workgroup of the one launch from so many bytes of values and flags on (many_bytes): those beyond kShortThreads only help with what
 // lies before the tile.  Calls as above, on other inputs every time, the single-pass kernel / 256 threads / 1024:
 //   segmented scan, fp32, byte flags, 65536: none set 8.8 / 10.0 / 6.8, 1 of 64 9.3 / 5.8 / 4.3;  bits, none set 8.3 / 7.9 / 6.6
 //   segmented sum, byte flags, none set: fp32, 65536 8.1 / 10.3 / 7.1; fp16, 105000 8.3 / 11.8 / 7.7; bytes, 160000 8.4 / 12.1 / 7.0
 //   scan, fp32, 65536 10.4 / 5.9 / 5.2;  20000 11.4 / 4.4 / 3.9
-// With 256 a vector whose segments reach far back took up to 45 % longer than the single-pass kernel.  Below the lines sixteen waves
-// cost more than they bring (sums of 3000 values 3.0 / 3.3 with the inputs in the L2, fp16 with byte flags, 20000 3.8 / 4.5).
+// With 256 a vector whose segments reach far back took up to 45 % longer than the single-pass kernel.  But sixteen waves start later
+// and have more to exchange, 0.1 (bytes) to 0.5 us (fp32), and where a flag is near they bring nothing: segmented scan with bits,
+// fp32, 20000, 1 of 64 set, 256 threads / 1024, repeated on the same inputs, 2.9 / 3.5, 65536 3.1 / 3.6; bytes 65536 3.0 / 3.1; with
+// byte flags, more of which every workgroup reads, fp32 20000 3.4 / 3.8, 40960 3.7 / 3.8.  So the lines lie where these calls come
+// out level, with bits where those without any flag set begin to fall behind the single-pass kernel (segmented sums of none set,
+// single-pass / 256: fp32 65536 8.2 / 7.8, 79000 8.6 / 8.8; fp16 105000 8.3 / 8.5, 118000 8.6 / 9.0).  Without flags: where a second or third
+// tile begins (scan, 256 threads / 1024, fp16 4096 2.5 / 2.6, 5000 3.1 / 2.7; bytes 6000 2.3 / 2.4, 7000 2.7 / 2.4).
 constexpr int kManyThreads = 1024;
-constexpr uint64_t many_bytes(bool flags) { return (flags ? 64u : 16u) << 10; }
 #ifndef MMV_SINGLE_BYTES
 #define MMV_SINGLE_BYTES (320u << 10)   // most values and flags, in bytes, of a vector that one launch takes
 #endif
+enum ShortFlags { kNoFlags = 0, kBitFlags = 1, kByteFlags = 2 };
 constexpr bool is_16_bit(mmv_dtype dt) { return dt == MMV_F16_F32 || dt == MMV_BF16_F32; }
-constexpr uint64_t single_bytes(mmv_dtype dt, bool flags) { return flags && is_16_bit(dt) ? MMV_SINGLE_BYTES / 5 * 4 : MMV_SINGLE_BYTES; }
+constexpr uint64_t many_bytes(mmv_dtype dt, int flags) {
+    constexpr uint64_t kb[3][3] = {{9, 9, 7}, {288, 240, 96}, {160, 128, 80}};   // no flags, bits, bytes; values of 4, 2, 1 bytes
+    return kb[flags][dt == MMV_F32_F32 ? 0 : is_16_bit(dt) ? 1 : 2] << 10;
+}
 #ifndef MMV_SHORT_MAX
 #define MMV_SHORT_MAX (1u << 21)        // most elements that two launches take
 #endif
 constexpr uint64_t short_max(mmv_op op, mmv_dtype dt) {
     const uint64_t n = MMV_SHORT_MAX;
     if (op == MMV_OP_SCAN) return is_16_bit(dt) ? n / 2 * 3 : 2 * n;
-    if (op == MMV_OP_SEGSCAN) return is_16_bit(dt) ? n / 4 * 3 : n;
     return op == MMV_OP_SEGSUM && dt == MMV_F32_F32 ? n / 2 * 3 : n;
 }
-
-enum ShortFlags { kNoFlags = 0, kBitFlags = 1, kByteFlags = 2 };
 
 struct ShortParams {
     const void *x;

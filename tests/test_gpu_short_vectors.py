@@ -1,6 +1,5 @@
 """Scans and sums of short vectors: one launch (the sum carried into a tile comes from the input itself) up to 320 KB of
-values and flags (16-bit values with flags: 256 KB), two (from the aggregates of the tiles before) up to 2^21 elements (16-bit segmented scans 3 * 2^19,
-fp32 sums and 16-bit mmv_scan 3 * 2^20, other mmv_scan 2^22), the single-pass kernels beyond.  Tiles have 2048 elements, a thread takes eight, a wave 512; whole numbers, so results are exact."""
+values and flags, two (from the aggregates of the tiles before) up to 2^21 elements (fp32 sums and 16-bit mmv_scan 3 * 2^20, other mmv_scan 2^22), the single-pass kernels beyond.  Tiles have 2048 elements, a thread takes eight, a wave 512; whole numbers, so results are exact."""
 import numpy as np
 import pytest
 import torch
@@ -15,10 +14,13 @@ TYPES = {"f32": (torch.float32, B.MMV_F32_F32), "f16": (torch.float16, B.MMV_F16
          "i8": (torch.int8, B.MMV_I8_I32), "u8": (torch.uint8, B.MMV_U8_XOR)}
 
 
+MANY_BITS, MANY_BYTES = {4: 288, 2: 240, 1: 96}, {4: 160, 2: 128, 1: 80}      # KB, by the size of a value
+
+
 def one_launch(dt, flag_bytes):
     """Most elements that one launch takes (8 * flag_bytes: bits of flags per element)."""
     size = torch.empty(0, dtype=TYPES[dt][0]).element_size()
-    return int(((256 if size == 2 else 320) << 10) / (size + flag_bytes)) // 32 * 32
+    return int((320 << 10) / (size + flag_bytes)) // 32 * 32
 
 
 def values(rng, n, dt):
@@ -237,14 +239,15 @@ def test_outputs_over_byte_flags(n):
 @pytest.mark.parametrize("packed", [True, False])
 @pytest.mark.parametrize("dt", list(TYPES))
 def test_single_flags_where_more_waves_help(dt, packed):
-    """One launch with 1024 threads from 64 KB of values and flags on (16 KB without flags): both sides of these lines, and the
+    """One launch with 1024 threads from so many bytes of values and flags on (MANY_BITS, MANY_BYTES; 7 or 9 KB without flags): both sides of these lines, and the
     start of the last segment at borders of the 128-bit words, just inside and outside what the threads hold from the
     beginning (one word each before the tile), and far back."""
     rng = np.random.default_rng(2390708)
     size = torch.empty(0, dtype=TYPES[dt][0]).element_size()
     per_elem, epl = size + (1 / 8 if packed else 1), 16 // size
-    line = int((64 << 10) / per_elem)
-    for n in (int((16 << 10) / size) // epl * epl - epl, (16 << 10) // size, line - 1, line + 1, one_launch(dt, per_elem - size) - 3):
+    scan_line = ((7 if size == 1 else 9) << 10) // size
+    line = int(((MANY_BITS if packed else MANY_BYTES)[size] << 10) / per_elem)
+    for n in (scan_line - epl, scan_line - 1, scan_line, line - 1, line + 1, one_launch(dt, per_elem - size) - 3):
         last_tile = (n - 1) // TILE * TILE
         near = 1024 * epl                                              # elements that the threads hold
         at = {1, epl - 1, epl, 5 * epl + 1, TILE - 1, TILE, TILE + epl // 2}

@@ -21,7 +21,7 @@ TILE = 65536          # largest workgroup tile (bytes)
 def first_beyond(op, dt):
     """The shortest length that takes the single-pass kernels."""
     code = B._DTYPES[TYPES[dt]]
-    for n in (3 << 19, 1 << 21, 3 << 20, 1 << 22):
+    for n in (1 << 21, 3 << 20, 1 << 22):
         if B.mmv_tile_elems(op, code, n) == SHORT_TILE and B.mmv_tile_elems(op, code, n + 1) != SHORT_TILE:
             return n + 1
     raise AssertionError("no line found")

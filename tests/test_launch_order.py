@@ -17,7 +17,7 @@ BYTES, BITS = 0, 1
 @pytest.fixture(scope="module")
 def record(tmp_path_factory, libmmvseg_path):
     """record(calls): what each of the calls (statements on `lib`, the loaded library) would have the device do;
-    record(calls, grids=True): the launches with their numbers of workgroups."""
+    record(calls, grids=True): the launches with their workgroups and the threads of each."""
     so = str(tmp_path_factory.mktemp("hip") / "libhip_recorder.so")
     subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-Wall", "-o", so, "tests/hip_recorder.c"], cwd=ROOT, check=True, timeout=120)
     child = textwrap.dedent("""
@@ -43,7 +43,7 @@ def record(tmp_path_factory, libmmvseg_path):
             assert lines[0] == "status 0", block
             # "launch _ZN..12short_kernelI..E.. grid block" -> "short_kernel" (events stay as they are)
             names = [re.search(r"\d+([a-z_]+_kernel)", line).group(1) if line.startswith("launch") else line for line in lines[1:]]
-            out.append([(name, int(line.split()[2])) for name, line in zip(names, lines[1:])] if grids else names)
+            out.append([(name, *map(int, line.split()[2:])) for name, line in zip(names, lines[1:])] if grids else names)
         return out
     return run
 
@@ -99,13 +99,26 @@ def test_overlapping_outputs_take_the_launches_they_are_safe_in(record, call, wa
 
 @pytest.mark.parametrize("call,want", [
     (segscan(65_536, F32, BYTES, OUT), ONE), (segscan(65_537, F32, BYTES, OUT), TWO), (segsum(163_840, I8, BYTES, OUT), ONE), (segsum(163_841, I8, BYTES, OUT), TWO),
-    (segsum(87_381, F16, BYTES, OUT), ONE), (segsum(87_382, F16, BYTES, OUT), TWO), (segscan(123_328, F16, BITS, OUT), ONE), (segscan(123_392, F16, BITS, OUT), TWO),
+    (segsum(109_226, F16, BYTES, OUT), ONE), (segsum(109_227, F16, BYTES, OUT), TWO), (segscan(154_176, F16, BITS, OUT), ONE), (segscan(154_240, F16, BITS, OUT), TWO),
     (scan(163_840, F16, OUT), ONE), (scan(163_841, F16, OUT), TWO), (scan(3 << 20, F16, OUT), TWO), (scan((3 << 20) + 1, F16, OUT), FILL),
-    (segscan(3 << 19, F16, BYTES, OUT), TWO), (segscan((3 << 19) + 1, F16, BYTES, OUT), PACK), (segscan((3 << 19) + 1, F32, BYTES, OUT), TWO),
-    (segsum((3 << 19) + 1, F16, BITS, OUT), TWO), (segsum(3 << 20, F32, BITS, OUT), TWO), (segsum((3 << 20) + 1, F32, BITS, OUT), [COUNT, "stream_kernel"]),
+    (segscan(1 << 21, F16, BYTES, OUT), TWO), (segscan((1 << 21) + 1, F16, BYTES, OUT), PACK), (segscan((1 << 21) + 1, F32, BITS, OUT), FILL),
+    (segsum(1 << 21, F16, BITS, OUT), TWO), (segsum(3 << 20, F32, BITS, OUT), TWO), (segsum((3 << 20) + 1, F32, BITS, OUT), [COUNT, "stream_kernel"]),
 ])
 def test_lines_between_the_forms(record, call, want):
     assert record([call]) == [want]
+
+
+@pytest.mark.parametrize("call,threads", [
+    (segscan(20_000, F32, BITS, OUT), 256), (segscan(65_536, F32, BITS, OUT), 256), (segscan(71_500, F32, BITS, OUT), 1024),
+    (segsum(32_767, F32, BYTES, OUT), 256), (segsum(32_768, F32, BYTES, OUT), 1024), (segsum(40_966, F16, BITS, OUT), 256),
+    (segsum(115_600, F16, BITS, OUT), 256), (segsum(115_700, F16, BITS, OUT), 1024), (segscan(43_690, F16, BYTES, OUT), 256), (segscan(43_691, F16, BYTES, OUT), 1024),
+    (segscan(87_300, I8, BITS, OUT), 256), (segscan(87_400, I8, BITS, OUT), 1024), (segsum(40_959, I8, BYTES, OUT), 256),
+    (segsum(40_960, I8, BYTES, OUT), 1024), (scan(2_303, F32, OUT), 256), (scan(2_304, F32, OUT), 1024),
+    (scan(7_167, I8, OUT), 256), (scan(7_168, I8, OUT), 1024),
+])
+def test_threads_of_the_one_launch(record, call, threads):
+    """The twelve waves more that read what lies before a tile pay only where a workgroup may have much to read."""
+    assert record([call], grids=True)[0][0][::2] == ("short_kernel", threads)
 
 
 @pytest.mark.parametrize("call,want", [
@@ -128,4 +141,4 @@ def test_rows_of_a_csr_tile_are_shared(record, n_rows, nnz, tiles, helpers):
     """One workgroup per tile is not enough where nearly all rows may start in one: a workgroup for every 8192 rows besides, from where a
     tile can hold more than 16384 rows, more rows than entries and twice its part."""
     prepare = "lib.mmv_spmv_csr_prepare(u64(%d), u64(100), u64(%d), vp(%d), vp(%d), vp(%d), size(1 << 40), None)" % (n_rows, nnz, X, F, WS)
-    assert record([prepare], grids=True)[0][0] == ("csr_plan_kernel", tiles + helpers)
+    assert record([prepare], grids=True)[0][0] == ("csr_plan_kernel", tiles + helpers, 256)
