@@ -91,7 +91,8 @@ typedef enum {
                                 same kernels with either: they are bound by launches, and a product would only add its
                                 latency.  Short are scans and sums of up to 2^21 elements (fp32 sums and
                                 16-bit mmv_scan: 3 * 2^20, other mmv_scan: 2^22) whose output overlaps no input
-                                (a scan's fp32 values may be its output) */
+                                (a scan's fp32 values may be its output).  Scans of fp32 values of any length take the same
+                                kernel with either as well, without speculation: sums from lane to lane, carried in 64 bits */
     MMV_VARIANT_INT_MAX = 0x7fffffff
 } mmv_variant;
 
@@ -130,14 +131,15 @@ size_t mmv_spmv_csr_workspace_bytes(uint64_t n_rows, uint64_t nnz);
  * the method subtracts two speculative prefixes of a row of 32 elements: a result is off by the rounding of that
  * row's prefix (about 32 * 2^-24 of the row's sum of |x|; the carries add one rounding per level), not by the
  * rounding of its own segment alone, so a segment of small values behind large ones in the same row of 32
- * loses relative accuracy.  (Short vectors, see MMV_VARIANT_SHUFFLE, are scanned without speculation: there a result depends on
- * its own segment alone, and floats are added up in 64 bits and rounded at the end; beyond 320 KB of values and flags the sums of whole
- * tiles of 2048 elements are rounded to 32 bits on the way.)
+ * loses relative accuracy.  (Short vectors and scans of fp32 values, see MMV_VARIANT_SHUFFLE, are scanned without speculation: there
+ * a result depends on its own segment alone.  Short vectors are added up in 64 bits and rounded at the end; beyond 320 KB of values and
+ * flags the sums of whole tiles of 2048 elements are rounded to 32 bits on the way.  Longer scans of fp32 values add up four values at
+ * a time in 32 bits, and those sums in 64.)
  * With fp32 inputs a position that starts a segment receives its input bit for bit.
  * An infinity or NaN makes the rest of its own segment non-finite, as the definition does, and can in addition turn
  * other positions of the same row of 32 and the segments that begin behind it in that row into NaN (Inf - Inf; not in
- * short vectors);
- * positions outside that row are not affected unless one of these segments reaches them.  A block of 2048 positions that all start segments is copied exactly. */
+ * short vectors, nor in scans of fp32 values);
+ * positions outside that row are not affected unless one of these segments reaches them. */
 mmv_status mmv_segscan(const void *d_x, const void *d_flags, uint64_t n, void *d_z,
                        mmv_dtype dt, mmv_flag_fmt ff, mmv_variant v,
                        void *d_ws, size_t ws_bytes, void *hip_stream);

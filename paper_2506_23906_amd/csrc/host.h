@@ -43,7 +43,7 @@ template <typename TT> inline int row_form_cpw_of(mmv_op op, bool mfma) {
 }
 inline int row_form_cpw(mmv_op op, mmv_dtype dt, bool mfma) {
     switch (dt) {
-        case MMV_F32_F32: return row_form_cpw_of<TF32>(op, mfma);
+        case MMV_F32_F32: return op == MMV_OP_SCAN ? lane_cpw<kPlainScan>() : lane_cpw<kScan>();   // (lane_tile)
         case MMV_F16_F32: return row_form_cpw_of<TF16>(op, mfma);
         case MMV_BF16_F32: return row_form_cpw_of<TBF16>(op, mfma);
         case MMV_I8_I32: return row_form_cpw_of<TI8>(op, mfma);
@@ -377,6 +377,8 @@ template <typename TT, int kOp, bool kMfma> hipError_t launch_variant(Params P, 
         if constexpr (kOp != kSum) {
             if (!narrow) kernel = stream_kernel<TT, kOp, kMfma, false, false>;
         }
+    } else if constexpr (sizeof(typename TT::in_t) == 4) {
+        kernel = seg_kernel<InLanes<TT>, kOp, false>;   // (both variants)
     } else {
         kernel = seg_kernel<TT, kOp, kMfma>;
         if constexpr (has_round_form<TT, kOp, kMfma>()) {

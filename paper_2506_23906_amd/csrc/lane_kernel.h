@@ -1,0 +1,256 @@
+// libmmvseg, part of the one translation unit mmvseg.hip (included there, in order).
+// The tile body of the scans of 32-bit values: a tile stays in registers, and its sums go from lane to lane.
+#pragma once
+
+namespace {
+
+// ---- scans of 32-bit values ------------------------------------------------------------------------------------------
+//
+// The roles are those of seg_tile (aggregate, descriptor, look-back, carry, store), but there is no speculation to take back: a wave
+// takes 256 elements at a time, four consecutive ones per lane as the 128-bit loads and stores have them, and the segmented pair goes
+// from element to element inside a lane and from lane to lane by DPP moves, so a result depends on its own segment alone.
+// The aggregate of a wave is the plain sum of what lies behind its last flag (a scalar position), which costs next to nothing, so a
+// tile publishes it as soon as its loads have landed, and only then makes its results.  Nothing but the words that the waves exchange
+// is in LDS.  (Row scans on the matrix cores need every value split three ways, the operand layout and the results moved
+// through LDS, and 112 registers of which a wave's values are 32: they took longer in both variants, which share this kernel.)
+// Sums are carried in 64 bits from lane to lane, from block to block and between tiles (wide_store); a result is rounded when the
+// carry into a lane is, and when it is added.  Error against 64 bits (2-norms), row scans -> now: 1 of 27 starts 6.8e-8 -> 5.0e-8, no
+// flags 2.2e-7 -> 3.9e-8; a start receives its input bit for bit.
+// What bounds it: the memory, at its rate for as much read as written.  Whole calls, the reset launch of 5 us included, row scans in LDS
+// (matrix cores) -> now: 2^27 values, half of them starts, a quarter one segment, the rest in short segments 197 -> 181 us; 1.5 * 10^8 in
+// segments of 80 214 -> 196 (6.4 TB/s without the reset), 5.2 * 10^7 without flags 83 -> 72; 8.2 * 10^6 21 -> 17; mmv_scan of 5 * 10^7 77.5 -> 72, 1.5 * 10^8 217 -> 197.
+// Tiles: 8 blocks per wave and three workgroups per compute unit (16 and two: lengths up to 2000, 9 * 10^7 127 us against 123; eight
+// waves per SIMD: 3 % slower); without flags every tile waits for all those before it, and longer ones pay: 16 blocks (5 * 10^7 72 us; 8: 76, 24: 75).
+
+constexpr int kBlockElems = 256;                             // four consecutive elements per lane
+constexpr int kChunkBlocks = kChunkElems / kBlockElems;
+
+template <int kWaves> struct LaneShared {
+    double wave_v[kWaves], carry;
+    uint32_t wave_f[kWaves];
+    uint32_t tile, ready, arrived;
+};
+
+// Lanes that must not take the value of the lane 1, 2, 4, 8 before them, of lane 15 of the row of lanes before theirs, of lane 31: a
+// flagged lane lies between.  (Scalars.)
+struct ScanMasks {
+    uint64_t shr1, shr2, shr4, shr8, bcast15, bcast31;
+};
+__device__ __forceinline__ ScanMasks scan_masks(uint64_t m) {   // m: the lanes that hold a flag
+    constexpr uint64_t kRow = 0x0001000100010001ull;            // first lanes of the rows of 16
+    ScanMasks k;
+    k.shr1 = m;
+    k.shr2 = k.shr1 | ((k.shr1 << 1) & ~kRow);
+    k.shr4 = k.shr2 | ((k.shr2 << 2) & ~(kRow * 0x3));
+    k.shr8 = k.shr4 | ((k.shr4 << 4) & ~(kRow * 0xF));
+    k.bcast15 = (k.shr8 | ((k.shr8 << 8) & ~(kRow * 0xFF))) | 0x0000FFFF0000FFFFull;   // (rows 0 and 2 take nothing)
+    const uint32_t hi = (uint32_t)(m >> 32);
+    k.bcast31 = ((uint64_t)(hi ? ~0u << __builtin_ctz(hi) : 0u) << 32) | 0xFFFFFFFFull;
+    return k;
+}
+template <int kCtrl, typename V> __device__ __forceinline__ V dpp_bound(V v) {   // a lane without a source reads 0
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, kCtrl, 0xF, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), kCtrl, 0xF, 0xF, true);
+    return __builtin_bit_cast(V, ((uint64_t)hi << 32) | lo);
+}
+// (what is left of a double without its upper half is below 2^-1042: nothing, once rounded)
+__device__ __forceinline__ double unless(uint64_t blocked, double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t hi = __builtin_amdgcn_inverse_ballot_w64(blocked) ? 0u : (uint32_t)(b >> 32);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | (uint32_t)b);
+}
+// Inclusive scan over the 64 lanes, restarted at the lanes that hold a flag (kFlagged).
+template <bool kFlagged> __device__ __forceinline__ double lane_scan(double v, const ScanMasks &k) {
+    constexpr uint64_t kOdd = 0x0000FFFF0000FFFFull, kUpper = 0xFFFFFFFFull;
+    double o;
+    o = dpp_bound<0x111>(v); v = (kFlagged ? unless(k.shr1, o) : o) + v;
+    o = dpp_bound<0x112>(v); v = (kFlagged ? unless(k.shr2, o) : o) + v;
+    o = dpp_bound<0x114>(v); v = (kFlagged ? unless(k.shr4, o) : o) + v;
+    o = dpp_bound<0x118>(v); v = (kFlagged ? unless(k.shr8, o) : o) + v;
+    o = dpp_bound<0x142>(v); v = unless(kFlagged ? k.bcast15 : kOdd, o) + v;
+    o = dpp_bound<0x143>(v); v = unless(kFlagged ? k.bcast31 : kUpper, o) + v;
+    return v;
+}
+
+constexpr int kAuxNt = 2;   // buffer accesses: non-temporal
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
+}
+
+// One tile.  A wave holds its whole span in registers: block b of lane l = its elements 256 b + 4 l .. + 3.
+template <typename TT, int kOp>
+__device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves> &sm, const uint32_t tile) {
+    typedef typename TT::in_t In;
+    constexpr int kWaves = TT::kWaves;
+    constexpr int kCpw = lane_cpw<kOp>();
+    constexpr int kBlocks = kCpw * kChunkBlocks;
+    constexpr bool kFlags = kOp == kScan;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const TileSpan span = tile_span(P.reg, tile, kWaves * kChunkElems);
+    const uint32_t span_elems = span.cpw * kChunkElems;
+    const uint64_t wave_base = span.base + (uint64_t)wave * span_elems;
+    const uint64_t left = wave_base < P.n ? P.n - wave_base : 0;
+    const int cnt = left < span_elems ? (int)left : (int)span_elems;      // elements of my span
+
+    // Buffer loads: what lies at or beyond cnt reads 0, without a branch (the 16-byte block of the last element is read whole).
+    const auto x_rsrc = make_rsrc((const In *)P.x + wave_base, (uint32_t)((cnt * (int)sizeof(In) + 15) & ~15));
+    uint32_t F[kCpw] = {};
+    v4u raw[kBlocks];
+    if constexpr (kFlags) {
+        const auto f_rsrc = make_rsrc(P.fw + (wave_base >> 5), (uint32_t)((cnt + 31) / 32 * 4));
+#pragma unroll
+        for (int c = 0; c < kCpw; ++c) F[c] = __builtin_amdgcn_raw_buffer_load_b32(f_rsrc, 4 * lane, 256 * c, kAuxNt);
+    }
+#pragma unroll
+    for (int b = 0; b < kBlocks; ++b) raw[b] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, 16 * lane, 1024 * b, kAuxNt);
+#if MMV_LOAD_PRIO
+    __builtin_amdgcn_s_setprio(0);
+#endif
+    if (cnt % 32 != 0) {   // (the end of the vector)
+#pragma unroll
+        for (int c = 0; c < kCpw; ++c) {
+            const int valid = cnt - kChunkElems * c - 32 * lane;
+            if (valid < 32) F[c] = valid > 0 ? F[c] & ((1u << valid) - 1u) : 0u;
+        }
+#pragma unroll
+        for (int b = 0; b < kBlocks; ++b)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (kBlockElems * b + 4 * lane + i >= cnt) raw[b][i] = 0;
+    }
+    // flags of the span: rows of 32 with any, first and last position (scalars)
+    uint64_t any[kCpw];
+    int first = kBlocks * kBlockElems, last = -1;
+#pragma unroll
+    for (int c = 0; c < kCpw; ++c) {
+        any[c] = kFlags ? __ballot(F[c] != 0) : 0;
+        if (any[c]) {
+            const int hi = 63 - __builtin_clzll(any[c]);
+            last = kChunkElems * c + 32 * hi + 31 - __builtin_clz((uint32_t)__builtin_amdgcn_readlane((int)F[c], hi));
+        }
+    }
+#pragma unroll
+    for (int c = kCpw - 1; c >= 0; --c)
+        if (any[c]) {
+            const int lo = __builtin_ctzll(any[c]);
+            first = kChunkElems * c + 32 * lo + __builtin_ctz((uint32_t)__builtin_amdgcn_readlane((int)F[c], lo));
+        }
+
+    // ---- aggregate: the sum of the span from its last flag on ----
+    double s = 0.0;
+    if (last < 0) {
+#pragma unroll
+        for (int b = 0; b < kBlocks; ++b)
+            s += (double)((from_bits<float>(raw[b][0]) + from_bits<float>(raw[b][1])) + (from_bits<float>(raw[b][2]) + from_bits<float>(raw[b][3])));
+    } else {
+#pragma unroll
+        for (int b = 0; b < kBlocks; ++b)
+            if (last < kBlockElems * (b + 1)) {
+                const int k = last - kBlockElems * b - 4 * lane;   // my elements from k on count
+                float t[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) t[i] = i >= k ? from_bits<float>(raw[b][i]) : 0.0f;
+                s += (double)((t[0] + t[1]) + (t[2] + t[3]));
+            }
+    }
+    s = wave_sum_wide(s);
+    if (lane == 0) {
+        sm.wave_v[wave] = s;
+        sm.wave_f[wave] = last >= 0;
+    }
+    __syncthreads();
+    double wex_v = 0.0, tagg_v = 0.0;
+    uint32_t wex_f = 0, tagg_f = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        if (w == wave) {
+            wex_v = tagg_v;
+            wex_f = tagg_f;
+        }
+        const double wv = sm.wave_v[w];
+        const uint32_t wf = sm.wave_f[w];
+        tagg_v = wf ? wv : tagg_v + wv;
+        tagg_f |= wf;
+    }
+    wex_f = __builtin_amdgcn_readfirstlane(wex_f);
+    tagg_f = __builtin_amdgcn_readfirstlane(tagg_f);
+    const bool final_now = tile == 0 || tagg_f;   // carry out does not depend on predecessors
+    if (tid == 0) wide_store(P.desc_v + tile, final_now ? kStatusPrefix : kStatusAggregate, tagg_v);
+
+    const auto z_rsrc = make_rsrc((float *)P.z + wave_base, 4u * (uint32_t)cnt);
+    // ---- results: blocks behind the first flag of the span first, the others once the carry of the tiles before is known ----
+    const bool closed = wex_f || tile == 0;       // the carry into the span is known already
+    const int first_block = first / kBlockElems;
+    double run = wex_v;                           // carry into the block at hand
+#pragma unroll 1
+    for (int pass = closed ? 1 : 0; pass < 2; ++pass) {
+        // (or the compiler makes the sums of every block ahead of the loop, and keeps them)
+#pragma unroll
+        for (int b = 0; b < kBlocks; ++b) asm volatile("" : "+v"(raw[b]));
+        int from = 0, upto = closed ? kBlocks : first_block + 1, store_from = 0;
+        if (pass == 0) from = first_block, upto = kBlocks, store_from = first_block + 1;   // (of the block of that flag: what it carries on)
+        if (pass == 1 && !closed) {
+            double tile_carry = 0.0;
+            if (wave == 0) {
+                if (first != 0 || !final_now) tile_carry = lookback_wide(P.desc_v, (int)tile, lane, P.hdr);
+                if (lane == 0) {
+                    if (!final_now) wide_store(P.desc_v + tile, kStatusPrefix, tile_carry + tagg_v);
+                    sm.carry = tile_carry;
+                    __hip_atomic_store(&sm.ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+            } else {
+                while (__hip_atomic_load(&sm.ready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0)
+                    __builtin_amdgcn_s_sleep(1);
+                tile_carry = sm.carry;
+            }
+            run = tile_carry + wex_v;
+        }
+#pragma unroll
+        for (int b = 0; b < kBlocks; ++b) {
+            const int c = b / kChunkBlocks, j = b % kChunkBlocks;
+            __builtin_amdgcn_sched_barrier(0);
+            if (b < from || b >= upto || kBlockElems * b >= cnt) continue;
+            const float x0 = from_bits<float>(raw[b][0]), x1 = from_bits<float>(raw[b][1]), x2 = from_bits<float>(raw[b][2]),
+                        x3 = from_bits<float>(raw[b][3]);
+            float o[4];
+            if (!kFlags || ((any[c] >> (8 * j)) & 0xFFull) == 0) {
+                const float p1 = x0 + x1, p2 = p1 + x2, p3 = p2 + x3;
+                const double inc = lane_scan<false>((double)p3, ScanMasks{});
+                const float ec = (float)(run + dpp_bound<0x138>(inc));   // wave_shr 1: lane 0 gets 0
+                run += wave_last(inc);
+                o[0] = ec + x0;
+                o[1] = ec + p1;
+                o[2] = ec + p2;
+                o[3] = ec + p3;
+            } else {
+                // (F[c] holds row l of the chunk in lane l: a lane needs four bits of row 8 j + l / 8)
+                const uint32_t word = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (8 * j + (lane >> 3)), (int)F[c]);
+                const uint32_t nib = (word >> (4 * (lane & 7))) & 0xFu;
+                const float p1 = (nib & 2u) ? x1 : x0 + x1, p2 = (nib & 4u) ? x2 : p1 + x2, p3 = (nib & 8u) ? x3 : p2 + x3;
+                const uint64_t m = __ballot(nib != 0);
+                const double inc = lane_scan<true>((double)p3, scan_masks(m));
+                double e = dpp_bound<0x138>(inc);
+                const uint64_t upto_first = (m & (0 - m)) | ((m & (0 - m)) - 1);   // lanes without a flag in a lane before them
+                e += unless(~upto_first, run);
+                const float ec = (float)e;
+                run = wave_last(inc);
+                o[0] = (nib & 1u) ? x0 : ec + x0;
+                o[1] = (nib & 3u) ? p1 : ec + p1;
+                o[2] = (nib & 7u) ? p2 : ec + p2;
+                o[3] = nib ? p3 : ec + p3;
+            }
+            if (b >= store_from) {
+                const v4u w = {to_bits(o[0]), to_bits(o[1]), to_bits(o[2]), to_bits(o[3])};
+                if (kBlockElems * (b + 1) <= cnt) {
+                    __builtin_amdgcn_raw_buffer_store_b128(w, z_rsrc, 16 * lane, 1024 * b, kAuxNt);
+                } else {   // (stores at or beyond cnt are dropped)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) __builtin_amdgcn_raw_buffer_store_b32(w[i], z_rsrc, 16 * lane + 4 * i, 1024 * b, kAuxNt);
+                }
+            }
+        }
+    }
+}
+
+}  // namespace

@@ -42,6 +42,7 @@
 #include "lanes.h"
 #include "tile_math.h"
 #include "seg_kernel.h"
+#include "lane_kernel.h"
 #include "sum_kernel.h"
 #include "stream_kernel.h"
 #include "seg_entry.h"

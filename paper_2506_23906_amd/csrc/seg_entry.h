@@ -23,17 +23,26 @@ template <typename Shared> __device__ __forceinline__ uint32_t take_tile(const P
     return __builtin_amdgcn_readfirstlane(own_index ? blockIdx.x : sm.tile);   // a scalar, like the wave index
 }
 
-template <typename TT> constexpr int seg_waves_per_simd() { return TT::kOneRound ? 6 : MMV_MIN_WAVES_PER_SIMD; }
+template <typename TT, int kOp> constexpr int seg_waves_per_simd() {
+    return TT::kOneRound || (kInLanes<TT> && kOp == kScan) ? 6 : MMV_MIN_WAVES_PER_SIMD;
+}
+template <typename TT, bool kLanes> struct SegSharedOf {
+    typedef SegShared<TT::kWaves, lds_rows<TT>()> type;
+};
+template <typename TT> struct SegSharedOf<TT, true> {
+    typedef LaneShared<TT::kWaves> type;
+};
 template <typename TT, int kOp, bool kMfma>
-__global__ __launch_bounds__(TT::kWaves * 64, seg_waves_per_simd<TT>()) void seg_kernel(Params P, const uint32_t *__restrict__) {
-    __shared__ SegShared<TT::kWaves, lds_rows<TT>()> sm;
+__global__ __launch_bounds__(TT::kWaves * 64, (seg_waves_per_simd<TT, kOp>())) void seg_kernel(Params P, const uint32_t *__restrict__) {
+    __shared__ typename SegSharedOf<TT, kInLanes<TT>>::type sm;
     // A workgroup that starts competes with the ones in the middle of their arithmetic: its ticket
     // and its loads go first (measured: 2 to 3 % on the long scans)
 #if MMV_LOAD_PRIO
     __builtin_amdgcn_s_setprio(MMV_LOAD_PRIO);
 #endif
     const uint32_t tile = take_tile(P, sm);
-    seg_tile<TT, kOp, kMfma>(P, sm, tile);
+    if constexpr (kInLanes<TT>) lane_tile<TT, kOp>(P, sm, tile);
+    else seg_tile<TT, kOp, kMfma>(P, sm, tile);
 }
 
 // The segmented sum of 8- and 16-bit inputs (speculation over whole chunks): its waves keep less in LDS and in

@@ -1,5 +1,6 @@
 // libmmvseg, part of the one translation unit mmvseg.hip (included there, in order).
-// The single-pass kernel: segmented scan, the unsegmented scan, and the segmented sum of short vectors of 8- and 16-bit values.
+// The single-pass kernel for 8- and 16-bit values: segmented scan, the unsegmented scan, and the segmented sum of vectors of one round of
+// workgroups.
 #pragma once
 
 namespace {
@@ -48,13 +49,6 @@ template <int kWaves, int kRows> struct SegShared {
 };
 
 // One tile, from the loads on.
-// A wave with a single chunk (fp32) keeps the row scans of phase A in its LDS rows for
-// phase B instead of making them a second time; with more chunks LDS holds only the last one made.
-// Matrix-core variant only: there it saves the second 3-way split and 50 registers (fp32 scan
-// 4-5 % faster); in the shuffle variant the same change was measured 3 % slower.
-template <typename TT, int kOp, bool kMfma> constexpr bool keeps_rows() {
-    return MMV_KEEP_ROWS != 0 && chunks_per_wave<TT, kOp, kMfma>() == 1 && kMfma;
-}
 // In the one-round form LDS holds one 32x32 tile of a wave at a time, half a chunk (37 instead of 74 KB per workgroup).
 template <typename TT> constexpr int lds_rows() { return TT::kOneRound ? kS : kRowsPerChunk; }
 template <typename TT, int kOp, bool kMfma>
@@ -74,18 +68,11 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
     // chunks per iteration of the chunk loops: all (unrolled), or MMV_ROLL_STEP with the registers
     // rotated by as many slots afterwards (the moves of a rotation do not depend on the distance)
     constexpr int kStep = kUnrollChunks ? kCpw : (kCpw >= 2 * MMV_ROLL_STEP && kCpw % MMV_ROLL_STEP == 0 ? MMV_ROLL_STEP : 1);
-    constexpr bool kKeepRows = keeps_rows<TT, kOp, kMfma>();
     constexpr bool kHalf = lds_rows<TT>() == kS;   // LDS holds the rows of one 32x32 tile
     // lane exchanges through the vector ALU for the sum-type kernels and the 16-bit scans (measured 2 %
-    // faster), through the LDS hardware for the int8 and fp32 scans (0.9 % faster / no difference)
+    // faster), through the LDS hardware for the int8 scans (0.9 % faster)
     constexpr bool kAluLanes = MMV_DPP_SCAN != 0 && (!kScanLike || TT::kEpl == 8);
     constexpr bool kCounts = kOp == kSum;        // output index = segment ordinal
-    // A chunk in which every position starts a segment is its own result (Algorithm "Revert Speculative
-    // Prefix Sums", the case of all flags set, taken here for 64 rows at once): with 32-bit inputs and one
-    // chunk per wave the striped registers are stored as they are, straight after the load (all-flag
-    // vectors 8 % faster).  Matrix-core variant only: in the other one the test cost 1 % on vectors without
-    // such chunks and gained 2 % on those with.
-    constexpr bool kDenseShortcut = MMV_DENSE_SHORTCUT != 0 && kOp == kScan && sizeof(In) == 4 && kKeepRows;
     // (the count of the segments before the tile comes from tables made by a
     // small kernel before this one, so that no chunk has to wait for it)
     // A tile that holds no flag hands on a plain sum, and its successors cannot finish before they have it.  In the
@@ -93,13 +80,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
     // phase A (which take several microseconds when all waves of a compute unit are at it): the wave whose loads
     // land last adds up the sums of all waves.  Without this a vector without flags ran 13 % slower than one
     // with a flag in every tile, each tile waiting 6 us for the slowest of the tiles before it.
-    // Floats are not a group, so x-bar(j) - x-bar(j - 1) is not x(j) bit for bit.  With 32-bit inputs the striped
-    // registers of the load hold exactly the four positions a lane stores, so a position that starts a segment
-    // gets its input itself, and the positions behind it in the lane's four run on from there (the case of set
-    // flags in Algorithm "Revert Speculative Prefix Sums", taken per element).  16-bit inputs do not need it: their
-    // row prefixes are exact in fp32 unless the exponents of a row differ widely.
-    constexpr bool kExactStarts = MMV_EXACT_STARTS != 0 && kOp == kScan && sizeof(In) == 4;
-    constexpr int kEarlyMode = !kScanLike ? 0 : (sizeof(In) == 1 ? MMV_EARLY_I8 : (sizeof(In) == 2 ? MMV_EARLY_F16 : (kOp == kPlainScan ? MMV_EARLY_F32_SCAN : (kMfma ? MMV_EARLY_F32 : MMV_EARLY_F32_SHUFFLE))));
+    constexpr int kEarlyMode = !kScanLike ? 0 : sizeof(In) == 1 ? MMV_EARLY_I8 : MMV_EARLY_F16;
     constexpr bool kEarly = kEarlyMode != 0;
     constexpr bool kEarlyLookback = kEarlyMode == 2;
     // mode 3: that wave asks for the descriptors of the tiles before at the end of its phase A and looks at them after
@@ -121,7 +102,6 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
     // ---- all inputs of my span: flag word of my row and raw values per chunk ----
     uint32_t F[kCpw];
     v4u raw[kCpw][2 * K];
-    v4u striped[kExactStarts && kKeepRows ? 2 * K : 1];   // the loaded words as they came, where phase A reorders raw[]
     // (the flag words go first: a wave knows whether its span holds a flag before the values have landed)
 #pragma unroll
     for (int c = 0; c < kCpw; ++c) {
@@ -217,7 +197,6 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
     }
     A run_v = A(0);
     uint32_t run_f = 0, run_c = 0;
-    bool dense_chunk = false;   // (uniform) the wave's chunk was stored in phase A already
 
     // ================= phase A: aggregates =================
 #pragma unroll 1
@@ -232,55 +211,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
         // ---- steps 1-4 for the aggregate of my row: last element after the revert, any flag ----
         const uint32_t has_flag = F[S] != 0;
         A agg_v;
-        if constexpr (kMfma && kKeepRows) {
-            // one chunk per wave: the row scans made here stay in the wave's LDS rows until phase B
-            if constexpr (kDenseShortcut) {
-                // A chunk all of whose positions start segments: the striped registers are the result.  The row
-                // scans are still made, for the aggregates; the test sits behind the first use of the loaded
-                // values, and the 0 / 1 operands are made before that, as they are without the branch (a branch
-                // ahead of the loads' first use, or operands made behind it: 1.5 to 3 % on vectors without such
-                // chunks).
-                typename SpecMfma<BT>::Operand op = SpecMfma<BT>::operand(lane);
-                SpecMfma<BT>::pin(op);
-                if constexpr (kExactStarts) {
-#pragma unroll
-                    for (int i = 0; i < 2 * K; ++i) striped[i] = raw[S][i];
-                }
-                operand_layout_write4(raw[S], rows, lane);
-                dense_chunk = cb + kChunkElems <= n && __ballot(F[S] != 0xFFFFFFFFu) == 0;
-                if (dense_chunk) {
-#pragma unroll
-                    for (int i = 0; i < 2 * K; ++i)
-                        __builtin_nontemporal_store(
-                            raw[S][i],
-                            reinterpret_cast<v4u *>((A *)P.z + cb + 1024u * (i / K) + raw_offset<BT, kMfma>(i % K, lane)));
-                }
-                operand_layout_read4(raw[S], rows, lane);
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    A acc[16];
-                    SpecMfma<BT>::run(raw[S] + t * K, lane, acc, op);
-                    store_spec_rows(rows, t, lane, acc);
-                }
-            } else {
-                if constexpr (kExactStarts) {
-#pragma unroll
-                    for (int i = 0; i < 2 * K; ++i) striped[i] = raw[S][i];
-                }
-                if constexpr (K > 1) to_operand_layout<K>(raw[S], rows, lane);
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    A acc[16];
-                    SpecMfma<BT>::run(raw[S] + t * K, lane, acc);
-                    store_spec_rows(rows, t, lane, acc);
-                }
-            }
-            rows[lane * kRowStride + kSlotZero] = 0;
-            wave_lds_sync();
-            const A last = from_bits<A>(rows[lane * kRowStride + kRowData + 31]);
-            const int slot = kSlotZero + last_flag_pos(F[S]);  // x-bar(start - 1)
-            agg_v = last - from_bits<A>(rows[lane * kRowStride + slot]);
-        } else if constexpr (kMfma) {
+        if constexpr (kMfma) {
             static_assert(K == 1 || !kHalf, "a whole chunk passes through LDS on its way into the operand layout");
             if constexpr (K > 1) to_operand_layout<K>(raw[S], rows, lane);
             agg_v = RowAgg<BT>::template run<kAluLanes>(raw[S], F[S], lane);
@@ -303,7 +234,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
             const A last = from_bits<A>(rows[lane * kRowStride + kRowData + 31]);
             const int slot = kSlotZero + last_flag_pos(F[S]);  // x-bar(start - 1)
             agg_v = last - from_bits<A>(rows[lane * kRowStride + slot]);
-            if constexpr (!kKeepRows) wave_lds_sync();  // the rows are read before the next chunk overwrites them
+            wave_lds_sync();  // the rows are read before the next chunk overwrites them
         }
         // segment starts in my row, position 0 of the whole vector not counted (sum only)
         const uint32_t cnt = __popc(row_start == 0 ? (F[S] & ~1u) : F[S]);
@@ -479,7 +410,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
             const int S = kUnrollChunks ? c : u;
             // a chunk is "open" when no flag of the tile precedes it
             const bool chunk_open = !(wex_f || __builtin_amdgcn_readfirstlane(pre_f[S]));
-            if (c < cpw_t && chunk_open == (pass == 1) && !(kDenseShortcut && dense_chunk)) {
+            if (c < cpw_t && chunk_open == (pass == 1)) {
                 const uint64_t cb = wave_base + (uint64_t)c * kChunkElems;
                 const bool chunk_full = cb + kChunkElems <= n;
                 const uint64_t row_start = cb + 32u * lane;
@@ -514,7 +445,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
                         spec_shuffle_tile<BT, kAluLanes>(raw[S] + t * K, lane, rows, at);
                     }
                 };
-                if constexpr (!kHalf && !kKeepRows) {   // (kept: still there from phase A)
+                if constexpr (!kHalf) {
 #pragma unroll
                     for (int t = 0; t < 2; ++t)
                         if ((rows_with_ends >> (32 * t)) & 0xFFFFFFFFull) make_rows(t, t);
@@ -553,26 +484,10 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
                                 const int slot = m ? kSlotZero + (31 - __clz(m)) : kSlotNegCarry;
                                 A b = from_bits<A>(rp[slot]);
                                 o[0] = from_bits<A>(xb[0]) - b;
-                                if constexpr (kExactStarts) {
-                                    const v4u xr = kKeepRows ? striped[kKeepRows ? j : 0] : raw[S][j];   // my four inputs
-                                    bool restarted = ((Fr >> p0) & 1u) != 0;
-                                    if (restarted) o[0] = from_bits<A>(xr[0]);
 #pragma unroll
-                                    for (int i = 1; i < 4; ++i) {
-                                        const A x = from_bits<A>(xr[i]);
-                                        if ((Fr >> (p0 + i)) & 1u) {
-                                            o[i] = x;
-                                            restarted = true;
-                                        } else {
-                                            o[i] = restarted ? o[i - 1] + x : from_bits<A>(xb[i]) - b;
-                                        }
-                                    }
-                                } else {
-#pragma unroll
-                                    for (int i = 1; i < 4; ++i) {
-                                        if ((Fr >> (p0 + i)) & 1u) b = from_bits<A>(xb[i - 1]);
-                                        o[i] = from_bits<A>(xb[i]) - b;
-                                    }
+                                for (int i = 1; i < 4; ++i) {
+                                    if ((Fr >> (p0 + i)) & 1u) b = from_bits<A>(xb[i - 1]);
+                                    o[i] = from_bits<A>(xb[i]) - b;
                                 }
                             }
                             const uint64_t e0 = cb + 256u * j + 4u * lane;

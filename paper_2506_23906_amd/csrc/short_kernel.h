@@ -132,16 +132,6 @@ template <typename A> struct Wide {
 template <> struct Wide<float> {
     typedef double type;
 };
-template <int kCtrl, int kRowMask, typename V> __device__ __forceinline__ V dpp_value(V v) {   // dpp_or_zero for 32 or 64 bits
-    if constexpr (sizeof(V) == 8) {
-        const uint64_t b = __builtin_bit_cast(uint64_t, v);
-        const uint64_t lo = dpp_or_zero<kCtrl, kRowMask>((uint32_t)b), hi = dpp_or_zero<kCtrl, kRowMask>((uint32_t)(b >> 32));
-        return __builtin_bit_cast(V, (hi << 32) | lo);
-    } else {
-        return from_bits<V>(dpp_or_zero<kCtrl, kRowMask>(to_bits(v)));
-    }
-}
-
 // Sum of the elements in one 128-bit word (floats in 64 bits from the first addition on: neighbours may cancel, or overflow 32).
 template <typename TT> __device__ __forceinline__ typename Wide<typename TT::acc_t>::type word_sum(const v4u &w) {
     typedef typename TT::acc_t A;
@@ -194,16 +184,6 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
     MMV_MAX_STEP(0x143, 0xC)
 #undef MMV_MAX_STEP
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
-
-template <typename V> __device__ __forceinline__ V wave_last(V v) {   // lane 63's
-    if constexpr (sizeof(V) == 8) {
-        const uint64_t b = __builtin_bit_cast(uint64_t, v);
-        const uint64_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
-        return __builtin_bit_cast(V, (hi << 32) | lo);
-    } else {
-        return from_bits<V>((uint32_t)__builtin_amdgcn_readlane((int)to_bits(v), 63));
-    }
 }
 
 // What a thread knows of its own elements.

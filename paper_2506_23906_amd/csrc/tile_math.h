@@ -70,7 +70,6 @@ struct TF32 {
     typedef float in_t;
     typedef float acc_t;
     static constexpr int kEpl = 4;
-    static constexpr int kMaxCpw = MMV_CPW_F32;
     static constexpr int kWaves = MMV_WAVES_F32;
     static constexpr mmv_dtype kDtype = MMV_F32_F32;
     static __device__ __forceinline__ acc_t widen(in_t v) { return v; }
@@ -84,14 +83,18 @@ constexpr int kRoundCpw = 2;
 template <typename TT> struct OneRound : TT {
     static constexpr bool kOneRound = true;
 };
+// A scan whose tiles stay in registers (lane_kernel.h).
+template <typename TT> struct InLanes : TT {};
+template <typename TT> constexpr bool kInLanes = false;
+template <typename TT> constexpr bool kInLanes<InLanes<TT>> = true;
+template <int kOp> constexpr int lane_cpw() { return kOp == kPlainScan ? MMV_CPW_F32_SCAN : MMV_CPW_F32; }
 // Most chunks a wave of seg_tile takes.  Bytes under exclusive or in the matrix-core variant hold four accumulators
 // of bit-plane sums per tile next to the raw words: two chunks fit the registers, four spill.  The scan without a
-// flag vector keeps no flag words and no carried flags, which leaves room for longer tiles of 16- and 32-bit inputs.
+// flag vector keeps no flag words and no carried flags, which leaves room for longer tiles of 16-bit inputs.
 template <typename TT, int kOp, bool kMfma> constexpr int chunks_per_wave() {
     if (TT::kDtype == MMV_U8_XOR && kMfma) return MMV_CPW_X8_MFMA;
     if (TT::kOneRound) return kRoundCpw;
     if (kOp == kPlainScan && sizeof(typename TT::in_t) == 2) return MMV_CPW_F16_SCAN;
-    if (kOp == kPlainScan && sizeof(typename TT::in_t) == 4) return MMV_CPW_F32_SCAN;
     return TT::kMaxCpw;
 }
 
@@ -123,32 +126,9 @@ template <typename TT, bool kMfma> __device__ __forceinline__ int raw_offset(int
 
 // One chunk from the striped layout (word w of lane l = elements (2048 / W) w + kEpl l ..,
 // W = 2 K words per lane) to the operand layout, through the wave's LDS rows.
-//   fp32 (K = 4): word 4t+q of lane (c, h) = positions 16h + 4q .. +3 of row 32t + c
 //   16-bit (K = 2): word 2t+ks of lane (c, h) = positions 16ks + 8h .. +7 of row 32t + c
 // The padded row strides keep the 128-bit accesses (almost) free of bank conflicts.
 template <int K> __device__ __forceinline__ void to_operand_layout(v4u (&raw)[2 * K], uint32_t *rows, int lane);
-
-// (the two halves of the fp32 form are also called one by one: between them the registers still hold the
-// striped layout)
-__device__ __forceinline__ void operand_layout_write4(const v4u (&raw)[8], uint32_t *rows, int lane) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-        *reinterpret_cast<v4u *>(rows + (8 * i + (lane >> 3)) * kRowStride + kRowData + 4 * (lane & 7)) = raw[i];
-}
-__device__ __forceinline__ void operand_layout_read4(v4u (&raw)[8], const uint32_t *rows, int lane) {
-    wave_lds_sync();
-    const int c = lane & 31, h = lane >> 5;
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            raw[4 * t + q] = *reinterpret_cast<const v4u *>(rows + (32 * t + c) * kRowStride + kRowData + 16 * h + 4 * q);
-    wave_lds_sync();
-}
-template <> __device__ __forceinline__ void to_operand_layout<4>(v4u (&raw)[8], uint32_t *rows, int lane) {
-    operand_layout_write4(raw, rows, lane);
-    operand_layout_read4(raw, rows, lane);
-}
 
 template <> __device__ __forceinline__ void to_operand_layout<2>(v4u (&raw)[4], uint32_t *rows, int lane) {
     constexpr int kStride = 20;  // dwords per row of 32 halves (16) + padding
@@ -404,17 +384,6 @@ template <bool kBf16> struct RawSumHalf {
 };
 template <> struct RawSum<TF16> : RawSumHalf<false> {};
 template <> struct RawSum<TBF16> : RawSumHalf<true> {};
-template <> struct RawSum<TF32> {
-    static __device__ __forceinline__ float run(const v4u *raw) {
-        float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-            for (int d = 0; d < 4; ++d) s[d] += from_bits<float>(raw[i][d]);
-        return (s[0] + s[1]) + (s[2] + s[3]);
-    }
-};
-
 // ---- steps 2-4 without the detour through LDS: row aggregates from the raw registers -----------------
 //
 // The aggregate of a row after the revert is x-bar(31) - x-bar(start - 1) = the sum of
@@ -512,28 +481,6 @@ template <bool kBf16> struct RowAggHalf {
 };
 template <> struct RowAgg<TF16> : RowAggHalf<false> {};
 template <> struct RowAgg<TBF16> : RowAggHalf<true> {};
-
-template <> struct RowAgg<TF32> {
-    template <bool kAlu> static __device__ __forceinline__ float run(const v4u *raw, uint32_t F, int lane) {
-        const int h = lane >> 5;
-        const Halves Fh = wave_halves<kAlu>(F, lane);   // flag words of rows c and 32 + c
-        float tot[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int st = last_flag_pos(t ? Fh.hi : Fh.lo);
-            float part = 0.0f;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)  // position 16h+4q+i
-                    part += (16 * h + 4 * q + i >= st) ? from_bits<float>(raw[4 * t + q][i]) : 0.0f;
-            const Halves ph = wave_halves<kAlu>(to_bits(part), lane);
-            tot[t] = from_bits<float>(ph.lo) + from_bits<float>(ph.hi);
-        }
-        return lane < 32 ? tot[0] : tot[1];
-    }
-};
-
 
 // Writes the 16 results of a lane into the LDS rows of 32x32 tile t of this wave.
 template <typename A>

@@ -28,12 +28,11 @@ namespace {
 #define MMV_CPW_F16 2    // most chunks per wave, 16-bit inputs (4 spills registers)
 #endif
 #ifndef MMV_CPW_F32
-#define MMV_CPW_F32 1    // most chunks per wave, fp32 inputs (2 spills registers)
+#define MMV_CPW_F32 1    // chunks per wave, fp32 inputs (2: two workgroups per compute unit instead of three, see lane_kernel.h)
 #endif
 // The scan without a flag vector (mmv_scan): every tile waits for the carry of the tiles before, so longer tiles
-// pay.  n = 2^28, % of peak: 16-bit inputs 3 chunks 70.8, 2 chunks 67 (4 spill); fp32 2 chunks 70.5 (shuffle 73.6)
-// although 24 bytes per lane spill, 1 chunk 60.6 (62.1); bytes: 5 or 6 chunks 66.7 against 74.5 with 4.
-// With flags the longer tiles lose (16-bit 78.5 -> 72 %; fp32 72 -> 62 %, 88 bytes spilled).
+// pay.  n = 2^28, % of peak: 16-bit inputs 3 chunks 70.8, 2 chunks 67 (4 spill); bytes: 5 or 6 chunks 66.7 against 74.5 with 4;
+// fp32: lane_kernel.h.  With flags the longer tiles lose (16-bit 78.5 -> 72 %).
 #ifndef MMV_CPW_F16_SCAN
 #define MMV_CPW_F16_SCAN 3
 #endif
@@ -46,14 +45,8 @@ namespace {
 #ifndef MMV_MIN_WAVES_PER_SIMD
 #define MMV_MIN_WAVES_PER_SIMD 4   // register budget: 512 / 4 = 128 VGPRs per lane
 #endif
-#ifndef MMV_KEEP_ROWS
-#define MMV_KEEP_ROWS 1   // 1: single-chunk waves of the matrix-core variant keep their row scans in LDS (see kKeepRows)
-#endif
 #ifndef MMV_DPP_SCAN
 #define MMV_DPP_SCAN 1   // 1: the sum-type kernels exchange lanes with DPP moves and v_permlane32_swap, 0: with lane shuffles through the LDS hardware
-#endif
-#ifndef MMV_DENSE_SHORTCUT
-#define MMV_DENSE_SHORTCUT 1   // 1: fp32 scans store a chunk whose positions all start segments straight from its registers
 #endif
 #ifndef MMV_ROLL_STEP
 #define MMV_ROLL_STEP 2
@@ -65,27 +58,12 @@ namespace {
 // 1 = the plain sum is published as soon as the tile's loads have landed; 2 = and the wave that publishes it looks
 // back for the carry at once; 3 = that wave asks for the descriptors of the tiles before when its phase A is done and
 // looks at them after the barrier (the look-back takes 3 to 4 us whoever has published what, so it pays to have the
-// poll under way early; 2 makes the wave late for the barrier).  Per input width (measured best on MI355X; 32-bit inputs
-// on the matrix cores: 3 makes the vector without flags 5 % faster and every vector with flags 2 % slower; without the
-// matrix cores it costs the vectors with flags nothing: MMV_EARLY_F32_SHUFFLE).
+// poll under way early; 2 makes the wave late for the barrier).  Per input width (measured best on MI355X).
 #ifndef MMV_EARLY_I8
 #define MMV_EARLY_I8 3
 #endif
 #ifndef MMV_EARLY_F16
 #define MMV_EARLY_F16 3
-#endif
-#ifndef MMV_EARLY_F32
-#define MMV_EARLY_F32 0
-#endif
-#ifndef MMV_EARLY_F32_SHUFFLE
-#define MMV_EARLY_F32_SHUFFLE 3   // 32-bit inputs without the matrix cores: one segment of 2^28 values 57 -> 64 % of peak, and
-                                  // nothing lost with flags (every flag set 78 -> 79.5 %, lengths U{1..64} 72 %): 2^30 stress 73 -> 75.3 %
-#endif
-#ifndef MMV_EARLY_F32_SCAN
-#define MMV_EARLY_F32_SCAN 3   // mmv_scan of 32-bit inputs: no tile has a flag, so nothing is there to lose
-#endif
-#ifndef MMV_EXACT_STARTS
-#define MMV_EXACT_STARTS 1   // 1: fp32 scans give a position that starts a segment its input bit for bit
 #endif
 #ifndef MMV_POLL_WINDOWS
 #define MMV_POLL_WINDOWS 1   // windows of 64 tile descriptors that a look-back started ahead of time asks for at once (2 and 4: 3 to 5 % slower, the descriptor loads compete with the streams)

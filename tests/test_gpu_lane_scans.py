@@ -1,0 +1,72 @@
+"""Scans of fp32 values of any length that the single-pass kernel takes (lane_tile): blocks of 256 elements carried from lane to lane."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2506_23906_amd import binding as B
+from parity_util import abs_scan, dev, flags_dev
+
+pytestmark = pytest.mark.gpu
+BLOCK, WAVE, TILE = 256, 2048, 16384
+BORDERS = [1, 3, 4, 255, 256, 257, 511, 2047, 2048, 2049, 16383, 16384, 16385, 32768, 49153]   # lanes, blocks, waves, tiles
+
+
+def flags_at(n, places):
+    f = np.zeros(n, dtype=np.uint8)
+    f[[p for p in places if p < n]] = 1
+    return f
+
+
+@pytest.mark.parametrize("packed", [True, False])
+@pytest.mark.parametrize("ragged", [1, 3, 255, 258, 2049, 16387])
+def test_flags_at_borders_and_the_bound_of_the_error(ragged, packed):
+    """A result is rounded where a lane's four values are added up (three times at most, each at most 2^-24 of A, the sum of |x| of its
+    segment so far), where the carry into the lane is, and when the two are added: 5 * 2^-24 * A.  What is carried in 64 bits adds
+    nothing that shows, and a start receives its input bit for bit."""
+    n = (1 << 21) + ragged
+    rng = np.random.default_rng(ragged)
+    x = rng.uniform(-1, 1, size=n).astype(np.float32)
+    patterns = {"none": [], "borders": BORDERS + [n - b for b in BORDERS], "one late": [n - 1], "one in a block": [40 * TILE + 777],
+                "a dense block": list(range(5 * TILE + 3 * BLOCK, 5 * TILE + 4 * BLOCK)), "all": range(n), "sparse": np.flatnonzero(rng.random(n) < 1e-3),
+                "lanes": np.flatnonzero(rng.random(n) < 0.2)}
+    for name, places in patterns.items():
+        f = flags_at(n, places)
+        print(n, packed, name, flush=True)
+        z = B.mmv_segscan(dev(x), flags_dev(f, packed), n=n).cpu().numpy()
+        err = np.abs(z.astype(np.float64) - oracle.segscan(x, f))
+        assert (err <= 5 * 2.0 ** -24 * abs_scan(x, f)).all(), name
+        assert np.array_equal(z[f == 1].view(np.uint32), x[f == 1].view(np.uint32)), name
+
+
+def test_values_that_are_not_finite_stay_in_their_segment():
+    n = (1 << 21) + 77
+    rng = np.random.default_rng(5)
+    x = rng.integers(-3, 4, size=n).astype(np.float32)
+    f = (rng.random(n) < 0.01).astype(np.uint8)
+    bad = np.concatenate([[b + d for b in (BLOCK, WAVE, TILE, 2 * TILE) for d in (-1, 0, 1)], rng.integers(0, n, size=200)])
+    x[bad] = rng.choice([np.inf, -np.inf, np.nan, 3e38], size=len(bad))
+    z = B.mmv_segscan(dev(x), flags_dev(f, True), n=n).cpu().numpy()
+    f[0] = 1
+    seg = np.cumsum(f)
+    touched = np.isin(seg, seg[bad])
+    assert np.array_equal(z[~touched], oracle.segscan(np.where(touched, 0, x).astype(np.float32), f)[~touched].astype(np.float32))
+    with np.errstate(invalid="ignore", over="ignore"):
+        for s in np.unique(seg[bad])[:100]:                    # (in 64 bits, rounded: what overflows 32 bits is infinite)
+            i = np.flatnonzero(seg == s)
+            assert np.array_equal(np.isnan(z[i]), np.isnan(np.cumsum(x[i].astype(np.float64)))), s
+
+
+@pytest.mark.parametrize("ragged", [1, 257, 4097, 32771])
+def test_without_flags(ragged):
+    """Beyond the short vectors; the carry of every tile comes from all those before it."""
+    n = (1 << 22) + ragged
+    x = np.random.default_rng(ragged).uniform(-1, 1, size=n).astype(np.float32)
+    none = np.zeros(n, dtype=np.uint8)
+    xt = dev(x)
+    want, bound = oracle.scan(x), 5 * 2.0 ** -24 * abs_scan(x, none)
+    for rep in range(3):
+        for z in (B.mmv_scan(xt, n=n, variant=("mfma", "shuffle")[rep % 2]), B.mmv_segscan(xt, flags_dev(none, True), n=n)):
+            assert (np.abs(z.cpu().numpy().astype(np.float64) - want) <= bound).all()
+    B.mmv_scan(xt, n=n, z=xt)                                  # over its own values
+    assert (np.abs(xt.cpu().numpy().astype(np.float64) - want) <= bound).all()
