@@ -73,6 +73,7 @@ template <bool kFlagged> __device__ __forceinline__ double lane_scan(double v, c
     return v;
 }
 
+// (The whole offset has to be in the lane's own one: the scalar offset of buffer instructions is not part of the check.)
 constexpr int kAuxNt = 2;   // buffer accesses: non-temporal
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
@@ -97,13 +98,16 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
     const auto x_rsrc = make_rsrc((const In *)P.x + wave_base, (uint32_t)((cnt * (int)sizeof(In) + 15) & ~15));
     uint32_t F[kCpw] = {};
     v4u raw[kBlocks];
+    int own = 16 * lane;             // my byte offset in a block
+    asm volatile("" : "+v"(own));   // (as an unknown, here and at the stores, so that the offset of a block is added by the
+                                     // instruction itself and not kept in a register from the start on)
     if constexpr (kFlags) {
         const auto f_rsrc = make_rsrc(P.fw + (wave_base >> 5), (uint32_t)((cnt + 31) / 32 * 4));
 #pragma unroll
-        for (int c = 0; c < kCpw; ++c) F[c] = __builtin_amdgcn_raw_buffer_load_b32(f_rsrc, 4 * lane, 256 * c, kAuxNt);
+        for (int c = 0; c < kCpw; ++c) F[c] = __builtin_amdgcn_raw_buffer_load_b32(f_rsrc, 4 * lane + 256 * c, 0, kAuxNt);
     }
 #pragma unroll
-    for (int b = 0; b < kBlocks; ++b) raw[b] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, 16 * lane, 1024 * b, kAuxNt);
+    for (int b = 0; b < kBlocks; ++b) raw[b] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, own + 1024 * b, 0, kAuxNt);
 #if MMV_LOAD_PRIO
     __builtin_amdgcn_s_setprio(0);
 #endif
@@ -241,12 +245,15 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
                 o[3] = nib ? p3 : ec + p3;
             }
             if (b >= store_from) {
+                asm volatile("" : "+v"(own));
                 const v4u w = {to_bits(o[0]), to_bits(o[1]), to_bits(o[2]), to_bits(o[3])};
                 if (kBlockElems * (b + 1) <= cnt) {
-                    __builtin_amdgcn_raw_buffer_store_b128(w, z_rsrc, 16 * lane, 1024 * b, kAuxNt);
-                } else {   // (stores at or beyond cnt are dropped)
+                    __builtin_amdgcn_raw_buffer_store_b128(w, z_rsrc, own + 1024 * b, 0, kAuxNt);
+                } else {
+                    float *z = (float *)P.z + wave_base;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) __builtin_amdgcn_raw_buffer_store_b32(w[i], z_rsrc, 16 * lane + 4 * i, 1024 * b, kAuxNt);
+                    for (int i = 0; i < 4; ++i)
+                        if (own / 4 + kBlockElems * b + i < cnt) z[own / 4 + kBlockElems * b + i] = o[i];
                 }
             }
         }

@@ -70,3 +70,24 @@ def test_without_flags(ragged):
             assert (np.abs(z.cpu().numpy().astype(np.float64) - want) <= bound).all()
     B.mmv_scan(xt, n=n, z=xt)                                  # over its own values
     assert (np.abs(xt.cpu().numpy().astype(np.float64) - want) <= bound).all()
+
+
+@pytest.mark.parametrize("ragged", [1, 4, 255, 257, 300, 2050, 4095, 16385])
+def test_nothing_is_written_behind_the_result(ragged):
+    """The last block, the waves behind it that have no elements, both kernels; and nothing of the words behind the flags counts."""
+    rng = np.random.default_rng(ragged)
+    for op, base in (("segscan", 1 << 21), ("scan", 1 << 22)):
+        n = base + ragged
+        x = rng.integers(-3, 4, size=n).astype(np.float32)
+        f = (rng.random(n) < 1e-3).astype(np.uint8) if op == "segscan" else np.zeros(n, dtype=np.uint8)
+        room = torch.full((n + 40_000,), 7.0, device="cuda")
+        xt = torch.full((n + 40_000,), float("nan"), device="cuda")
+        xt[:n] = dev(x)
+        if op == "scan":
+            B.mmv_scan(xt[:n], n=n, z=room[:n])
+        else:
+            bits = torch.full(((n + 31) // 32 + 2000,), -1, dtype=torch.int32, device="cuda")
+            bits[:(n + 31) // 32] = flags_dev(f, True)[:(n + 31) // 32]
+            B.mmv_segscan(xt[:n], bits[:(n + 31) // 32], n=n, z=room[:n])
+        assert np.array_equal(room[:n].cpu().numpy(), oracle.segscan(x, f).astype(np.float32)), op
+        assert bool((room[n:] == 7.0).all()), op
