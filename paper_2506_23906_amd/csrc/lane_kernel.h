@@ -73,12 +73,6 @@ template <bool kFlagged> __device__ __forceinline__ double lane_scan(double v, c
     return v;
 }
 
-// (The whole offset has to be in the lane's own one: the scalar offset of buffer instructions is not part of the check.)
-constexpr int kAuxNt = 2;   // buffer accesses: non-temporal
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
-}
-
 // One tile.  A wave holds its whole span in registers: block b of lane l = its elements 256 b + 4 l .. + 3.
 template <typename TT, int kOp>
 __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves> &sm, const uint32_t tile) {

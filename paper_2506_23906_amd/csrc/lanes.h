@@ -18,6 +18,14 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Buffer loads and stores: what lies at or beyond `bytes` reads 0 and is not written, without a branch.  (The whole offset has to be in
+// the lane's own one: the scalar offset of these instructions is not part of that check.)  (What is loaded in a branch
+// that not all lanes take is waited for before the next one: the branch that a lane does not take sets its registers.)
+constexpr int kAuxNt = 2;   // non-temporal
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
+}
+
 __device__ __forceinline__ uint64_t desc_load(const uint64_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

@@ -50,3 +50,32 @@ def test_long_masks_dense_and_sparse_stretches(packed, n):
             m[c:d] = rng.random(d - c, dtype=np.float32) < density
     x = np.arange(n, dtype=np.uint32).view(np.int32) * np.int32(-1640531527)
     check(n, m, x, packed, int(m.sum()))
+
+
+@pytest.mark.parametrize("packed", [True, False])
+@pytest.mark.parametrize("base", [1 << 18, 1 << 22, 1 << 26])            # 16 words per wave in one launch; 64; two groups of them
+def test_set_bits_behind_the_mask_do_not_count(base, packed):
+    """Ragged ends of words, of lanes, of waves that have no positions; what lies behind mask and values is all ones."""
+    rng = np.random.default_rng(base)
+    for ragged in (1, 15, 31, 33, 64, 1025, 40_001):
+        n = base + ragged
+        m = (rng.random(n, dtype=np.float32) < 0.1).astype(np.uint8)
+        x = rng.integers(-2 ** 31, 2 ** 31, size=n, dtype=np.int64).astype(np.int32)
+        xt = torch.full((n + 70_000,), -1, dtype=torch.int32, device="cuda")
+        xt[:n] = dev(x)
+        if packed:
+            words = (n + 31) // 32
+            mask = torch.full((words + 4000,), -1, dtype=torch.int32, device="cuda")
+            mask[:words] = flags_dev(m, True)[:words]
+            if n % 32:
+                mask[words - 1] |= -1 << (n % 32)
+            mask = mask[:words]
+        else:
+            mask = torch.full((n + 70_000,), 255, dtype=torch.uint8, device="cuda")
+            mask[:n] = dev(m)
+            mask = mask[:n]
+        ref = x[m == 1]
+        out = torch.full((len(ref) + 70_000,), 7, dtype=torch.int32, device="cuda")
+        _, count = B.mmv_compress(xt[:n], mask, n, out=out)
+        assert int(count.item()) == len(ref), (packed, n)
+        assert np.array_equal(out[:len(ref)].cpu().numpy(), ref) and bool((out[len(ref):] == 7).all()), (packed, n)
