@@ -191,7 +191,7 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
         if (pass == 1 && !closed) {
             double tile_carry = 0.0;
             if (wave == 0) {
-                if (first != 0 || !final_now) tile_carry = lookback_wide(P.desc_v, (int)tile, lane, P.hdr);
+                if (first != 0 || !final_now) tile_carry = lookback<double>(P.desc_v, (int)tile, lane, poll_lanes(P.num_tiles, P.first_round), P.hdr);
                 if (lane == 0) {
                     if (!final_now) wide_store(P.desc_v + tile, kStatusPrefix, tile_carry + tagg_v);
                     sm.carry = tile_carry;

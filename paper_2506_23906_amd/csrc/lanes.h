@@ -77,69 +77,6 @@ template <typename T, bool kAlu = true> __device__ __forceinline__ T wave_sum(T 
     return from_bits<T>((uint32_t)__builtin_amdgcn_readlane((int)to_bits(v), 63));
 }
 
-// Sum of the payloads of the predecessor tiles back to (and including) the first
-// one whose descriptor says "prefix".  The whole wave polls 64 descriptors at a
-// time.  Tile -1 counts as prefix 0, so the loop always ends there at the latest.
-// (Polling 128 or 256 descriptors per round trip was measured 3-9 % slower on long
-// chains: the polls are served by the memory side and compete with the streams,
-// and in steady state the nearest "prefix" is within 64 tiles anyway.)
-// kPolled windows of 64 descriptors may have been loaded by the caller itself, some time ago (lookback_poll: lane l
-// of window w holds the descriptor of tile  tile - 1 - 64 w - l); they are used as far as they suffice, then the loop
-// polls as usual.
-template <int kWindows>
-__device__ __forceinline__ void lookback_poll(const uint64_t *desc, int tile, int lane, uint64_t (&polled)[kWindows]) {
-#pragma unroll
-    for (int w = 0; w < kWindows; ++w) {
-        const int idx = tile - 1 - 64 * w - lane;
-        polled[w] = idx >= 0 ? desc_load(desc + idx) : (kStatusPrefix << 62);
-    }
-}
-template <typename T, bool kAlu, int kPolled>
-__device__ T lookback_from(const uint64_t *desc, int tile, int lane, uint32_t *hdr, const uint64_t *polled) {
-    T carry = T(0);
-    int pos = tile - 1;
-    uint32_t spins = 0;
-    int window = 0;     // windows done
-    bool fresh = true;  // the polled copy of this window has not been tried
-    while (true) {
-        const int idx = pos - lane;
-        uint64_t d = 0;
-        bool have = false;
-#pragma unroll
-        for (int w = 0; w < kPolled; ++w)
-            if (fresh && window == w) {
-                d = polled[w];
-                have = true;
-            }
-        if (!have) d = idx >= 0 ? desc_load(desc + idx) : (kStatusPrefix << 62);
-        fresh = false;
-        const uint32_t st = (uint32_t)(d >> 62);
-        const uint64_t invalid = __ballot(st == kStatusInvalid);
-        const uint64_t stop = __ballot(st == kStatusPrefix);
-        const int first_stop = stop ? (__ffsll((unsigned long long)stop) - 1) : 64;
-        const uint64_t need = first_stop >= 63 ? ~0ull : ((2ull << first_stop) - 1ull);
-        if (invalid & need) {
-            if (++spins > kMaxSpins) {
-                if (lane == 0) __hip_atomic_store(hdr + kHdrError, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                break;
-            }
-            __builtin_amdgcn_s_sleep(2);
-            continue;
-        }
-        const T v = lane <= first_stop ? from_bits<T>((uint32_t)d) : T(0);
-        carry += wave_sum<T, kAlu>(v);
-        if (stop) break;
-        pos -= 64;
-        ++window;
-        fresh = true;
-    }
-    return carry;
-}
-template <typename T, bool kAlu = true>
-__device__ T lookback(const uint64_t *desc, int tile, int lane, uint32_t *hdr) {
-    return lookback_from<T, kAlu, 0>(desc, tile, lane, hdr, nullptr);
-}
-
 // dpp_or_zero for values of 32 or 64 bits.
 template <int kCtrl, int kRowMask, typename V> __device__ __forceinline__ V dpp_value(V v) {
     if constexpr (sizeof(V) == 8) {
@@ -164,6 +101,8 @@ template <typename V> __device__ __forceinline__ V wave_last(V v) {   // lane 63
 __device__ __forceinline__ void wide_store(uint64_t *p, uint64_t status, double v) {
     __hip_atomic_store(p, (status << 62) | (__builtin_bit_cast(uint64_t, v) >> 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+template <typename T> __device__ __forceinline__ T desc_value(uint64_t d) { return from_bits<T>((uint32_t)d); }
+template <> __device__ __forceinline__ double desc_value<double>(uint64_t d) { return __builtin_bit_cast(double, d << 2); }
 __device__ __forceinline__ double wave_sum_wide(double v) {   // as wave_sum
     v += dpp_value<0x111, 0xF>(v);
     v += dpp_value<0x112, 0xF>(v);
@@ -173,36 +112,54 @@ __device__ __forceinline__ double wave_sum_wide(double v) {   // as wave_sum
     v += dpp_value<0x143, 0xC>(v);
     return wave_last(v);
 }
-// As lookback, over such descriptors, kPollLanes tiles at a time, and of those only the ones that are still missing are asked for again.
-// Every descriptor read goes past the L2 to the memory side, where all tiles in flight ask for the same few lines, and there it
-// costs more than the round trips that a wide window saves: scan of 1.5 * 10^8 fp32 values 217 us with windows of 64 asked for whole,
-// 200 (64), 197 (32, 16) and 215 (8) with only the missing ones; without any look-back (wrong results) 194.
-constexpr int kPollLanes = 16;
-__device__ __forceinline__ double lookback_wide(const uint64_t *desc, int tile, int lane, uint32_t *hdr) {
-    double carry = 0.0;
+
+// Sum of the payloads of the predecessor tiles back to (and including) the first one whose descriptor says "prefix".  Tile -1
+// counts as prefix 0, so the loop always ends there at the latest.  The wave takes `lanes` descriptors at a time, and asks again only
+// for those of them that are needed and still missing: every such read goes past the L2 to the memory side, where all tiles in
+// flight ask for the same few lines, and there it costs more than the round trips that a wide window saves.  Scan of 1.5 * 10^8
+// fp32 values: 217 us with windows of 64 asked for whole, 200 (64), 197 (32, 16) and 215 (8) with only the missing ones; without
+// any look-back (wrong results) 194.  Segmented sum of 2^28 bytes 69.4 (64, whole), 67.6 (64), 65.5 (16).
+// Where all tiles are resident at once they also publish at once, and a tile walks through all those before it: windows of 64 there
+// (scan of 5.8 * 10^6 fp16 values 13.7, with windows of 16 15.8).
+// The caller may have asked for the first window itself, some time ago (kPolled, lookback_poll).
+#ifndef MMV_POLL_LANES
+#define MMV_POLL_LANES 16
+#endif
+__device__ __forceinline__ int poll_lanes(uint32_t num_tiles, uint32_t first_round) { return num_tiles <= first_round ? 64 : MMV_POLL_LANES; }
+__device__ __forceinline__ uint64_t lookback_poll(const uint64_t *desc, int tile, int lane, int lanes) {
+    const int idx = tile - 1 - lane;
+    return idx < 0 ? kStatusPrefix << 62 : lane < lanes ? desc_load(desc + idx) : 0;
+}
+template <typename T, bool kAlu = true, bool kPolled = false>
+__device__ T lookback(const uint64_t *desc, int tile, int lane, int lanes, uint32_t *hdr, uint64_t polled = 0) {
+    T carry = T(0);
     uint32_t spins = 0;
-    for (int pos = tile - 1;; pos -= kPollLanes) {
+    int pos = tile - 1;
+    uint64_t d = polled;
+    bool ask = !kPolled && lane < lanes;
+    while (true) {
         const int idx = pos - lane;
-        uint64_t d = idx >= 0 ? 0 : kStatusPrefix << 62;
-        bool missing = lane < kPollLanes && idx >= 0;
-        uint64_t stop;
-        int first_stop;
-        while (true) {
-            if (missing) d = desc_load(desc + idx);
-            const uint32_t st = (uint32_t)(d >> 62);
-            stop = __ballot(lane < kPollLanes && st == kStatusPrefix);
-            first_stop = stop ? __ffsll((unsigned long long)stop) - 1 : kPollLanes - 1;
-            missing = lane <= first_stop && st == kStatusInvalid;
-            if (__ballot(missing) == 0) break;
+        if (ask) d = idx >= 0 ? desc_load(desc + idx) : kStatusPrefix << 62;
+        const uint32_t st = (uint32_t)(d >> 62);
+        const uint64_t stop = __ballot(lane < lanes && st == kStatusPrefix);
+        const int first_stop = stop ? __ffsll((unsigned long long)stop) - 1 : lanes - 1;
+        ask = lane <= first_stop && st == kStatusInvalid;
+        if (__ballot(ask) != 0) {
             if (++spins > kMaxSpins) {
                 if (lane == 0) __hip_atomic_store(hdr + kHdrError, kErrLookback, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return carry;
+                break;
             }
             __builtin_amdgcn_s_sleep(2);
+            continue;
         }
-        carry += wave_sum_wide(lane <= first_stop ? __builtin_bit_cast(double, d << 2) : 0.0);
-        if (stop) return carry;
+        const T v = lane <= first_stop ? desc_value<T>(d) : T(0);
+        if constexpr (sizeof(T) == 8) carry += wave_sum_wide(v);
+        else carry += wave_sum<T, kAlu>(v);
+        if (stop) break;
+        pos -= lanes;
+        ask = lane < lanes;
     }
+    return carry;
 }
 
 // Number of segment starts before span `span` of a tile (0: before the tile), from the counts per tile and (kUseSpans, or

@@ -216,7 +216,7 @@ __global__ __launch_bounds__(kCompressWaves * 64, 8) void compress_kernel(
         if (tid == 0) desc_store(desc + tile, tile == 0 ? kStatusPrefix : kStatusAggregate, tile_cnt);
         if (wave == 0) {
             uint32_t carry = 0;
-            if (tile > 0) carry = lookback<uint32_t>(desc, (int)tile, lane, hdr);
+            if (tile > 0) carry = lookback<uint32_t>(desc, (int)tile, lane, poll_lanes(num_tiles, first_round), hdr);
             if (lane == 0) {
                 if (tile > 0) desc_store(desc + tile, kStatusPrefix, carry + tile_cnt);
                 s_carry = carry;

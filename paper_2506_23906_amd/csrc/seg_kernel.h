@@ -166,7 +166,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
                 if constexpr (kEarlyLookback) {
                     // ... and it looks back for the carry of the tiles before right away, so that the tile's own
                     // prefix is out for its successors a whole phase A earlier (the other waves go on meanwhile)
-                    const A carry_in = lookback<A, kAluLanes>(P.desc_v, (int)tile, lane, P.hdr);
+                    const A carry_in = lookback<A, kAluLanes>(P.desc_v, (int)tile, lane, TT::kOneRound ? 64 : poll_lanes(P.num_tiles, P.first_round), P.hdr);
                     if (lane == 0) {
                         desc_store(P.desc_v + tile, kStatusPrefix, to_bits(carry_in + total));
                         sm.carry_v = to_bits(carry_in);
@@ -326,9 +326,9 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
         sm.wave_f[wave] = run_f;
         sm.wave_c[wave] = run_c;
     }
-    uint64_t polled[MMV_POLL_WINDOWS] = {};
+    uint64_t polled = 0;
     if constexpr (kAsyncLookback) {
-        if (i_published) lookback_poll(P.desc_v, (int)tile, lane, polled);
+        if (i_published) polled = lookback_poll(P.desc_v, (int)tile, lane, TT::kOneRound ? 64 : poll_lanes(P.num_tiles, P.first_round));
     }
     __syncthreads();
 
@@ -378,7 +378,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
             const bool looked_back = (kEarlyLookback || kAsyncLookback) && !final_now;
             if constexpr (kAsyncLookback) {
                 if (i_published) {
-                    tile_carry = lookback_from<A, kAluLanes, MMV_POLL_WINDOWS>(P.desc_v, (int)tile, lane, P.hdr, polled);
+                    tile_carry = lookback<A, kAluLanes, true>(P.desc_v, (int)tile, lane, TT::kOneRound ? 64 : poll_lanes(P.num_tiles, P.first_round), P.hdr, polled);
                     if (lane == 0) {
                         desc_store(P.desc_v + tile, kStatusPrefix, to_bits(tile_carry + tagg_v));
                         sm.carry_v = to_bits(tile_carry);
@@ -387,7 +387,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
                 }
             }
             if (wave == 0 && !looked_back) {
-                if (tile > 0 && !head_flagged) tile_carry = lookback<A, kAluLanes>(P.desc_v, (int)tile, lane, P.hdr);
+                if (tile > 0 && !head_flagged) tile_carry = lookback<A, kAluLanes>(P.desc_v, (int)tile, lane, TT::kOneRound ? 64 : poll_lanes(P.num_tiles, P.first_round), P.hdr);
                 if (lane == 0) {
                     if (!final_now) desc_store(P.desc_v + tile, kStatusPrefix, to_bits(tile_carry + tagg_v));
                     sm.carry_v = to_bits(tile_carry);

@@ -435,7 +435,7 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
     float tile_carry = 0.0f;
     // (a tile whose carry goes out as it is and whose first open end is none needs no carry in)
     const bool wanted = __ballot((on[0] && !ex_f) || (on[1] && !(ex_f | f[0]))) != 0;
-    if (tile > 0 && (wanted || !final_now)) tile_carry = lookback<float, true>(P.desc_v, (int)tile, lane, P.hdr);
+    if (tile > 0 && (wanted || !final_now)) tile_carry = lookback<float, true>(P.desc_v, (int)tile, lane, poll_lanes(P.num_tiles, P.first_round), P.hdr);
     if (lane == 0 && !final_now) desc_store(P.desc_v + tile, kStatusPrefix, to_bits(tile_carry + tagg_v));
     // ---- step 6 for the outputs that were waiting ----
     if (!ex_f) ex_v += tile_carry;

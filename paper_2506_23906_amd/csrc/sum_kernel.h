@@ -510,7 +510,7 @@ __device__ __forceinline__ void sum_tile(const Params &P, SumShared<TT> &sm, con
         // carry of the predecessor tiles by decoupled look-back
         A tile_carry = A(0);
         if (wave == 0) {
-            if (tile > 0 && !head_flagged) tile_carry = lookback<A, true>(P.desc_v, (int)tile, lane, P.hdr);
+            if (tile > 0 && !head_flagged) tile_carry = lookback<A, true>(P.desc_v, (int)tile, lane, poll_lanes(P.num_tiles, P.first_round), P.hdr);
             if (lane == 0) {
                 if (!final_now) desc_store(P.desc_v + tile, kStatusPrefix, to_bits(tile_carry + tagg_v));
                 sm.carry_v = to_bits(tile_carry);

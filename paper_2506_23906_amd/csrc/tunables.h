@@ -65,9 +65,6 @@ namespace {
 #ifndef MMV_EARLY_F16
 #define MMV_EARLY_F16 3
 #endif
-#ifndef MMV_POLL_WINDOWS
-#define MMV_POLL_WINDOWS 1   // windows of 64 tile descriptors that a look-back started ahead of time asks for at once (2 and 4: 3 to 5 % slower, the descriptor loads compete with the streams)
-#endif
 #ifndef MMV_CHUNK_SUM
 #define MMV_CHUNK_SUM 1   // 1: the segmented sum of 8- and 16-bit inputs on long vectors speculates over whole chunks
 #endif
