@@ -307,13 +307,14 @@ template <typename TT> struct SumSlot {
     uint32_t F, Fnext;
     v4u raw[2 * (16 / TT::kEpl)];
 };
+// (By buffer loads: with branches for the ends of vector and span, as many loads might have been under way as not, and every chunk began with
+// a wait for all of them, also those of the chunk after it.  fp16, 6.7 * 10^7 values, 6 % starts 42.2 -> 41.0 us the call, 1.1 * 10^8,
+// 0.1 % 50.6 -> 48.6, 1.9 * 10^8 without the matrix cores 133.7 -> 127.9; 2.25 * 10^8 bytes without them 74.7 -> 71.3, on them level.)
 template <typename TT>
-__device__ __forceinline__ void sum_load_slot(const Params &P, uint64_t chunk_base, int lane, SumSlot<TT> &slot) {
-    const uint64_t rs = chunk_base + 32u * lane;
-    slot.F = slot.Fnext = 0;
-    if (rs < P.n) slot.F = __builtin_nontemporal_load(P.fw + (rs >> 5));
-    if (rs + 32 < P.n) slot.Fnext = __builtin_nontemporal_load(P.fw + (rs >> 5) + 1);
-    load_raw<TT, true>((const typename TT::in_t *)P.x, chunk_base, P.n, lane, slot.raw);
+__device__ __forceinline__ void sum_load_slot(__amdgpu_buffer_rsrc_t x, __amdgpu_buffer_rsrc_t fw, int chunk, int lane, SumSlot<TT> &slot) {
+    slot.F = __builtin_amdgcn_raw_buffer_load_b32(fw, 4 * lane + 256 * chunk, 0, kAuxNt);
+    slot.Fnext = __builtin_amdgcn_raw_buffer_load_b32(fw, 4 * lane + 256 * chunk + 4, 0, kAuxNt);
+    load_raw<TT, true>(x, (uint32_t)kChunkElems * (uint32_t)chunk, lane, slot.raw);
 }
 
 // One tile.  A wave takes the chunks of its span one after the other, a few of them in flight ahead of the one at
@@ -346,10 +347,14 @@ __device__ __forceinline__ void sum_tile(const Params &P, SumShared<TT> &sm, con
     static_assert(kWaves == (int)kSpans, "one span per wave");
     const uint32_t count_part = starts_before_part<true>(P, tile, wave, lane);
     __builtin_amdgcn_sched_barrier(0);
+    // (the flag word behind the span says whether its last position ends a segment)
+    const uint64_t left = wave_base < n ? n - wave_base : 0;
+    const uint32_t span_elems = (uint32_t)cpw_t * kChunkElems, mine = left < span_elems ? (uint32_t)left : span_elems;
+    const auto x_rsrc = make_rsrc((const typename TT::in_t *)P.x + wave_base, (mine * (uint32_t)sizeof(typename TT::in_t) + 15) & ~15u);
+    const auto f_rsrc = make_rsrc(P.fw + (wave_base >> 5), left > span_elems ? span_elems / 8 + 4 : (mine + 31) / 32 * 4);
     SumSlot<TT> slot[kDepth];
 #pragma unroll
-    for (int i = 0; i < kDepth; ++i)
-        if (i < cpw_t) sum_load_slot<TT>(P, wave_base + (uint64_t)i * kChunkElems, lane, slot[i]);
+    for (int i = 0; i < kDepth; ++i) sum_load_slot<TT>(x_rsrc, f_rsrc, i, lane, slot[i]);
 #if MMV_LOAD_PRIO
     __builtin_amdgcn_s_setprio(0);
 #endif
@@ -370,6 +375,7 @@ __device__ __forceinline__ void sum_tile(const Params &P, SumShared<TT> &sm, con
                 const uint64_t row_start = cb + 32u * lane;
                 v4u(&raw)[2 * K] = slot[i].raw;
                 uint32_t F = slot[i].F;
+                if (cb + kChunkElems > n) mask_raw<TT, true>(cb < n ? (int)(n - cb) : 0, lane, raw);
                 if (row_start + 32 > n) F = row_start < n ? (F & ((1u << (uint32_t)(n - row_start)) - 1u)) : 0u;   // bits beyond n do not count
                 if (c == 0) head_flagged = (__builtin_amdgcn_readfirstlane(F) & 1u) != 0;
                 if constexpr (K > 1) to_operand_layout<K>(raw, rows, lane);
@@ -472,7 +478,7 @@ __device__ __forceinline__ void sum_tile(const Params &P, SumShared<TT> &sm, con
             }
             // the registers of this chunk take the chunk that many ahead
             __builtin_amdgcn_sched_barrier(0);
-            if (c + kDepth < cpw_t) sum_load_slot<TT>(P, wave_base + (uint64_t)(c + kDepth) * kChunkElems, lane, slot[i]);
+            sum_load_slot<TT>(x_rsrc, f_rsrc, c + kDepth, lane, slot[i]);   // (behind the span: nothing is read)
             __builtin_amdgcn_sched_barrier(0);
         }
     }

@@ -179,6 +179,32 @@ __device__ __forceinline__ void load_raw(const typename TT::in_t *x, uint64_t ch
             raw[t * K + i] = load128(x, chunk_base + 1024u * t + raw_offset<TT, kMfma>(i, lane), n, full);
 }
 
+// The same by buffer loads, for kernels that have more than one chunk under way: a fixed number of loads and no branch, so that the
+// compiler knows how many are behind those that it waits for.  `at`: first element of the chunk behind the base of the resource, whose
+// size is rounded up to whole 16-byte blocks; what the last of them holds beyond the end is cleared by mask_raw.
+template <typename TT, bool kMfma>
+__device__ __forceinline__ void load_raw(__amdgpu_buffer_rsrc_t rsrc, uint32_t at, int lane, v4u (&raw)[2 * (16 / TT::kEpl)]) {
+    constexpr int K = 16 / TT::kEpl, kSize = sizeof(typename TT::in_t);
+    const int own = kSize * ((int)at + raw_offset<TT, kMfma>(0, lane));
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            raw[t * K + i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, own + kSize * (1024 * t + (raw_offset<TT, kMfma>(i, 0) - raw_offset<TT, kMfma>(0, 0))), 0, kAuxNt);
+}
+// Clears the bytes of a word from `valid` on.
+__device__ __forceinline__ void mask_word(v4u &w, int valid) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) w[d] = valid >= 4 * d + 4 ? w[d] : valid > 4 * d ? w[d] & ((1u << (8 * (valid - 4 * d))) - 1u) : 0u;
+}
+template <typename TT, bool kMfma> __device__ __forceinline__ void mask_raw(int left, int lane, v4u (&raw)[2 * (16 / TT::kEpl)]) {   // `left`: elements of the chunk
+    constexpr int K = 16 / TT::kEpl, kSize = sizeof(typename TT::in_t);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < K; ++i) mask_word(raw[t * K + i], kSize * (left - 1024 * t - raw_offset<TT, kMfma>(i, lane)));
+}
+
 // ---- step 1, matrix-core form: x-bar of 32x32 tile t from the raw registers ------------------------------
 
 template <typename TT> struct SpecMfma;
