@@ -221,6 +221,8 @@ inline uint64_t tiles_for(uint64_t n, mmv_op op, mmv_dtype dt) {
     const uint64_t a = tile_plan(op, dt, n, true).tiles, b = tile_plan(op, dt, n, false).tiles;
     return a > b ? a : b;
 }
+// Bytes of x where 32-bit offsets reach all of it, else 0.
+inline uint32_t x_bytes_of(uint64_t n_cols) { return n_cols > (1ull << 30) ? 0u : n_cols == (1ull << 30) ? ~0u : n_cols ? 4u * (uint32_t)n_cols : 1u; }
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 inline bool aligned4(const void *p) { return ((uintptr_t)p & 3u) == 0; }
 
@@ -371,7 +373,7 @@ template <typename TT, int kOp, bool kMfma> hipError_t launch_variant(Params P, 
     void (*kernel)(Params, const uint32_t *);
     int which = 0;
     if constexpr (stream_form<TT, kOp>()) {
-        const bool narrow = kOp == kSum || P.cols_narrow;   // (a long x, whatever the matrix: the form for long vectors)
+        const bool narrow = kOp == kSum || P.x_bytes != 0;   // (a long x, whatever the matrix: the form for long vectors)
         which = !narrow ? 1 : plan.short_form ? 2 : 0;
         kernel = which == 2 ? stream_kernel<TT, kOp, kMfma, true, true> : stream_kernel<TT, kOp, kMfma, true, false>;
         if constexpr (kOp != kSum) {

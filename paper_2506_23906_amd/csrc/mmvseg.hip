@@ -201,7 +201,7 @@ mmv_status mmv_spmv_coo(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
     P.row = d_row;
     P.col = d_col;
     P.xv = d_x;
-    P.cols_narrow = n_cols <= (1ull << 30) ? 1u : 0u;
+    P.x_bytes = x_bytes_of(n_cols);
     P.y = d_y;
     P.hdr = (uint32_t *)ws;
     P.desc_v = (uint64_t *)(ws + L.desc_v);
@@ -273,7 +273,7 @@ mmv_status mmv_spmv_coo_run(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, cons
     P.row = d_row;
     P.col = d_col;
     P.xv = d_x;
-    P.cols_narrow = n_cols <= (1ull << 30) ? 1u : 0u;
+    P.x_bytes = x_bytes_of(n_cols);
     P.y = d_y;
     P.hdr = (uint32_t *)ws;
     P.desc_v = (uint64_t *)(ws + L.desc_v);
@@ -442,7 +442,7 @@ mmv_status mmv_spmv_csr(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, const in
     P.n = nnz;
     P.col = d_col;
     P.xv = d_x;
-    P.cols_narrow = n_cols <= (1ull << 30) ? 1u : 0u;
+    P.x_bytes = x_bytes_of(n_cols);
     P.y = d_y;
     P.rowmap = (const uint32_t *)(ws + C.rowmap);
     P.out_cap = n_rows;
@@ -498,7 +498,7 @@ mmv_status mmv_spmv_csr_run(uint64_t n_rows, uint64_t n_cols, uint64_t nnz, cons
     P.n = nnz;
     P.col = d_col;
     P.xv = d_x;
-    P.cols_narrow = n_cols <= (1ull << 30) ? 1u : 0u;
+    P.x_bytes = x_bytes_of(n_cols);
     P.y = d_y;
     P.rowmap = (const uint32_t *)(ws + C.rowmap);
     P.out_cap = n_rows;

@@ -106,6 +106,26 @@ __device__ __forceinline__ void stream_load(const Params &P, uint64_t unit_base,
 #pragma unroll
     for (int i = 0; i < 4; ++i) s.raw[i] = load128((const float *)P.x, unit_base + 256u * i + 4u * lane, P.n, full);
 }
+// The same by buffer loads: a fixed number of them and no branch, so that the compiler knows how many are behind those that it waits
+// for.  Of a unit behind the tile, or of what lies behind the end, nothing is read; columns there are 0.  Sums of 10^8 values, byte flags, 1 %
+// starts 103.0 -> 99.5 us the call, 1.5 * 10^8, bits 121.5 -> 116.5; COO product of 3.4 * 10^7 entries in scattered columns, whose first
+// gathers go out as their columns arrive, 242 -> 233.  COO products of up to 2.6 * 10^6 entries (kShort: loads of a second unit that
+// may not be there) 14.8 -> 15.3, CSR products of 1.15 * 10^7 33.0 -> 33.8, 6.3 * 10^7 level: these keep the branches.
+template <int kOp, bool kShort> constexpr bool buffered_loads() { return kOp == kSum || (kOp == kSpmv && !kShort); }
+struct StreamArrays {
+    __amdgpu_buffer_rsrc_t fw, x, col;
+};
+template <bool kProduct>
+__device__ __forceinline__ void stream_load(const StreamArrays &A, int unit, int lane, StreamSlot<kProduct> &s) {
+    s.fw = __builtin_amdgcn_raw_buffer_load_b32(A.fw, 4 * ((lane & 31) + (lane >> 5)) + 128 * unit, 0, kAuxNt);
+    const int own = 16 * lane + 4 * kUnitElems * unit;
+    if constexpr (kProduct) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s.col[i] = __builtin_amdgcn_raw_buffer_load_b128(A.col, own + 1024 * i, 0, kAuxNt);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s.raw[i] = __builtin_amdgcn_raw_buffer_load_b128(A.x, own + 1024 * i, 0, kAuxNt);
+}
 
 // kNarrow: x has at most 2^30 entries, so byte offsets into it fit 32 bits (one register per address, no 64-bit
 // additions: SpMV with short rows 8 % faster, with scattered columns 2 %).
@@ -116,6 +136,7 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
     constexpr bool kProduct = kOp != kSum;
     constexpr bool kCounts = kOp != kSpmv;   // the index of an output is the ordinal of its segment
     constexpr int kDepth = kShort ? kShortRounds : kProduct ? MMV_STREAM_DEPTH_SPMV : MMV_STREAM_DEPTH_SUM;
+    constexpr bool kBuffered = buffered_loads<kOp, kShort>();
     static_assert(kWaves == (int)kSpans, "units are dealt to eight waves");
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -179,9 +200,26 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
     }
     __builtin_amdgcn_sched_barrier(0);
     StreamSlot<kProduct> slot[kDepth];
+    StreamArrays arrays;
+    __amdgpu_buffer_rsrc_t xv;
+    if constexpr (kBuffered) {
+        // (the flag word behind the tile says whether its last position ends a segment; the 16-byte block of the last entry is read whole)
+        const uint64_t left = n - span.base;
+        const uint32_t tile_elems = (uint32_t)units * kUnitElems, entries = left < tile_elems ? (uint32_t)left : tile_elems;
+        const uint32_t bytes = (4 * entries + 15) & ~15u;
+        arrays.fw = make_rsrc(P.fw + (span.base >> 5), left > tile_elems ? tile_elems / 8 + 4 : (entries + 31) / 32 * 4);
+        arrays.x = make_rsrc((const float *)P.x + span.base, bytes);
+        if constexpr (kProduct) {
+            arrays.col = make_rsrc(P.col + span.base, bytes);
+            xv = make_rsrc(P.xv, P.x_bytes);
+        }
 #pragma unroll
-    for (int i = 0; i < kDepth; ++i)
-        if (kWaves * i + wave < units) stream_load<kProduct>(P, span.base + (uint64_t)(kWaves * i + wave) * kUnitElems, lane, slot[i]);
+        for (int i = 0; i < kDepth; ++i) stream_load<kProduct>(arrays, kWaves * i + wave, lane, slot[i]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < kDepth; ++i)
+            if (kWaves * i + wave < units) stream_load<kProduct>(P, span.base + (uint64_t)(kWaves * i + wave) * kUnitElems, lane, slot[i]);
+    }
 #if MMV_LOAD_PRIO
     __builtin_amdgcn_s_setprio(0);
 #endif
@@ -251,7 +289,6 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
                 const bool full = ub + kUnitElems <= n;
                 v4u(&raw)[4] = slot[i].raw;
                 if constexpr (kProduct) {   // product vector p(i) = val(i) * x(col(i))
-                    // (columns beyond the last entry were loaded as 0: their gathers stay inside x)
                     constexpr int kBatch = kNarrow ? 4 : 1;   // words of columns whose gathers are under way together (64-bit addresses: one, or the registers do not suffice)
                     float xg[kBatch][4];
 #pragma unroll
@@ -260,8 +297,13 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
                         for (int j = 0; j < kBatch; ++j)
 #pragma unroll
                             for (int k = 0; k < 4; ++k) {
+                                // (buffered: columns of what lies behind the end, in the block of the last entry, may be anything; such a
+                                // gather reads nothing where it would leave x, or x[0].  Else they were loaded as 0.)
                                 const uint32_t at = slot[i].col[j0 + j][k];
-                                xg[j][k] = kNarrow ? *reinterpret_cast<const float *>(reinterpret_cast<const char *>(P.xv) + (at << 2)) : P.xv[at];
+                                if constexpr (kBuffered && kNarrow) xg[j][k] = from_bits<float>(__builtin_amdgcn_raw_buffer_load_b32(xv, (int)(at << 2), 0, 0));
+                                else if constexpr (kBuffered) xg[j][k] = P.xv[full || ub + 256u * (j0 + j) + 4u * lane + k < n ? at : 0u];
+                                else if constexpr (kNarrow) xg[j][k] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(P.xv) + (at << 2));
+                                else xg[j][k] = P.xv[at];
                             }
                         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -270,13 +312,13 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
                             for (int k = 0; k < 4; ++k) raw[j0 + j][k] = to_bits(from_bits<float>(raw[j0 + j][k]) * xg[j][k]);
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                    if (!full) {   // (x[0] may be infinite)
+                }
+                if (!full) {   // (SpMV: x[0] may be infinite)
 #pragma unroll
-                        for (int j = 0; j < 4; ++j)
+                    for (int j = 0; j < 4; ++j)
 #pragma unroll
-                            for (int k = 0; k < 4; ++k)
-                                if (ub + 256u * j + 4u * lane + k >= n) raw[j][k] = 0;
-                    }
+                        for (int k = 0; k < 4; ++k)
+                            if (ub + 256u * j + 4u * lane + k >= n) raw[j][k] = 0;
                 }
                 const Halves w = wave_halves<true>(slot[i].fw, lane);
                 uint32_t F = w.lo;                                    // flag word of row c (both halves of the wave)
@@ -388,8 +430,10 @@ __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__r
             if constexpr (kShort) continue;
             // the registers of this unit take the one that many rounds ahead
             __builtin_amdgcn_sched_barrier(0);
-            if (q + kWaves * kDepth < units) stream_load<kProduct>(P, span.base + (uint64_t)(kWaves * (u + kDepth) + wave) * kUnitElems, lane, slot[i]);
-            else slot[i] = StreamSlot<kProduct>{};   // (or the compiler keeps the old columns in registers all the way through)
+            if constexpr (kBuffered && !kProduct) stream_load<kProduct>(arrays, q + kWaves * kDepth, lane, slot[i]);
+            else if (q + kWaves * kDepth >= units) slot[i] = StreamSlot<kProduct>{};   // (or the compiler keeps the old columns in registers all the way through)
+            else if constexpr (kBuffered) stream_load<kProduct>(arrays, q + kWaves * kDepth, lane, slot[i]);
+            else stream_load<kProduct>(P, span.base + (uint64_t)(kWaves * (u + kDepth) + wave) * kUnitElems, lane, slot[i]);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
