@@ -15,6 +15,7 @@ import torch  # imported before the library so that both share one HIP runtime
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmmvseg.so")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 
 MMV_OK = 0
 MMV_F32_F32, MMV_F16_F32, MMV_BF16_F32, MMV_I8_I32, MMV_U8_XOR = 0, 1, 2, 3, 4
@@ -40,6 +41,10 @@ _OUT_DTYPE = {MMV_F32_F32: torch.float32, MMV_F16_F32: torch.float32, MMV_BF16_F
 _VARIANTS = {"mfma": MMV_VARIANT_MFMA, "shuffle": MMV_VARIANT_SHUFFLE}
 
 _lib = None
+# The calls that programs make over and over go through csrc/marshal.cpp where all their arguments are given: it does what the
+# lines below each of them do, and answers None where they have to (arguments left out, errors).  Host time of a call on 3000 values, us:
+# segmented scan 4.7 -> 3.3, segmented sum 5.1 -> 3.5, scan 4.3 -> 3.5, COMPRESS 5.1 -> 3.6 (the launch itself takes 2.9).
+_marshal = None
 
 
 class MmvError(RuntimeError):
@@ -48,11 +53,11 @@ class MmvError(RuntimeError):
 
 def load() -> ctypes.CDLL:
     """Loads libmmvseg.so; raises if it has not been built (there is no fallback path)."""
-    global _lib
+    global _lib, _marshal
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise MmvError("libmmvseg.so is not built: run `python -m paper_2506_23906_amd.build` "
+    if not os.path.exists(LIB_PATH) or not os.path.exists(MARSHAL_PATH):
+        raise MmvError("libmmvseg.so and _marshal.so are not built: run `python -m paper_2506_23906_amd.build` "
                        "(or __graft_entry__.build()) first")
     lib = ctypes.CDLL(LIB_PATH)
     vp, u64, sz, i32 = ctypes.c_void_p, ctypes.c_uint64, ctypes.c_size_t, ctypes.c_int
@@ -100,7 +105,10 @@ def load() -> ctypes.CDLL:
     lib.mmv_segsum_scd.restype = i32
     lib.mmv_segscan_sscr.argtypes = [vp, vp, u64, vp, i32, i32, i32, vp, sz, vp]
     lib.mmv_segscan_sscr.restype = i32
-    _lib = lib
+    from . import _marshal as marshal
+    marshal.bind(*(ctypes.cast(getattr(lib, name), vp).value for name in
+                   ("mmv_segscan", "mmv_segsum", "mmv_scan", "mmv_compress", "mmv_spmv_coo", "mmv_spmv_csr", "mmv_spmv_coo_run", "mmv_spmv_csr_run")))
+    _lib, _marshal = lib, marshal
     return lib
 
 
@@ -158,6 +166,12 @@ def new_workspace(op: int, dt: int, ff: int, n: int, device=None) -> torch.Tenso
 def mmv_segscan(x: torch.Tensor, flags: torch.Tensor, n: int | None = None, z: torch.Tensor | None = None,
                 variant: str = "mfma", ws: torch.Tensor | None = None, stream=None) -> torch.Tensor:
     """Segmented inclusive scan of x under segment-start flags; returns z (fp32 or int32)."""
+    if _marshal is not None:
+        st = _marshal.segscan(x, flags, n, z, variant, ws, stream)
+        if st is not None:
+            if st:
+                _check(st, "mmv_segscan")
+            return z
     lib = load()
     n = x.numel() if n is None else n
     dt, ff = _DTYPES[x.dtype], _flag_fmt(flags)
@@ -186,6 +200,12 @@ def mmv_segsum(x: torch.Tensor, flags: torch.Tensor, n: int | None = None, out: 
                nseg: torch.Tensor | None = None, variant: str = "mfma", ws: torch.Tensor | None = None,
                stream=None):
     """Segmented sum; returns (out, nseg) where nseg is a one-element int64 device tensor."""
+    if _marshal is not None:
+        st = _marshal.segsum(x, flags, n, out, nseg, variant, ws, stream)
+        if st is not None:
+            if st:
+                _check(st, "mmv_segsum")
+            return out, nseg
     lib = load()
     n = x.numel() if n is None else n
     dt, ff = _DTYPES[x.dtype], _flag_fmt(flags)
@@ -205,6 +225,12 @@ def mmv_spmv_coo(n_rows: int, n_cols: int, row: torch.Tensor, col: torch.Tensor,
                  x: torch.Tensor, y: torch.Tensor | None = None, variant: str = "mfma",
                  ws: torch.Tensor | None = None, stream=None) -> torch.Tensor:
     """y = A x for a row-sorted COO matrix (int32 indices, fp32 values)."""
+    if _marshal is not None:
+        st = _marshal.spmv_coo(n_rows, n_cols, None, row, col, val, x, y, variant, ws, stream)
+        if st is not None:
+            if st:
+                _check(st, "mmv_spmv_coo")
+            return y
     lib = load()
     nnz = val.numel()
     if y is None:
@@ -233,6 +259,12 @@ def mmv_spmv_coo_run(n_rows: int, n_cols: int, row: torch.Tensor, col: torch.Ten
                      x: torch.Tensor, ws: torch.Tensor, y: torch.Tensor | None = None, variant: str = "mfma",
                      stream=None) -> torch.Tensor:
     """Second step: y = A x with the plan that mmv_spmv_coo_prepare left in ws."""
+    if _marshal is not None:
+        st = _marshal.spmv_coo_run(n_rows, n_cols, None, row, col, val, x, y, variant, ws, stream)
+        if st is not None:
+            if st:
+                _check(st, "mmv_spmv_coo_run")
+            return y
     if y is None:
         y = torch.empty(n_rows, dtype=torch.float32, device=val.device)
     st = load().mmv_spmv_coo_run(n_rows, n_cols, val.numel(), _dev(row, "row"), _dev(col, "col"), _dev(val, "val"),
@@ -258,6 +290,12 @@ def mmv_spmv_csr_run(n_rows: int, n_cols: int, rowptr: torch.Tensor, col: torch.
                      x: torch.Tensor, ws: torch.Tensor, y: torch.Tensor | None = None, variant: str = "mfma",
                      stream=None) -> torch.Tensor:
     """Second step: y = A x with the plan that mmv_spmv_csr_prepare left in ws."""
+    if _marshal is not None:
+        st = _marshal.spmv_csr_run(n_rows, n_cols, None, rowptr, col, val, x, y, variant, ws, stream)
+        if st is not None:
+            if st:
+                _check(st, "mmv_spmv_csr_run")
+            return y
     if y is None:
         y = torch.empty(n_rows, dtype=torch.float32, device=val.device)
     st = load().mmv_spmv_csr_run(n_rows, n_cols, val.numel(), _dev(rowptr, "rowptr"), _dev(col, "col"), _dev(val, "val"),
@@ -311,6 +349,12 @@ def mmv_spmv_csr(n_rows: int, n_cols: int, rowptr: torch.Tensor, col: torch.Tens
                  x: torch.Tensor, y: torch.Tensor | None = None, variant: str = "mfma",
                  ws: torch.Tensor | None = None, stream=None, nnz: int | None = None) -> torch.Tensor:
     """y = A x for a CSR matrix (int32 row pointers and column indices, fp32 values)."""
+    if _marshal is not None:
+        st = _marshal.spmv_csr(n_rows, n_cols, nnz, rowptr, col, val, x, y, variant, ws, stream)
+        if st is not None:
+            if st:
+                _check(st, "mmv_spmv_csr")
+            return y
     lib = load()
     nnz = val.numel() if nnz is None else nnz
     if y is None:
@@ -327,6 +371,12 @@ def mmv_spmv_csr(n_rows: int, n_cols: int, rowptr: torch.Tensor, col: torch.Tens
 def mmv_scan(x: torch.Tensor, n: int | None = None, z: torch.Tensor | None = None, variant: str = "mfma",
              ws: torch.Tensor | None = None, stream=None) -> torch.Tensor:
     """Unsegmented inclusive scan; returns z (fp32 or int32)."""
+    if _marshal is not None:
+        st = _marshal.scan(x, n, z, variant, ws, stream)
+        if st is not None:
+            if st:
+                _check(st, "mmv_scan")
+            return z
     lib = load()
     n = x.numel() if n is None else n
     dt = _DTYPES[x.dtype]
@@ -343,6 +393,12 @@ def mmv_scan(x: torch.Tensor, n: int | None = None, z: torch.Tensor | None = Non
 def mmv_compress(x: torch.Tensor | None, mask: torch.Tensor, n: int, out: torch.Tensor | None = None,
                  count: torch.Tensor | None = None, ws: torch.Tensor | None = None, stream=None):
     """COMPRESS of a 32-bit vector (or of the positions, x=None); returns (out, count)."""
+    if _marshal is not None:
+        st = _marshal.compress(x, mask, n, out, count, ws, stream)
+        if st is not None:
+            if st:
+                _check(st, "mmv_compress")
+            return out, count
     lib = load()
     ff = _flag_fmt(mask)
     if x is not None and x.element_size() != 4:

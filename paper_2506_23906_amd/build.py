@@ -1,4 +1,5 @@
-"""Builds libmmvseg.so (HIP, gfx950 only) next to this file with hipcc."""
+"""Builds libmmvseg.so (HIP, gfx950 only) next to this file with hipcc, and the argument marshalling of the binding
+(_marshal.so, a CPython extension on torch's headers) with g++."""
 from __future__ import annotations
 
 import os
@@ -10,6 +11,8 @@ ROOT = os.path.dirname(HERE)
 SRC = os.path.join(HERE, "csrc", "mmvseg.hip")
 LIB = os.path.join(HERE, "libmmvseg.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+MARSHAL_SRC = os.path.join(HERE, "csrc", "marshal.cpp")
+MARSHAL_LIB = os.path.join(HERE, "_marshal.so")
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -33,7 +36,33 @@ def build(verbose: bool = False, extra: list[str] | None = None, out: str | None
     if verbose and err.strip():
         sys.stderr.write(err + "\n")
     os.replace(tmp, lib)
+    if out is None:
+        build_marshal(verbose)
     return lib
+
+
+def build_marshal(verbose: bool = False) -> str:
+    """Compiles the argument marshalling (host code only) against the installed torch."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    tmp = MARSHAL_LIB + ".tmp.%d" % os.getpid()
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", os.path.join(ROOT, "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", "/opt/rocm/include"]
+    for path in cpp_extension.include_paths():
+        cmd += ["-isystem", path]
+    cmd += ["-o", tmp, MARSHAL_SRC, "-L" + libs, "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stderr + "\n")
+        raise RuntimeError("g++ failed building _marshal.so")
+    if verbose and res.stderr.strip():
+        sys.stderr.write(res.stderr + "\n")
+    os.replace(tmp, MARSHAL_LIB)
+    return MARSHAL_LIB
 
 
 if __name__ == "__main__":

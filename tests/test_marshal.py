@@ -1,0 +1,72 @@
+"""The binding's calls through the extension that marshals their arguments, and what it leaves to the lines in Python."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2506_23906_amd import binding as B
+from paper_2506_23906_amd import workloads as W
+
+
+def test_what_it_does_not_know_is_left_to_python(libmmvseg_path):
+    B.load()
+    m, t = B._marshal, torch.zeros(64)
+    f = torch.zeros(64, dtype=torch.uint8)
+    for z, ws in ((t, f), (None, f), (t, None)):               # CPU tensors, arguments left out
+        assert m.segscan(t, f, None, z, "mfma", ws, None) is None
+    assert m.scan(t, 3.0, t, "mfma", f, None) is None and m.scan(t, 3, t, "other", f, None) is None
+    assert m.compress(None, f, 64, t, t, f, None) is None
+    assert m.spmv_csr(8, 8, None, t, t, t, t, t, "mfma", f, None) is None
+    with pytest.raises(TypeError):
+        m.segscan(t, f)
+    with pytest.raises(TypeError):
+        m.bind(1)
+    with pytest.raises(B.MmvError):                            # ... which raises what it raised before
+        B.mmv_segscan(t, f, z=t, ws=f)
+
+
+@pytest.mark.gpu
+def test_both_ways_give_the_same(monkeypatch):
+    n = 5000
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    rng = np.random.default_rng(3)
+    row, col, val, xv = W.spmv_coo_zipf(700, 600, 9000, cap=300, seed=5)
+    rowptr, f = dev(W.csr_rowptr(row, 700)), dev((rng.random(n) < 0.1).astype(np.uint8))
+    row, col, val, xv = dev(row), dev(col), dev(val), dev(xv)
+    bits = dev(W.pack_flags(f.cpu().numpy()).view(np.int32))
+    x = dev(rng.integers(-3, 4, size=n).astype(np.float32))
+    side = torch.cuda.Stream()
+
+    def calls(how):
+        new = lambda k, dt=torch.float32: torch.zeros(k, dtype=dt, device="cuda")
+        out = []
+        for xt in (x, x.half(), x.bfloat16(), x.to(torch.int8)):
+            dt = B._DTYPES[xt.dtype]
+            for fl in (f, bits):
+                ff = B._flag_fmt(fl)
+                out.append(B.mmv_segscan(xt, fl, n=n, z=new(n, B._OUT_DTYPE[dt]), ws=B.new_workspace(B.MMV_OP_SEGSCAN, dt, ff, n), **how))
+                out += B.mmv_segsum(xt, fl, out=new(n, B._OUT_DTYPE[dt]), nseg=new(1, torch.int64), variant="shuffle",
+                                    ws=B.new_workspace(B.MMV_OP_SEGSUM, dt, ff, n), n=n, **how)
+            out.append(B.mmv_scan(xt, n=n - 7, z=new(n, B._OUT_DTYPE[dt]), ws=B.new_workspace(B.MMV_OP_SCAN, dt, 1, n), **how))
+        for v in (x, None):
+            out += B.mmv_compress(v, f, n, out=new(n, torch.float32 if v is not None else torch.int32), count=new(1, torch.int64),
+                                  ws=B.new_workspace(B.MMV_OP_COMPRESS, B.MMV_I8_I32, 0, n), **how)
+        ws = B.new_workspace(B.MMV_OP_SPMV_COO, B.MMV_F32_F32, B.MMV_FLAGS_PACKED32, val.numel())
+        out.append(B.mmv_spmv_coo(700, 600, row, col, val, xv, y=new(700), ws=ws, **how))
+        ws = B.mmv_spmv_coo_prepare(700, 600, row, col, **how)
+        out.append(B.mmv_spmv_coo_run(700, 600, row, col, val, xv, ws, y=new(700), **how))
+        ws = B.workspace(B.mmv_spmv_csr_workspace_bytes(700, val.numel()))
+        out.append(B.mmv_spmv_csr(700, 600, rowptr, col, val, xv, y=new(700), ws=ws, **how))
+        ws = B.mmv_spmv_csr_prepare(700, 600, rowptr, col, **how)
+        out.append(B.mmv_spmv_csr_run(700, 600, rowptr, col, val, xv, ws, y=new(700), **how))
+        torch.cuda.synchronize()
+        return out
+
+    here = calls({})
+    with torch.cuda.stream(side):
+        there = calls({})
+    named = calls({"stream": side})
+    monkeypatch.setattr(B, "_marshal", None)
+    python = calls({})
+    assert len(here) == len(python) == len(named) == len(there)
+    for a, b, c, d in zip(here, python, named, there):
+        assert torch.equal(a, b) and torch.equal(c, b) and torch.equal(d, b)
