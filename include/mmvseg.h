@@ -92,7 +92,8 @@ typedef enum {
                                 latency.  Short are scans and sums of up to 2^21 elements (fp32 sums and
                                 16-bit mmv_scan: 3 * 2^20, other mmv_scan: 2^22) whose output overlaps no input
                                 (a scan's fp32 values may be its output).  Scans of fp32 values of any length take the same
-                                kernel with either as well, without speculation: sums from lane to lane, carried in 64 bits */
+                                kernel with either as well, without speculation: sums from lane to lane, carried in 64 bits;
+                                 so do segmented scans of more than 2^24 and up to 3 * 2^23 16-bit values with MMV_VARIANT_MFMA */
     MMV_VARIANT_INT_MAX = 0x7fffffff
 } mmv_variant;
 

@@ -43,7 +43,7 @@ template <typename TT> inline int row_form_cpw_of(mmv_op op, bool mfma) {
 }
 inline int row_form_cpw(mmv_op op, mmv_dtype dt, bool mfma) {
     switch (dt) {
-        case MMV_F32_F32: return op == MMV_OP_SCAN ? lane_cpw<kPlainScan>() : lane_cpw<kScan>();   // (lane_tile)
+        case MMV_F32_F32: return op == MMV_OP_SCAN ? lane_cpw<TF32, kPlainScan>() : lane_cpw<TF32, kScan>();   // (lane_tile)
         case MMV_F16_F32: return row_form_cpw_of<TF16>(op, mfma);
         case MMV_BF16_F32: return row_form_cpw_of<TBF16>(op, mfma);
         case MMV_I8_I32: return row_form_cpw_of<TI8>(op, mfma);
@@ -86,16 +86,21 @@ inline int waves_of(mmv_dtype dt) {   // (SpMV has a tile plan of its own)
 // mmv_scan 25.4 -> 23.6; fp16 20 * 10^6 28.2 / 30.3 -> 22.9 / 25.7, 25 * 10^6 30.8 / 34.7 -> 27.4 / 29.4.
 // Longer vectors: three workgroups take 5 % more than two (the memory is short of neither, and more tiles are being read and
 // written at a time: bytes 2^26 62.2 -> 65.3, 2^28 235 -> 245).  16-bit values: up to 1024 chunks per wave two workgroups are level
-// (12 * 10^6 17.0 / 18.5 -> 15.3 / 19.2, 14 * 10^6 18.5 / 20.6 -> 18.5 / 21.6); on the matrix cores the form spills 20 registers and is
-// 20 % slower, and its row scans by vector instructions have a larger error (30 % starts 5.5e-9 against 4.9e-9).
+// (12 * 10^6 17.0 / 18.5 -> 15.3 / 19.2, 14 * 10^6 18.5 / 20.6 -> 18.5 / 21.6).  On the matrix cores the form spills 20 registers and is
+// 20 % slower; segmented scans of that variant take the form in lanes there (lane_kernel.h), whose error is smaller than that of either
+// row scan (fp16, lengths up to 512 1.7e-8 against 2.1e-8, one segment 2.5e-8 against 2e-7): 17 * 10^6 26.0 / 29.7 -> 22.8 / 25.1,
+// 20 * 10^6 28.5 / 31.4 -> 24.8 / 27.1, 25 * 10^6 31.6 / 35.0 -> 30.2 / 31.3.  Not outside this range: 8 * 10^6 12.9 / 15.0 -> 14.4 / 15.7
+// (a wave's blocks one after the other), 1.8 * 10^8 181 / 213 -> 188 / 189 (two workgroups per compute unit 186 / 192); and not for
+// mmv_scan: tiles of three chunks, 12 * 10^6 19.3 -> 21.2, 5 * 10^7 59.0 -> 57.9, 1.8 * 10^8 195.5 -> 196.5.
 template <typename TT, int kOp, bool kMfma> constexpr bool has_round_form() {
-    return (kOp == kScan || kOp == kPlainScan) && (TT::kDtype == MMV_I8_I32 || (sizeof(typename TT::in_t) <= 2 && !kMfma));
+    return (kOp == kScan || kOp == kPlainScan) && (TT::kDtype == MMV_I8_I32 || (sizeof(typename TT::in_t) <= 2 && !kMfma) || (kOp == kScan && sizeof(typename TT::in_t) == 2));
 }
 constexpr uint64_t kRoundTiles = 3 * kComputeUnits;
 constexpr bool round_form(mmv_op op, mmv_dtype dt, uint64_t chunks, bool mfma) {   // `chunks`: per wave, of the whole vector
     if ((op != MMV_OP_SEGSCAN && op != MMV_OP_SCAN) || dt == MMV_F32_F32 || chunks > (uint64_t)kRoundCpw * kRoundTiles) return false;
     if (dt == MMV_I8_I32) return true;
-    return !mfma && (dt == MMV_U8_XOR || chunks > (uint64_t)kRoundCpw * kResident);
+    if (dt == MMV_U8_XOR) return !mfma;
+    return (!mfma || op == MMV_OP_SEGSCAN) && chunks > (uint64_t)kRoundCpw * kResident;
 }
 struct TilePlan {
     TileRegions reg;
@@ -103,7 +108,7 @@ struct TilePlan {
     uint32_t unit;         // elements that one step of a region's `cpw` stands for: one chunk per wave (stream form: one unit of 1024)
     uint32_t body_elems;   // elements of a tile in the middle of the vector
     bool chunk_form;       // segmented sum: the kernel that streams through long spans (sum_kernel) takes it
-    bool round_form;       // scans of 8- and 16-bit values: all tiles resident at once (OneRound)
+    bool round_form;       // scans of 8- and 16-bit values: all tiles resident at once (OneRound, InLanes)
     bool short_form;       // stream form: at most kShortUnits units per tile, which a wave loads at once
 };
 inline TilePlan tile_plan(mmv_op op, mmv_dtype dt, uint64_t n, bool mfma = true) {
@@ -379,13 +384,14 @@ template <typename TT, int kOp, bool kMfma> hipError_t launch_variant(Params P, 
         if constexpr (kOp != kSum) {
             if (!narrow) kernel = stream_kernel<TT, kOp, kMfma, false, false>;
         }
-    } else if constexpr (sizeof(typename TT::in_t) == 4) {
+    } else if constexpr (lane_form<TT, kOp>()) {
         kernel = seg_kernel<InLanes<TT>, kOp, false>;   // (both variants)
     } else {
         kernel = seg_kernel<TT, kOp, kMfma>;
         if constexpr (has_round_form<TT, kOp, kMfma>()) {
             which = plan.round_form ? 2 : 0;
-            if (plan.round_form) kernel = seg_kernel<OneRound<TT>, kOp, kMfma>;
+            typedef std::conditional_t<sizeof(typename TT::in_t) == 2 && kMfma, InLanes<TT>, OneRound<TT>> Round;
+            if (plan.round_form) kernel = seg_kernel<Round, kOp, kMfma && !kInLanes<Round>>;
         }
         if constexpr (chunk_sum_kernel<TT, kOp, kMfma>()) {
             which = plan.chunk_form ? 1 : 0;

@@ -1,5 +1,5 @@
 // libmmvseg, part of the one translation unit mmvseg.hip (included there, in order).
-// The tile body of the scans of 32-bit values: a tile stays in registers, and its sums go from lane to lane.
+// The tile body of the scans of 32-bit values, and of some of 16-bit ones: a tile stays in registers, and its sums go from lane to lane.
 #pragma once
 
 namespace {
@@ -21,6 +21,10 @@ namespace {
 // segments of 80 214 -> 196 (6.4 TB/s without the reset), 5.2 * 10^7 without flags 83 -> 72; 8.2 * 10^6 21 -> 17; mmv_scan of 5 * 10^7 77.5 -> 72, 1.5 * 10^8 217 -> 197.
 // Tiles: 8 blocks per wave and three workgroups per compute unit (16 and two: lengths up to 2000, 9 * 10^7 127 us against 123; eight
 // waves per SIMD: 3 % slower); without flags every tile waits for all those before it, and longer ones pay: 16 blocks (5 * 10^7 72 us; 8: 76, 24: 75).
+// Conditions on blocks are made anew in each pass: hoisted, they took a pair of scalar registers each, and 15 to 83 of those spilled.
+// 16-bit values (segmented scans that fill 512 to 768 workgroups, round_form in host.h): 64-bit loads, so that a lane's four results are
+// one store; their results are rounded once, from 64 bits.  62 to 78 registers, where the form with row scans on the matrix cores needs
+// more than the 80 that three workgroups per compute unit leave: fp16 20 * 10^6 28.5 -> 24.8 us the call.
 
 constexpr int kBlockElems = 256;                             // four consecutive elements per lane
 constexpr int kChunkBlocks = kChunkElems / kBlockElems;
@@ -73,12 +77,46 @@ template <bool kFlagged> __device__ __forceinline__ double lane_scan(double v, c
     return v;
 }
 
+// The four values of a lane in a block, as loaded, and what lies from `valid` on cleared.
+template <typename In> struct LaneRaw {
+    typedef v2u type;
+    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, int at) { return __builtin_amdgcn_raw_buffer_load_b64(r, at, 0, kAuxNt); }
+    static __device__ __forceinline__ void mask(type &w, int valid) {
+#pragma unroll
+        for (int d = 0; d < 2; ++d) w[d] = valid >= 2 * d + 2 ? w[d] : valid > 2 * d ? w[d] & 0xFFFFu : 0u;
+    }
+};
+template <> struct LaneRaw<float> {
+    typedef v4u type;
+    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, int at) { return __builtin_amdgcn_raw_buffer_load_b128(r, at, 0, kAuxNt); }
+    static __device__ __forceinline__ void mask(type &w, int valid) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) w[d] = valid > d ? w[d] : 0u;
+    }
+};
+template <typename TT> __device__ __forceinline__ float lane_value(const typename LaneRaw<typename TT::in_t>::type &w, int i) {
+    typedef typename TT::in_t In;
+    if constexpr (sizeof(In) == 4) return from_bits<float>(w[i]);
+    else return TT::widen(__builtin_bit_cast(In, (uint16_t)(w[i / 2] >> (16 * (i & 1)))));
+}
+// Carry into a lane plus a sum inside it.  16-bit values: added in 64 bits, one rounding.
+template <typename TT> struct LaneCarry {
+    double e;
+    __device__ __forceinline__ float plus(float p) const { return (float)(e + (double)p); }
+};
+template <> struct LaneCarry<InLanes<TF32>> {
+    float e;
+    __device__ __forceinline__ explicit LaneCarry(double v) : e((float)v) {}
+    __device__ __forceinline__ float plus(float p) const { return e + p; }
+};
+
 // One tile.  A wave holds its whole span in registers: block b of lane l = its elements 256 b + 4 l .. + 3.
 template <typename TT, int kOp>
 __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves> &sm, const uint32_t tile) {
     typedef typename TT::in_t In;
     constexpr int kWaves = TT::kWaves;
-    constexpr int kCpw = lane_cpw<kOp>();
+    constexpr int kCpw = lane_cpw<TT, kOp>();
+    typedef LaneRaw<In> Raw;
     constexpr int kBlocks = kCpw * kChunkBlocks;
     constexpr bool kFlags = kOp == kScan;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -91,8 +129,9 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
     // Buffer loads: what lies at or beyond cnt reads 0, without a branch (the 16-byte block of the last element is read whole).
     const auto x_rsrc = make_rsrc((const In *)P.x + wave_base, (uint32_t)((cnt * (int)sizeof(In) + 15) & ~15));
     uint32_t F[kCpw] = {};
-    v4u raw[kBlocks];
-    int own = 16 * lane;             // my byte offset in a block
+    typename Raw::type raw[kBlocks];
+    int from_x = 4 * (int)sizeof(In) * lane, own = 16 * lane;   // my byte offsets in a block of values and of results
+    asm volatile("" : "+v"(from_x));
     asm volatile("" : "+v"(own));   // (as an unknown, here and at the stores, so that the offset of a block is added by the
                                      // instruction itself and not kept in a register from the start on)
     if constexpr (kFlags) {
@@ -101,7 +140,7 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
         for (int c = 0; c < kCpw; ++c) F[c] = __builtin_amdgcn_raw_buffer_load_b32(f_rsrc, 4 * lane + 256 * c, 0, kAuxNt);
     }
 #pragma unroll
-    for (int b = 0; b < kBlocks; ++b) raw[b] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, own + 1024 * b, 0, kAuxNt);
+    for (int b = 0; b < kBlocks; ++b) raw[b] = Raw::load(x_rsrc, from_x + kBlockElems * (int)sizeof(In) * b);
 #if MMV_LOAD_PRIO
     __builtin_amdgcn_s_setprio(0);
 #endif
@@ -112,10 +151,7 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
             if (valid < 32) F[c] = valid > 0 ? F[c] & ((1u << valid) - 1u) : 0u;
         }
 #pragma unroll
-        for (int b = 0; b < kBlocks; ++b)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (kBlockElems * b + 4 * lane + i >= cnt) raw[b][i] = 0;
+        for (int b = 0; b < kBlocks; ++b) Raw::mask(raw[b], cnt - kBlockElems * b - 4 * lane);
     }
     // flags of the span: rows of 32 with any, first and last position (scalars)
     uint64_t any[kCpw];
@@ -140,7 +176,7 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
     if (last < 0) {
 #pragma unroll
         for (int b = 0; b < kBlocks; ++b)
-            s += (double)((from_bits<float>(raw[b][0]) + from_bits<float>(raw[b][1])) + (from_bits<float>(raw[b][2]) + from_bits<float>(raw[b][3])));
+            s += (double)((lane_value<TT>(raw[b], 0) + lane_value<TT>(raw[b], 1)) + (lane_value<TT>(raw[b], 2) + lane_value<TT>(raw[b], 3)));
     } else {
 #pragma unroll
         for (int b = 0; b < kBlocks; ++b)
@@ -148,7 +184,7 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
                 const int k = last - kBlockElems * b - 4 * lane;   // my elements from k on count
                 float t[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) t[i] = i >= k ? from_bits<float>(raw[b][i]) : 0.0f;
+                for (int i = 0; i < 4; ++i) t[i] = i >= k ? lane_value<TT>(raw[b], i) : 0.0f;
                 s += (double)((t[0] + t[1]) + (t[2] + t[3]));
             }
     }
@@ -186,6 +222,15 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
         // (or the compiler makes the sums of every block ahead of the loop, and keeps them)
 #pragma unroll
         for (int b = 0; b < kBlocks; ++b) asm volatile("" : "+v"(raw[b]));
+        // (... nor the conditions: a pair of scalar registers each, and the scalar registers did not suffice)
+        int end = cnt;
+        asm volatile("" : "+s"(end));
+        uint64_t rows[kCpw];
+#pragma unroll
+        for (int c = 0; c < kCpw; ++c) {
+            rows[c] = any[c];
+            asm volatile("" : "+s"(rows[c]));
+        }
         int from = 0, upto = closed ? kBlocks : first_block + 1, store_from = 0;
         if (pass == 0) from = first_block, upto = kBlocks, store_from = first_block + 1;   // (of the block of that flag: what it carries on)
         if (pass == 1 && !closed) {
@@ -208,19 +253,18 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
         for (int b = 0; b < kBlocks; ++b) {
             const int c = b / kChunkBlocks, j = b % kChunkBlocks;
             __builtin_amdgcn_sched_barrier(0);
-            if (b < from || b >= upto || kBlockElems * b >= cnt) continue;
-            const float x0 = from_bits<float>(raw[b][0]), x1 = from_bits<float>(raw[b][1]), x2 = from_bits<float>(raw[b][2]),
-                        x3 = from_bits<float>(raw[b][3]);
+            if (b < from || b >= upto || kBlockElems * b >= end) continue;
+            const float x0 = lane_value<TT>(raw[b], 0), x1 = lane_value<TT>(raw[b], 1), x2 = lane_value<TT>(raw[b], 2), x3 = lane_value<TT>(raw[b], 3);
             float o[4];
-            if (!kFlags || ((any[c] >> (8 * j)) & 0xFFull) == 0) {
+            if (!kFlags || ((rows[c] >> (8 * j)) & 0xFFull) == 0) {
                 const float p1 = x0 + x1, p2 = p1 + x2, p3 = p2 + x3;
                 const double inc = lane_scan<false>((double)p3, ScanMasks{});
-                const float ec = (float)(run + dpp_bound<0x138>(inc));   // wave_shr 1: lane 0 gets 0
+                const LaneCarry<TT> ec{run + dpp_bound<0x138>(inc)};   // wave_shr 1: lane 0 gets 0
                 run += wave_last(inc);
-                o[0] = ec + x0;
-                o[1] = ec + p1;
-                o[2] = ec + p2;
-                o[3] = ec + p3;
+                o[0] = ec.plus(x0);
+                o[1] = ec.plus(p1);
+                o[2] = ec.plus(p2);
+                o[3] = ec.plus(p3);
             } else {
                 // (F[c] holds row l of the chunk in lane l: a lane needs four bits of row 8 j + l / 8)
                 const uint32_t word = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (8 * j + (lane >> 3)), (int)F[c]);
@@ -231,23 +275,23 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
                 double e = dpp_bound<0x138>(inc);
                 const uint64_t upto_first = (m & (0 - m)) | ((m & (0 - m)) - 1);   // lanes without a flag in a lane before them
                 e += unless(~upto_first, run);
-                const float ec = (float)e;
+                const LaneCarry<TT> ec{e};
                 run = wave_last(inc);
-                o[0] = (nib & 1u) ? x0 : ec + x0;
-                o[1] = (nib & 3u) ? p1 : ec + p1;
-                o[2] = (nib & 7u) ? p2 : ec + p2;
-                o[3] = nib ? p3 : ec + p3;
+                o[0] = (nib & 1u) ? x0 : ec.plus(x0);
+                o[1] = (nib & 3u) ? p1 : ec.plus(p1);
+                o[2] = (nib & 7u) ? p2 : ec.plus(p2);
+                o[3] = nib ? p3 : ec.plus(p3);
             }
             if (b >= store_from) {
                 asm volatile("" : "+v"(own));
                 const v4u w = {to_bits(o[0]), to_bits(o[1]), to_bits(o[2]), to_bits(o[3])};
-                if (kBlockElems * (b + 1) <= cnt) {
+                if (kBlockElems * (b + 1) <= end) {
                     __builtin_amdgcn_raw_buffer_store_b128(w, z_rsrc, own + 1024 * b, 0, kAuxNt);
                 } else {
                     float *z = (float *)P.z + wave_base;
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        if (own / 4 + kBlockElems * b + i < cnt) z[own / 4 + kBlockElems * b + i] = o[i];
+                        if (own / 4 + kBlockElems * b + i < end) z[own / 4 + kBlockElems * b + i] = o[i];
                 }
             }
         }

@@ -83,11 +83,16 @@ constexpr int kRoundCpw = 2;
 template <typename TT> struct OneRound : TT {
     static constexpr bool kOneRound = true;
 };
-// A scan whose tiles stay in registers (lane_kernel.h).
+// A scan whose tiles stay in registers (lane_kernel.h); 16-bit values: two chunks per wave at most, the longest that round_form makes.
 template <typename TT> struct InLanes : TT {};
 template <typename TT> constexpr bool kInLanes = false;
 template <typename TT> constexpr bool kInLanes<InLanes<TT>> = true;
-template <int kOp> constexpr int lane_cpw() { return kOp == kPlainScan ? MMV_CPW_F32_SCAN : MMV_CPW_F32; }
+template <typename TT, int kOp> constexpr int lane_cpw() {
+    if (sizeof(typename TT::in_t) == 2) return kRoundCpw;
+    return kOp == kPlainScan ? MMV_CPW_F32_SCAN : MMV_CPW_F32;
+}
+// Whether vectors of every length take that form (16-bit values: some, see round_form in host.h).
+template <typename TT, int kOp> constexpr bool lane_form() { return (kOp == kScan || kOp == kPlainScan) && sizeof(typename TT::in_t) == 4; }
 // Most chunks a wave of seg_tile takes.  Bytes under exclusive or in the matrix-core variant hold four accumulators
 // of bit-plane sums per tile next to the raw words: two chunks fit the registers, four spill.  The scan without a
 // flag vector keeps no flag words and no carried flags, which leaves room for longer tiles of 16-bit inputs.

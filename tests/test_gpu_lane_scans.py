@@ -91,3 +91,26 @@ def test_nothing_is_written_behind_the_result(ragged):
             B.mmv_segscan(xt[:n], bits[:(n + 31) // 32], n=n, z=room[:n])
         assert np.array_equal(room[:n].cpu().numpy(), oracle.segscan(x, f).astype(np.float32)), op
         assert bool((room[n:] == 7.0).all()), op
+
+
+@pytest.mark.parametrize("ragged", [1, 2, 7, 259, 2051, 16386])
+@pytest.mark.parametrize("tt", [torch.float16, torch.bfloat16])
+def test_16_bit_values(tt, ragged):
+    """Segmented scans just above 2^24 elements.  A lane's four values are added up in 32 bits (three roundings at most, each at most
+    2^-24 of A), the rest in 64, and the result is rounded once: 4 * 2^-24 * A.  Nothing behind the inputs counts, nothing is written
+    behind the result."""
+    n = (1 << 24) + ragged
+    rng = np.random.default_rng(ragged)
+    room, words = torch.full((n + 40_000,), 7.0, device="cuda"), (n + 31) // 32
+    xt = torch.full((n + 40_000,), float("nan"), device="cuda", dtype=tt)
+    xt[:n] = dev(rng.standard_normal(n, dtype=np.float32)).to(tt)
+    x = xt[:n].float().cpu().numpy()
+    for places in ([], BORDERS + [n - b for b in BORDERS], np.flatnonzero(rng.random(n, dtype=np.float32) < 0.2), range(n)):
+        f = flags_at(n, places)
+        print(tt, n, len(places), flush=True)
+        bits = torch.full((words + 2000,), -1, dtype=torch.int32, device="cuda")
+        bits[:words] = flags_dev(f, True)[:words]
+        z = B.mmv_segscan(xt[:n], bits[:words], n=n, z=room[:n]).cpu().numpy()
+        assert (np.abs(z.astype(np.float64) - oracle.segscan(x, f)) <= 4 * 2.0 ** -24 * abs_scan(x, f)).all()
+        assert np.array_equal(z[f == 1].view(np.uint32), x[f == 1].view(np.uint32))
+        assert bool((room[n:] == 7.0).all())

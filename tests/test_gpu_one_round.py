@@ -1,6 +1,6 @@
 """Scans of 8- and 16-bit values in one round of three workgroups per compute unit: up to 768 tiles of 16384 elements, then tiles of
-16384 and of 32768 that make 768 together, up to 25165824 elements; 16-bit values only without the matrix cores and from
-16777217 elements on.  Whole numbers: exact."""
+16384 and of 32768 that make 768 together, up to 25165824 elements; 16-bit values only from 16777217
+elements on, mmv_scan of them only without the matrix cores.  Whole numbers: exact."""
 import numpy as np
 import pytest
 import torch
