@@ -48,6 +48,13 @@ template <int kWaves, int kRows> struct SegShared {
     uint32_t tile, carry_v, carry_c, ready, arrived;
 };
 
+// Descriptors that a look-back takes at a time (lookback in lanes.h).  Tiles of bytes hold four times the elements of fp32 ones, so fewer
+// of them are in flight and ask for the same lines: without flags, windows of 64 -> 16: 5 * 10^7 bytes 50.6 -> 52.3 us, segmented 52.3 -> 54.9, 10^8
+// 90.5 -> 90.6, 2^28 224.8 -> 223.0.  16-bit values, 64 / 32 / 16: segmented, 10^8 115.3 / 111.7 / 111.8, mmv_scan 3 * 10^7 39.1 / 39.6 / 40.4.
+template <typename TT> __device__ __forceinline__ int seg_poll_lanes(const Params &P) {
+    return TT::kOneRound || sizeof(typename TT::in_t) == 1 || P.num_tiles <= P.first_round ? 64 : 32;
+}
+
 // One tile, from the loads on.
 // In the one-round form LDS holds one 32x32 tile of a wave at a time, half a chunk (37 instead of 74 KB per workgroup).
 template <typename TT> constexpr int lds_rows() { return TT::kOneRound ? kS : kRowsPerChunk; }
@@ -166,7 +173,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
                 if constexpr (kEarlyLookback) {
                     // ... and it looks back for the carry of the tiles before right away, so that the tile's own
                     // prefix is out for its successors a whole phase A earlier (the other waves go on meanwhile)
-                    const A carry_in = lookback<A, kAluLanes>(P.desc_v, (int)tile, lane, TT::kOneRound ? 64 : poll_lanes(P.num_tiles, P.first_round), P.hdr);
+                    const A carry_in = lookback<A, kAluLanes>(P.desc_v, (int)tile, lane, seg_poll_lanes<TT>(P), P.hdr);
                     if (lane == 0) {
                         desc_store(P.desc_v + tile, kStatusPrefix, to_bits(carry_in + total));
                         sm.carry_v = to_bits(carry_in);
@@ -328,7 +335,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
     }
     uint64_t polled = 0;
     if constexpr (kAsyncLookback) {
-        if (i_published) polled = lookback_poll(P.desc_v, (int)tile, lane, TT::kOneRound ? 64 : poll_lanes(P.num_tiles, P.first_round));
+        if (i_published) polled = lookback_poll(P.desc_v, (int)tile, lane, seg_poll_lanes<TT>(P));
     }
     __syncthreads();
 
@@ -378,7 +385,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
             const bool looked_back = (kEarlyLookback || kAsyncLookback) && !final_now;
             if constexpr (kAsyncLookback) {
                 if (i_published) {
-                    tile_carry = lookback<A, kAluLanes, true>(P.desc_v, (int)tile, lane, TT::kOneRound ? 64 : poll_lanes(P.num_tiles, P.first_round), P.hdr, polled);
+                    tile_carry = lookback<A, kAluLanes, true>(P.desc_v, (int)tile, lane, seg_poll_lanes<TT>(P), P.hdr, polled);
                     if (lane == 0) {
                         desc_store(P.desc_v + tile, kStatusPrefix, to_bits(tile_carry + tagg_v));
                         sm.carry_v = to_bits(tile_carry);
@@ -387,7 +394,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
                 }
             }
             if (wave == 0 && !looked_back) {
-                if (tile > 0 && !head_flagged) tile_carry = lookback<A, kAluLanes>(P.desc_v, (int)tile, lane, TT::kOneRound ? 64 : poll_lanes(P.num_tiles, P.first_round), P.hdr);
+                if (tile > 0 && !head_flagged) tile_carry = lookback<A, kAluLanes>(P.desc_v, (int)tile, lane, seg_poll_lanes<TT>(P), P.hdr);
                 if (lane == 0) {
                     if (!final_now) desc_store(P.desc_v + tile, kStatusPrefix, to_bits(tile_carry + tagg_v));
                     sm.carry_v = to_bits(tile_carry);
