@@ -135,7 +135,8 @@ size_t mmv_spmv_csr_workspace_bytes(uint64_t n_rows, uint64_t nnz);
  * loses relative accuracy.  (Short vectors and scans of fp32 values, see MMV_VARIANT_SHUFFLE, are scanned without speculation: there
  * a result depends on its own segment alone.  Short vectors are added up in 64 bits and rounded at the end; beyond 320 KB of values and
  * flags the sums of whole tiles of 2048 elements are rounded to 32 bits on the way.  Longer scans of fp32 values add up four values at
- * a time in 32 bits, and those sums in 64.)
+ * a time in 32 bits, and those sums in 64; values so large that four of them might overflow 32 bits are added up in 64 throughout, so
+ * that a finite prefix stays finite.)
  * With fp32 inputs a position that starts a segment receives its input bit for bit.
  * An infinity or NaN makes the rest of its own segment non-finite, as the definition does, and can in addition turn
  * other positions of the same row of 32 and the segments that begin behind it in that row into NaN (Inf - Inf; not in

@@ -16,6 +16,10 @@ namespace {
 // Sums are carried in 64 bits from lane to lane, from block to block and between tiles (wide_store); a result is rounded when the
 // carry into a lane is, and when it is added.  Error against 64 bits (2-norms), row scans -> now: 1 of 27 starts 6.8e-8 -> 5.0e-8, no
 // flags 2.2e-7 -> 3.9e-8; a start receives its input bit for bit.
+// Inside a lane, neighbours may overflow 32 bits where no prefix does (a segment that goes on from -3e38 over 2e38 and 2e38).  A wave that
+// this can happen to adds up in 64 throughout, its aggregate a second time: one that holds a flag looks for values of 2^125 or more while
+// its loads arrive; in any other the aggregate, added up in the order of the results, is not finite where one of theirs was not.
+// (Sums in 64 bits for every wave: 3 * 10^6 values 9.7 -> 10.0 us the call, 8.2 * 10^6 14.2 -> 15.0; this way 9.8 and 14.0.)
 // What bounds it: the memory, at its rate for as much read as written.  Whole calls, the reset launch of 5 us included, row scans in LDS
 // (matrix cores) -> now: 2^27 values, half of them starts, a quarter one segment, the rest in short segments 197 -> 181 us; 1.5 * 10^8 in
 // segments of 80 214 -> 196 (6.4 TB/s without the reset), 5.2 * 10^7 without flags 83 -> 72; 8.2 * 10^6 21 -> 17; mmv_scan of 5 * 10^7 77.5 -> 72, 1.5 * 10^8 217 -> 197.
@@ -23,7 +27,7 @@ namespace {
 // waves per SIMD: 3 % slower); without flags every tile waits for all those before it, and longer ones pay: 16 blocks (5 * 10^7 72 us; 8: 76, 24: 75).
 // Conditions on blocks are made anew in each pass: hoisted, they took a pair of scalar registers each, and 15 to 83 of those spilled.
 // 16-bit values (segmented scans that fill 512 to 768 workgroups, round_form in host.h): 64-bit loads, so that a lane's four results are
-// one store; their results are rounded once, from 64 bits.  62 to 78 registers, where the form with row scans on the matrix cores needs
+// one store; their results are rounded once, from 64 bits.  70 to 78 registers, where the form with row scans on the matrix cores needs
 // more than the 80 that three workgroups per compute unit leave: fp16 20 * 10^6 28.5 -> 24.8 us the call.
 
 constexpr int kBlockElems = 256;                             // four consecutive elements per lane
@@ -78,8 +82,25 @@ template <bool kFlagged> __device__ __forceinline__ double lane_scan(double v, c
 }
 
 // The four values of a lane in a block, as loaded, and what lies from `valid` on cleared.
+// Large: whether any of the values looked at is 2^125 or more in magnitude (as whole numbers: the bits of a value grow with it, those
+// of a negative one as unsigned ones).  Four values below that do not overflow 32 bits, and fp16 ones never do.
 template <typename In> struct LaneRaw {
     typedef v2u type;
+    typedef int16_t v2i16 __attribute__((ext_vector_type(2)));
+    typedef uint16_t v2u16 __attribute__((ext_vector_type(2)));
+    static constexpr bool kMayOverflow = std::is_same_v<In, typename TBF16::in_t>;
+    struct Large {
+        v2i16 up = 0;
+        v2u16 down = 0;
+        __device__ __forceinline__ void add(const type &w) {
+#pragma unroll
+            for (int d = 0; d < 2; ++d) {
+                up = __builtin_elementwise_max(up, __builtin_bit_cast(v2i16, (uint32_t)w[d]));
+                down = __builtin_elementwise_max(down, __builtin_bit_cast(v2u16, (uint32_t)w[d]));
+            }
+        }
+        __device__ __forceinline__ bool any() const { return up.x >= 0x7E00 || up.y >= 0x7E00 || down.x >= 0xFE00 || down.y >= 0xFE00; }
+    };
     static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, int at) { return __builtin_amdgcn_raw_buffer_load_b64(r, at, 0, kAuxNt); }
     static __device__ __forceinline__ void mask(type &w, int valid) {
 #pragma unroll
@@ -88,6 +109,19 @@ template <typename In> struct LaneRaw {
 };
 template <> struct LaneRaw<float> {
     typedef v4u type;
+    static constexpr bool kMayOverflow = true;
+    struct Large {
+        int32_t up = 0;
+        uint32_t down = 0;
+        __device__ __forceinline__ void add(const type &w) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                up = up > (int32_t)w[d] ? up : (int32_t)w[d];
+                down = down > w[d] ? down : w[d];
+            }
+        }
+        __device__ __forceinline__ bool any() const { return up >= 0x7E000000 || down >= 0xFE000000u; }
+    };
     static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, int at) { return __builtin_amdgcn_raw_buffer_load_b128(r, at, 0, kAuxNt); }
     static __device__ __forceinline__ void mask(type &w, int valid) {
 #pragma unroll
@@ -99,16 +133,21 @@ template <typename TT> __device__ __forceinline__ float lane_value(const typenam
     if constexpr (sizeof(In) == 4) return from_bits<float>(w[i]);
     else return TT::widen(__builtin_bit_cast(In, (uint16_t)(w[i / 2] >> (16 * (i & 1)))));
 }
-// Carry into a lane plus a sum inside it.  16-bit values: added in 64 bits, one rounding.
-template <typename TT> struct LaneCarry {
+// Carry into a lane plus a sum inside it.  16-bit values, and sums in 64 bits: added in 64 bits, one rounding.
+template <typename TT, typename Sum> struct LaneCarry {
     double e;
-    __device__ __forceinline__ float plus(float p) const { return (float)(e + (double)p); }
+    __device__ __forceinline__ float plus(Sum p) const { return (float)(e + (double)p); }
 };
-template <> struct LaneCarry<InLanes<TF32>> {
+template <> struct LaneCarry<InLanes<TF32>, float> {
     float e;
     __device__ __forceinline__ explicit LaneCarry(double v) : e((float)v) {}
     __device__ __forceinline__ float plus(float p) const { return e + p; }
 };
+__device__ __forceinline__ double wave_first(double v) {   // of a value that is the same in all lanes: in scalar registers
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    return __builtin_bit_cast(double, (hi << 32) | lo);
+}
 
 // One tile.  A wave holds its whole span in registers: block b of lane l = its elements 256 b + 4 l .. + 3.
 template <typename TT, int kOp>
@@ -173,13 +212,16 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
 
     // ---- aggregate: the sum of the span from its last flag on ----
     double s = 0.0;
-    if (last < 0) {
+    bool large = false;   // sums inside a lane may overflow 32 bits where no prefix does
+    if (last < 0) {       // (added up in the order of the results: where one of those overflows, this is not finite)
 #pragma unroll
         for (int b = 0; b < kBlocks; ++b)
-            s += (double)((lane_value<TT>(raw[b], 0) + lane_value<TT>(raw[b], 1)) + (lane_value<TT>(raw[b], 2) + lane_value<TT>(raw[b], 3)));
+            s += (double)(((lane_value<TT>(raw[b], 0) + lane_value<TT>(raw[b], 1)) + lane_value<TT>(raw[b], 2)) + lane_value<TT>(raw[b], 3));
     } else {
+        [[maybe_unused]] typename Raw::Large l;
 #pragma unroll
-        for (int b = 0; b < kBlocks; ++b)
+        for (int b = 0; b < kBlocks; ++b) {
+            if constexpr (Raw::kMayOverflow) l.add(raw[b]);
             if (last < kBlockElems * (b + 1)) {
                 const int k = last - kBlockElems * b - 4 * lane;   // my elements from k on count
                 float t[4];
@@ -187,8 +229,24 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
                 for (int i = 0; i < 4; ++i) t[i] = i >= k ? lane_value<TT>(raw[b], i) : 0.0f;
                 s += (double)((t[0] + t[1]) + (t[2] + t[3]));
             }
+        }
+        if constexpr (Raw::kMayOverflow) large = __ballot(l.any()) != 0;
     }
     s = wave_sum_wide(s);
+    if constexpr (Raw::kMayOverflow) {
+        large = large || !__builtin_isfinite(s);
+        if (large) {
+            s = 0.0;
+#pragma unroll
+            for (int b = 0; b < kBlocks; ++b) {
+                __builtin_amdgcn_sched_barrier(0);
+                asm volatile("" : "+v"(raw[b]));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s += kBlockElems * b + 4 * lane + i >= last ? (double)lane_value<TT>(raw[b], i) : 0.0;
+            }
+            s = wave_sum_wide(s);
+        }
+    }
     if (lane == 0) {
         sm.wave_v[wave] = s;
         sm.wave_f[wave] = last >= 0;
@@ -209,6 +267,10 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
     }
     wex_f = __builtin_amdgcn_readfirstlane(wex_f);
     tagg_f = __builtin_amdgcn_readfirstlane(tagg_f);
+    if constexpr (sizeof(In) == 2) {   // (two chunks of bf16 values spill without; fp32 ones have the room, and are up to 4 % faster)
+        wex_v = wave_first(wex_v);
+        tagg_v = wave_first(tagg_v);
+    }
     const bool final_now = tile == 0 || tagg_f;   // carry out does not depend on predecessors
     if (tid == 0) wide_store(P.desc_v + tile, final_now ? kStatusPrefix : kStatusAggregate, tagg_v);
 
@@ -249,52 +311,62 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
             }
             run = tile_carry + wex_v;
         }
+        auto blocks = [&](auto zero) {
+            typedef decltype(zero) Sum;
 #pragma unroll
-        for (int b = 0; b < kBlocks; ++b) {
-            const int c = b / kChunkBlocks, j = b % kChunkBlocks;
-            __builtin_amdgcn_sched_barrier(0);
-            if (b < from || b >= upto || kBlockElems * b >= end) continue;
-            const float x0 = lane_value<TT>(raw[b], 0), x1 = lane_value<TT>(raw[b], 1), x2 = lane_value<TT>(raw[b], 2), x3 = lane_value<TT>(raw[b], 3);
-            float o[4];
-            if (!kFlags || ((rows[c] >> (8 * j)) & 0xFFull) == 0) {
-                const float p1 = x0 + x1, p2 = p1 + x2, p3 = p2 + x3;
-                const double inc = lane_scan<false>((double)p3, ScanMasks{});
-                const LaneCarry<TT> ec{run + dpp_bound<0x138>(inc)};   // wave_shr 1: lane 0 gets 0
-                run += wave_last(inc);
-                o[0] = ec.plus(x0);
-                o[1] = ec.plus(p1);
-                o[2] = ec.plus(p2);
-                o[3] = ec.plus(p3);
-            } else {
-                // (F[c] holds row l of the chunk in lane l: a lane needs four bits of row 8 j + l / 8)
-                const uint32_t word = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (8 * j + (lane >> 3)), (int)F[c]);
-                const uint32_t nib = (word >> (4 * (lane & 7))) & 0xFu;
-                const float p1 = (nib & 2u) ? x1 : x0 + x1, p2 = (nib & 4u) ? x2 : p1 + x2, p3 = (nib & 8u) ? x3 : p2 + x3;
-                const uint64_t m = __ballot(nib != 0);
-                const double inc = lane_scan<true>((double)p3, scan_masks(m));
-                double e = dpp_bound<0x138>(inc);
-                const uint64_t upto_first = (m & (0 - m)) | ((m & (0 - m)) - 1);   // lanes without a flag in a lane before them
-                e += unless(~upto_first, run);
-                const LaneCarry<TT> ec{e};
-                run = wave_last(inc);
-                o[0] = (nib & 1u) ? x0 : ec.plus(x0);
-                o[1] = (nib & 3u) ? p1 : ec.plus(p1);
-                o[2] = (nib & 7u) ? p2 : ec.plus(p2);
-                o[3] = nib ? p3 : ec.plus(p3);
-            }
-            if (b >= store_from) {
-                asm volatile("" : "+v"(own));
-                const v4u w = {to_bits(o[0]), to_bits(o[1]), to_bits(o[2]), to_bits(o[3])};
-                if (kBlockElems * (b + 1) <= end) {
-                    __builtin_amdgcn_raw_buffer_store_b128(w, z_rsrc, own + 1024 * b, 0, kAuxNt);
+            for (int b = 0; b < kBlocks; ++b) {
+                const int c = b / kChunkBlocks, j = b % kChunkBlocks;
+                __builtin_amdgcn_sched_barrier(0);
+                if (b < from || b >= upto || kBlockElems * b >= end) continue;
+                const float x0 = lane_value<TT>(raw[b], 0), x1 = lane_value<TT>(raw[b], 1), x2 = lane_value<TT>(raw[b], 2), x3 = lane_value<TT>(raw[b], 3);
+                float o[4];
+                if (!kFlags || ((rows[c] >> (8 * j)) & 0xFFull) == 0) {
+                    const Sum p0 = x0, p1 = p0 + x1, p2 = p1 + x2, p3 = p2 + x3;
+                    const double inc = lane_scan<false>((double)p3, ScanMasks{});
+                    const LaneCarry<TT, Sum> ec{run + dpp_bound<0x138>(inc)};   // wave_shr 1: lane 0 gets 0
+                    run += wave_last(inc);
+                    o[0] = ec.plus(p0);
+                    o[1] = ec.plus(p1);
+                    o[2] = ec.plus(p2);
+                    o[3] = ec.plus(p3);
                 } else {
-                    float *z = (float *)P.z + wave_base;
+                    // (F[c] holds row l of the chunk in lane l: a lane needs four bits of row 8 j + l / 8)
+                    const uint32_t word = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (8 * j + (lane >> 3)), (int)F[c]);
+                    const uint32_t nib = (word >> (4 * (lane & 7))) & 0xFu;
+                    const Sum p0 = x0, p1 = (nib & 2u) ? (Sum)x1 : p0 + x1, p2 = (nib & 4u) ? (Sum)x2 : p1 + x2, p3 = (nib & 8u) ? (Sum)x3 : p2 + x3;
+                    const uint64_t m = __ballot(nib != 0);
+                    const double inc = lane_scan<true>((double)p3, scan_masks(m));
+                    double e = dpp_bound<0x138>(inc);
+                    const uint64_t upto_first = (m & (0 - m)) | ((m & (0 - m)) - 1);   // lanes without a flag in a lane before them
+                    e += unless(~upto_first, run);
+                    const LaneCarry<TT, Sum> ec{e};
+                    run = wave_last(inc);
+                    o[0] = (nib & 1u) ? x0 : ec.plus(p0);
+                    o[1] = (nib & 3u) ? (float)p1 : ec.plus(p1);
+                    o[2] = (nib & 7u) ? (float)p2 : ec.plus(p2);
+                    o[3] = nib ? (float)p3 : ec.plus(p3);
+                    if constexpr (sizeof(Sum) == 8) {   // (a NaN that starts a segment, bit for bit)
+                        o[1] = (nib & 2u) ? x1 : o[1];
+                        o[2] = (nib & 4u) ? x2 : o[2];
+                        o[3] = (nib & 8u) ? x3 : o[3];
+                    }
+                }
+                if (b >= store_from) {
+                    asm volatile("" : "+v"(own));
+                    const v4u w = {to_bits(o[0]), to_bits(o[1]), to_bits(o[2]), to_bits(o[3])};
+                    if (kBlockElems * (b + 1) <= end) {
+                        __builtin_amdgcn_raw_buffer_store_b128(w, z_rsrc, own + 1024 * b, 0, kAuxNt);
+                    } else {
+                        float *z = (float *)P.z + wave_base;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (own / 4 + kBlockElems * b + i < end) z[own / 4 + kBlockElems * b + i] = o[i];
+                        for (int i = 0; i < 4; ++i)
+                            if (own / 4 + kBlockElems * b + i < end) z[own / 4 + kBlockElems * b + i] = o[i];
+                    }
                 }
             }
-        }
+        };
+        if (Raw::kMayOverflow && large) blocks(0.0);
+        else blocks(0.0f);
     }
 }
 

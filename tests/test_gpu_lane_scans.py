@@ -54,7 +54,47 @@ def test_values_that_are_not_finite_stay_in_their_segment():
     with np.errstate(invalid="ignore", over="ignore"):
         for s in np.unique(seg[bad])[:100]:                    # (in 64 bits, rounded: what overflows 32 bits is infinite)
             i = np.flatnonzero(seg == s)
-            assert np.array_equal(np.isnan(z[i]), np.isnan(np.cumsum(x[i].astype(np.float64)))), s
+            want = np.cumsum(x[i].astype(np.float64))
+            assert np.array_equal(np.isnan(z[i]), np.isnan(want)), s
+            gone = np.flatnonzero(~np.isfinite(want.astype(np.float32)))[:1]     # up to there the segment is finite
+            upto = gone[0] if len(gone) else len(i)
+            assert (np.abs(z[i][:upto] - want[:upto]) <= 5 * 2.0 ** -24 * np.cumsum(np.abs(x[i][:upto].astype(np.float64)))).all(), s
+
+
+@pytest.mark.parametrize("op,n,tt", [("segscan", (1 << 21) + 5, torch.float32), ("scan", (1 << 22) + 5, torch.float32), ("segscan", (1 << 24) + 5, torch.bfloat16)])
+def test_sums_that_overflow_inside_a_lane_only(op, n, tt):
+    """Prefixes are whole multiples of 2^125, at most seven in magnitude: finite, and every sum in 64 bits is exact, while two neighbours
+    may add up to fourteen, beyond 32 bits."""
+    rng = np.random.default_rng(n)
+    for density in (0.0, 1e-5, 1e-3, 0.2) if op == "segscan" else (0.0,):
+        f = (rng.random(n, dtype=np.float32) < density).astype(np.uint8)
+        for places in (1.0, 1e-4):                             # everywhere; a few, most waves without
+            want, start = np.full(n, -7, dtype=np.int64), f.copy()
+            start[0] = 1
+            even = want[::2]
+            new = rng.random(len(even), dtype=np.float32) < places
+            even[new] = rng.integers(-7, 8, size=int(new.sum()))
+            want[1:-1:2] = (want[:-2:2] + want[2::2]) // 2     # (so that no step is longer than seven)
+            x = np.diff(want, prepend=0)
+            assert np.abs(x).max() == 7
+            x[start == 1] = want[start == 1]
+            x = np.ldexp(x.astype(np.float32), 125)
+            want = np.ldexp(want.astype(np.float32), 125)
+            print(op, n, tt, density, places, flush=True)
+            xt = dev(x).to(tt)
+            z = B.mmv_scan(xt, n=n) if op == "scan" else B.mmv_segscan(xt, flags_dev(f, True), n=n)
+            assert np.array_equal(z.cpu().numpy(), want), (density, places)
+            if op == "segscan":                                # the lane's four values from a start inside it on
+                lone = np.zeros(n, dtype=np.float32)
+                at = np.arange(1, n - 8, 4096 + 5)
+                lone[at - 1], lone[at], lone[at + 1], lone[at + 2] = 3e38, -3e38, 2e38, 2e38
+                g = f.copy()
+                g[at - 1] = g[at] = 1
+                g[at + 1] = g[at + 2] = 0                      # (2e38 and 2e38 alone are infinite)
+                lt = dev(lone).to(tt)
+                z = B.mmv_segscan(lt, flags_dev(g, True), n=n).cpu().numpy()
+                low = lt.float().cpu().numpy()
+                assert (np.abs(z - oracle.segscan(low, g)) <= 5 * 2.0 ** -24 * abs_scan(low, g)).all()
 
 
 @pytest.mark.parametrize("ragged", [1, 257, 4097, 32771])
