@@ -226,8 +226,12 @@ inline uint64_t tiles_for(uint64_t n, mmv_op op, mmv_dtype dt) {
     const uint64_t a = tile_plan(op, dt, n, true).tiles, b = tile_plan(op, dt, n, false).tiles;
     return a > b ? a : b;
 }
-// Bytes of x where 32-bit offsets reach all of it, else 0.
+// Bytes of x where 32-bit offsets reach all of it, else 0.  2^30 entries are one byte more than it can say: loads that check their range
+// (buffered_loads) would read 0 for the last entry, so these products take the form for a longer x.
 inline uint32_t x_bytes_of(uint64_t n_cols) { return n_cols > (1ull << 30) ? 0u : n_cols == (1ull << 30) ? ~0u : n_cols ? 4u * (uint32_t)n_cols : 1u; }
+template <int kOp, bool kShort> constexpr bool narrow_x(uint32_t x_bytes) {
+    return kOp == kSum || (x_bytes != 0 && !(x_bytes == ~0u && buffered_loads<kOp, kShort>()));
+}
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 inline bool aligned4(const void *p) { return ((uintptr_t)p & 3u) == 0; }
 
@@ -378,7 +382,8 @@ template <typename TT, int kOp, bool kMfma> hipError_t launch_variant(Params P, 
     void (*kernel)(Params, const uint32_t *);
     int which = 0;
     if constexpr (stream_form<TT, kOp>()) {
-        const bool narrow = kOp == kSum || P.x_bytes != 0;   // (a long x, whatever the matrix: the form for long vectors)
+        // (a long x, whatever the matrix: the form for long vectors)
+        const bool narrow = plan.short_form ? narrow_x<kOp, true>(P.x_bytes) : narrow_x<kOp, false>(P.x_bytes);
         which = !narrow ? 1 : plan.short_form ? 2 : 0;
         kernel = which == 2 ? stream_kernel<TT, kOp, kMfma, true, true> : stream_kernel<TT, kOp, kMfma, true, false>;
         if constexpr (kOp != kSum) {

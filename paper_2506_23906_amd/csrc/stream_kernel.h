@@ -127,7 +127,7 @@ __device__ __forceinline__ void stream_load(const StreamArrays &A, int unit, int
     for (int i = 0; i < 4; ++i) s.raw[i] = __builtin_amdgcn_raw_buffer_load_b128(A.x, own + 1024 * i, 0, kAuxNt);
 }
 
-// kNarrow: x has at most 2^30 entries, so byte offsets into it fit 32 bits (one register per address, no 64-bit
+// kNarrow: x has at most 2^30 entries (loads that check their range: fewer, see x_bytes_of), so byte offsets into it fit 32 bits (one register per address, no 64-bit
 // additions: SpMV with short rows 8 % faster, with scattered columns 2 %).
 template <typename TT, int kOp, bool kMfma, bool kNarrow, bool kShort>
 __device__ __forceinline__ void stream_tile(const Params &P, const uint32_t *__restrict__ hints, StreamShared<TT::kWaves> &sm,

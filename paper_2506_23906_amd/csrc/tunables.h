@@ -184,7 +184,7 @@ struct Params {
     uint32_t first_one;     // plain scan of a flag vector: element 0 counts as 1 whatever it holds
     const int32_t *col;
     const float *xv;
-    uint32_t x_bytes;       // spmv: bytes of x (0: more than 2^30 entries)
+    uint32_t x_bytes;       // spmv: bytes of x (0: more than 2^30 entries; ~0: 2^30 of them, see x_bytes_of)
     float *y;
     uint32_t *hdr;          // workspace header
     uint64_t *desc_v;       // value descriptors, one per tile

@@ -122,6 +122,29 @@ def test_spmv_with_columns_beyond_32_bit_byte_offsets():
         assert np.array_equal(y.cpu().numpy().astype(np.float64), ref)
 
 
+@pytest.mark.parametrize("nnz", [40_001, 4_300_001])                 # a tile that a wave loads at once; the form that gathers by buffer loads
+@pytest.mark.parametrize("more", [-1, 0, 1, 1000])
+def test_spmv_at_the_reach_of_32_bit_byte_offsets(more, nnz):
+    """x of 2^30 + more entries, of which the last and the first are used; behind the last entry lie columns far outside x."""
+    n_cols, n_rows = (1 << 30) + more, nnz // 7
+    rng = np.random.default_rng(nnz + more)
+    row = np.sort(rng.integers(0, n_rows, size=nnz)).astype(np.int32)
+    places = np.array([0, 1, n_cols - 2, n_cols - 1])
+    which = rng.integers(0, 4, size=nnz)
+    val = rng.integers(-2, 3, size=nnz).astype(np.float32)
+    x = torch.zeros(n_cols, dtype=torch.float32, device="cuda")
+    x[places.tolist()] = torch.tensor([1.0, 3.0, 5.0, 7.0], device="cuda")
+    ref = np.bincount(row, weights=val.astype(np.float64) * np.array([1.0, 3.0, 5.0, 7.0])[which], minlength=n_rows)
+    col = torch.full((nnz + 64,), 0x7FFFFFF0, dtype=torch.int32, device="cuda")
+    col[:nnz] = dev(places[which].astype(np.int32))
+    rowptr = dev(np.searchsorted(row, np.arange(n_rows + 1)).astype(np.int32))
+    for variant in ("mfma", "shuffle"):
+        y = B.mmv_spmv_coo(n_rows, n_cols, dev(row), col[:nnz], dev(val), x, variant=variant)
+        assert np.array_equal(y.cpu().numpy().astype(np.float64), ref), variant
+        y = B.mmv_spmv_csr(n_rows, n_cols, rowptr, col[:nnz], dev(val), x, variant=variant)
+        assert np.array_equal(y.cpu().numpy().astype(np.float64), ref), variant
+
+
 def test_csr_of_more_tiles_than_the_tables_without_prefix_sums_cover():
     n_cols = 4096
     lengths = varied_lengths(1.5 * 4110 * 128 * UNIT, 700)
