@@ -9,6 +9,7 @@ been built, loading raises.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 
 import torch  # imported before the library so that both share one HIP runtime
@@ -42,7 +43,8 @@ _VARIANTS = {"mfma": MMV_VARIANT_MFMA, "shuffle": MMV_VARIANT_SHUFFLE}
 
 _lib = None
 # The calls that programs make over and over go through csrc/marshal.cpp where all their arguments are given: it does what the
-# lines below each of them do, and answers None where they have to (arguments left out, errors).  Host time of a call on 3000 values, us:
+# lines below each of them do, and answers None where they have to (arguments left out, errors).  Where it is not built, or for another
+# torch, they do it all.  Host time of a call on 3000 values, us:
 # segmented scan 4.7 -> 3.3, segmented sum 5.1 -> 3.5, scan 4.3 -> 3.5, COMPRESS 5.1 -> 3.6 (the launch itself takes 2.9).
 _marshal = None
 
@@ -56,8 +58,8 @@ def load() -> ctypes.CDLL:
     global _lib, _marshal
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH) or not os.path.exists(MARSHAL_PATH):
-        raise MmvError("libmmvseg.so and _marshal.so are not built: run `python -m paper_2506_23906_amd.build` "
+    if not os.path.exists(LIB_PATH):
+        raise MmvError("libmmvseg.so is not built: run `python -m paper_2506_23906_amd.build` "
                        "(or __graft_entry__.build()) first")
     lib = ctypes.CDLL(LIB_PATH)
     vp, u64, sz, i32 = ctypes.c_void_p, ctypes.c_uint64, ctypes.c_size_t, ctypes.c_int
@@ -105,9 +107,15 @@ def load() -> ctypes.CDLL:
     lib.mmv_segsum_scd.restype = i32
     lib.mmv_segscan_sscr.argtypes = [vp, vp, u64, vp, i32, i32, i32, vp, sz, vp]
     lib.mmv_segscan_sscr.restype = i32
-    from . import _marshal as marshal
-    marshal.bind(*(ctypes.cast(getattr(lib, name), vp).value for name in
-                   ("mmv_segscan", "mmv_segsum", "mmv_scan", "mmv_compress", "mmv_spmv_coo", "mmv_spmv_csr", "mmv_spmv_coo_run", "mmv_spmv_csr_run")))
+    try:
+        marshal = importlib.import_module(__package__ + "._marshal")
+    except ImportError:
+        marshal = None
+    if getattr(marshal, "torch_version", None) != torch.__version__:
+        marshal = None
+    if marshal is not None:
+        marshal.bind(*(ctypes.cast(getattr(lib, name), vp).value for name in
+                       ("mmv_segscan", "mmv_segsum", "mmv_scan", "mmv_compress", "mmv_spmv_coo", "mmv_spmv_csr", "mmv_spmv_coo_run", "mmv_spmv_csr_run")))
     _lib, _marshal = lib, marshal
     return lib
 

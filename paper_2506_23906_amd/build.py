@@ -35,21 +35,22 @@ def build(verbose: bool = False, extra: list[str] | None = None, out: str | None
         raise RuntimeError("hipcc failed building libmmvseg.so")
     if verbose and err.strip():
         sys.stderr.write(err + "\n")
-    os.replace(tmp, lib)
-    if out is None:
-        build_marshal(verbose)
+    marshal = compile_marshal(verbose) if out is None else None
+    os.replace(tmp, lib)              # (both are there before either is replaced)
+    if marshal:
+        os.replace(marshal, MARSHAL_LIB)
     return lib
 
 
-def build_marshal(verbose: bool = False) -> str:
-    """Compiles the argument marshalling (host code only) against the installed torch."""
+def compile_marshal(verbose: bool = False) -> str:
+    """Compiles the argument marshalling (host code only) against the installed torch; returns the file made."""
     import sysconfig
 
     import torch
     from torch.utils import cpp_extension
     tmp = MARSHAL_LIB + ".tmp.%d" % os.getpid()
     libs = os.path.join(os.path.dirname(torch.__file__), "lib")
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM", "-DMMV_TORCH_VERSION=\"%s\"" % torch.__version__,
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", os.path.join(ROOT, "include"),
            "-isystem", sysconfig.get_paths()["include"], "-isystem", "/opt/rocm/include"]
     for path in cpp_extension.include_paths():
@@ -61,8 +62,7 @@ def build_marshal(verbose: bool = False) -> str:
         raise RuntimeError("g++ failed building _marshal.so")
     if verbose and res.stderr.strip():
         sys.stderr.write(res.stderr + "\n")
-    os.replace(tmp, MARSHAL_LIB)
-    return MARSHAL_LIB
+    return tmp
 
 
 if __name__ == "__main__":

@@ -182,4 +182,8 @@ PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_marshal", "Argument marshalling
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal(void) { return PyModule_Create(&g_module); }
+PyMODINIT_FUNC PyInit__marshal(void) {
+    PyObject *m = PyModule_Create(&g_module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", MMV_TORCH_VERSION) < 0) Py_CLEAR(m);   // (binding.py uses it with this one only)
+    return m;
+}

@@ -32,8 +32,8 @@ def golden_sec2():
 
 @pytest.fixture(scope="session")
 def libmmvseg_path():
-    """Path of the built C-ABI library; builds it only if nothing is there."""
+    """Path of the built C-ABI library; builds it only if it or the extension beside it is not there."""
     from paper_2506_23906_amd import binding, build
-    if not os.path.exists(binding.LIB_PATH):
+    if not os.path.exists(binding.LIB_PATH) or not os.path.exists(binding.MARSHAL_PATH):
         build.build()
     return binding.LIB_PATH

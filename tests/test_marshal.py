@@ -1,9 +1,14 @@
 """The binding's calls through the extension that marshals their arguments, and what it leaves to the lines in Python."""
+import os
+import sys
+import types
+
 import numpy as np
 import pytest
 import torch
 
 from paper_2506_23906_amd import binding as B
+from paper_2506_23906_amd import build
 from paper_2506_23906_amd import workloads as W
 
 
@@ -22,6 +27,33 @@ def test_what_it_does_not_know_is_left_to_python(libmmvseg_path):
         m.bind(1)
     with pytest.raises(B.MmvError):                            # ... which raises what it raised before
         B.mmv_segscan(t, f, z=t, ws=f)
+
+
+@pytest.mark.parametrize("module", [None, types.SimpleNamespace(torch_version="another")])   # not built; built for another torch
+def test_the_library_loads_without_the_extension(libmmvseg_path, monkeypatch, tmp_path, module):
+    monkeypatch.setitem(sys.modules, B.__package__ + "._marshal", module)
+    monkeypatch.delattr(sys.modules[B.__package__], "_marshal", raising=False)
+    monkeypatch.setattr(B, "MARSHAL_PATH", str(tmp_path / "_marshal.so"))
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "_marshal", None)
+    assert B.load().mmv_status_string(0) and B._marshal is None
+    with pytest.raises(B.MmvError):
+        B.mmv_segscan(torch.zeros(64), torch.zeros(64, dtype=torch.uint8))
+
+
+def test_a_failed_compilation_replaces_nothing(monkeypatch, tmp_path):
+    def run(cmd, **_):
+        made = cmd[cmd.index("-o") + 1]
+        assert os.path.dirname(made) == str(tmp_path)
+        open(made, "w").write("new")
+        return types.SimpleNamespace(returncode=1 if cmd[0] == "g++" else 0, stderr="")
+    for name in ("LIB", "MARSHAL_LIB"):
+        (tmp_path / name).write_text("old")
+        monkeypatch.setattr(build, name, str(tmp_path / name))
+    monkeypatch.setattr(build, "subprocess", types.SimpleNamespace(run=run))
+    with pytest.raises(RuntimeError):
+        build.build()
+    assert (tmp_path / "LIB").read_text() == (tmp_path / "MARSHAL_LIB").read_text() == "old"
 
 
 @pytest.mark.gpu
