@@ -69,27 +69,40 @@ def test_both_ways_give_the_same(monkeypatch):
     side = torch.cuda.Stream()
 
     def calls(how):
-        new = lambda k, dt=torch.float32: torch.zeros(k, dtype=dt, device="cuda")
+        kept = []   # every tensor until the end: a kernel on another stream may still use it, and its memory goes to the next one made
+        def keep(tensor):
+            kept.append(tensor)
+            return tensor
+        new = lambda k, dt=torch.float32: keep(torch.zeros(k, dtype=dt, device="cuda"))
+        scratch = lambda *a: keep(B.new_workspace(*a))
         out = []
-        for xt in (x, x.half(), x.bfloat16(), x.to(torch.int8)):
-            dt = B._DTYPES[xt.dtype]
+        def call(entry, *a, **kw):
+            side.wait_stream(torch.cuda.current_stream())      # (behind the fills)
+            r = entry(*a, **kw, **how)
+            out.extend(r if isinstance(r, tuple) else [r])
+        for xt in (x, x.half(), x.bfloat16(), x.to(torch.int8), x.to(torch.int8).view(torch.uint8)):
+            dt = B._DTYPES[keep(xt).dtype]
             for fl in (f, bits):
                 ff = B._flag_fmt(fl)
-                out.append(B.mmv_segscan(xt, fl, n=n, z=new(n, B._OUT_DTYPE[dt]), ws=B.new_workspace(B.MMV_OP_SEGSCAN, dt, ff, n), **how))
-                out += B.mmv_segsum(xt, fl, out=new(n, B._OUT_DTYPE[dt]), nseg=new(1, torch.int64), variant="shuffle",
-                                    ws=B.new_workspace(B.MMV_OP_SEGSUM, dt, ff, n), n=n, **how)
-            out.append(B.mmv_scan(xt, n=n - 7, z=new(n, B._OUT_DTYPE[dt]), ws=B.new_workspace(B.MMV_OP_SCAN, dt, 1, n), **how))
+                call(B.mmv_segscan, xt, fl, n=n, z=new(n, B._OUT_DTYPE[dt]), ws=scratch(B.MMV_OP_SEGSCAN, dt, ff, n))
+                call(B.mmv_segsum, xt, fl, out=new(n, B._OUT_DTYPE[dt]), nseg=new(1, torch.int64), variant="shuffle",
+                     ws=scratch(B.MMV_OP_SEGSUM, dt, ff, n), n=n)
+            call(B.mmv_scan, xt, n=n - 7, z=new(n, B._OUT_DTYPE[dt]), ws=scratch(B.MMV_OP_SCAN, dt, 1, n))
         for v in (x, None):
-            out += B.mmv_compress(v, f, n, out=new(n, torch.float32 if v is not None else torch.int32), count=new(1, torch.int64),
-                                  ws=B.new_workspace(B.MMV_OP_COMPRESS, B.MMV_I8_I32, 0, n), **how)
-        ws = B.new_workspace(B.MMV_OP_SPMV_COO, B.MMV_F32_F32, B.MMV_FLAGS_PACKED32, val.numel())
-        out.append(B.mmv_spmv_coo(700, 600, row, col, val, xv, y=new(700), ws=ws, **how))
-        ws = B.mmv_spmv_coo_prepare(700, 600, row, col, **how)
-        out.append(B.mmv_spmv_coo_run(700, 600, row, col, val, xv, ws, y=new(700), **how))
-        ws = B.workspace(B.mmv_spmv_csr_workspace_bytes(700, val.numel()))
-        out.append(B.mmv_spmv_csr(700, 600, rowptr, col, val, xv, y=new(700), ws=ws, **how))
-        ws = B.mmv_spmv_csr_prepare(700, 600, rowptr, col, **how)
-        out.append(B.mmv_spmv_csr_run(700, 600, rowptr, col, val, xv, ws, y=new(700), **how))
+            call(B.mmv_compress, v, f, n, out=new(n, torch.float32 if v is not None else torch.int32), count=new(1, torch.int64),
+                 ws=scratch(B.MMV_OP_COMPRESS, B.MMV_I8_I32, 0, n))
+        coo = lambda: scratch(B.MMV_OP_SPMV_COO, B.MMV_F32_F32, B.MMV_FLAGS_PACKED32, val.numel())
+        csr = lambda: keep(B.workspace(B.mmv_spmv_csr_workspace_bytes(700, val.numel())))
+        call(B.mmv_spmv_coo, 700, 600, row, col, val, xv, y=new(700), ws=coo())
+        ws = coo()
+        call(B.mmv_spmv_coo_prepare, 700, 600, row, col, ws=ws)
+        out.pop()                                              # (the plan)
+        call(B.mmv_spmv_coo_run, 700, 600, row, col, val, xv, ws, y=new(700))
+        call(B.mmv_spmv_csr, 700, 600, rowptr, col, val, xv, y=new(700), ws=csr())
+        ws = csr()
+        call(B.mmv_spmv_csr_prepare, 700, 600, rowptr, col, ws=ws)
+        out.pop()
+        call(B.mmv_spmv_csr_run, 700, 600, rowptr, col, val, xv, ws, y=new(700))
         torch.cuda.synchronize()
         return out
 
