@@ -124,8 +124,8 @@ __global__ __launch_bounds__(kCompressWaves * 64, 8) void compress_kernel(
     const uint32_t positions = left < kSpan ? (uint32_t)left : kSpan;                // of my wave
     if constexpr (kBytes) {
         constexpr int kLoads = kWords / 16;   // 1024 mask bytes of the wave each
-        // (the 16-byte block of the last byte is read whole.  All loads under way at once: with the end of the mask looked after by a
-        // branch per lane, each was waited for before the next.  2^26 bytes, 30 % selected 81.0 -> 80.5 us the call, 1.3 * 10^7 bits,
+        // (the 16-byte block of the last byte is read whole.  All loads under way at once, of four groups all but the last four (60 registers):
+        // with the end of the mask looked after by a branch per lane, each was waited for before the next.  2^26 bytes, 30 % selected 81.0 -> 80.5 us the call, 1.3 * 10^7 bits,
         // 8 % 18.6 -> 18.0)
         const auto rsrc = make_rsrc((const uint8_t *)mask + span, (positions + 15) & ~15u);
         v4u b[kGroups][kLoads];

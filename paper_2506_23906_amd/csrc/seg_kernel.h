@@ -87,12 +87,10 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
     // phase A (which take several microseconds when all waves of a compute unit are at it): the wave whose loads
     // land last adds up the sums of all waves.  Without this a vector without flags ran 13 % slower than one
     // with a flag in every tile, each tile waiting 6 us for the slowest of the tiles before it.
-    constexpr int kEarlyMode = !kScanLike ? 0 : sizeof(In) == 1 ? MMV_EARLY_I8 : MMV_EARLY_F16;
-    constexpr bool kEarly = kEarlyMode != 0;
-    constexpr bool kEarlyLookback = kEarlyMode == 2;
-    // mode 3: that wave asks for the descriptors of the tiles before at the end of its phase A and looks at them after
-    // the barrier (the look-back takes 3 to 4 us whatever has been published: the poll is under way meanwhile)
-    constexpr bool kAsyncLookback = kEarlyMode == 3;
+    // That wave also asks for the descriptors of the tiles before at the end of its phase A and looks at them after the
+    // barrier: the look-back takes 3 to 4 us whoever has published what, so it pays to have the poll under way early (looking
+    // back at once makes the wave late for the barrier).
+    constexpr bool kEarly = kScanLike;
 
     // the wave index as a scalar: everything derived from it (the wave's span, chunk bases, the
     // "whole chunk inside the vector" tests, base addresses of loads and stores) then lives in scalar
@@ -170,16 +168,6 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
             if (!flagged) {
                 i_published = true;
                 if (lane == 0) desc_store(P.desc_v + tile, kStatusAggregate, to_bits(total));
-                if constexpr (kEarlyLookback) {
-                    // ... and it looks back for the carry of the tiles before right away, so that the tile's own
-                    // prefix is out for its successors a whole phase A earlier (the other waves go on meanwhile)
-                    const A carry_in = lookback<A, kAluLanes>(P.desc_v, (int)tile, lane, seg_poll_lanes<TT>(P), P.hdr);
-                    if (lane == 0) {
-                        desc_store(P.desc_v + tile, kStatusPrefix, to_bits(carry_in + total));
-                        sm.carry_v = to_bits(carry_in);
-                        __hip_atomic_store(&sm.ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    }
-                }
             }
         }
     }
@@ -334,7 +322,7 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
         sm.wave_c[wave] = run_c;
     }
     uint64_t polled = 0;
-    if constexpr (kAsyncLookback) {
+    if constexpr (kEarly) {
         if (i_published) polled = lookback_poll(P.desc_v, (int)tile, lane, seg_poll_lanes<TT>(P));
     }
     __syncthreads();
@@ -382,8 +370,8 @@ __device__ __forceinline__ void seg_tile(const Params &P, SegShared<TT::kWaves, 
             // ---- step 5c, second half: carry of the predecessor tiles by decoupled look-back ----
             A tile_carry = A(0);
             // (a tile without flags, other than tile 0, has looked back already where kEarly is set)
-            const bool looked_back = (kEarlyLookback || kAsyncLookback) && !final_now;
-            if constexpr (kAsyncLookback) {
+            const bool looked_back = kEarly && !final_now;
+            if constexpr (kEarly) {
                 if (i_published) {
                     tile_carry = lookback<A, kAluLanes, true>(P.desc_v, (int)tile, lane, seg_poll_lanes<TT>(P), P.hdr, polled);
                     if (lane == 0) {

@@ -327,8 +327,6 @@ template <> struct SpecMfma<TF32> {
         }
         return op;
     }
-    // keeps the compiler from moving the making of the operand past this point
-    static __device__ __forceinline__ void pin(Operand &op) { asm volatile("" : "+v"(op.a[0]), "+v"(op.a[1])); }
     static __device__ __forceinline__ void run(const v4u *raw, int lane, float (&acc)[16]) {
         run(raw, lane, acc, operand(lane));
     }

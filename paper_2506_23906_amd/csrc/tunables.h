@@ -54,17 +54,6 @@ namespace {
 #ifndef MMV_LOAD_PRIO
 #define MMV_LOAD_PRIO 1   // wave priority while a workgroup takes its ticket and issues its loads (0: off)
 #endif
-// Scan kernels, tiles without any flag: 0 = the aggregate is published after phase A, as for every other tile;
-// 1 = the plain sum is published as soon as the tile's loads have landed; 2 = and the wave that publishes it looks
-// back for the carry at once; 3 = that wave asks for the descriptors of the tiles before when its phase A is done and
-// looks at them after the barrier (the look-back takes 3 to 4 us whoever has published what, so it pays to have the
-// poll under way early; 2 makes the wave late for the barrier).  Per input width (measured best on MI355X).
-#ifndef MMV_EARLY_I8
-#define MMV_EARLY_I8 3
-#endif
-#ifndef MMV_EARLY_F16
-#define MMV_EARLY_F16 3
-#endif
 #ifndef MMV_CHUNK_SUM
 #define MMV_CHUNK_SUM 1   // 1: the segmented sum of 8- and 16-bit inputs on long vectors speculates over whole chunks
 #endif
