@@ -17,9 +17,9 @@ namespace {
 // carry into a lane is, and when it is added.  Error against 64 bits (2-norms), row scans -> now: 1 of 27 starts 6.8e-8 -> 5.0e-8, no
 // flags 2.2e-7 -> 3.9e-8; a start receives its input bit for bit.
 // Inside a lane, neighbours may overflow 32 bits where no prefix does (a segment that goes on from -3e38 over 2e38 and 2e38).  A wave that
-// this can happen to adds up in 64 throughout, its aggregate a second time: one that holds a flag looks for values of 2^125 or more while
-// its loads arrive; in any other the aggregate, added up in the order of the results, is not finite where one of theirs was not.
-// (Sums in 64 bits for every wave: 3 * 10^6 values 9.7 -> 10.0 us the call, 8.2 * 10^6 14.2 -> 15.0; this way 9.8 and 14.0.)
+// holds values that large (LaneRaw::Large, asked while its loads arrive) adds up in 64 throughout, its aggregate a second time.  What
+// asking costs: 3 * 10^6 values, 4 % starts 9.5 us the call with and without, 1.5 * 10^8 without flags 204.7 -> 205.1, 2^27 of three kinds of
+// segments 178.9 -> 180.9.  (Sums in 64 bits for every wave: 3 * 10^6 values 10.0, 8.2 * 10^6 14.2 -> 15.0.)
 // What bounds it: the memory, at its rate for as much read as written.  Whole calls, the reset launch of 5 us included, row scans in LDS
 // (matrix cores) -> now: 2^27 values, half of them starts, a quarter one segment, the rest in short segments 197 -> 181 us; 1.5 * 10^8 in
 // segments of 80 214 -> 196 (6.4 TB/s without the reset), 5.2 * 10^7 without flags 83 -> 72; 8.2 * 10^6 21 -> 17; mmv_scan of 5 * 10^7 77.5 -> 72, 1.5 * 10^8 217 -> 197.
@@ -82,8 +82,8 @@ template <bool kFlagged> __device__ __forceinline__ double lane_scan(double v, c
 }
 
 // The four values of a lane in a block, as loaded, and what lies from `valid` on cleared.
-// Large: whether any of the values looked at is 2^125 or more in magnitude (as whole numbers: the bits of a value grow with it, those
-// of a negative one as unsigned ones).  Four values below that do not overflow 32 bits, and fp16 ones never do.
+// Large: whether any of the values looked at is 2^125 or more in magnitude (or a NaN).  Four values below that do not overflow 32 bits,
+// and fp16 ones never do.  bf16 values are compared as whole numbers: their bits grow with them, those of a negative one as unsigned ones.
 template <typename In> struct LaneRaw {
     typedef v2u type;
     typedef int16_t v2i16 __attribute__((ext_vector_type(2)));
@@ -111,16 +111,12 @@ template <> struct LaneRaw<float> {
     typedef v4u type;
     static constexpr bool kMayOverflow = true;
     struct Large {
-        int32_t up = 0;
-        uint32_t down = 0;
+        float m = 0.0f;
         __device__ __forceinline__ void add(const type &w) {
 #pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                up = up > (int32_t)w[d] ? up : (int32_t)w[d];
-                down = down > w[d] ? down : w[d];
-            }
+            for (int d = 0; d < 4; ++d) m = __builtin_elementwise_maximum(m, fabsf(from_bits<float>(w[d])));
         }
-        __device__ __forceinline__ bool any() const { return up >= 0x7E000000 || down >= 0xFE000000u; }
+        __device__ __forceinline__ bool any() const { return !(m < 0x1p125f); }   // (a NaN stays one)
     };
     static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, int at) { return __builtin_amdgcn_raw_buffer_load_b128(r, at, 0, kAuxNt); }
     static __device__ __forceinline__ void mask(type &w, int valid) {
@@ -213,15 +209,15 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
     // ---- aggregate: the sum of the span from its last flag on ----
     double s = 0.0;
     bool large = false;   // sums inside a lane may overflow 32 bits where no prefix does
-    if (last < 0) {       // (added up in the order of the results: where one of those overflows, this is not finite)
+    if (__builtin_expect(last >= 0, 1)) {
+        if constexpr (Raw::kMayOverflow) {
+            typename Raw::Large l;
+#pragma unroll
+            for (int b = 0; b < kBlocks; ++b) l.add(raw[b]);
+            large = __ballot(l.any()) != 0;
+        }
 #pragma unroll
         for (int b = 0; b < kBlocks; ++b)
-            s += (double)(((lane_value<TT>(raw[b], 0) + lane_value<TT>(raw[b], 1)) + lane_value<TT>(raw[b], 2)) + lane_value<TT>(raw[b], 3));
-    } else {
-        [[maybe_unused]] typename Raw::Large l;
-#pragma unroll
-        for (int b = 0; b < kBlocks; ++b) {
-            if constexpr (Raw::kMayOverflow) l.add(raw[b]);
             if (last < kBlockElems * (b + 1)) {
                 const int k = last - kBlockElems * b - 4 * lane;   // my elements from k on count
                 float t[4];
@@ -229,13 +225,20 @@ __device__ __forceinline__ void lane_tile(const Params &P, LaneShared<TT::kWaves
                 for (int i = 0; i < 4; ++i) t[i] = i >= k ? lane_value<TT>(raw[b], i) : 0.0f;
                 s += (double)((t[0] + t[1]) + (t[2] + t[3]));
             }
+    } else {
+#pragma unroll
+        for (int b = 0; b < kBlocks; ++b)
+            s += (double)((lane_value<TT>(raw[b], 0) + lane_value<TT>(raw[b], 1)) + (lane_value<TT>(raw[b], 2) + lane_value<TT>(raw[b], 3)));
+        if constexpr (Raw::kMayOverflow) {
+            typename Raw::Large l;
+#pragma unroll
+            for (int b = 0; b < kBlocks; ++b) l.add(raw[b]);
+            large = __ballot(l.any()) != 0;
         }
-        if constexpr (Raw::kMayOverflow) large = __ballot(l.any()) != 0;
     }
     s = wave_sum_wide(s);
     if constexpr (Raw::kMayOverflow) {
-        large = large || !__builtin_isfinite(s);
-        if (large) {
+        if (large) {   // (a second time, in 64 bits)
             s = 0.0;
 #pragma unroll
             for (int b = 0; b < kBlocks; ++b) {
