@@ -180,8 +180,8 @@ mmv_status mmv_segscan_static(const void *d_x, const void *d_flags, uint64_t n, 
  * count); pass out_capacity = n to be safe.  The number of segments must be
  * below 2^32 (counts are carried in 32 bits).
  * Speed on long vectors (n = 2^28, 0.1 % of the flags set, % of the HBM peak): 8- and 16-bit inputs are fastest
- * with MMV_VARIANT_MFMA (bytes 58 % against 48 %, fp16 69 % against 61 %: the same kernel, its 32x32 tiles
- * scanned by the matrix cores or by vector instructions), fp32 inputs are about as fast with either (78 % and 80 %). */
+ * with MMV_VARIANT_MFMA (bytes 62 % against 51 %, fp16 73 % against 66 %: the same kernel, its 32x32 tiles
+ * scanned by the matrix cores or by vector instructions), fp32 inputs are about as fast with either (78 % and 77 %). */
 mmv_status mmv_segsum(const void *d_x, const void *d_flags, uint64_t n,
                       void *d_out, uint64_t out_capacity, uint64_t *d_nseg,
                       mmv_dtype dt, mmv_flag_fmt ff, mmv_variant v,

@@ -89,7 +89,8 @@ inline int waves_of(mmv_dtype dt) {   // (SpMV has a tile plan of its own)
 // (12 * 10^6 17.0 / 18.5 -> 15.3 / 19.2, 14 * 10^6 18.5 / 20.6 -> 18.5 / 21.6).  On the matrix cores the form spills 20 registers and is
 // 20 % slower; segmented scans of that variant take the form in lanes there (lane_kernel.h), whose error is smaller than that of either
 // row scan (fp16, lengths up to 512 1.7e-8 against 2.1e-8, one segment 2.5e-8 against 2e-7): 17 * 10^6 26.0 / 29.7 -> 22.8 / 25.1,
-// 20 * 10^6 28.5 / 31.4 -> 24.8 / 27.1, 25 * 10^6 31.6 / 35.0 -> 30.2 / 31.3.  Not outside this range: 8 * 10^6 12.9 / 15.0 -> 14.4 / 15.7
+// 20 * 10^6 28.5 / 31.4 -> 24.8 / 27.1, 25 * 10^6 31.6 / 35.0 -> 30.2 / 31.3; bf16 25.8 / 29.3 -> 22.0 / 25.1, 27.6 / 31.6 -> 24.7 / 26.6,
+// 30.7 / 35.0 -> 29.5 / 31.1.  Not outside this range: 8 * 10^6 12.9 / 15.0 -> 14.4 / 15.7
 // (a wave's blocks one after the other), 1.8 * 10^8 181 / 213 -> 188 / 189 (two workgroups per compute unit 186 / 192); and not for
 // mmv_scan: tiles of three chunks, 12 * 10^6 19.3 -> 21.2, 5 * 10^7 59.0 -> 57.9, 1.8 * 10^8 195.5 -> 196.5.
 template <typename TT, int kOp, bool kMfma> constexpr bool has_round_form() {

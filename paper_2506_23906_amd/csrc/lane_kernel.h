@@ -20,9 +20,11 @@ namespace {
 // holds values that large (LaneRaw::Large, asked while its loads arrive) adds up in 64 throughout, its aggregate a second time.  What
 // asking costs: 3 * 10^6 values, 4 % starts 9.5 us the call with and without, 1.5 * 10^8 without flags 204.7 -> 205.1, 2^27 of three kinds of
 // segments 178.9 -> 180.9.  (Sums in 64 bits for every wave: 3 * 10^6 values 10.0, 8.2 * 10^6 14.2 -> 15.0.)
-// What bounds it: the memory, at its rate for as much read as written.  Whole calls, the reset launch of 5 us included, row scans in LDS
+// What bounds it: the memory, at its rate for as much read as written (fp32: every byte moved once at 5.9 to 6.2 TB/s, vector pipes 25 to 40 %
+// busy; one round of 16-bit values: 5.0 TB/s and 39 %, a wave lives 13.5 us of the kernel's 24.6).  Whole calls, the reset launch of 5 us included, row scans in LDS
 // (matrix cores) -> now: 2^27 values, half of them starts, a quarter one segment, the rest in short segments 197 -> 181 us; 1.5 * 10^8 in
-// segments of 80 214 -> 196 (6.4 TB/s without the reset), 5.2 * 10^7 without flags 83 -> 72; 8.2 * 10^6 21 -> 17; mmv_scan of 5 * 10^7 77.5 -> 72, 1.5 * 10^8 217 -> 197.
+// segments of 80 214 -> 196 (6.4 TB/s without the reset), 5.2 * 10^7 without flags 83 -> 72; 8.2 * 10^6 21 -> 17; mmv_scan of 5 * 10^7 77.5 -> 72.7, 1.5 * 10^8 217 -> 199.
+// 1.5 * 10^8 starts 193 -> 196: the row scans stored a chunk of starts as it was loaded.
 // Tiles: 8 blocks per wave and three workgroups per compute unit (16 and two: lengths up to 2000, 9 * 10^7 127 us against 123; eight
 // waves per SIMD: 3 % slower); without flags every tile waits for all those before it, and longer ones pay: 16 blocks (5 * 10^7 72 us; 8: 76, 24: 75).
 // Conditions on blocks are made anew in each pass: hoisted, they took a pair of scalar registers each, and 15 to 83 of those spilled.

@@ -50,7 +50,8 @@ template <int kWaves, int kRows> struct SegShared {
 
 // Descriptors that a look-back takes at a time (lookback in lanes.h).  Tiles of bytes hold four times the elements of fp32 ones, so fewer
 // of them are in flight and ask for the same lines: without flags, windows of 64 -> 16: 5 * 10^7 bytes 50.6 -> 52.3 us, segmented 52.3 -> 54.9, 10^8
-// 90.5 -> 90.6, 2^28 224.8 -> 223.0.  16-bit values, 64 / 32 / 16: segmented, 10^8 115.3 / 111.7 / 111.8, mmv_scan 3 * 10^7 39.1 / 39.6 / 40.4.
+// 90.5 -> 90.6, 2^28 224.8 -> 223.0.  16-bit values, 64 / 32 / 16: segmented, 10^8 115.3 / 111.7 / 111.8, mmv_scan 3 * 10^7 39.1 / 39.6 / 40.4
+// (windows of 64 read whole, as before, against these of 32, timed in turn: mmv_scan of 3 * 10^7 fp16 values 38.7 / 38.8, 10^8 111.0 / 108.2, 2^28 285.6 / 279.0).
 template <typename TT> __device__ __forceinline__ int seg_poll_lanes(const Params &P) {
     return TT::kOneRound || sizeof(typename TT::in_t) == 1 || P.num_tiles <= P.first_round ? 64 : 32;
 }
